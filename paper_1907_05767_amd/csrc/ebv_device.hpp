@@ -2,12 +2,13 @@
  * Device building blocks for the EbV LU kernels (gfx950, wave64).
  *
  * Elimination (Eq. 6-a, 6-c) is blocked in 64 x 64 tiles.  A diagonal tile is
- * factored in LDS in four 16-column panels (tile_lu16): one wave runs the 16
- * pivot steps of a panel with one row per lane and the pivot row broadcast
- * by readlane, one wave solves the 16 U rows beside it, and the rank-16
+ * factored in LDS in four 16-column strips (tile_lu64): every wave runs the 16
+ * pivot steps of a strip's diagonal block in registers, the pivot row
+ * broadcast within 16-lane rows by DPP, and carries a share of the U rows
+ * beside it, the L columns below it and the identity along; the rank-16
  * update of the rest runs on the matrix cores.  The inverses of the tile's
  * two triangular factors follow by block recursion on the matrix cores
- * (tile_inv16), so that every triangular solve against a diagonal tile --
+ * (tile_inv_off), so that every triangular solve against a diagonal tile --
  * the U blocks right of it, the L blocks below it, the blocks of a
  * substitution -- becomes a 64 x 64 product.  The rank-64 trailing update,
  * where the flops are, runs on the FP64 (or FP32) matrix cores.
@@ -145,7 +146,6 @@ template <typename T> struct TileSmem {
     T t0[TB * LDT];   /* diagonal tile / staged operand / operator tile */
     T t1[TB * LDT];   /* inverses of the factors / B operand / staged solved block */
     T rinv[TB];       /* reciprocals of the pivots of t0 */
-    T aux[32 + 256];  /* tile_lu16 scratch */
     int ticket;
     int zflag;        /* zero-pivot report shared by the workgroup */
     int avail;        /* blocks known solved (multi-workgroup solves) */
@@ -332,257 +332,281 @@ __device__ __forceinline__ void wave_mma16_acc(typename vec4<T>::type &acc, FA &
         acc = mfma16(fa(lr, acc_row<T>(lk, ks)), b[ks], acc);
 }
 
-/*
- * Doolittle LU (Eq. 6-a, 6-c) of the 64 x 64 tile S in LDS (pitch LDT), in
- * place, blocked in four 16-column panels.  Per panel, wave 0 alone:
- *   - factors the panel: 16 pivot steps, two at a time, with one row per
- *     lane and the panel's 16 columns in registers; the two pivot rows' lanes
- *     write them to LDS and every lane reads them back as a broadcast (a
- *     wave's LDS accesses complete in order, so no barrier is involved);
- *   - solves the 16 U rows to the panel's right against the panel's
- *     unit-lower block (one column per lane), reading the L coefficients as
- *     broadcasts from a transposed copy in LDS;
- * then all waves apply the rank-16 update to the rest on the matrix cores.
- * aux: 32 + 16*16 elements of LDS scratch.  rinv receives 1/U_kk.  Rows and
- * columns past nvalid must hold the identity, which the sweep keeps.
- * Returns 0 or k+1 for the first exactly-zero pivot k < nvalid (the same in
- * every thread).  While wave 0 factors panel p >= 1, waves 1..3 call
- * done(p - 1, 0): panel p - 1 (its columns below the diagonal, its rows right
- * of the diagonal, its diagonal block and rinv) is final then and no longer
- * touched, so a caller can start publishing it; from p >= 2 they first call
- * done(p - 2, 1), where a caller can wait for the previous panel's stores
- * (a panel later, so that no barrier of the factorization waits for memory;
- * done(2, 1) is left to the caller, after the factorization).
- */
-struct NoPanelHook {
+/* ------------------------------------------- 16 x 16 blocks in lanes --- */
+
+/* The same 16 values in each of the four 16-lane rows of a wave can be
+ * broadcast within the row by the data path of the instruction that uses
+ * them (DPP row_newbcast), FP64 included, so an elimination step over
+ * registers costs one fused multiply-add per element: no LDS round trip and
+ * no readlane. */
+template <int K, typename T> __device__ __forceinline__ T row_bcast(T v)
+{
+    return __builtin_amdgcn_update_dpp(v, v, 0x150 + K, 0xf, 0xf, true);
+}
+
+/* One elimination step over a lane's registers: with the row held by lane K
+ * of each 16-lane row as the pivot row, a[j] -= f a[j](lane K) for j > K and
+ * x[j] -= f x[j](lane K) for all j.  The compiler does not fold the broadcast
+ * into the FP64 multiply-add, so the block is written out (a mov and a
+ * multiply-add per element instead took 1.5x the issue slots).  A DPP read
+ * needs two wait states after a vector write of the register, which the
+ * compiler does not count across inline assembly: the s_nop covers the
+ * writes before the block, and a[K + 1], the only register the next step's
+ * broadcast reads, is written first, at least eight instructions before the
+ * block's end. */
+#define EBV_ROW_FMA(N, C, J)                                                                                           \
+    ".if " C "\n\tv_fmac_" N "_dpp %" J ", %" J ", -%[f] row_newbcast:%c[k] row_mask:0xf bank_mask:0xf\n\t.endif\n\t"
+#define EBV_ROW_A(N, OP)                                                                                               \
+    EBV_ROW_FMA(N, "%c[k] + 1 " OP " 1", "1") EBV_ROW_FMA(N, "%c[k] + 1 " OP " 2", "2")                                \
+    EBV_ROW_FMA(N, "%c[k] + 1 " OP " 3", "3") EBV_ROW_FMA(N, "%c[k] + 1 " OP " 4", "4")                                \
+    EBV_ROW_FMA(N, "%c[k] + 1 " OP " 5", "5") EBV_ROW_FMA(N, "%c[k] + 1 " OP " 6", "6")                                \
+    EBV_ROW_FMA(N, "%c[k] + 1 " OP " 7", "7") EBV_ROW_FMA(N, "%c[k] + 1 " OP " 8", "8")                                \
+    EBV_ROW_FMA(N, "%c[k] + 1 " OP " 9", "9") EBV_ROW_FMA(N, "%c[k] + 1 " OP " 10", "10")                              \
+    EBV_ROW_FMA(N, "%c[k] + 1 " OP " 11", "11") EBV_ROW_FMA(N, "%c[k] + 1 " OP " 12", "12")                            \
+    EBV_ROW_FMA(N, "%c[k] + 1 " OP " 13", "13") EBV_ROW_FMA(N, "%c[k] + 1 " OP " 14", "14")                            \
+    EBV_ROW_FMA(N, "%c[k] + 1 " OP " 15", "15")
+#define EBV_ROW_STEP(N)                                                                                                \
+    "s_nop 1\n\t" EBV_ROW_A(N, "==")                                                                                   \
+    EBV_ROW_FMA(N, "1", "16") EBV_ROW_FMA(N, "1", "17") EBV_ROW_FMA(N, "1", "18") EBV_ROW_FMA(N, "1", "19")            \
+    EBV_ROW_FMA(N, "1", "20") EBV_ROW_FMA(N, "1", "21") EBV_ROW_FMA(N, "1", "22") EBV_ROW_FMA(N, "1", "23")            \
+    EBV_ROW_A(N, "<")
+#define EBV_ROW_ARGS(a, x)                                                                                             \
+    "+v"(a[0]), "+v"(a[1]), "+v"(a[2]), "+v"(a[3]), "+v"(a[4]), "+v"(a[5]), "+v"(a[6]), "+v"(a[7]), "+v"(a[8]),        \
+        "+v"(a[9]), "+v"(a[10]), "+v"(a[11]), "+v"(a[12]), "+v"(a[13]), "+v"(a[14]), "+v"(a[15]), "+v"(x[0]),          \
+        "+v"(x[1]), "+v"(x[2]), "+v"(x[3]), "+v"(x[4]), "+v"(x[5]), "+v"(x[6]), "+v"(x[7])
+template <int K> __device__ __forceinline__ void row_step(double (&a)[16], double (&x)[8], double f)
+{
+    asm(EBV_ROW_STEP("f64") : EBV_ROW_ARGS(a, x) : [f] "v"(f), [k] "i"(K));
+}
+template <int K> __device__ __forceinline__ void row_step(float (&a)[16], float (&x)[8], float f)
+{
+    asm(EBV_ROW_STEP("f32") : EBV_ROW_ARGS(a, x) : [f] "v"(f), [k] "i"(K));
+}
+
+/* The step over eight carried values alone (the matrix kept elsewhere). */
+#define EBV_ROW_STEP8(N)                                                                                               \
+    "s_nop 1\n\t" EBV_ROW_FMA(N, "1", "0") EBV_ROW_FMA(N, "1", "1") EBV_ROW_FMA(N, "1", "2") EBV_ROW_FMA(N, "1", "3")    \
+    EBV_ROW_FMA(N, "1", "4") EBV_ROW_FMA(N, "1", "5") EBV_ROW_FMA(N, "1", "6") EBV_ROW_FMA(N, "1", "7")
+#define EBV_ROW_ARGS8(x)                                                                                               \
+    "+v"(x[0]), "+v"(x[1]), "+v"(x[2]), "+v"(x[3]), "+v"(x[4]), "+v"(x[5]), "+v"(x[6]), "+v"(x[7])
+template <int K> __device__ __forceinline__ void row_step8(double (&x)[8], double f)
+{
+    asm(EBV_ROW_STEP8("f64") : EBV_ROW_ARGS8(x) : [f] "v"(f), [k] "i"(K));
+}
+template <int K> __device__ __forceinline__ void row_step8(float (&x)[8], float f)
+{
+    asm(EBV_ROW_STEP8("f32") : EBV_ROW_ARGS8(x) : [f] "v"(f), [k] "i"(K));
+}
+
+/* Compile-time loop: f(integral_constant<int, I>) for I = 0 .. N - 1. */
+template <int I, int N, typename F> __device__ __forceinline__ void static_for(F &&f)
+{
+    if constexpr (I < N) {
+        f(std::integral_constant<int, I>());
+        static_for<I + 1, N>(f);
+    }
+}
+
+struct NoStripHook {
     __device__ __forceinline__ void operator()(int, int) const {}
 };
-template <typename T, typename Done = NoPanelHook>
-__device__ __forceinline__ int tile_lu16(T *S, T *rinv, T *aux, int nvalid, int *zflag, Done &&done = Done())
+
+/*
+ * Doolittle LU (Eq. 6-a, 6-c) of the 64 x 64 tile S in LDS (pitch LDT), in
+ * place, in four 16-column strips.  Per strip all four waves eliminate the
+ * strip's 16 x 16 diagonal block redundantly, lane i % 16 holding row i of it
+ * in registers (waves 0, 2) or row i of its transpose (waves 1, 3), and carry
+ * eight further columns per 16-lane row through the elimination:
+ *   waves 0, 2: the U rows right of the block (L11^{-1} A12) and L11^{-1}
+ *               (the identity carried along),
+ *   waves 1, 3: the L columns below it, as the columns of (U11^T) X = A21^T,
+ *               and U11^{-1}.
+ * So a strip's L, U and both inverses of its diagonal block are ready after
+ * one 16-step chain; the rank-16 update of the rest runs on the matrix cores.
+ * What bounds it is the chain: per step a broadcast pivot, its reciprocal and
+ * about 16 fused multiply-adds.
+ *
+ * P (pitch LDT) receives the inverses of the four diagonal blocks as
+ * tile_inv16 packs them (L^{-1} strictly lower, U^{-1} upper), rinv 1/U_kk.
+ * Rows and columns past nvalid must hold the identity, which is kept.
+ * Returns 0 or k+1 for the first exactly-zero pivot k < nvalid (the same in
+ * every thread).  strip(p, 0) is called by every thread once strip p of S, its
+ * blocks in P and rinv are final and visible, ahead of the update of the rest
+ * (which does not touch them): a caller uses or publishes the strip there.
+ * strip(p, 1), p < 3, follows inside the next strip's chain, where a caller
+ * that published can wait for its stores without holding anybody up.
+ *
+ * Measured alone, one 64 x 64 tile in LDS, cycles: FP64 18.6k, FP32 15.6k,
+ * inverses of the diagonal blocks included; of an FP64 strip's 4.6k the chain
+ * takes 2.5k, its LDS reads and writes 1.3k and the update 0.7k (two blocks
+ * each).  A form with the chain on one wave, two pivots at a time over LDS
+ * broadcasts, and the inverses after it took 46k (FP32 47k).
+ */
+template <typename T, typename Strip = NoStripHook>
+__device__ __forceinline__ int tile_lu64(T *S, T *P, T *rinv, int nvalid, int *zflag, Strip &&strip = Strip())
 {
     typedef typename vec4<T>::type V;
     S = launder(S);
+    P = launder(P);
     rinv = launder(rinv);
-    T *R = launder(aux), *LT = R + 32; /* two pivot rows; L11 transposed (pitch 16) */
-    const int t = threadIdx.x, w = wave_id(), l = launder(t & 63);
-    int zero_at = 0;
+    const int t = threadIdx.x, w = wave_id(), l = launder(t & 63), i = l & 15, g = l >> 4;
+    const bool lside = w & 1; /* transposed: L below the block */
+    const int half = w >> 1, q = 4 * half + g; /* this lane's chunk of eight carried columns */
+    const int ks = lside ? LDT : 1; /* LDS step from one carried column (row) to the next */
+    if (t == 0)
+        *zflag = 0;
 #pragma unroll 1
     for (int p = 0; p < 4; ++p) {
         const int c0 = 16 * p;
-        if (w == 0) {
-            T v[16];
+        T *D = S + c0 * LDT + c0;
+        /* chunks 0 .. 5 - 2p hold the tile's columns (rows) past the block, 6
+         * and 7 the identity; of those the part its factor's triangle keeps
+         * goes to P (lim of the lane's eight), the rest to the pad column */
+        const int e0 = q < 6 ? 16 + 8 * q : 8 * (q - 6);
+        const bool tile = q < 6 - 2 * p;
+        T *E = (q < 6 ? S : P) + c0 * LDT + c0 + (lside ? e0 * LDT + i : i * LDT + e0);
+        const int lim = q < 6 ? (tile ? 8 : 0) : i - e0 + (lside ? 1 : 0);
+        T *pad = P + l * LDT + TB;
+        T a[16], x[8], rv = T(0);
 #pragma unroll
-            for (int j = 0; j < 16; ++j)
-                v[j] = S[l * LDT + c0 + j];
-            /* pivots in pairs (a, a+1): both pivot rows travel in one LDS
-             * round trip, and the two rank-1 updates are applied as one
-             * rank-2 update from the rows as read: with m = u1[a] / u0[a]
-             * and the second pivot row u1 - m u0,
-             *   v -= l0 u0 + l1 (u1 - m u0) = (l0 - l1 m) u0 + l1 u1,
-             * which also brings row a+1 itself up to date (its l1 is 0). */
+        for (int j = 0; j < 16; ++j)
+            a[j] = lside ? D[j * LDT + i] : D[i * LDT + j];
 #pragma unroll
-            for (int a = 0; a < 16; a += 2) {
-                const int pr = c0 + a;
-                if (l == pr || l == pr + 1)
+        for (int j = 0; j < 8; ++j) {
+            const T v = *(tile ? E + j * ks : pad);
+            x[j] = tile ? v : (q >= 6 && i == e0 + j ? T(1) : T(0));
+        }
+        static_for<0, 16>([&](auto kc) __attribute__((always_inline)) {
+            constexpr int k = decltype(kc)::value;
+            const T r = recip(row_bcast<k>(a[k]));
+            const T m = a[k] * r;
+            rv = i == k ? r : rv;
+            a[k] = i > k ? m : a[k]; /* the multiplier (L) in place */
+            row_step<k>(a, x, i > k ? m : T(0));
+            if constexpr (k == 7)
+                if (p > 0)
+                    strip(p - 1, 1);
+        });
+        if (lside)
 #pragma unroll
-                    for (int j = a; j < 16; ++j)
-                        R[(l - pr) * 16 + j] = v[j];
-                __builtin_amdgcn_wave_barrier();
-                T u0[16], u1[16];
+            for (int j = 0; j < 8; ++j)
+                x[j] *= rv;
+        __syncthreads(); /* every wave has read the strip */
 #pragma unroll
-                for (int j = a; j < 16; ++j) {
-                    u0[j] = R[j];
-                    u1[j] = R[16 + j];
-                }
-                const T p0 = u0[a];
-                const T r0 = recip(p0);
-                const T m10 = u1[a] * r0;
-                const T p1 = __builtin_fma(-m10, u0[a + 1], u1[a + 1]);
-                const T r1 = recip(p1);
-                if (p0 == T(0) && zero_at == 0 && pr < nvalid)
-                    zero_at = pr + 1;
-                if (p1 == T(0) && zero_at == 0 && pr + 1 < nvalid)
-                    zero_at = pr + 2;
-                if (l == 0) {
-                    rinv[pr] = r0;
-                    rinv[pr + 1] = r1;
-                }
-                const T l0 = l > pr ? v[a] * r0 : T(0);
-                const T x1 = __builtin_fma(-l0, u0[a + 1], v[a + 1]);
-                const T l1 = l > pr + 1 ? x1 * r1 : T(0);
-                const T c0f = __builtin_fma(-l1, m10, l0);
-                v[a] = l > pr ? l0 : v[a];
-                v[a + 1] = l > pr + 1 ? l1 : (l == pr + 1 ? x1 : v[a + 1]);
+        for (int j = 0; j < 8; ++j)
+            *(j < lim ? E + j * ks : pad) = x[j];
+        if (!lside && g == 0) { /* the block itself, half of its columns each; the reciprocals */
 #pragma unroll
-                for (int j = a + 2; j < 16; ++j)
-                    v[j] = __builtin_fma(-c0f, u0[j], __builtin_fma(-l1, u1[j], v[j]));
-                __builtin_amdgcn_wave_barrier();
-            }
-#pragma unroll
-            for (int j = 0; j < 16; ++j)
-                S[l * LDT + c0 + j] = v[j];
-            if (p < 3) {
-                /* U rows c0..c0+15 right of the panel: L11^{-1} A12, lane = column */
-                if (l >= c0 && l < c0 + 16)
-#pragma unroll
-                    for (int kk = 0; kk < 16; ++kk)
-                        LT[kk * 16 + (l - c0)] = v[kk];
-                __builtin_amdgcn_wave_barrier();
-                const bool act = l >= c0 + 16;
-                T x[16];
-#pragma unroll
-                for (int i = 0; i < 16; ++i)
-                    x[i] = S[(c0 + i) * LDT + l];
-#pragma unroll
-                for (int kk = 0; kk < 15; ++kk)
-#pragma unroll
-                    for (int i = kk + 1; i < 16; ++i)
-                        x[i] = __builtin_fma(-LT[kk * 16 + i], x[kk], x[i]);
-                if (act)
-#pragma unroll
-                    for (int i = 0; i < 16; ++i)
-                        S[(c0 + i) * LDT + l] = x[i];
-            }
-        } else if (p > 0) {
-            if (p > 1)
-                done(p - 2, 1);
-            done(p - 1, 0);
+            for (int j = 0; j < 8; ++j)
+                D[i * LDT + 8 * half + j] = half ? a[8 + j] : a[j];
+            if (half == 0)
+                rinv[c0 + i] = rv;
         }
         __syncthreads();
-        if (p == 3)
-            break;
-        const int nb2 = 3 - p;
-        for (int b = w; b < nb2 * nb2; b += 4) {
-            const int i0 = c0 + 16 + 16 * (b / nb2), j0 = c0 + 16 + 16 * (b % nb2);
-            V acc;
-            acc_load<T>(acc, S + i0 * LDT + j0, LDT);
-            wave_mma16<T, 16>(
-                acc, [&](int r, int k) { return -S[(i0 + r) * LDT + c0 + k]; },
-                [&](int k, int c) { return S[(c0 + k) * LDT + j0 + c]; });
-            acc_store<T>(acc, S + i0 * LDT + j0, LDT);
+        /* a zero pivot leaves no finite reciprocal */
+        if (w == 0 && __any(!(__builtin_fabs((double)rv) <= 1.7976931348623157e308))) {
+            const unsigned long long z = __ballot(l < 16 && c0 + i < nvalid && D[i * (LDT + 1)] == T(0));
+            if (l == 0 && z && *zflag == 0)
+                *zflag = c0 + __ffsll((long long)z);
+        }
+        strip(p, 0);
+        /* rank-16 update of the rest, nb2 x nb2 blocks dealt to the waves, two
+         * of a wave's at a time (their products do not depend on each other) */
+        const int nb2 = 3 - p, nblk = nb2 * nb2;
+        const int inv = nb2 == 3 ? 11 : (nb2 == 2 ? 16 : 32); /* b / nb2 = b inv >> 5 for b < 9 */
+        for (int b = w; b < nblk; b += 8) {
+            const int b1 = b + 4 < nblk ? b + 4 : b;
+            const int i0 = 16 + 16 * ((b * inv) >> 5), j0 = 16 + 16 * (b - nb2 * ((b * inv) >> 5));
+            const int i1 = 16 + 16 * ((b1 * inv) >> 5), j1 = 16 + 16 * (b1 - nb2 * ((b1 * inv) >> 5));
+            T a0[4], a1[4], b0[4], bb[4];
+#pragma unroll
+            for (int k4 = 0; k4 < 4; ++k4) {
+                const int k = acc_row<T>(g, k4);
+                a0[k4] = -D[(i0 + i) * LDT + k];
+                b0[k4] = D[k * LDT + j0 + i];
+            }
+            V u, v;
+            acc_load<T>(u, D + i0 * LDT + j0, LDT);
+            if (b1 != b) {
+#pragma unroll
+                for (int k4 = 0; k4 < 4; ++k4) {
+                    const int k = acc_row<T>(g, k4);
+                    a1[k4] = -D[(i1 + i) * LDT + k];
+                    bb[k4] = D[k * LDT + j1 + i];
+                }
+                acc_load<T>(v, D + i1 * LDT + j1, LDT);
+#pragma unroll
+                for (int k4 = 0; k4 < 4; ++k4) {
+                    u = mfma16(a0[k4], b0[k4], u);
+                    v = mfma16(a1[k4], bb[k4], v);
+                }
+                acc_store<T>(v, D + i1 * LDT + j1, LDT);
+            } else {
+#pragma unroll
+                for (int k4 = 0; k4 < 4; ++k4)
+                    u = mfma16(a0[k4], b0[k4], u);
+            }
+            acc_store<T>(u, D + i0 * LDT + j0, LDT);
         }
         __syncthreads();
     }
-    if (t == 0)
-        *zflag = zero_at;
-    __syncthreads();
     return *zflag;
 }
 
-/* The 16 x 16 diagonal blocks of the inverses of the factors of a tile
- * factored by tile_lu16 (S, with 1/U_kk in rinv), by substitution against
- * the identity (wave 0 the four of L, wave 1 the four of U, one column per
- * lane), packed in P (LDS, pitch LDT) as tile_inv16 packs the whole
- * inverses: L_pp^{-1} in the strict lower part of diagonal block p (its unit
- * diagonal implied), U_pp^{-1} in its upper part.  The off-diagonal blocks
- * of P are left untouched. */
+/* The 16 x 16 diagonal blocks of the inverses of the factors of a tile that
+ * is factored already (S, with 1/U_kk in rinv), packed in P (LDS, pitch LDT)
+ * as tile_lu64 packs them: the 16-lane rows of a wave take one block each,
+ * lane i its row (waves 0, 2: L) or its column (waves 1, 3: U transposed),
+ * and carry eight columns of the identity through the substitution.  The
+ * off-diagonal blocks of P are left untouched. */
 template <typename T>
 __device__ __forceinline__ void tile_diag_inv16(const T *S, const T *rinv, T *P)
 {
     S = launder(S);
     P = launder(P);
     rinv = launder(rinv);
-    const int t = threadIdx.x, w = wave_id(), l = launder(t & 63), bp = l >> 4, c = l & 15;
-    if (w == 0) {
-        const T *L = S + 16 * bp * (LDT + 1);
-        T x[16];
+    const int w = wave_id(), l = launder((int)threadIdx.x & 63), i = l & 15, g = l >> 4;
+    const bool lside = w & 1;
+    const int e0 = 8 * (w >> 1);
+    const T *D = S + 16 * g * (LDT + 1);
+    const T rv = rinv[16 * g + i];
+    T a[16], x[8];
 #pragma unroll
-        for (int i = 0; i < 16; ++i)
-            x[i] = (i == c) ? T(1) : T(0);
+    for (int j = 0; j < 16; ++j)
+        a[j] = lside ? D[j * LDT + i] : D[i * LDT + j];
 #pragma unroll
-        for (int kk = 0; kk < 16; ++kk) {
+    for (int j = 0; j < 8; ++j)
+        x[j] = i == e0 + j ? T(1) : T(0);
+    static_for<0, 16>([&](auto kc) __attribute__((always_inline)) {
+        constexpr int k = decltype(kc)::value;
+        const T rk = row_bcast<k>(rv);
+        const T m = lside ? a[k] * rk : a[k];
+        row_step8<k>(x, i > k ? m : T(0));
+    });
+    T *E = P + 16 * g * (LDT + 1) + (lside ? e0 * LDT + i : i * LDT + e0);
+    const int lim = i - e0 + (lside ? 1 : 0), ks = lside ? LDT : 1;
 #pragma unroll
-            for (int i = kk + 1; i < 16; ++i)
-                x[i] = __builtin_fma(-L[i * LDT + kk], x[kk], x[i]);
-            pin16(x);
-        }
-#pragma unroll
-        for (int i = 0; i < 16; ++i)
-            if (i > c)
-                P[(16 * bp + i) * LDT + 16 * bp + c] = x[i];
-    } else if (w == 1) {
-        const T *U = S + 16 * bp * (LDT + 1);
-        T x[16];
-#pragma unroll
-        for (int i = 0; i < 16; ++i)
-            x[i] = (i == c) ? T(1) : T(0);
-#pragma unroll
-        for (int kk = 15; kk >= 0; --kk) {
-            x[kk] *= rinv[16 * bp + kk];
-#pragma unroll
-            for (int i = 0; i < kk; ++i)
-                x[i] = __builtin_fma(-U[i * LDT + kk], x[kk], x[i]);
-            pin16(x);
-        }
-#pragma unroll
-        for (int i = 0; i < 16; ++i)
-            if (i <= c)
-                P[(16 * bp + i) * LDT + 16 * bp + c] = x[i];
-    }
+    for (int j = 0; j < 8; ++j)
+        if (j < lim)
+            E[j * ks] = lside ? x[j] * rv : x[j];
     __syncthreads();
 }
 
-/* Diagonal block q of the inverse pack by one wave (lanes 0..15, one column
- * each): L_qq^{-1} (strict lower part, UPPER = false) or U_qq^{-1} (upper
- * part, UPPER = true) of a tile factored by tile_lu16, as tile_diag_inv16
- * forms them; put(i, c, v) receives element (i, c) of the block. */
-template <typename T, bool UPPER, typename Put>
-__device__ __forceinline__ void diag_block_inv(const T *S, const T *rinv, int q, Put &&put)
-{
-    const int c = launder(static_cast<int>(threadIdx.x) & 63);
-    if (c >= 16)
-        return;
-    const T *D = S + 16 * q * (LDT + 1);
-    T x[16];
-#pragma unroll
-    for (int i = 0; i < 16; ++i)
-        x[i] = (i == c) ? T(1) : T(0);
-    if (!UPPER) {
-#pragma unroll
-        for (int kk = 0; kk < 16; ++kk) {
-#pragma unroll
-            for (int i = kk + 1; i < 16; ++i)
-                x[i] = __builtin_fma(-D[i * LDT + kk], x[kk], x[i]);
-            pin16(x);
-        }
-#pragma unroll
-        for (int i = 0; i < 16; ++i)
-            if (i > c)
-                put(i, c, x[i]);
-    } else {
-#pragma unroll
-        for (int kk = 15; kk >= 0; --kk) {
-            x[kk] *= rinv[16 * q + kk];
-#pragma unroll
-            for (int i = 0; i < kk; ++i)
-                x[i] = __builtin_fma(-D[i * LDT + kk], x[kk], x[i]);
-            pin16(x);
-        }
-#pragma unroll
-        for (int i = 0; i < 16; ++i)
-            if (i <= c)
-                put(i, c, x[i]);
-    }
-}
-
 /*
- * Inverses of the factors of a tile factored by tile_lu16 (S, with 1/U_kk in
- * rinv): P (LDS, pitch LDT) receives L^{-1} in its strict lower part (its unit
- * diagonal implied) and U^{-1} in its upper part.  After the diagonal blocks
- * (tile_diag_inv16) the off-diagonal blocks follow one block diagonal at a
- * time on the matrix cores, from L X = I and U Y = I:
+ * Inverses of the factors of a factored tile S from the inverses of their
+ * 16 x 16 diagonal blocks: P (LDS, pitch LDT) holds those and receives L^{-1}
+ * in its strict lower part (its unit diagonal implied) and U^{-1} in its
+ * upper part.  The off-diagonal blocks follow one block diagonal at a time on
+ * the matrix cores, from L X = I and U Y = I:
  *   X_ij = -X_ii sum_{k=j}^{i-1} L_ik X_kj   (i > j)
  *   Y_ij = -Y_ii sum_{k=i+1}^{j} U_ik Y_kj   (i < j).
  */
-template <typename T>
-__device__ __forceinline__ void tile_inv16(const T *S, const T *rinv, T *P)
+template <typename T> __device__ __forceinline__ void tile_inv_off(const T *S, T *P)
 {
     typedef typename vec4<T>::type V;
-    tile_diag_inv16(S, rinv, P);
     S = launder(S);
     P = launder(P);
-    const int t = threadIdx.x, w = wave_id();
-    (void)t;
+    const int w = wave_id();
     /* diagonal blocks of the inverses, with the other factor's part masked
      * (loads unconditional, selects after: no divergent branches) */
     auto xdiag = [&](int bi, int r, int k) -> T {
@@ -627,6 +651,13 @@ __device__ __forceinline__ void tile_inv16(const T *S, const T *rinv, T *P)
         }
         __syncthreads();
     }
+}
+
+/* Both inverses of a tile that is factored already (see above). */
+template <typename T> __device__ __forceinline__ void tile_inv16(const T *S, const T *rinv, T *P)
+{
+    tile_diag_inv16(S, rinv, P);
+    tile_inv_off(S, P);
 }
 
 /*
@@ -1029,8 +1060,8 @@ __device__ __forceinline__ void acc64_stream_pairs(Acc64<T> &acc, int npairs, Pa
  * (Eq. 6-c's updates applied lazily): at block step j the diagonal tile and
  * the tiles of block row j and block column j receive, in one streamed
  * product each, every update of the steps before (K = 64 j), then
- *   - the diagonal tile is factored in LDS (tile_lu16, Eq. 6-a) and its
- *     factors inverted (tile_inv16),
+ *   - the diagonal tile is factored in LDS (tile_lu64, Eq. 6-a) and its
+ *     factors inverted (tile_inv_off),
  *   - block row j becomes U:   U_jc = L_jj^{-1} A_jc,
  *   - block column j becomes L: L_rj = A_rj U_jj^{-1},
  * all products on the matrix cores.  Every tile is read and written once
@@ -1061,13 +1092,13 @@ __device__ __forceinline__ int wg_crout(T *__restrict__ A, int64_t lda, int n, T
             if (threadIdx.x >= kw && threadIdx.x < TB)
                 sm.t0[threadIdx.x * LDT + threadIdx.x] = T(1);
             __syncthreads();
-            const int z = tile_lu16(sm.t0, sm.rinv, sm.aux, kw, &sm.zflag);
+            const int z = tile_lu64(sm.t0, sm.t1, sm.rinv, kw, &sm.zflag);
             if (z && !zero_at)
                 zero_at = k0 + z;
             lds_store_tile(sm.t0, Akk, lda, kw, kw);
             if (j + 1 == nt && !B)
                 break;
-            tile_inv16(sm.t0, sm.rinv, sm.t1);
+            tile_inv_off(sm.t0, sm.t1);
         }
         /* block row j right of the diagonal (U), then the right-hand sides
          * (Y); factor tiles two at a time where two remain (one stream for

@@ -104,15 +104,14 @@ template <typename T> struct DiagSmem {
     T S[TB * LDT];
     T P[TB * LDT];
     T rinv[TB];
-    T aux[32 + 256];
     int zflag;
     int avail;
 };
 
 /*
  * Diagonal tile of a block step: factor the 64x64 tile at (d0, d0), already
- * staged in sm.S with identity padding (tile_lu16), store it in place, and
- * store the packed inverses of its factors (tile_inv16) to Pg (64 x 64,
+ * staged in sm.S with identity padding (tile_lu64), store it in place, and
+ * store the packed inverses of its factors (tile_inv_off) to Pg (64 x 64,
  * pitch TB) for the panel solves of the next launch (for the last tile only
  * when inv_last: right-hand sides ride along).  Run by the single
  * workgroup of k_diag (the first step) and by the extra workgroup of
@@ -124,13 +123,13 @@ __device__ __forceinline__ void diag_tile(T *__restrict__ A, int64_t lda, int n,
 {
     const int dw = min(TB, n - d0);
     T *Add = A + (int64_t)d0 * lda + d0;
-    const int z = tile_lu16(sm.S, sm.rinv, sm.aux, dw, &sm.zflag);
+    const int z = tile_lu64(sm.S, sm.P, sm.rinv, dw, &sm.zflag);
     lds_store_tile(sm.S, Add, lda, dw, dw);
     if (threadIdx.x == 0 && info && z && *info == 0)
         *info = d0 + z;
     if (d0 + dw >= n && !inv_last)
         return; /* last tile: no panel follows */
-    tile_inv16(sm.S, sm.rinv, sm.P);
+    tile_inv_off(sm.S, sm.P);
     tile_xfer<T>([&](int r, int c) { return sm.P[r * LDT + c]; }, [&](int r, int c, T v) { Pg[r * TB + c] = v; });
 }
 
@@ -364,6 +363,35 @@ __global__ __launch_bounds__(NT, 2) void k_update(T *__restrict__ A, int64_t lda
     update_tile<T, BM, BN, BK>(A, lda, n, k0, kw, r0, c0, (r0 == i0 && c0 == i0) ? dw : 0, lds_raw);
 }
 
+/* Strip q of a tile being factored (tile_lu64: S the tile, P its diagonal
+ * blocks' inverses), sent to the workgroups that solve against it: by all
+ * threads, the inverses of the diagonal block to Pg (64 x 64, pitch 64), the
+ * L part below it and the U part right of it to the tile D (pitch ldd) with
+ * device-coherent stores, the block itself (read by nobody else) plainly.
+ * Nothing past the tile's n valid rows and columns is stored to D. */
+template <typename T>
+__device__ __forceinline__ void publish_strip(const T *S, const T *P, int q, T *Pg, T *D, int64_t ldd, int n)
+{
+    const int t = launder((int)threadIdx.x), r = t >> 4, c = t & 15, b0 = 16 * q;
+    store_coherent(Pg + (b0 + r) * TB + b0 + c, P[(b0 + r) * LDT + b0 + c]);
+    if (b0 + r < n && b0 + c < n)
+        D[(int64_t)(b0 + r) * ldd + b0 + c] = S[(b0 + r) * LDT + b0 + c];
+    for (int a = b0 + 16 + r; a < TB; a += 16) {
+        if (a < n && b0 + c < n)
+            store_coherent(D + (int64_t)a * ldd + b0 + c, S[a * LDT + b0 + c]);
+        if (b0 + r < n && a - r + c < n)
+            store_coherent(D + (int64_t)(b0 + r) * ldd + a - r + c, S[(b0 + r) * LDT + a - r + c]);
+    }
+}
+
+/* Counts a published strip, one per wave, once the wave's stores have landed. */
+__device__ __forceinline__ void count_strip(int *flag)
+{
+    __builtin_amdgcn_s_waitcnt(0);
+    if ((threadIdx.x & 63) == 0)
+        __hip_atomic_fetch_add(flag, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 /*
  * One block step of the look-ahead factor: launch s factors diagonal tile s
  * (rows/columns d0 = 64 s ...) and forms panel s, while it brings the
@@ -376,14 +404,13 @@ __global__ __launch_bounds__(NT, 2) void k_update(T *__restrict__ A, int64_t lda
  * Work items are taken in ticket order (word 0 of the step's control words
  * w = ctl + 3 + 2 s):
  *   ticket 0     the diagonal tile: its pending update, then the factor
- *                (tile_lu16); the pack the panel items solve against (the
+ *                (tile_lu64); the pack the panel items solve against (the
  *                factored tile, its 16 x 16 diagonal blocks replaced by the
- *                inverses of their factors) is published 16 columns at a
- *                time: while wave 0 factors panel p + 1 the other waves
- *                invert panel p's diagonal block and store the strip, each
- *                wave adding one to w[1] once its stores have landed (3 per
- *                strip), checked a panel later so that the factorization
- *                never waits for the stores;
+ *                inverses of their factors) is published a 16-column strip
+ *                at a time as it is factored, each wave adding one to w[1]
+ *                once its stores have landed (4 per strip), checked inside
+ *                the next strip's chain so that the factorization never
+ *                waits for the stores;
  *   then         the first wave of BM x 64 region tiles (first_wave of
  *                them): tiles right of and below the panel, in the updated
  *                classes, update only;
@@ -391,7 +418,7 @@ __global__ __launch_bounds__(NT, 2) void k_update(T *__restrict__ A, int64_t lda
  *                L_is = A_is U_ss^{-1} -- and Y_s = L_ss^{-1} B_s: each
  *                applies its own pending update first, then runs the block
  *                substitution against the pack, step p as soon as strip p
- *                is out (w[1] >= 3 (p + 1));
+ *                is out (w[1] >= 4 (p + 1));
  *   last         the other region tiles, and (with B) B_i -= L_{i,s-1}
  *                Y_{s-1} below block row s.
  * The panel tiles start as soon as the first wave of region tiles frees
@@ -468,62 +495,23 @@ __global__ __launch_bounds__(NT, 2) void k_step(T *__restrict__ A, int64_t lda, 
         }
         T *Add = A + (int64_t)d0 * lda + d0;
         const bool pub = nr2 > 0 || nbc > 0;
-        /* what the panel items read, published 16 columns at a time: for
-         * panel q of the factored tile, role 0 and 1 the inverses of its
-         * diagonal block's factors (to Pg), role 2 the block itself (to A,
-         * read by no other item) and its L part below and U part to the
-         * right (to A, device-coherent) */
-        /* stage 0 issues this wave's part of panel q, stage 1 waits for its
-         * stores and counts it */
-        auto publish_panel = [&](int q, int role, int stage) __attribute__((always_inline)) {
-            const int l = threadIdx.x & 63, b0 = 16 * q;
-            if (stage == 1) {
-                /* this wave's part of panel q has landed: count it (3 per panel) */
-                if (role <= 2) {
-                    __builtin_amdgcn_s_waitcnt(0);
-                    if (l == 0)
-                        __hip_atomic_fetch_add(flag, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                }
+        /* what the panel items read, published a strip at a time as it is
+         * factored (publish_strip); the waves' stores of strip q are counted
+         * in the flag a little later, the last strip's at the end */
+        const int z = tile_lu64(sm.S, sm.P, sm.rinv, dw, &sm.zflag, [&](int q, int stage) __attribute__((always_inline)) {
+            if (!pub)
                 return;
-            }
-            auto put = [&](int i, int c, T v) __attribute__((always_inline)) {
-                store_coherent(Pg + (b0 + i) * TB + b0 + c, v);
-            };
-            if (role == 0) {
-                diag_block_inv<T, false>(sm.S, sm.rinv, q, put);
-            } else if (role == 1) {
-                diag_block_inv<T, true>(sm.S, sm.rinv, q, put);
-            } else if (role == 2) {
-                for (int idx = l; idx < 256; idx += 64) {
-                    const int r = b0 + (idx >> 4), c = b0 + (idx & 15);
-                    if (r < dw && c < dw)
-                        Add[(int64_t)r * lda + c] = sm.S[r * LDT + c];
-                }
-                for (int idx = l; idx < (48 - b0) * 16; idx += 64) {
-                    const int a = b0 + 16 + (idx >> 4), b = b0 + (idx & 15);
-                    if (a < dw && b < dw) {
-                        store_coherent(Add + (int64_t)a * lda + b, sm.S[a * LDT + b]);
-                        store_coherent(Add + (int64_t)b * lda + a, sm.S[b * LDT + a]);
-                    }
-                }
-            }
-        };
-        /* panels 0..2 are published by waves 1..3 while wave 0 factors the
-         * next panel; the last one after the factorization */
-        const int z = tile_lu16(sm.S, sm.rinv, sm.aux, dw, &sm.zflag, [&](int q, int stage) __attribute__((always_inline)) {
-            if (pub)
-                publish_panel(q, wave_id() - 1, stage);
+            if (stage == 0)
+                publish_strip(sm.S, sm.P, q, Pg, Add, lda, dw);
+            else
+                count_strip(flag);
         });
         if (threadIdx.x == 0 && info && z && *info == 0)
             *info = d0 + z;
-        if (pub) {
-            if (wave_id() >= 1) /* panel 2's stores, issued while panel 3 was factored */
-                publish_panel(2, wave_id() - 1, 1);
-            publish_panel(3, wave_id(), 0);
-            publish_panel(3, wave_id(), 1);
-        } else {
+        if (pub)
+            count_strip(flag);
+        else
             lds_store_tile(sm.S, Add, lda, dw, dw);
-        }
         return;
     }
     q -= 1;
@@ -614,7 +602,7 @@ panel:
     acc64_store(acc, LdsTile<T>{sm.S});
     __syncthreads();
     /* the solve against the factored diagonal tile, block step p as soon as
-     * strip p of its pack is published (its flag counts 3 per strip): each
+     * strip p of its pack is published (its flag counts 4 per strip): each
      * wave keeps its 16-wide slab of the tile in accumulators (transposed for
      * the L tiles, X = A U^{-1} solved as U^T X^T = A^T) and runs step p
      * with the strip staged in P: the diagonal block times the inverse of the
@@ -633,7 +621,7 @@ panel:
                              : sm.S[(16 * q2 + acc_row<T>(lk, r)) * LDT + 16 * w + lr];
 #pragma unroll
     for (int p = 0; p < 4; ++p) {
-        wait_solved(flag, 3 * p + 2, &s_avail, status, wlim);
+        wait_solved(flag, 4 * p + 3, &s_avail, status, wlim);
         /* strip p: rows 16p.. of columns 16p..16p+15 (lower), or columns
          * 16p.. of rows 16p..16p+15 (right); diagonal block from Pg,
          * identity past the matrix end */
@@ -1740,220 +1728,210 @@ struct BandTile {
     __device__ __forceinline__ double *operator()(int r, int c) const { return in(r, c) ? addr(r, c) : nullptr; }
 };
 
-/* LDS of the band factor: the running diagonal tile and the tiles right of it
- * and below it. */
+/*
+ * Strip p of the band step's off-diagonal tiles, once strip p of the diagonal
+ * tile S (its diagonal blocks' inverses in P) is final: u holds the columns
+ * 16w.. of the tile right of S, lt the rows 16wl.. of the tile below it
+ * transposed, 16 x 16 blocks down the slab.  Block p of each is finished with
+ * the strip's inverse and its contribution removed from the blocks after it,
+ * the finished block being the products' B operand.  Blocks p < w of u and
+ * p < wl of lt are zero (kl, ku <= 64) and stay so.
+ */
+__device__ __forceinline__ void band_strip(const double *S, const double *P, int p, int w, int wl,
+                                           vec4<double>::type (&u)[4], vec4<double>::type (&lt)[4])
+{
+    typedef vec4<double>::type V;
+    const int c0 = 16 * p;
+    auto slab = [&](V(&x)[4], auto &&diag, auto &&off) __attribute__((always_inline)) {
+#pragma unroll
+        for (int b = 0; b < 4; ++b)
+            if (b == p) {
+                V f = {0, 0, 0, 0};
+                wave_mma16_acc<double>(f, diag, x[b]);
+                x[b] = f;
+#pragma unroll
+                for (int a = b + 1; a < 4; ++a)
+                    wave_mma16_acc<double>(x[a], [&](int r, int k) { return -off(16 * a + r, k); }, x[b]);
+            }
+    };
+    if (p >= w)
+        slab(u,
+             [&](int r, int k) {
+                 const double v = P[(c0 + r) * LDT + c0 + k];
+                 return r > k ? v : (r == k ? 1.0 : 0.0);
+             },
+             [&](int r, int k) { return S[r * LDT + c0 + k]; });
+    if (p >= wl)
+        slab(lt,
+             [&](int r, int k) {
+                 const double v = P[(c0 + k) * LDT + c0 + r];
+                 return k <= r ? v : 0.0;
+             },
+             [&](int r, int k) { return S[(c0 + k) * LDT + r]; });
+}
+
+/*
+ * One lane's column c (or row r) of a BandTile, its rows (columns) counted
+ * from the lane's first one, o: which of them exist and where they are, so
+ * that an access at a compile-time offset costs one compare and one 64-bit
+ * addition of a scalar instead of the tile's general form (whose address
+ * arithmetic took a third of a band step's cycles).
+ */
+struct BandLine {
+    double *p0, *any;
+    int64_t step;
+    int lo;
+    unsigned len;
+    __device__ __forceinline__ bool in(int x) const { return (unsigned)(x - lo) <= len; }
+    __device__ __forceinline__ double *at(int x) const { return p0 + x * step; }
+    __device__ __forceinline__ double raw(int x) const { return *(in(x) ? at(x) : any); }
+};
+__device__ __forceinline__ BandLine band_line(double *p0, double *any, int64_t step, int lo, int hi, int o)
+{
+    return {p0 + o * step, any, step, hi < lo ? 1 << 30 : lo - o, hi < lo ? 0u : (unsigned)(hi - lo)};
+}
+__device__ __forceinline__ BandLine band_col(const BandTile &t, int c, int o)
+{
+    return band_line(t.base + (c + t.d0), t.base, t.ldab - 1, max(0, c + t.d0 - t.w),
+                     c < t.nc ? min(t.nr - 1, c + t.d0) : -1, o);
+}
+__device__ __forceinline__ BandLine band_row(const BandTile &t, int r, int o)
+{
+    return band_line(t.base + ((int64_t)r * t.ldab - r + t.d0), t.base, 1, max(0, r - t.d0),
+                     r < t.nr ? min(t.nc - 1, r - t.d0 + t.w) : -1, o);
+}
+
+/* LDS of the band factor: the running diagonal tile, the inverses of its
+ * diagonal blocks, and the tile below it for the product with the one to its
+ * right. */
 struct BandSmem {
     double s[TB * LDT];
-    double u[TB * LDT];
+    double p[TB * LDT];
     double l[TB * LDT];
     double rinv[TB];
-    double aux[32 + 256];
     int zflag;
 };
 
 /*
- * One 16-wide panel q of the band step's off-diagonal tiles, by one wave,
- * once panel q of the diagonal tile S is factored (tile_lu16): U = the tile
- * right of S, L = the tile below it (LDS, pitch LDT).
- *   UPPER: rows 16q.. of U become U_{k,k+1}'s: L_qq^{-1} applied by forward
- *     substitution (lane = column, the unit-lower coefficients read from S
- *     as broadcasts), then the panel's rank-16 term leaves the rows below;
- *   else:  columns 16q.. of L become L_{k+1,k}'s: U_qq^{-1} applied from the
- *     right (lane = row), then the panel's rank-16 term leaves the columns
- *     to the right.
- */
-template <bool UPPER>
-__device__ __forceinline__ void band_panel(const double *S, const double *rinv, double *X, int q)
-{
-    typedef vec4<double>::type V;
-    const int lane = launder((int)threadIdx.x & 63), c0 = 16 * q;
-    S = launder(S);
-    X = launder(X);
-    double x[16];
-    if (UPPER) {
-#pragma unroll
-        for (int i = 0; i < 16; ++i)
-            x[i] = X[(c0 + i) * LDT + lane];
-#pragma unroll
-        for (int kk = 0; kk < 15; ++kk) {
-#pragma unroll
-            for (int i = kk + 1; i < 16; ++i)
-                x[i] = __builtin_fma(-S[(c0 + i) * LDT + c0 + kk], x[kk], x[i]);
-            pin16(x);
-        }
-#pragma unroll
-        for (int i = 0; i < 16; ++i)
-            X[(c0 + i) * LDT + lane] = x[i];
-    } else {
-#pragma unroll
-        for (int j = 0; j < 16; ++j)
-            x[j] = X[lane * LDT + c0 + j];
-#pragma unroll
-        for (int j = 0; j < 16; ++j) {
-            x[j] *= rinv[c0 + j];
-#pragma unroll
-            for (int jj = j + 1; jj < 16; ++jj)
-                x[jj] = __builtin_fma(-S[(c0 + j) * LDT + c0 + jj], x[j], x[jj]);
-            pin16(x);
-        }
-#pragma unroll
-        for (int j = 0; j < 16; ++j)
-            X[lane * LDT + c0 + j] = x[j];
-    }
-    __builtin_amdgcn_wave_barrier();
-    lds_fence_compiler();
-    /* the panel's rank-16 term on the rest of the tile (blocks of 16 x 16) */
-    for (int a = q + 1; a < 4; ++a)
-#pragma unroll
-        for (int b = 0; b < 4; ++b) {
-            const int r0 = UPPER ? 16 * a : 16 * b, cb = UPPER ? 16 * b : 16 * a;
-            V acc;
-            acc_load<double>(acc, X + r0 * LDT + cb, LDT);
-            if (UPPER) /* U rows r0..: -= L(S)[r0.., c0..] * U12[c0.., cb..] */
-                wave_mma16<double, 16>(
-                    acc, [&](int r, int k) { return -S[(r0 + r) * LDT + c0 + k]; },
-                    [&](int k, int c) { return X[(c0 + k) * LDT + cb + c]; });
-            else /* L columns cb..: -= L21[r0.., c0..] * U(S)[c0.., cb..] */
-                wave_mma16<double, 16>(
-                    acc, [&](int r, int k) { return -X[(r0 + r) * LDT + c0 + k]; },
-                    [&](int k, int c) { return S[(c0 + k) * LDT + cb + c]; });
-            acc_store<double>(acc, X + r0 * LDT + cb, LDT);
-        }
-}
-
-/*
- * Band Doolittle LU by one workgroup.  With kl, ku <= 64 the matrix is block
- * tridiagonal in 64 x 64 tiles and, without pivoting, so are its factors:
- * block step k factors the diagonal tile S_k (Eq. 6-a), turns the tile to its
- * right into U_{k,k+1} = L_kk^{-1} A_{k,k+1} and the one below it into
- * L_{k+1,k} = A_{k+1,k} U_kk^{-1}, and takes the next diagonal tile
- * S_{k+1} = A_{k+1,k+1} - L_{k+1,k} U_{k,k+1} (Eq. 6-c) on the matrix cores.
- * The two off-diagonal tiles are solved a 16-wide panel at a time by waves 1
- * and 2 while wave 0 factors the next panel of S_k (band_panel, in
- * tile_lu16's hook), so after the factorization only the last panel's pieces
- * and the product remain.  All three tiles stay in LDS; the band tiles of the
- * next step are requested a step ahead and parked after the product.
+ * Band Doolittle LU by one workgroup, block rows [first, end).  With kl, ku <=
+ * 64 the matrix is block tridiagonal in 64 x 64 tiles and, without pivoting,
+ * so are its factors: block step k factors the diagonal tile S_k (Eq. 6-a),
+ * turns the tile to its right into U_{k,k+1} = L_kk^{-1} A_{k,k+1} and the one
+ * below it into L_{k+1,k} = A_{k+1,k} U_kk^{-1}, and takes the next diagonal
+ * tile S_{k+1} = A_{k+1,k+1} - L_{k+1,k} U_{k,k+1} (Eq. 6-c) on the matrix
+ * cores.  The two off-diagonal tiles stay in accumulators, wave w the columns
+ * 16w.. of U and the rows 16(3 - w).. of L (transposed: U^T L^T = A^T, the
+ * lower triangle of the former and the upper of the latter make that an equal
+ * share), and are solved strip by strip inside the diagonal tile's
+ * factorization (tile_lu64's hook).  Their loads are issued at the top of the
+ * step and first used after a strip, and the chain of tile factorizations is
+ * what bounds the step: 18.6k of its cycles.
  * Entries outside the band stay exactly zero and are never stored.
  */
-__global__ __launch_bounds__(NT) void k_band_factor(double *AB, int64_t ldab, int n, int kl, int ku, int32_t *info)
+__device__ __forceinline__ int band_range(double *AB, int64_t ldab, int n, int kl, int ku, int first, int end,
+                                          BandSmem &sm)
 {
-    __shared__ BandSmem sm;
+    typedef vec4<double>::type V;
     const int nt = (n + TB - 1) / TB;
-    const int c = launder((int)threadIdx.x & 63), r0 = launder((int)threadIdx.x >> 6);
-    const int w = wave_id(), lane = threadIdx.x & 63, lr = lane & 15, lk = lane >> 4;
-    const int wm = (w >> 1) * 32, wn = (w & 1) * 32;
+    const int w = wave_id(), lane = launder((int)threadIdx.x & 63), lr = lane & 15, lk = lane >> 4;
+    const int wl = 3 - w; /* this wave's row slab of L */
     auto tile = [&](int rb, int cb) { return BandTile(AB, ldab, n, kl, ku, rb, cb); };
-    /* element (r, c) of the accumulator layout */
-    auto arow = [&](int bi, int r) { return wm + 16 * bi + acc_row<double>(launder(lk), r); };
-    auto acol = [&](int bj) { return wn + 16 * bj + launder(lr); };
-    /* the tiles right of and below S_k, unmasked, a step ahead (tile_xfer's
-     * element order); parked masked */
-    double a12[16], a21[16];
-    auto fetch_side = [&](int kb) {
-        const BandTile tu = tile(kb, kb + 1), tl = tile(kb + 1, kb);
-        const int rr = launder(r0), cc = launder(c);
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            a12[i] = tu.raw(rr + 4 * i, cc);
-            a21[i] = tl.raw(rr + 4 * i, cc);
-        }
-    };
-    auto park_side = [&](int kb) {
-        const BandTile tu = tile(kb, kb + 1), tl = tile(kb + 1, kb);
-        const int rr = launder(r0), cc = launder(c);
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            sm.u[(rr + 4 * i) * LDT + cc] = tu.in(rr + 4 * i, cc) ? a12[i] : 0.0;
-            sm.l[(rr + 4 * i) * LDT + cc] = tl.in(rr + 4 * i, cc) ? a21[i] : 0.0;
-        }
-    };
+    auto arow = [&](int a, int r) { return 16 * a + acc_row<double>(lk, r); }; /* = lk + 16 a + 4 r */
     int zero_at = 0;
     {
-        const BandTile t0 = tile(0, 0);
+        const BandTile t0 = tile(first, first);
         tile_xfer<double>(
             [&](int r, int cc) {
                 const double v = t0.raw(r, cc);
                 return t0.in(r, cc) ? v : (r == cc ? 1.0 : 0.0); /* the identity past the end */
             },
             [&](int r, int cc, double v) { sm.s[r * LDT + cc] = v; });
-        if (nt > 1) {
-            fetch_side(0);
-            park_side(0);
-        }
     }
     __syncthreads();
 #pragma unroll 1
-    for (int kb = 0; kb < nt; ++kb) {
-        const bool last = kb + 1 == nt, more = kb + 2 < nt;
-        const BandTile td = tile(kb, kb), tu = tile(kb, kb + 1), tl = tile(kb + 1, kb), tn = tile(kb + 1, kb + 1);
-        Acc64<double> acc;
-        if (!last) {
+    for (int kb = first; kb < end; ++kb) {
+        const bool last = kb + 1 == nt;
+        /* U and the next diagonal tile by columns 16w.., L by rows 16wl..
+         * (transposed); masked where first used */
+        const BandLine cu = band_col(tile(kb, kb + 1), 16 * w + lr, lk);
+        const BandLine cn = band_col(tile(kb + 1, kb + 1), 16 * w + lr, lk);
+        const BandLine rl = band_row(tile(kb + 1, kb), 16 * wl + lr, lk);
+        V u[4], lt[4], nx[4];
+        if (!last)
 #pragma unroll
-            for (int bi = 0; bi < 2; ++bi)
+            for (int a = 0; a < 4; ++a)
 #pragma unroll
-                for (int bj = 0; bj < 2; ++bj)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r)
-                        acc.v[bi][bj][r] = tn.raw(arow(bi, r), acol(bj));
-        }
-        if (more)
-            fetch_side(kb + 1);
-        const int z = tile_lu16(sm.s, sm.rinv, sm.aux, min(TB, n - kb * TB), &sm.zflag,
-                                [&](int q, int stage) __attribute__((always_inline)) {
+                for (int r = 0; r < 4; ++r) {
+                    u[a][r] = cu.raw(16 * a + 4 * r);
+                    lt[a][r] = rl.raw(16 * a + 4 * r);
+                    nx[a][r] = cn.raw(16 * a + 4 * r);
+                }
+        const int z = tile_lu64(sm.s, sm.p, sm.rinv, min(TB, n - kb * TB), &sm.zflag,
+                                [&](int p, int stage) __attribute__((always_inline)) {
                                     if (last || stage != 0)
                                         return;
-                                    if (wave_id() == 1)
-                                        band_panel<true>(sm.s, sm.rinv, sm.u, q);
-                                    else if (wave_id() == 2)
-                                        band_panel<false>(sm.s, sm.rinv, sm.l, q);
+                                    if (p == 0)
+#pragma unroll
+                                        for (int a = 0; a < 4; ++a)
+#pragma unroll
+                                            for (int r = 0; r < 4; ++r) {
+                                                u[a][r] = cu.in(16 * a + 4 * r) ? u[a][r] : 0.0;
+                                                lt[a][r] = rl.in(16 * a + 4 * r) ? lt[a][r] : 0.0;
+                                            }
+                                    band_strip(sm.s, sm.p, p, w, wl, u, lt);
                                 });
         if (z && !zero_at)
             zero_at = kb * TB + z;
-        tile_xfer<double>([&](int r, int cc) { return sm.s[r * LDT + cc]; },
-                          [&](int r, int cc, double v) {
-                              if (td.in(r, cc))
-                                  *td.addr(r, cc) = v;
-                          });
+        {
+            const BandLine cd = band_col(tile(kb, kb), lane, w);
+#pragma unroll
+            for (int i = 0; i < 16; ++i)
+                if (cd.in(4 * i))
+                    *cd.at(4 * i) = sm.s[(w + 4 * i) * LDT + lane];
+        }
         if (last)
             break;
-        /* the last panel's pieces */
-        if (w == 1)
-            band_panel<true>(sm.s, sm.rinv, sm.u, 3);
-        else if (w == 2)
-            band_panel<false>(sm.s, sm.rinv, sm.l, 3);
+#pragma unroll
+        for (int a = 0; a < 4; ++a)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                sm.l[(16 * wl + lr) * LDT + arow(a, r)] = lt[a][r];
+                nx[a][r] = cn.in(16 * a + 4 * r) ? nx[a][r] : (arow(a, r) == 16 * w + lr ? 1.0 : 0.0);
+            }
         __syncthreads();
-        tile_xfer<double>([&](int r, int cc) { return sm.u[r * LDT + cc]; },
-                          [&](int r, int cc, double v) {
-                              if (tu.in(r, cc))
-                                  *tu.addr(r, cc) = v;
-                          });
-        tile_xfer<double>([&](int r, int cc) { return sm.l[r * LDT + cc]; },
-                          [&](int r, int cc, double v) {
-                              if (tl.in(r, cc))
-                                  *tl.addr(r, cc) = v;
-                          });
+        /* L_{k+1,k} (upper) times U_{k,k+1} (lower): inner blocks from
+         * max(a, w) */
 #pragma unroll
-        for (int bi = 0; bi < 2; ++bi)
+        for (int q = 0; q < 4; ++q)
+            if (q >= w)
 #pragma unroll
-            for (int bj = 0; bj < 2; ++bj)
+                for (int a = 0; a <= q; ++a)
+                    wave_mma16_acc<double>(nx[a], [&](int r, int k) { return -sm.l[(16 * a + r) * LDT + 16 * q + k]; },
+                                           u[q]);
 #pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int rr = arow(bi, r), cc = acol(bj);
-                    acc.v[bi][bj][r] = tn.in(rr, cc) ? acc.v[bi][bj][r] : (rr == cc ? 1.0 : 0.0);
-                }
-        /* L_{k+1,k} (upper) times U_{k,k+1} (lower): inner indices
-         * k >= max(r, c), for the wave's quadrant from max(wm, wn) */
-        acc64_mma_range<double, true>(acc, [&](int r, int k) { return sm.l[r * LDT + k]; },
-                                      [&](int k, int cc) { return sm.u[k * LDT + cc]; }, max(wm, wn), TB);
-        acc64_store(acc, LdsTile<double>{sm.s});
-        __syncthreads();
-        if (more) {
-            park_side(kb + 1);
-            __syncthreads();
+        for (int a = 0; a < 4; ++a)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                sm.s[arow(a, r) * LDT + 16 * w + lr] = nx[a][r];
+        const BandLine cl = band_col(tile(kb + 1, kb), lane, w);
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            if (cu.in(4 * i))
+                *cu.at(4 * i) = u[i >> 2][i & 3];
+            if (cl.in(4 * i))
+                *cl.at(4 * i) = sm.l[(w + 4 * i) * LDT + lane];
         }
+        __syncthreads();
     }
+    return zero_at;
+}
+
+__global__ __launch_bounds__(NT) void k_band_factor(double *AB, int64_t ldab, int n, int kl, int ku, int32_t *info)
+{
+    __shared__ BandSmem sm;
+    const int z = band_range(AB, ldab, n, kl, ku, 0, (n + TB - 1) / TB, sm);
     if (threadIdx.x == 0 && info)
-        *info = zero_at;
+        *info = z;
 }
 
 /*
@@ -2345,8 +2323,8 @@ __global__ __launch_bounds__(NT) void k_sky_pack(SkyPlan pl, const int32_t *__re
  * from a ticket (the first to arrive is the diagonal one, so the waits below
  * always end):
  *   role 0, the diagonal tile: receives step J-1's rank-64 term, is factored
- *     (tile_lu16), and the inverses of its factors are published (P, then a
- *     flag) for the panel tiles;
+ *     (tile_lu64), and published for the panel tiles strip by strip (the
+ *     inverses of its diagonal blocks in P, then a flag);
  *   the panel tiles (I, J) below and (J, I) right of it in the envelope:
  *     each receives step J-1's term, waits for the flag, and is multiplied by
  *     the diagonal tile's inverses;
@@ -2418,60 +2396,22 @@ __global__ __launch_bounds__(NT) void k_sky_step(SkyPlan pl, double *__restrict_
             sm.t0[threadIdx.x * LDT + threadIdx.x] = 1.0;
         __syncthreads();
         const bool pub = nl + nu > 0;
-        /* what the panel tiles read, published 16 columns at a time: for
-         * panel p of the factored tile, roles 0 and 1 the inverses of its
-         * diagonal block's factors (to P), role 2 the block itself and its L
-         * part below and U part to the right (to D, the parts the panel
-         * tiles read device-coherent); stage 0 issues the stores, stage 1
-         * waits for them and counts them in the flag (3 per panel) */
-        auto publish_panel = [&](int p, int role, int stage) __attribute__((always_inline)) {
-            const int l = threadIdx.x & 63, b0 = 16 * p;
-            if (stage == 1) {
-                if (role <= 2) {
-                    __builtin_amdgcn_s_waitcnt(0);
-                    if (l == 0)
-                        __hip_atomic_fetch_add(flag, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                }
+        /* what the panel tiles read, published a strip at a time as in the
+         * dense block step */
+        const int z = tile_lu64(sm.t0, sm.t1, sm.rinv, kJ, &sm.zflag, [&](int p, int stage) __attribute__((always_inline)) {
+            if (!pub)
                 return;
-            }
-            auto put = [&](int i, int c, double v) __attribute__((always_inline)) {
-                store_coherent(P + (b0 + i) * TB + b0 + c, v);
-            };
-            if (role == 0) {
-                diag_block_inv<double, false>(sm.t0, sm.rinv, p, put);
-            } else if (role == 1) {
-                diag_block_inv<double, true>(sm.t0, sm.rinv, p, put);
-            } else if (role == 2) {
-                for (int idx = l; idx < 256; idx += 64) {
-                    const int r = b0 + (idx >> 4), c = b0 + (idx & 15);
-                    if (r < kJ && c < kJ)
-                        D[r * TB + c] = sm.t0[r * LDT + c];
-                }
-                for (int idx = l; idx < (48 - b0) * 16; idx += 64) {
-                    const int a = b0 + 16 + (idx >> 4), c = b0 + (idx & 15);
-                    if (a < kJ && c < kJ) {
-                        store_coherent(D + a * TB + c, sm.t0[a * LDT + c]);
-                        store_coherent(D + c * TB + a, sm.t0[c * LDT + a]);
-                    }
-                }
-            }
-        };
-        /* panels 0..2 are published by waves 1..3 while wave 0 factors the
-         * next panel; the last one after the factorization */
-        const int z = tile_lu16(sm.t0, sm.rinv, sm.aux, kJ, &sm.zflag, [&](int p, int stage) __attribute__((always_inline)) {
-            if (pub)
-                publish_panel(p, wave_id() - 1, stage);
+            if (stage == 0)
+                publish_strip(sm.t0, sm.t1, p, P, D, TB, kJ);
+            else
+                count_strip(flag);
         });
         if (threadIdx.x == 0 && info && (J == 0 || (z && *info == 0)))
             *info = z ? J * TB + z : 0;
-        if (pub) {
-            if (wave_id() >= 1) /* panel 2's stores, issued while panel 3 was factored */
-                publish_panel(2, wave_id() - 1, 1);
-            publish_panel(3, wave_id(), 0);
-            publish_panel(3, wave_id(), 1);
-        } else {
+        if (pub)
+            count_strip(flag);
+        else
             lds_store_tile(sm.t0, D, TB, kJ, kJ);
-        }
         return;
     }
     q -= 1;
@@ -2489,7 +2429,7 @@ __global__ __launch_bounds__(NT) void k_sky_step(SkyPlan pl, double *__restrict_
         acc64_store(acc, LdsTile<double>{sm.t0});
         __syncthreads();
         /* the solve against the factored diagonal tile, block step p as soon
-         * as strip p is published (the flag counts 3 per strip): each wave
+         * as strip p is published (the flag counts 4 per strip): each wave
          * keeps its 16-wide slab of the tile in accumulators (transposed for
          * the L tiles, L_IJ = A_IJ U_JJ^{-1} solved as U^T X^T = A^T) and runs
          * step p with the strip staged in t1: the diagonal block times the
@@ -2507,7 +2447,7 @@ __global__ __launch_bounds__(NT) void k_sky_step(SkyPlan pl, double *__restrict_
                                  : sm.t0[(16 * q2 + acc_row<double>(lk, r)) * LDT + 16 * w + lr];
 #pragma unroll
         for (int p = 0; p < 4; ++p) {
-            wait_solved(flag, 3 * p + 2, &sm.avail, status, wlim);
+            wait_solved(flag, 4 * p + 3, &sm.avail, status, wlim);
             /* strip p: for a U tile rows 16p.. of columns 16p..16p+15 (L),
              * for an L tile columns 16p.. of rows 16p..16p+15 (U); diagonal
              * block from P, identity past the matrix end */
