@@ -71,7 +71,8 @@ enum {
     EBV_OP_BATCHED_MIXED = 6,
     EBV_OP_FACTOR_SOLVE = 7,
     EBV_OP_BAND_SOLVE = 8,
-    EBV_OP_INVERSE = 9
+    EBV_OP_INVERSE = 9,
+    EBV_OP_BAND_SEGMENTS = 10
 };
 
 /* Order in which the workgroups of a ragged batch take its systems. */
@@ -359,18 +360,25 @@ int64_t ebv_noalloc_max_n(void);
  * row-wise: a_ij at AB[i*ldab + (j - i + kl)], ldab >= kl+ku+1.  Slots that
  * fall outside the matrix are ignored.  This build supports
  * 0 <= kl, ku <= 64 (EBV_ERR_UNSUPPORTED otherwise).
- * The factor is one workgroup walking the block-tridiagonal 64 x 64 tile
- * structure; the solve first forms, in parallel, the inverses of the
- * diagonal tiles' factors and copies of the off-diagonal tiles (into ws),
- * then sweeps the 64-row blocks forward and backward, two matrix-core
- * products per block.
+ * The factor is a chain over the block-tridiagonal 64 x 64 tiles, walked by
+ * one workgroup, or, given a workspace, by one workgroup per segment of block
+ * rows: each starts a few block rows early, the diagonal tile it started from
+ * is checked against the one its predecessor ended with, and a segment that
+ * does not agree to the last bits is factored again in order.  The solve
+ * first forms, in parallel, the inverses of the diagonal tiles' factors and
+ * their products with the off-diagonal tiles (into ws), then sweeps the
+ * 64-row blocks forward and backward, one matrix-core product per block, long
+ * bands in segments checked the same way.
  *   info   device int32 or NULL: the factor's zero pivot (1-based) or 0; the
  *          solve sets it to 0.
- *   ws     ebv_workspace_size(EBV_OP_BAND, F64, n, 0, 1) bytes (0: NULL
- *          allowed) for the factor; ebv_workspace_size(EBV_OP_BAND_SOLVE,
- *          F64, n, nrhs, 1) = ceil(n / 64) * 128 KiB for the solve (per
- *          64-row block the inverses of the diagonal tile's factors and the
- *          two off-diagonal band tiles, overwritten).
+ *   ws     the factor: NULL or anything less for the one-workgroup chain
+ *          (EBV_OP_BAND needs 0 bytes), ebv_workspace_size(
+ *          EBV_OP_BAND_SEGMENTS, F64, n, 0, 1) bytes for the segments (0 for
+ *          n <= 960, where they bring nothing; about 112 KiB per 64 rows, a
+ *          copy of the band as tiles); the solve: ebv_workspace_size(
+ *          EBV_OP_BAND_SOLVE, F64, n, nrhs, 1) = ceil(n / 64) * 128 KiB (per
+ *          64-row block the inverses of the diagonal tile's factors, the two
+ *          products and the sweeps' room, overwritten).
  */
 int ebv_lu_factor_band(ebv_handle h, int64_t n, int64_t kl, int64_t ku, double *AB, int64_t ldab,
                        int32_t *info, void *ws, size_t ws_bytes, hipStream_t stream);

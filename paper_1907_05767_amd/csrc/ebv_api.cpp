@@ -357,6 +357,12 @@ size_t ebv_workspace_size(int op, ebv_dtype dtype, int64_t n, int64_t nrhs, int6
         return ebv::factor_ws_bytes(elem, n) + ebv::trsv_xb_bytes(elem, n);
     case EBV_OP_INVERSE:
         return align_up((size_t)((n + 63) / 64) * 64 * 64 * elem);
+    case EBV_OP_BAND_SEGMENTS: {
+        size_t bytes = 0;
+        if (n <= INT32_MAX)
+            (void)ebv::band_ws(nullptr, n, bytes);
+        return align_up(bytes);
+    }
     case EBV_OP_BAND_SOLVE: /* per 64-row block: two inverses, two band tiles */
         return align_up((size_t)((n + 63) / 64) * 4 * 64 * 64 * sizeof(double));
     default:
@@ -940,9 +946,9 @@ int ebv_lu_factor_band(ebv_handle h, int64_t n, int64_t kl, int64_t ku, double *
     int st = ebv_init();
     if (st != EBV_OK)
         return st;
-    if (!ws_ok(ws, ws_bytes, ebv_workspace_size(EBV_OP_BAND, EBV_F64, n, 0, 1)))
-        return EBV_ERR_WORKSPACE;
-    return hip_status(ebv::band_factor(AB, ldab, (int)n, (int)kl, (int)ku, info, stream));
+    /* without (enough of) the segments' workspace: the serial chain */
+    const bool segments = ws_ok(ws, ws_bytes, ebv_workspace_size(EBV_OP_BAND_SEGMENTS, EBV_F64, n, 0, 1));
+    return hip_status(ebv::band_factor(AB, ldab, (int)n, (int)kl, (int)ku, info, segments ? ws : nullptr, stream));
 }
 
 int ebv_lu_solve_band(ebv_handle h, int64_t n, int64_t kl, int64_t ku, int64_t nrhs, const double *AB, int64_t ldab,

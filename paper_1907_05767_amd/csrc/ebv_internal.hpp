@@ -127,7 +127,17 @@ hipError_t batched_run(int count, const int *ns, const int64_t *offA, T *A, cons
 hipError_t batched_mixed_run(int count, const int *ns, const int64_t *offA, const double *A, const int64_t *offB,
                              double *B, const int *order, int32_t *info, int *queue, float *W, float *R32,
                              double *X, int max_iter, double tol, int32_t *iters, int grid, hipStream_t st);
-hipError_t band_factor(double *AB, int64_t ldab, int n, int kl, int ku, int32_t *info, hipStream_t st);
+/* Workspace of the segmented band factor (ws may be null: sizes only): per
+ * segment its first zero pivot, whether its start agreed with its
+ * predecessor's end and both diagonal tiles; then the band as tiles.  bytes =
+ * 0 where the serial chain is used. */
+struct BandWs {
+    int *zero, *ok;
+    double *sstart, *send, *pk;
+};
+BandWs band_ws(void *ws, int64_t n, size_t &bytes);
+/* ws: band_ws(n) bytes or null (the serial chain). */
+hipError_t band_factor(double *AB, int64_t ldab, int n, int kl, int ku, int32_t *info, void *ws, hipStream_t st);
 hipError_t band_solve(const double *AB, int64_t ldab, int n, int kl, int ku, double *B, int64_t ldb, int nrhs,
                       double *P, hipStream_t st);
 template <typename T>

@@ -1812,23 +1812,62 @@ struct BandSmem {
     int zflag;
 };
 
+/* One workgroup's share of a band factorization: block rows first .. end - 1,
+ * started at block row begin <= first (those before first are computed and
+ * dropped).  With pk the tiles are read from there (k_band_pack), else from
+ * the band itself; s0 is the first diagonal tile where it is known (64 x 64,
+ * else A's); sstart and send receive the diagonal tiles that the factor of
+ * block rows first and end starts from (each if not null). */
+struct BandRange {
+    int begin, first, end;
+    const double *pk, *s0;
+    double *sstart, *send;
+};
+
+/* Tiles per block row in k_band_pack's storage: the diagonal one, the one
+ * right of it and the one below it, as a lane of band_range holds them: the
+ * 16 values of lane l of wave w in pairs at ((8w + h) 64 + l) 2. */
+constexpr int kBandPackTiles = 3;
+typedef double d2 __attribute__((ext_vector_type(2)));
+
+__device__ __forceinline__ void band_pack_load(const double *P, vec4<double>::type (&v)[4])
+{
+    const d2 *q = reinterpret_cast<const d2 *>(P) + wave_id() * 512 + (threadIdx.x & 63);
+#pragma unroll
+    for (int h = 0; h < 8; ++h) {
+        const d2 x = q[64 * h];
+        v[h >> 1][2 * (h & 1)] = x[0];
+        v[h >> 1][2 * (h & 1) + 1] = x[1];
+    }
+}
+__device__ __forceinline__ void band_pack_store(double *P, const vec4<double>::type (&v)[4])
+{
+    d2 *q = reinterpret_cast<d2 *>(P) + wave_id() * 512 + (threadIdx.x & 63);
+#pragma unroll
+    for (int h = 0; h < 8; ++h)
+        q[64 * h] = d2{v[h >> 1][2 * (h & 1)], v[h >> 1][2 * (h & 1) + 1]};
+}
+
 /*
- * Band Doolittle LU by one workgroup, block rows [first, end).  With kl, ku <=
- * 64 the matrix is block tridiagonal in 64 x 64 tiles and, without pivoting,
- * so are its factors: block step k factors the diagonal tile S_k (Eq. 6-a),
- * turns the tile to its right into U_{k,k+1} = L_kk^{-1} A_{k,k+1} and the one
- * below it into L_{k+1,k} = A_{k+1,k} U_kk^{-1}, and takes the next diagonal
- * tile S_{k+1} = A_{k+1,k+1} - L_{k+1,k} U_{k,k+1} (Eq. 6-c) on the matrix
- * cores.  The two off-diagonal tiles stay in accumulators, wave w the columns
- * 16w.. of U and the rows 16(3 - w).. of L (transposed: U^T L^T = A^T, the
- * lower triangle of the former and the upper of the latter make that an equal
+ * Band Doolittle LU by one workgroup (see BandRange).  With kl, ku <= 64 the
+ * matrix is block tridiagonal in 64 x 64 tiles and, without pivoting, so are
+ * its factors: block step k factors the diagonal tile S_k (Eq. 6-a), turns
+ * the tile to its right into U_{k,k+1} = L_kk^{-1} A_{k,k+1} and the one below
+ * it into L_{k+1,k} = A_{k+1,k} U_kk^{-1}, and takes the next diagonal tile
+ * S_{k+1} = A_{k+1,k+1} - L_{k+1,k} U_{k,k+1} (Eq. 6-c) on the matrix cores.
+ * The two off-diagonal tiles stay in accumulators, wave w the columns 16w..
+ * of U and the rows 16(3 - w).. of L (transposed: U^T L^T = A^T; the lower
+ * triangle of the former and the upper of the latter make that an equal
  * share), and are solved strip by strip inside the diagonal tile's
  * factorization (tile_lu64's hook).  Their loads are issued at the top of the
- * step and first used after a strip, and the chain of tile factorizations is
- * what bounds the step: 18.6k of its cycles.
- * Entries outside the band stay exactly zero and are never stored.
+ * step and first used after a strip.  Entries outside the band stay exactly
+ * zero and are never stored.  The step is bound by its chain, the tile
+ * factorization (18.6k of 40k cycles): 16.8 us from packed tiles, 20.6 us from
+ * the band itself (address arithmetic and scattered loads), 26 us before the
+ * off-diagonal tiles moved into accumulators.
  */
-__device__ __forceinline__ int band_range(double *AB, int64_t ldab, int n, int kl, int ku, int first, int end,
+template <bool PACKED>
+__device__ __forceinline__ int band_range(double *AB, int64_t ldab, int n, int kl, int ku, const BandRange &R,
                                           BandSmem &sm)
 {
     typedef vec4<double>::type V;
@@ -1836,10 +1875,22 @@ __device__ __forceinline__ int band_range(double *AB, int64_t ldab, int n, int k
     const int w = wave_id(), lane = launder((int)threadIdx.x & 63), lr = lane & 15, lk = lane >> 4;
     const int wl = 3 - w; /* this wave's row slab of L */
     auto tile = [&](int rb, int cb) { return BandTile(AB, ldab, n, kl, ku, rb, cb); };
+    auto packed = [&](int kb, int i) { return R.pk + ((int64_t)kb * kBandPackTiles + i) * TB * TB; };
     auto arow = [&](int a, int r) { return 16 * a + acc_row<double>(lk, r); }; /* = lk + 16 a + 4 r */
     int zero_at = 0;
-    {
-        const BandTile t0 = tile(first, first);
+    if (R.s0) {
+        tile_xfer<double>([&](int r, int c) { return R.s0[r * TB + c]; },
+                          [&](int r, int c, double v) { sm.s[r * LDT + c] = v; });
+    } else if (PACKED) {
+        V d[4];
+        band_pack_load(packed(R.begin, 0), d);
+#pragma unroll
+        for (int a = 0; a < 4; ++a)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                sm.s[arow(a, r) * LDT + 16 * w + lr] = d[a][r];
+    } else {
+        const BandTile t0 = tile(R.begin, R.begin);
         tile_xfer<double>(
             [&](int r, int cc) {
                 const double v = t0.raw(r, cc);
@@ -1848,29 +1899,43 @@ __device__ __forceinline__ int band_range(double *AB, int64_t ldab, int n, int k
             [&](int r, int cc, double v) { sm.s[r * LDT + cc] = v; });
     }
     __syncthreads();
+    auto save_tile = [&](double *G) {
+        tile_xfer<double>([&](int r, int c) { return sm.s[r * LDT + c]; },
+                          [&](int r, int c, double v) { G[r * TB + c] = v; });
+    };
 #pragma unroll 1
-    for (int kb = first; kb < end; ++kb) {
-        const bool last = kb + 1 == nt;
+    for (int kb = R.begin; kb < R.end; ++kb) {
+        const bool last = kb + 1 == nt, own = kb >= R.first;
+        if (kb == R.first && R.sstart)
+            save_tile(R.sstart);
         /* U and the next diagonal tile by columns 16w.., L by rows 16wl..
-         * (transposed); masked where first used */
+         * (transposed); from the band unmasked, the mask applied where they
+         * are first used */
         const BandLine cu = band_col(tile(kb, kb + 1), 16 * w + lr, lk);
         const BandLine cn = band_col(tile(kb + 1, kb + 1), 16 * w + lr, lk);
         const BandLine rl = band_row(tile(kb + 1, kb), 16 * wl + lr, lk);
         V u[4], lt[4], nx[4];
-        if (!last)
+        if (!last) {
+            if (PACKED) {
+                band_pack_load(packed(kb, 1), u);
+                band_pack_load(packed(kb, 2), lt);
+                band_pack_load(packed(kb + 1, 0), nx);
+            } else {
 #pragma unroll
-            for (int a = 0; a < 4; ++a)
+                for (int a = 0; a < 4; ++a)
 #pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    u[a][r] = cu.raw(16 * a + 4 * r);
-                    lt[a][r] = rl.raw(16 * a + 4 * r);
-                    nx[a][r] = cn.raw(16 * a + 4 * r);
-                }
+                    for (int r = 0; r < 4; ++r) {
+                        u[a][r] = cu.raw(16 * a + 4 * r);
+                        lt[a][r] = rl.raw(16 * a + 4 * r);
+                        nx[a][r] = cn.raw(16 * a + 4 * r);
+                    }
+            }
+        }
         const int z = tile_lu64(sm.s, sm.p, sm.rinv, min(TB, n - kb * TB), &sm.zflag,
                                 [&](int p, int stage) __attribute__((always_inline)) {
                                     if (last || stage != 0)
                                         return;
-                                    if (p == 0)
+                                    if (!PACKED && p == 0)
 #pragma unroll
                                         for (int a = 0; a < 4; ++a)
 #pragma unroll
@@ -1880,9 +1945,9 @@ __device__ __forceinline__ int band_range(double *AB, int64_t ldab, int n, int k
                                             }
                                     band_strip(sm.s, sm.p, p, w, wl, u, lt);
                                 });
-        if (z && !zero_at)
-            zero_at = kb * TB + z;
-        {
+        if (own) {
+            if (z && !zero_at)
+                zero_at = kb * TB + z;
             const BandLine cd = band_col(tile(kb, kb), lane, w);
 #pragma unroll
             for (int i = 0; i < 16; ++i)
@@ -1896,7 +1961,8 @@ __device__ __forceinline__ int band_range(double *AB, int64_t ldab, int n, int k
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 sm.l[(16 * wl + lr) * LDT + arow(a, r)] = lt[a][r];
-                nx[a][r] = cn.in(16 * a + 4 * r) ? nx[a][r] : (arow(a, r) == 16 * w + lr ? 1.0 : 0.0);
+                if (!PACKED)
+                    nx[a][r] = cn.in(16 * a + 4 * r) ? nx[a][r] : (arow(a, r) == 16 * w + lr ? 1.0 : 0.0);
             }
         __syncthreads();
         /* L_{k+1,k} (upper) times U_{k,k+1} (lower): inner blocks from
@@ -1913,44 +1979,205 @@ __device__ __forceinline__ int band_range(double *AB, int64_t ldab, int n, int k
 #pragma unroll
             for (int r = 0; r < 4; ++r)
                 sm.s[arow(a, r) * LDT + 16 * w + lr] = nx[a][r];
-        const BandLine cl = band_col(tile(kb + 1, kb), lane, w);
+        if (own) {
+            const BandLine cl = band_col(tile(kb + 1, kb), lane, w);
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            if (cu.in(4 * i))
-                *cu.at(4 * i) = u[i >> 2][i & 3];
-            if (cl.in(4 * i))
-                *cl.at(4 * i) = sm.l[(w + 4 * i) * LDT + lane];
+            for (int i = 0; i < 16; ++i) {
+                if (cu.in(4 * i))
+                    *cu.at(4 * i) = u[i >> 2][i & 3];
+                if (cl.in(4 * i))
+                    *cl.at(4 * i) = sm.l[(w + 4 * i) * LDT + lane];
+            }
         }
         __syncthreads();
     }
+    if (R.send && R.end < nt)
+        save_tile(R.send);
+    __syncthreads();
     return zero_at;
 }
 
+/* The whole chain by one workgroup: short bands, and callers without the
+ * workspace of the segmented form. */
 __global__ __launch_bounds__(NT) void k_band_factor(double *AB, int64_t ldab, int n, int kl, int ku, int32_t *info)
 {
     __shared__ BandSmem sm;
-    const int z = band_range(AB, ldab, n, kl, ku, 0, (n + TB - 1) / TB, sm);
+    const BandRange R{0, 0, (n + TB - 1) / TB, nullptr, nullptr, nullptr, nullptr};
+    const int z = band_range<false>(AB, ldab, n, kl, ku, R, sm);
     if (threadIdx.x == 0 && info)
         *info = z;
 }
 
 /*
- * Operands of the band substitutions, one workgroup per 64-row block b (all
- * independent), four 64 x 64 tiles (pitch 64) at P + b * 4 * 4096: L_bb^{-1}
- * (unit diagonal and zeros above written out), U_bb^{-1} (zeros below), the
- * band tile L_{b,b-1} left of the diagonal and the band tile U_{b,b+1} right
- * of it (zero where the band or the matrix has no element).  The inverses
- * come from the factored diagonal tile (tile_inv16; a partial last tile is
- * padded with the identity).  With every mask applied here, the sweep reads
- * contiguous, unmasked operands.
+ * The band factor in segments.  The only thing block row k hands to the next
+ * is the diagonal tile S_{k+1}, and for the diagonally dominant systems of
+ * Eq. 2 what S_k was fades quadratically fast: a change D of S_k arrives in
+ * S_{k+1} as B S^{-1} D S^{-1} C with B, C the off-diagonal tiles, a factor of
+ * about 1e-3 per block row for 64 + 1 + 64 diagonals of row sum 0.5.  So the
+ * block rows are split into segments, one workgroup each, and a segment
+ * starts kBandWarm block rows early from A's own tile, which leaves the
+ * starting error below the last bit.  That is checked, not assumed: the tile
+ * a segment started from is compared with the one its predecessor ended with
+ * (k_band_check), and segments that do not agree to two units in the last
+ * place of the row's largest element are factored again from the true tile,
+ * in order (k_band_fix) -- for a matrix that forgets slowly all of them, which
+ * costs what the serial chain costs.
+ *
+ * Segments are four block rows long (longer once that makes more than 256,
+ * one per compute unit): at n = 16384 the chain is 10 steps instead of 256.
+ * Below 16 block rows the serial chain is as fast (10 steps, and four more
+ * launches).  Before that the band is copied as tiles (k_band_pack: the
+ * segments' early rows are written by their neighbours, and the chain then
+ * loads whole vectors without masks).  n = 16384, 64 + 1 + 64: 190 us (pack 8,
+ * segments 168, check and fix 11) against 5.3 ms for the chain of 256.
+ */
+constexpr int kBandWarm = 6;
+
+__device__ __forceinline__ BandRange band_segment(const BandWs &ws, int nt, int m, int j, bool again)
+{
+    BandRange R;
+    R.first = j * m;
+    R.end = min(nt, R.first + m);
+    R.begin = again ? R.first : max(0, R.first - kBandWarm);
+    R.pk = ws.pk;
+    R.s0 = again ? ws.send + (int64_t)(j - 1) * TB * TB : nullptr;
+    R.sstart = again ? nullptr : ws.sstart + (int64_t)j * TB * TB;
+    R.send = ws.send + (int64_t)j * TB * TB;
+    return R;
+}
+
+__global__ __launch_bounds__(NT) void k_band_pack(double *AB, int64_t ldab, int n, int kl, int ku, double *P)
+{
+    typedef vec4<double>::type V;
+    const int kb = blockIdx.x, nt = (n + TB - 1) / TB;
+    const int w = wave_id(), l = threadIdx.x & 63, lr = l & 15, lk = l >> 4, wl = 3 - w;
+    auto tile = [&](int rb, int cb) { return BandTile(AB, ldab, n, kl, ku, rb, cb); };
+    const bool last = kb + 1 == nt; /* nothing right of or below the last tile */
+    const BandLine cd = band_col(tile(kb, kb), 16 * w + lr, lk);
+    const BandLine cu = last ? cd : band_col(tile(kb, kb + 1), 16 * w + lr, lk);
+    const BandLine rl = last ? cd : band_row(tile(kb + 1, kb), 16 * wl + lr, lk);
+    V d[4], u[4], lt[4];
+#pragma unroll
+    for (int a = 0; a < 4; ++a)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int x = 16 * a + 4 * r;
+            d[a][r] = cd.raw(x);
+            u[a][r] = cu.raw(x);
+            lt[a][r] = rl.raw(x);
+        }
+#pragma unroll
+    for (int a = 0; a < 4; ++a)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int x = 16 * a + 4 * r;
+            d[a][r] = cd.in(x) ? d[a][r] : (lk + x == 16 * w + lr ? 1.0 : 0.0); /* the identity past the end */
+            u[a][r] = !last && cu.in(x) ? u[a][r] : 0.0;
+            lt[a][r] = !last && rl.in(x) ? lt[a][r] : 0.0;
+        }
+    double *G = P + (int64_t)kb * kBandPackTiles * TB * TB;
+    band_pack_store(G, d);
+    band_pack_store(G + TB * TB, u);
+    band_pack_store(G + 2 * TB * TB, lt);
+}
+
+__global__ __launch_bounds__(NT) void k_band_segments(double *AB, int64_t ldab, int n, int kl, int ku, BandWs ws,
+                                                      int m)
+{
+    __shared__ BandSmem sm;
+    const int j = blockIdx.x;
+    const int z = band_range<true>(AB, ldab, n, kl, ku, band_segment(ws, (n + TB - 1) / TB, m, j, false), sm);
+    if (threadIdx.x == 0)
+        ws.zero[j] = z;
+}
+
+/* Whether the diagonal tile T that a segment started from is the true one S
+ * (64 x 64 each) to 2^-51 of the largest element of S's row; the same in every
+ * thread.  Not a number is never equal. */
+__device__ __forceinline__ bool band_same_tile(const double *S, const double *T)
+{
+    const int w = wave_id(), l = threadIdx.x & 63;
+    double s[16], t[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+        s[i] = S[(w + 4 * i) * TB + l];
+        t[i] = T[(w + 4 * i) * TB + l];
+    }
+    bool same = true;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+        double m = fabs(s[i]);
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1)
+            m = fmax(m, __shfl_xor(m, o));
+        same = same && fabs(s[i] - t[i]) <= 0x1p-51 * m;
+    }
+    return __syncthreads_and(same);
+}
+
+__global__ __launch_bounds__(NT) void k_band_check(BandWs ws)
+{
+    const int j = blockIdx.x + 1;
+    const bool ok = band_same_tile(ws.send + (int64_t)(j - 1) * TB * TB, ws.sstart + (int64_t)j * TB * TB);
+    if (threadIdx.x == 0)
+        ws.ok[j] = ok;
+}
+
+__global__ __launch_bounds__(NT) void k_band_fix(double *AB, int64_t ldab, int n, int kl, int ku, BandWs ws, int m,
+                                                 int nseg, int32_t *info)
+{
+    __shared__ BandSmem sm;
+    __shared__ int first_zero;
+    const int nt = (n + TB - 1) / TB;
+    bool mine = true;
+    for (int j = 1 + threadIdx.x; j < nseg; j += NT)
+        mine = mine && ws.ok[j];
+    if (!__syncthreads_and(mine)) {
+        bool redone = false; /* segment j - 1 was factored again */
+        for (int j = 1; j < nseg; ++j) {
+            const bool ok = redone ? band_same_tile(ws.send + (int64_t)(j - 1) * TB * TB, ws.sstart + (int64_t)j * TB * TB)
+                                   : ws.ok[j] != 0;
+            redone = !ok;
+            if (ok)
+                continue;
+            const int z = band_range<true>(AB, ldab, n, kl, ku, band_segment(ws, nt, m, j, true), sm);
+            if (threadIdx.x == 0)
+                ws.zero[j] = z;
+        }
+    }
+    if (threadIdx.x == 0)
+        first_zero = 0x7fffffff;
+    __syncthreads();
+    for (int j = threadIdx.x; j < nseg; j += NT)
+        if (ws.zero[j])
+            atomicMin(&first_zero, ws.zero[j]);
+    __syncthreads();
+    if (threadIdx.x == 0 && info)
+        *info = first_zero == 0x7fffffff ? 0 : first_zero;
+}
+
+/*
+ * Operands of the band substitutions (Eq. 1), one workgroup per 64-row block
+ * b, kBandSolveTiles 64 x 64 tiles at P + b * 4 * 4096:
+ *   0  the inverses of the diagonal tile's factors, packed (tile_inv16),
+ *   1  M_b = L_bb^{-1} L_{b,b-1}: forward,  y_b = L_bb^{-1} b_b - M_b y_{b-1},
+ *   2  N_b = U_bb^{-1} U_{b,b+1}: backward, x_b = U_bb^{-1} y_b - N_b x_{b+1},
+ *   3  room for the segmented sweeps (BandSweep).
+ * M and N lie as the matrix cores' left operand (band_pack_load's order: lane
+ * (lr, lk) of wave w holds row 16w + lr, columns 16a + acc_row(lk, r)), zero
+ * where the band or the matrix has no element.  With the product of the two
+ * triangular operators taken here, in parallel, the chain has one 64 x 64
+ * product per block instead of two.
  */
 constexpr int kBandSolveTiles = 4;
 
 __global__ __launch_bounds__(NT) void k_band_packs(const double *AB, int64_t ldab, int n, int kl, int ku,
                                                    double *__restrict__ P)
 {
+    typedef vec4<double>::type V;
     __shared__ TileSmem<double> sm;
     const int b = blockIdx.x, nt = (n + TB - 1) / TB;
+    const int w = wave_id(), l = threadIdx.x & 63, lr = l & 15, lk = l >> 4;
     double *AB_ = const_cast<double *>(AB);
     const BandTile t(AB_, ldab, n, kl, ku, b, b);
     tile_xfer<double>(
@@ -1965,154 +2192,375 @@ __global__ __launch_bounds__(NT) void k_band_packs(const double *AB, int64_t lda
     __syncthreads();
     tile_inv16(sm.t0, sm.rinv, sm.t1);
     double *Pb = P + (int64_t)b * kBandSolveTiles * TB * TB;
-    tile_xfer<double>(
-        [&](int r, int c) { return sm.t1[r * LDT + c]; },
-        [&](int r, int c, double v) {
-            Pb[r * TB + c] = r > c ? v : (r == c ? 1.0 : 0.0);
-            Pb[TB * TB + r * TB + c] = r <= c ? v : 0.0;
-        });
-    /* the off-diagonal band tiles (the first block's left one and the last
-     * block's right one lie outside the matrix: zero) */
-    const BandTile tlft(AB_, ldab, n, kl, ku, b, b - 1), trgt(AB_, ldab, n, kl, ku, b, b + 1);
-    const bool has_l = b > 0, has_r = b + 1 < nt;
-    tile_xfer<double>(
-        [&](int r, int c) {
-            const double v = tlft.raw(r, c);
-            return (has_l && tlft.in(r, c)) ? v : 0.0;
-        },
-        [&](int r, int c, double v) { Pb[2 * TB * TB + r * TB + c] = v; });
-    tile_xfer<double>(
-        [&](int r, int c) {
-            const double v = trgt.raw(r, c);
-            return (has_r && trgt.in(r, c)) ? v : 0.0;
-        },
-        [&](int r, int c, double v) { Pb[3 * TB * TB + r * TB + c] = v; });
+    tile_xfer<double>([&](int r, int c) { return sm.t1[r * LDT + c]; },
+                      [&](int r, int c, double v) { Pb[r * TB + c] = v; });
+    for (int side = 0; side < 2; ++side) {
+        const int o = side ? b + 1 : b - 1;
+        if (o < 0 || o >= nt)
+            continue; /* outside the matrix: never read */
+        const BandTile to(AB_, ldab, n, kl, ku, b, o);
+        __syncthreads();
+        tile_xfer<double>(
+            [&](int r, int c) {
+                const double v = to.raw(r, c);
+                return to.in(r, c) ? v : 0.0;
+            },
+            [&](int r, int c, double v) { sm.t0[r * LDT + c] = v; });
+        __syncthreads();
+        Acc64<double> acc;
+        acc64_zero(acc);
+        auto off = [&](int k, int c) { return sm.t0[k * LDT + c]; };
+        if (side)
+            acc64_mma<double, false>(acc, InvUFull<double>{sm.t1}, off);
+        else
+            acc64_mma<double, false>(acc, InvL<double>{sm.t1}, off);
+        __syncthreads();
+        acc64_store(acc, LdsTile<double>{sm.t0});
+        __syncthreads();
+        V v[4];
+#pragma unroll
+        for (int a = 0; a < 4; ++a)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                v[a][r] = sm.t0[(16 * w + lr) * LDT + 16 * a + acc_row<double>(lk, r)];
+        band_pack_store(Pb + (1 + side) * TB * TB, v);
+    }
 }
 
 /*
- * Band substitutions (Eq. 7) by one workgroup for up to 16 right-hand sides,
- * 64-row blocks in order:
- *   forward,  y_b = L_bb^{-1} (b_b - L_{b,b-1} y_{b-1}),
- *   backward, x_b = U_bb^{-1} (y_b - U_{b,b+1} x_{b+1}).
- * Each block is two 64 x 64 by 64 x 16 products on the matrix cores (wave w
- * the rows 16w..16w+15; lane group g supplies inner indices 16q + 4g .. +3,
- * contiguous in the operand tiles of k_band_packs, so a lane loads each
- * group of four as one 32-byte vector), the operands of a block loaded two
- * blocks ahead in a ring of three register sets.  The previous block's
- * solution stays in LDS for the next product; each solved block is written
- * to B.
+ * The band substitutions of up to 16 right-hand sides (one chunk of B's
+ * columns).  The blocks are taken in positions, 0 the first one solved.  With
+ * m < nt block rows the positions are split into segments as the factor's
+ * are: a segment starts kBandSweepWarm positions early from zero, which the
+ * products M_b (N_b), about 0.05 in norm at a row sum of 0.5, fade below the
+ * last bit; its start is compared with its predecessor's end (k_band_sweep_check)
+ * and it is swept again from there if they disagree (k_band_sweep_fix).  Its
+ * own operands are then formed ahead (k_band_z): z_b = L_bb^{-1} b_b, held in
+ * tile 3 of the block, whose rest holds the segment's ends and flags.
+ * n = 16384, 8 right-hand sides: 40 us a direction and 22 us for the operands,
+ * against 1.42 ms for two chains of 256 with two products a block.
  */
-constexpr int BXP = 17; /* LDS pitch of a 64 x 16 block of right-hand sides */
-
-struct BandSweepOps {
-    d4 a1[4], a2[4]; /* off-diagonal band tile, diagonal tile's inverse */
-    double y[4];     /* the block's right-hand sides (accumulator layout) */
-};
-
-struct BandSweepArgs {
+struct BandSweep {
     int n;
-    const double *P;
-    double *B;
+    double *P, *B;
     int64_t ldb;
-    int nrhs_here;
+    int nrhs, m; /* columns from B on; positions per segment */
 };
+constexpr int kBandSweepWarm = 16;
+constexpr int kBandSweepChunks = 2; /* chunks of right-hand sides side by side (tile 3 has room for two) */
 
-template <bool FWD>
-__device__ __forceinline__ void band_sweep_load(const BandSweepArgs &a, int b, BandSweepOps &o)
+/* A 64 x 16 block of right-hand sides as its waves' accumulators: lane l of
+ * wave w holds four values, in pairs at (128 h + 64 w + ...): pair h of them
+ * at ((4h + w) 64 + l) 2. */
+__device__ __forceinline__ void band_y_store(double *Y, const d4 &y)
 {
-    const int w = wave_id(), lane = threadIdx.x & 63, lr = lane & 15, lk = lane >> 4;
-    const int row = 16 * w + lr, b0 = b * TB;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        const int rb = b0 + 16 * w + acc_row<double>(lk, r);
-        o.y[r] = a.B[(rb < a.n && lr < a.nrhs_here) ? (int64_t)rb * a.ldb + lr : 0];
-    }
-    const double *Pb = a.P + (int64_t)b * kBandSolveTiles * TB * TB + row * TB + 4 * lk;
-    const double *Pinv = Pb + (FWD ? 0 : TB * TB), *Poff = Pb + (FWD ? 2 : 3) * TB * TB;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        o.a1[q] = *reinterpret_cast<const d4 *>(Poff + 16 * q);
-        o.a2[q] = *reinterpret_cast<const d4 *>(Pinv + 16 * q);
-    }
+    d2 *q = reinterpret_cast<d2 *>(Y) + 64 * wave_id() + (threadIdx.x & 63);
+    q[0] = d2{y[0], y[1]};
+    q[256] = d2{y[2], y[3]};
+}
+__device__ __forceinline__ d4 band_y_load(const double *Y, int w)
+{
+    const d2 *q = reinterpret_cast<const d2 *>(Y) + 64 * w + (threadIdx.x & 63);
+    const d2 a = q[0], b = q[256];
+    return d4{a[0], a[1], b[0], b[1]};
 }
 
-template <bool FWD>
-__device__ __forceinline__ void band_sweep_block(const BandSweepArgs &a, const BandSweepOps &o, bool has_off, int b,
-                                                 double *xs, double *ys)
+/* Places in tile 3: of block b (in solve order position pos) the formed
+ * z_b, and of a segment the state it started from and ended with and, in its
+ * third position, whether its successor's start agreed. */
+__device__ __forceinline__ double *band_room(const BandSweep &a, int b)
 {
-    const int w = wave_id(), lane = threadIdx.x & 63, lr = lane & 15, lk = lane >> 4;
-    const int b0 = b * TB;
-    d4 acc;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        const int rb = b0 + 16 * w + acc_row<double>(lk, r);
-        acc[r] = (rb < a.n && lr < a.nrhs_here) ? o.y[r] : 0.0;
-    }
-    if (has_off)
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-#pragma unroll
-            for (int ks = 0; ks < 4; ++ks)
-                acc = mfma16(-o.a1[q][ks], xs[(16 * q + 4 * lk + ks) * BXP + lr], acc);
-#pragma unroll
-    for (int r = 0; r < 4; ++r)
-        ys[(16 * w + acc_row<double>(lk, r)) * BXP + lr] = acc[r];
-    __syncthreads();
-    d4 x = {0.0, 0.0, 0.0, 0.0};
+    return a.P + ((int64_t)b * kBandSolveTiles + 3) * TB * TB;
+}
+template <bool FWD> __device__ __forceinline__ int band_blk(const BandSweep &a, int pos)
+{
+    return FWD ? pos : (a.n + TB - 1) / TB - 1 - pos;
+}
+template <bool FWD> __device__ __forceinline__ double *band_start(const BandSweep &a, int j, int ch)
+{
+    return band_room(a, band_blk<FWD>(a, j * a.m)) + (2 + ch) * TB * 16;
+}
+template <bool FWD> __device__ __forceinline__ double *band_end(const BandSweep &a, int j, int ch)
+{
+    return band_room(a, band_blk<FWD>(a, j * a.m + 1)) + (2 + ch) * TB * 16;
+}
+template <bool FWD> __device__ __forceinline__ int *band_ok(const BandSweep &a, int j, int ch)
+{
+    return reinterpret_cast<int *>(band_room(a, band_blk<FWD>(a, j * a.m + 2)) + (2 + ch) * TB * 16);
+}
+
+/* z_b = L_bb^{-1} b_b (FWD) or U_bb^{-1} y_b: the left operand, rows 16w + lr
+ * of the pack, columns 16q + 4 lk + ks, and the right one from B, columns
+ * past the last read as zero. */
+struct BandZ {
+    double p[16], y[16];
+};
+__device__ __forceinline__ void band_z_load(const BandSweep &a, int b, int c0, BandZ &o)
+{
+    const int w = wave_id(), l = threadIdx.x & 63, lr = l & 15, lk = l >> 4;
+    const double *Pr = a.P + (int64_t)b * kBandSolveTiles * TB * TB + (16 * w + lr) * TB + 4 * lk;
 #pragma unroll
     for (int q = 0; q < 4; ++q)
 #pragma unroll
+        for (int ks = 0; ks < 4; ++ks) {
+            o.p[4 * q + ks] = Pr[16 * q + ks];
+            const int row = b * TB + 16 * q + 4 * lk + ks;
+            o.y[4 * q + ks] = a.B[(int64_t)min(row, a.n - 1) * a.ldb + min(c0 + lr, a.nrhs - 1)];
+        }
+}
+template <bool FWD> __device__ __forceinline__ d4 band_z_product(const BandSweep &a, int b, int c0, const BandZ &o)
+{
+    const int w = wave_id(), l = threadIdx.x & 63, lr = l & 15, lk = l >> 4, r = 16 * w + lr;
+    d4 z = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) {
+            const int k = 16 * q + 4 * lk + ks;
+            const double p = o.p[4 * q + ks];
+            const double f = FWD ? (r > k ? p : (r == k ? 1.0 : 0.0)) : (r <= k ? p : 0.0);
+            z = mfma16(f, (b * TB + k < a.n && c0 + lr < a.nrhs) ? o.y[4 * q + ks] : 0.0, z);
+        }
+    return z;
+}
+
+template <bool FWD> __global__ __launch_bounds__(NT) void k_band_z(BandSweep a)
+{
+    const int b = blockIdx.x, ch = blockIdx.y;
+    BandZ o;
+    band_z_load(a, b, 16 * ch, o);
+    band_y_store(band_room(a, b) + ch * TB * 16, band_z_product<FWD>(a, b, 16 * ch, o));
+}
+
+/* y -= M_b y_prev, y_prev (all four waves') in LDS. */
+__device__ __forceinline__ void band_sweep_product(d4 &y, const vec4<double>::type (&M)[4], const double *prev)
+{
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const d4 x = band_y_load(prev, q);
+#pragma unroll
         for (int ks = 0; ks < 4; ++ks)
-            x = mfma16(o.a2[q][ks], ys[(16 * q + 4 * lk + ks) * BXP + lr], x);
+            y = mfma16(-M[q][ks], x[ks], y);
+    }
+}
+__device__ __forceinline__ void band_sweep_put(const BandSweep &a, int b, int c0, const d4 &y)
+{
+    const int w = wave_id(), l = threadIdx.x & 63, lr = l & 15, lk = l >> 4;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-        const int rr = 16 * w + acc_row<double>(lk, r), rb = b0 + rr;
-        xs[rr * BXP + lr] = x[r];
-        if (rb < a.n && lr < a.nrhs_here)
-            a.B[(int64_t)rb * a.ldb + lr] = x[r];
+        const int row = b * TB + 16 * w + acc_row<double>(lk, r);
+        if (row < a.n && c0 + lr < a.nrhs)
+            a.B[(int64_t)row * a.ldb + c0 + lr] = y[r];
     }
-    __syncthreads();
 }
 
-template <bool FWD> __device__ __forceinline__ void band_sweep(const BandSweepArgs &a, double *xs, double *ys)
+/* Positions begin .. end - 1 of one segment, those from first on written to B;
+ * from y0 (the state before begin) or from zero.  One product per position;
+ * its operands are loaded two positions ahead in a ring of three register
+ * sets.  The state before first goes to start, the last to end_. */
+template <bool FWD>
+__device__ __forceinline__ void band_sweep_segment(const BandSweep &a, int ch, int begin, int first, int end,
+                                                   const double *y0, double *start, double *end_, double (*ybuf)[TB * 16])
+{
+    struct Ops {
+        vec4<double>::type M[4];
+        d4 z;
+    };
+    auto load = [&](int pos, Ops &o) {
+        const int b = band_blk<FWD>(a, min(pos, end - 1));
+        band_pack_load(a.P + ((int64_t)b * kBandSolveTiles + (FWD ? 1 : 2)) * TB * TB, o.M);
+        o.z = band_y_load(band_room(a, b) + ch * TB * 16, wave_id());
+    };
+    if (y0) {
+        band_y_store(ybuf[0], band_y_load(y0, wave_id()));
+        __syncthreads();
+    }
+    int cur = 0;
+    auto step = [&](int pos, const Ops &o) __attribute__((always_inline)) {
+        d4 y = o.z;
+        if (pos > begin || y0)
+            band_sweep_product(y, o.M, ybuf[cur]);
+        cur ^= 1;
+        band_y_store(ybuf[cur], y);
+        if (pos >= first)
+            band_sweep_put(a, band_blk<FWD>(a, pos), 16 * ch, y);
+        if (start && pos == first - 1)
+            band_y_store(start, y);
+        if (end_ && pos == end - 1)
+            band_y_store(end_, y);
+        __syncthreads();
+    };
+    Ops o0, o1, o2;
+    load(begin, o0);
+    load(begin + 1, o1);
+    for (int pos = begin; pos < end; pos += 3) {
+        load(pos + 2, o2);
+        step(pos, o0);
+        if (pos + 1 >= end)
+            break;
+        load(pos + 3, o0);
+        step(pos + 1, o1);
+        if (pos + 2 >= end)
+            break;
+        load(pos + 4, o1);
+        step(pos + 2, o2);
+    }
+}
+
+template <bool FWD> __global__ __launch_bounds__(NT) void k_band_sweep_segments(BandSweep a)
+{
+    __shared__ double ybuf[2][TB * 16];
+    const int j = blockIdx.x, ch = blockIdx.y, nt = (a.n + TB - 1) / TB;
+    const int first = j * a.m, end = min(nt, first + a.m);
+    band_sweep_segment<FWD>(a, ch, max(0, first - kBandSweepWarm), first, end, nullptr,
+                            j > 0 ? band_start<FWD>(a, j, ch) : nullptr, end < nt ? band_end<FWD>(a, j, ch) : nullptr,
+                            ybuf);
+}
+
+/* Whether the state T a segment started from is its predecessor's end S to
+ * 2^-51 of the block's largest value in each right-hand side; the same in
+ * every thread. */
+__device__ __forceinline__ bool band_same_state(const double *S, const double *T, double (*cmax)[16])
+{
+    const int w = wave_id(), l = threadIdx.x & 63;
+    const d4 s = band_y_load(S, w), t = band_y_load(T, w);
+    double m = fmax(fmax(fabs(s[0]), fabs(s[1])), fmax(fabs(s[2]), fabs(s[3])));
+    m = fmax(m, __shfl_xor(m, 16));
+    m = fmax(m, __shfl_xor(m, 32));
+    __syncthreads();
+    if (l < 16)
+        cmax[w][l] = m;
+    __syncthreads();
+    m = fmax(fmax(cmax[0][l & 15], cmax[1][l & 15]), fmax(cmax[2][l & 15], cmax[3][l & 15]));
+    bool same = true;
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+        same = same && fabs(s[r] - t[r]) <= 0x1p-51 * m;
+    return __syncthreads_and(same);
+}
+
+template <bool FWD> __global__ __launch_bounds__(NT) void k_band_sweep_check(BandSweep a)
+{
+    __shared__ double cmax[4][16];
+    const int j = blockIdx.x, ch = blockIdx.y;
+    const bool ok = band_same_state(band_end<FWD>(a, j, ch), band_start<FWD>(a, j + 1, ch), cmax);
+    if (threadIdx.x == 0)
+        *band_ok<FWD>(a, j, ch) = ok;
+}
+
+template <bool FWD> __global__ __launch_bounds__(NT) void k_band_sweep_fix(BandSweep a, int nseg)
+{
+    __shared__ double ybuf[2][TB * 16], cmax[4][16];
+    const int ch = blockIdx.x, nt = (a.n + TB - 1) / TB;
+    bool mine = true;
+    for (int j = threadIdx.x; j < nseg - 1; j += NT)
+        mine = mine && *band_ok<FWD>(a, j, ch);
+    if (__syncthreads_and(mine))
+        return;
+    bool redone = false; /* segment j was swept again */
+    for (int j = 0; j < nseg - 1; ++j) {
+        const bool ok = redone ? band_same_state(band_end<FWD>(a, j, ch), band_start<FWD>(a, j + 1, ch), cmax)
+                               : *band_ok<FWD>(a, j, ch) != 0;
+        redone = !ok;
+        if (ok)
+            continue;
+        const int first = (j + 1) * a.m, end = min(nt, first + a.m);
+        band_sweep_segment<FWD>(a, ch, first, first, end, band_end<FWD>(a, j, ch), nullptr,
+                                end < nt ? band_end<FWD>(a, j + 1, ch) : nullptr, ybuf);
+    }
+}
+
+/* Both substitutions of a short band by one workgroup per chunk, the diagonal
+ * products taken in the chain: one launch, operands loaded a block ahead. */
+template <bool FWD> __device__ __forceinline__ void band_sweep_whole(const BandSweep &a, int ch, double (*ybuf)[TB * 16])
 {
     const int nt = (a.n + TB - 1) / TB;
-    auto blk = [&](int i) { return FWD ? i : nt - 1 - i; };
-    /* three operand sets in a ring: each block's loads are issued two
-     * blocks before it is solved */
-    BandSweepOps o[3];
-    band_sweep_load<FWD>(a, blk(0), o[0]);
-    if (nt > 1)
-        band_sweep_load<FWD>(a, blk(1), o[1]);
-#pragma unroll 1
-    for (int i = 0; i < nt; i += 3) {
-        if (i + 2 < nt)
-            band_sweep_load<FWD>(a, blk(i + 2), o[2]);
-        band_sweep_block<FWD>(a, o[0], i > 0, blk(i), xs, ys);
-        if (i + 1 >= nt)
+    struct Ops {
+        vec4<double>::type M[4];
+        BandZ z;
+    };
+    auto load = [&](int pos, Ops &o) {
+        const int b = band_blk<FWD>(a, min(pos, nt - 1));
+        band_pack_load(a.P + ((int64_t)b * kBandSolveTiles + (FWD ? 1 : 2)) * TB * TB, o.M);
+        band_z_load(a, b, 16 * ch, o.z);
+    };
+    int cur = 0;
+    auto step = [&](int pos, const Ops &o) __attribute__((always_inline)) {
+        const int b = band_blk<FWD>(a, pos);
+        d4 y = band_z_product<FWD>(a, b, 16 * ch, o.z);
+        if (pos > 0)
+            band_sweep_product(y, o.M, ybuf[cur]);
+        cur ^= 1;
+        band_y_store(ybuf[cur], y);
+        band_sweep_put(a, b, 16 * ch, y);
+        __syncthreads();
+    };
+    Ops o0, o1;
+    load(0, o0);
+    for (int pos = 0; pos < nt; pos += 2) {
+        load(pos + 1, o1);
+        step(pos, o0);
+        if (pos + 1 >= nt)
             break;
-        if (i + 3 < nt)
-            band_sweep_load<FWD>(a, blk(i + 3), o[0]);
-        band_sweep_block<FWD>(a, o[1], true, blk(i + 1), xs, ys);
-        if (i + 2 >= nt)
-            break;
-        if (i + 4 < nt)
-            band_sweep_load<FWD>(a, blk(i + 4), o[1]);
-        band_sweep_block<FWD>(a, o[2], true, blk(i + 2), xs, ys);
+        load(pos + 2, o0);
+        step(pos + 1, o1);
     }
 }
-
-__global__ __launch_bounds__(NT) void k_band_solve(BandSweepArgs a)
+__global__ __launch_bounds__(NT) void k_band_sweep(BandSweep a)
 {
-    __shared__ double xs[TB * BXP], ys[TB * BXP];
-    band_sweep<true>(a, xs, ys);
-    band_sweep<false>(a, xs, ys);
+    __shared__ double ybuf[2][TB * 16];
+    band_sweep_whole<true>(a, blockIdx.x, ybuf);
+    band_sweep_whole<false>(a, blockIdx.x, ybuf);
 }
 
-hipError_t band_factor(double *AB, int64_t ldab, int n, int kl, int ku, int32_t *info, hipStream_t st)
+/* Block rows per segment of a band of nt of them: short segments make the
+ * chain short, and 256 of them fill the compute units. */
+static int band_segment_rows(int nt, int least) { return std::max(least, (nt + 255) / 256); }
+
+BandWs band_ws(void *ws, int64_t n, size_t &bytes)
 {
-    hipLaunchKernelGGL(k_band_factor, dim3(1), dim3(NT), 0, st, AB, ldab, n, kl, ku, info);
+    const int nt = (int)((n + TB - 1) / TB), m = band_segment_rows(nt, 4), nseg = (nt + m - 1) / m;
+    BandWs b{};
+    bytes = 0;
+    if (nt < 16)
+        return b;
+    const size_t tiles = (2 * sizeof(int) * (size_t)nseg + 255) / 256 * 256, tile = sizeof(double) * TB * TB;
+    const size_t pk = tiles + 2 * (size_t)nseg * tile;
+    bytes = pk + (size_t)nt * kBandPackTiles * tile;
+    if (ws) {
+        char *p = static_cast<char *>(ws);
+        b.zero = reinterpret_cast<int *>(p);
+        b.ok = b.zero + nseg;
+        b.sstart = reinterpret_cast<double *>(p + tiles);
+        b.send = reinterpret_cast<double *>(p + tiles + (size_t)nseg * tile);
+        b.pk = reinterpret_cast<double *>(p + pk);
+    }
+    return b;
+}
+
+hipError_t band_factor(double *AB, int64_t ldab, int n, int kl, int ku, int32_t *info, void *ws, hipStream_t st)
+{
+    size_t bytes = 0;
+    const BandWs b = band_ws(ws, n, bytes);
+    if (!ws || bytes == 0) {
+        hipLaunchKernelGGL(k_band_factor, dim3(1), dim3(NT), 0, st, AB, ldab, n, kl, ku, info);
+        return hipGetLastError();
+    }
+    const int nt = (n + TB - 1) / TB, m = band_segment_rows(nt, 4), nseg = (nt + m - 1) / m;
+    hipLaunchKernelGGL(k_band_pack, dim3(nt), dim3(NT), 0, st, AB, ldab, n, kl, ku, b.pk);
+    hipLaunchKernelGGL(k_band_segments, dim3(nseg), dim3(NT), 0, st, AB, ldab, n, kl, ku, b, m);
+    hipLaunchKernelGGL(k_band_check, dim3(nseg - 1), dim3(NT), 0, st, b);
+    hipLaunchKernelGGL(k_band_fix, dim3(1), dim3(NT), 0, st, AB, ldab, n, kl, ku, b, m, nseg, info);
     return hipGetLastError();
+}
+
+template <bool FWD> static void band_sweep_launch(const BandSweep &a, int nt, int nch, hipStream_t st)
+{
+    const int nseg = (nt + a.m - 1) / a.m;
+    hipLaunchKernelGGL((k_band_z<FWD>), dim3(nt, nch), dim3(NT), 0, st, a);
+    hipLaunchKernelGGL((k_band_sweep_segments<FWD>), dim3(nseg, nch), dim3(NT), 0, st, a);
+    hipLaunchKernelGGL((k_band_sweep_check<FWD>), dim3(nseg - 1, nch), dim3(NT), 0, st, a);
+    hipLaunchKernelGGL((k_band_sweep_fix<FWD>), dim3(nch), dim3(NT), 0, st, a, nseg);
 }
 
 hipError_t band_solve(const double *AB, int64_t ldab, int n, int kl, int ku, double *B, int64_t ldb, int nrhs,
@@ -2121,9 +2569,19 @@ hipError_t band_solve(const double *AB, int64_t ldab, int n, int kl, int ku, dou
     const int nt = (n + TB - 1) / TB;
     hipLaunchKernelGGL(k_band_packs, dim3(nt), dim3(NT), 0, st, AB, ldab, n, kl, ku, P);
     hipError_t e = hipGetLastError();
-    for (int c0 = 0; c0 < nrhs && e == hipSuccess; c0 += 16) {
-        const BandSweepArgs a{n, P, B + c0, ldb, min(16, nrhs - c0)};
-        hipLaunchKernelGGL(k_band_solve, dim3(1), dim3(NT), 0, st, a);
+    /* segments from 48 block rows on: their 24 positions and four launches a
+     * direction against a chain of nt in one launch for both */
+    const bool seg = nt >= 48;
+    const int step = 16 * (seg ? kBandSweepChunks : 65535);
+    for (int c0 = 0; c0 < nrhs && e == hipSuccess; c0 += step) {
+        const int nc = min(step, nrhs - c0), nch = (nc + 15) / 16;
+        const BandSweep a{n, P, B + c0, ldb, nc, band_segment_rows(nt, 8)};
+        if (seg) {
+            band_sweep_launch<true>(a, nt, nch, st);
+            band_sweep_launch<false>(a, nt, nch, st);
+        } else {
+            hipLaunchKernelGGL(k_band_sweep, dim3(nch), dim3(NT), 0, st, a);
+        }
         e = hipGetLastError();
     }
     return e;

@@ -22,7 +22,7 @@ HEADER_PATH = os.path.join(os.path.dirname(_HERE), "include", "ebv.h")
 
 F64, F32 = 0, 1
 (OP_FACTOR, OP_SOLVE, OP_BATCHED, OP_ADJOINT, OP_MIXED, OP_BAND, OP_BATCHED_MIXED, OP_FACTOR_SOLVE,
- OP_BAND_SOLVE, OP_INVERSE) = range(10)
+ OP_BAND_SOLVE, OP_INVERSE, OP_BAND_SEGMENTS) = range(11)
 ORDER_EBV, ORDER_INDEX, ORDER_LONGEST_FIRST = 0, 1, 2
 ORDER_NAMES = {"ebv": ORDER_EBV, "index": ORDER_INDEX, "longest": ORDER_LONGEST_FIRST}
 # the autotuner's table for this GPU, loaded into the default handle when present
@@ -406,7 +406,10 @@ def lu_factor_band_(AB: torch.Tensor, kl: int, ku: int, info: Optional[torch.Ten
     if info is None:
         info = torch.zeros(1, dtype=torch.int32, device=AB.device)
     if ws is None:
-        ws = workspace(OP_BAND, F64, n, 0, 1, AB.device)
+        try:  # the segments' workspace; without it one workgroup walks the whole band
+            ws = workspace(OP_BAND_SEGMENTS, F64, n, 0, 1, AB.device)
+        except torch.cuda.OutOfMemoryError:
+            ws = None
     w, wb = _ws_args(ws)
     _check(lib().ebv_lu_factor_band(handle(), n, kl, ku, _p(AB), wd, _p(info), w, wb, _stream()),
            "ebv_lu_factor_band")

@@ -1,0 +1,114 @@
+"""GPU parity: the band factor and substitutions in segments (checked starts,
+repeated where they disagree) against the oracle and the one-workgroup chain."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_1907_05767_amd import ebv, inputs
+from tests.gpu_util import case, dev, fwd_err, host
+
+pytestmark = pytest.mark.gpu
+
+
+def _mask(n, kl, ku):
+    j = np.arange(n)[:, None] + np.arange(kl + ku + 1)[None, :] - kl
+    return (j >= 0) & (j < n)
+
+
+def _run(AB, kl, ku, B, ws=None):
+    t, X = dev(AB), dev(B)
+    info = ebv.lu_factor_band_(t, kl, ku, ws=ws)
+    ebv.lu_solve_band_(t, kl, ku, X)
+    torch.cuda.synchronize()
+    return host(t), host(X), int(info.item())
+
+
+def _serial_ws():
+    """A workspace too small for the segments: the one-workgroup chain."""
+    return torch.empty(512, dtype=torch.uint8, device="cuda")
+
+
+# 15 | 16 block rows: chain | segments of the factor; 47 | 48: of the sweeps;
+# whole and partial last tiles and last segments, every chunking of the columns
+@pytest.mark.parametrize("n,kl,ku,nrhs", [(960, 64, 64, 1), (961, 64, 64, 2), (1024, 3, 64, 16), (1100, 64, 0, 17),
+                                          (3008, 64, 64, 33), (3009, 1, 2, 1), (3072, 64, 64, 40), (3200, 0, 0, 3),
+                                          (5000, 33, 64, 16), (6147, 64, 31, 5)])
+def test_band_segments_parity(n, kl, ku, nrhs):
+    case(f"band segments n={n} kl={kl} ku={ku} nrhs={nrhs}")
+    AB, B = inputs.band(n, kl, ku, 0.9, n), inputs.rhs(n, nrhs, n + 1)
+    LU_ref, _ = oracle.lu_factor_band(AB, kl, ku)
+    X_ref = oracle.lu_solve_band(LU_ref, kl, ku, B)
+    LU, X, info = _run(AB, kl, ku, B)
+    LU1, X1, _ = _run(AB, kl, ku, B, _serial_ws())
+    m = _mask(n, kl, ku)
+    assert info == 0
+    assert np.abs(np.where(m, LU - LU_ref, 0)).max() <= 1e-12
+    assert np.abs(np.where(m, LU1 - LU_ref, 0)).max() <= 1e-12
+    assert fwd_err(X, X_ref) <= 1e-12 and fwd_err(X1, X_ref) <= 1e-12
+
+
+def _grid(n):
+    """Five-point Laplacian on a grid 64 wide: a chain that forgets slowly
+    (about 0.9 per block row), so no segment's early start is good enough."""
+    AB = np.zeros((n, 129))
+    i = np.arange(n)
+    AB[:, 64] = 4.0
+    AB[i >= 64, 0] = -1.0
+    AB[i < n - 64, 128] = -1.0
+    AB[i % 64 != 0, 63] = -1.0
+    AB[(i % 64 != 63) & (i < n - 1), 65] = -1.0
+    return AB
+
+
+@pytest.mark.parametrize("n", [1024, 3136])
+def test_band_segments_repeated_where_they_disagree(n):
+    case(f"band segments, slow decay n={n}")
+    AB, B = _grid(n), inputs.rhs(n, 3, 7)
+    LU_ref, _ = oracle.lu_factor_band(AB, 64, 64)
+    X_ref = oracle.lu_solve_band(LU_ref, 64, 64, B)
+    LU, X, info = _run(AB, 64, 64, B)
+    assert info == 0
+    # pivots within 1..4 and multipliers below 1: no growth; kappa below
+    # 8 / (2 - 2 cos(pi / 65)) = 3.5e3, times eps times a small factor
+    assert np.abs(np.where(_mask(n, 64, 64), LU - LU_ref, 0)).max() <= 1e-12
+    assert fwd_err(X, X_ref) <= 1e-11
+
+
+@pytest.mark.parametrize("cols", [(0,), (700,)])
+def test_band_sweep_local_right_hand_side(cols):
+    """A right-hand side in one row: the solution decays over the segments and
+    keeps its relative accuracy block by block."""
+    n = 3200
+    case(f"band segments, local right-hand side {cols}")
+    AB, B = inputs.band(n, 64, 64, 0.9, 5), np.zeros((n, 1))
+    B[list(cols)] = 1.0
+    LU_ref, _ = oracle.lu_factor_band(AB, 64, 64)
+    X_ref = oracle.lu_solve_band(LU_ref, 64, 64, B)
+    _, X, _ = _run(AB, 64, 64, B)
+    blocks = np.arange(0, n, 64)
+    err = np.maximum.reduceat(np.abs(X - X_ref)[:, 0], blocks) / np.maximum.reduceat(np.abs(X_ref)[:, 0], blocks)
+    # each block's values are products of at most 50 contractions, each with a
+    # relative error of a few 64 eps
+    assert err.max() <= 50 * 64 * 4 * 2.2e-16
+
+
+@pytest.mark.parametrize("rows", [(5,), (1400,), (2047, 900), (4,)])
+def test_band_segments_zero_pivot(rows):
+    """A row and column that meet nothing, with a zero diagonal: the first one
+    is reported, also where it lies in a later segment."""
+    n = 2048
+    case(f"band segments zero pivots {rows}")
+    AB = inputs.band(n, 64, 64, 0.5, 6)
+    for r in rows:
+        AB[r, :] = 0.0
+        for d in range(-64, 65):
+            if 0 <= r + d < n:
+                AB[r + d, 64 - d] = 0.0
+    _, info_ref = oracle.lu_factor_band(AB, 64, 64)
+    t = dev(AB)
+    info = ebv.lu_factor_band_(t, 64, 64)
+    torch.cuda.synchronize()
+    assert int(info.item()) == info_ref == min(rows) + 1
