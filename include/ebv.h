@@ -214,10 +214,13 @@ int ebv_lu_factor(ebv_handle h, ebv_dtype dtype, int64_t n, void *A, int64_t lda
  *   info   device int32[batch] or NULL: set to 0, or (batch = 1) to -status
  *          when a bounded wait gave up (X is then invalid).
  *   ws     ebv_workspace_size(EBV_OP_SOLVE, dtype, n, nrhs, batch) bytes when
- *          batch = 1: three int32 control words padded to 256 bytes, then
- *          the exchange rows of the solved blocks (ceil(n/64)*64 x 16
- *          elements) and the partial sums of the helper workgroups
- *          (2 * ceil(n/64) blocks of 64 x 16 elements); none when batch > 1.
+ *          batch = 1: the int32 control words padded to 256 bytes, then,
+ *          for each of up to four chunks of 16 right-hand sides that are
+ *          solved side by side (fewer when the workspace holds fewer; one is
+ *          the least), the exchange rows of the solved blocks
+ *          (ceil(n/64)*64 x 16 elements) and the partial sums of the helper
+ *          workgroups (2 * ceil(n/64) blocks of 64 x 16 elements); none when
+ *          batch > 1.
  */
 int ebv_lu_solve(ebv_handle h, ebv_dtype dtype, int64_t n, int64_t nrhs, const void *LU, int64_t lda,
                  void *B, int64_t ldb, int64_t batch, int64_t strideLU, int64_t strideB, int32_t *info,
@@ -236,7 +239,8 @@ int ebv_lu_solve(ebv_handle h, ebv_dtype dtype, int64_t n, int64_t nrhs, const v
  *          gave up in the factor or the solve gives -status).
  *   ws     ebv_workspace_size(EBV_OP_FACTOR_SOLVE, dtype, n, nrhs, 1) bytes:
  *          the factor's layout (the backward substitution uses its first
- *          three control words), then the exchange rows of the solved blocks
+ *          control words), then per chunk of right-hand sides, as for
+ *          ebv_lu_solve, the exchange rows of the solved blocks
  *          (ceil(n/64)*64 x 16 elements) and the partial sums of the
  *          helper workgroups (2 * ceil(n/64) blocks of 64 x 16 elements).
  */

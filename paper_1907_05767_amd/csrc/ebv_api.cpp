@@ -81,7 +81,16 @@ int hip_status(hipError_t e) { return e == hipSuccess ? EBV_OK : EBV_ERR_HIP; }
 /* Multi-workgroup triangular solves: status, ticket and solved-block
  * counters, then the exchange buffer of the solved rows. */
 size_t trsv_ctl_bytes() { return align_up(sizeof(int) * ebv::kCtlHead); }
-size_t trsv_ws_bytes(int64_t n, size_t elem) { return trsv_ctl_bytes() + ebv::trsv_xb_bytes(elem, n); }
+size_t trsv_ws_bytes(int64_t n, int64_t nrhs, size_t elem)
+{
+    return trsv_ctl_bytes() + ebv::trsv_chunks(nrhs) * ebv::trsv_xb_bytes(elem, n);
+}
+/* Chunks of right-hand sides whose exchange rows fit `bytes` (at least one:
+ * the callers' check), no more than the call has. */
+int trsv_fit(size_t bytes, size_t elem, int64_t n, int64_t nrhs)
+{
+    return (int)std::min<size_t>(ebv::trsv_chunks(nrhs), bytes / ebv::trsv_xb_bytes(elem, n));
+}
 
 
 /* Mixed precision (dense): [factor workspace: control words + diagonal
@@ -89,12 +98,12 @@ size_t trsv_ws_bytes(int64_t n, size_t elem) { return trsv_ctl_bytes() + ebv::tr
  * [A32 n*n floats][R32 n*nrhs floats][R64 n*nrhs doubles] */
 struct MixedLayout {
     size_t trsv, dtile, xb, conv, mbits, rbits, xbits, a32, r32, r64, total;
-    MixedLayout(int64_t n, int64_t nrhs)
+    MixedLayout(int64_t n, int64_t nrhs, int chunks)
     {
         trsv = 0; /* the factor's first control words serve the solves */
         dtile = 0;
         xb = ebv::factor_ws_bytes(sizeof(float), n);
-        conv = xb + ebv::trsv_xb_bytes(sizeof(float), n);
+        conv = xb + chunks * ebv::trsv_xb_bytes(sizeof(float), n);
         mbits = conv + 8;
         rbits = conv + kAlign;
         xbits = rbits + align_up(8 * (size_t)nrhs);
@@ -172,6 +181,23 @@ struct ebv_ctx {
 namespace {
 
 bool handle_ok(const ebv_ctx *h) { return h != nullptr && h->magic == kMagic; }
+
+/* The two substitutions of a solve on one system's factors (modes of
+ * dense_trsv), the workspace's control words and exchange rows. */
+template <typename T>
+hipError_t trsv_pair(int m1, int m2, const void *LU, int64_t lda, int64_t n, void *B, int64_t ldb, int64_t nrhs,
+                     void *ws, size_t ws_bytes, int32_t *info, hipStream_t st, const ebv_ctx &h)
+{
+    int *wsi = (int *)ws;
+    T *xb = (T *)((char *)ws + trsv_ctl_bytes());
+    const int chunks = trsv_fit(ws_bytes - trsv_ctl_bytes(), sizeof(T), n, nrhs);
+    const hipError_t e = ebv::dense_trsv<T>(m1, (const T *)LU, lda, (int)n, (T *)B, ldb, (int)nrhs, wsi, xb, chunks,
+                                            nullptr, info, st, ebv::TrsvStart::fresh, h.dense.wait_limit);
+    if (e != hipSuccess)
+        return e;
+    return ebv::dense_trsv<T>(m2, (const T *)LU, lda, (int)n, (T *)B, ldb, (int)nrhs, wsi, xb, chunks, nullptr, info,
+                              st, ebv::TrsvStart::running, h.dense.wait_limit);
+}
 
 int batched_slot(ebv_dtype dtype, int mixed) { return mixed ? 2 : (dtype == EBV_F32 ? 1 : 0); }
 
@@ -346,15 +372,15 @@ size_t ebv_workspace_size(int op, ebv_dtype dtype, int64_t n, int64_t nrhs, int6
         return 0;
     case EBV_OP_SOLVE:
     case EBV_OP_ADJOINT:
-        return batch <= 1 ? trsv_ws_bytes(n, elem) : 0;
+        return batch <= 1 ? trsv_ws_bytes(n, nrhs, elem) : 0;
     case EBV_OP_BATCHED:
         return BatchedLayout(n, nrhs, false).total;
     case EBV_OP_BATCHED_MIXED:
         return BatchedLayout(n, nrhs, true).total;
     case EBV_OP_MIXED:
-        return MixedLayout(n, nrhs).total;
+        return MixedLayout(n, nrhs, ebv::trsv_chunks(nrhs)).total;
     case EBV_OP_FACTOR_SOLVE:
-        return ebv::factor_ws_bytes(elem, n) + ebv::trsv_xb_bytes(elem, n);
+        return ebv::factor_ws_bytes(elem, n) + ebv::trsv_chunks(nrhs) * ebv::trsv_xb_bytes(elem, n);
     case EBV_OP_INVERSE:
         return align_up((size_t)((n + 63) / 64) * 64 * 64 * elem);
     case EBV_OP_BAND_SEGMENTS: {
@@ -532,29 +558,14 @@ int ebv_lu_solve(ebv_handle h, ebv_dtype dtype, int64_t n, int64_t nrhs, const v
     if (st != EBV_OK)
         return st;
     hipError_t e = hipSuccess;
-    if (info && (e = ebv::fill_i32(info, batch, 0, stream)) != hipSuccess)
+    if (batch > 1 && info && (e = ebv::fill_i32(info, batch, 0, stream)) != hipSuccess)
         return EBV_ERR_HIP;
     if (batch == 1) {
         const size_t elem = dtype == EBV_F32 ? sizeof(float) : sizeof(double);
-        if (!ws_ok(ws, ws_bytes, trsv_ws_bytes(n, elem)))
+        if (!ws_ok(ws, ws_bytes, trsv_ws_bytes(n, 1, elem)))
             return EBV_ERR_WORKSPACE;
-        int *wsi = (int *)ws;
-        void *xb = (char *)ws + trsv_ctl_bytes();
-        if ((e = ebv::fill_i32(wsi, 1, 0, stream)) != hipSuccess)
-            return EBV_ERR_HIP;
-        if (dtype == EBV_F64) {
-            e = ebv::dense_trsv<double>(0, (const double *)LU, lda, (int)n, (double *)B, ldb, (int)nrhs, wsi,
-                                        (double *)xb, nullptr, info, stream, false, h->dense.wait_limit);
-            if (e == hipSuccess)
-                e = ebv::dense_trsv<double>(1, (const double *)LU, lda, (int)n, (double *)B, ldb, (int)nrhs, wsi,
-                                            (double *)xb, nullptr, info, stream, false, h->dense.wait_limit);
-        } else {
-            e = ebv::dense_trsv<float>(0, (const float *)LU, lda, (int)n, (float *)B, ldb, (int)nrhs, wsi,
-                                       (float *)xb, nullptr, info, stream, false, h->dense.wait_limit);
-            if (e == hipSuccess)
-                e = ebv::dense_trsv<float>(1, (const float *)LU, lda, (int)n, (float *)B, ldb, (int)nrhs, wsi,
-                                           (float *)xb, nullptr, info, stream, false, h->dense.wait_limit);
-        }
+        e = dtype == EBV_F64 ? trsv_pair<double>(0, 1, LU, lda, n, B, ldb, nrhs, ws, ws_bytes, info, stream, *h)
+                             : trsv_pair<float>(0, 1, LU, lda, n, B, ldb, nrhs, ws, ws_bytes, info, stream, *h);
     } else {
         e = dtype == EBV_F64
                 ? ebv::batch_solve<double>(false, (const double *)LU, lda, (int)n, strideLU, (double *)B, ldb, strideB, (int)nrhs, batch, stream)
@@ -591,11 +602,12 @@ int ebv_lu_factor_solve(ebv_handle h, ebv_dtype dtype, int64_t n, int64_t nrhs, 
     if (!ws_ok(ws, ws_bytes, ebv::factor_ws_bytes(elem, n) + ebv::trsv_xb_bytes(elem, n)))
         return EBV_ERR_WORKSPACE;
     const int ni = (int)n, nr = (int)nrhs;
+    const int chunks = trsv_fit(ws_bytes - ebv::factor_ws_bytes(elem, n), elem, n, nrhs);
     const hipError_t e = dtype == EBV_F64
-                             ? ebv::factor_solve<double>((double *)A, lda, ni, info, ws, h->dense, &h->prof, stream,
-                                                         (double *)B, ldb, nr)
-                             : ebv::factor_solve<float>((float *)A, lda, ni, info, ws, h->dense, &h->prof, stream,
-                                                        (float *)B, ldb, nr);
+                             ? ebv::factor_solve<double>((double *)A, lda, ni, info, ws, chunks, h->dense, &h->prof,
+                                                         stream, (double *)B, ldb, nr)
+                             : ebv::factor_solve<float>((float *)A, lda, ni, info, ws, chunks, h->dense, &h->prof,
+                                                        stream, (float *)B, ldb, nr);
     return hip_status(e);
 }
 
@@ -636,11 +648,13 @@ int ebv_lu_factor_solve_noalloc(ebv_handle h, ebv_dtype dtype, int64_t n, int64_
      * control words and marks the exchange rows, so nothing left in the
      * array by an earlier call is read */
     const int ni = (int)n, nr = (int)nrhs;
+    const size_t elem = dtype == EBV_F32 ? sizeof(float) : sizeof(double);
+    const int chunks = trsv_fit(kScratchBytes - ebv::factor_ws_bytes(elem, n), elem, n, nrhs);
     const hipError_t e = dtype == EBV_F64
-                             ? ebv::factor_solve<double>((double *)A, lda, ni, info, d.scratch, h->dense, &h->prof,
-                                                         stream, (double *)B, ldb, nr)
-                             : ebv::factor_solve<float>((float *)A, lda, ni, info, d.scratch, h->dense, &h->prof,
-                                                        stream, (float *)B, ldb, nr);
+                             ? ebv::factor_solve<double>((double *)A, lda, ni, info, d.scratch, chunks, h->dense,
+                                                         &h->prof, stream, (double *)B, ldb, nr)
+                             : ebv::factor_solve<float>((float *)A, lda, ni, info, d.scratch, chunks, h->dense,
+                                                        &h->prof, stream, (float *)B, ldb, nr);
     return hip_status(e);
 }
 
@@ -718,6 +732,7 @@ int ebv_pipeline_factor_solve(ebv_handle h, ebv_dtype dtype, int64_t count, int6
     const size_t elem = dtype == EBV_F32 ? sizeof(float) : sizeof(double);
     if (!ws_ok(ws, ws_bytes, ebv::factor_ws_bytes(elem, n) + ebv::trsv_xb_bytes(elem, n)))
         return EBV_ERR_WORKSPACE;
+    const int chunks = trsv_fit(ws_bytes - ebv::factor_ws_bytes(elem, n), elem, n, nrhs);
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess)
         return EBV_ERR_HIP;
@@ -757,11 +772,11 @@ int ebv_pipeline_factor_solve(ebv_handle h, ebv_dtype dtype, int64_t count, int6
         if (e == hipSuccess) {
             int32_t *inf = info ? info + s : nullptr;
             e = dtype == EBV_F64
-                    ? (nrhs > 0 ? ebv::factor_solve<double>((double *)dA[k], n, (int)n, inf, ws, h->dense, &h->prof,
+                    ? (nrhs > 0 ? ebv::factor_solve<double>((double *)dA[k], n, (int)n, inf, ws, chunks, h->dense, &h->prof,
                                                             compute, (double *)dB[k], nrhs, (int)nrhs)
                                 : ebv::dense_factor<double>((double *)dA[k], n, (int)n, inf, ws, h->dense, &h->prof,
                                                             compute))
-                    : (nrhs > 0 ? ebv::factor_solve<float>((float *)dA[k], n, (int)n, inf, ws, h->dense, &h->prof,
+                    : (nrhs > 0 ? ebv::factor_solve<float>((float *)dA[k], n, (int)n, inf, ws, chunks, h->dense, &h->prof,
                                                            compute, (float *)dB[k], nrhs, (int)nrhs)
                                 : ebv::dense_factor<float>((float *)dA[k], n, (int)n, inf, ws, h->dense, &h->prof,
                                                            compute));
@@ -1126,28 +1141,13 @@ int ebv_lu_solve_adjoint(ebv_handle h, ebv_dtype dtype, int64_t n, int64_t nrhs,
         return st;
     hipError_t e = hipSuccess;
     const bool f64 = dtype == EBV_F64;
-    if (info && (e = ebv::fill_i32(info, batch, 0, stream)) != hipSuccess)
+    if (batch > 1 && info && (e = ebv::fill_i32(info, batch, 0, stream)) != hipSuccess)
         return EBV_ERR_HIP;
     if (batch == 1) {
-        if (!ws_ok(ws, ws_bytes, trsv_ws_bytes(n, f64 ? sizeof(double) : sizeof(float))))
+        if (!ws_ok(ws, ws_bytes, trsv_ws_bytes(n, 1, f64 ? sizeof(double) : sizeof(float))))
             return EBV_ERR_WORKSPACE;
-        int *wsi = (int *)ws;
-        void *xb = (char *)ws + trsv_ctl_bytes();
-        if ((e = ebv::fill_i32(wsi, 1, 0, stream)) != hipSuccess)
-            return EBV_ERR_HIP;
-        if (f64) {
-            e = ebv::dense_trsv<double>(2, (const double *)LU, lda, (int)n, (double *)Bbar, ldb, (int)nrhs, wsi,
-                                        (double *)xb, nullptr, info, stream, false, h->dense.wait_limit);
-            if (e == hipSuccess)
-                e = ebv::dense_trsv<double>(3, (const double *)LU, lda, (int)n, (double *)Bbar, ldb, (int)nrhs, wsi,
-                                            (double *)xb, nullptr, info, stream, false, h->dense.wait_limit);
-        } else {
-            e = ebv::dense_trsv<float>(2, (const float *)LU, lda, (int)n, (float *)Bbar, ldb, (int)nrhs, wsi,
-                                       (float *)xb, nullptr, info, stream, false, h->dense.wait_limit);
-            if (e == hipSuccess)
-                e = ebv::dense_trsv<float>(3, (const float *)LU, lda, (int)n, (float *)Bbar, ldb, (int)nrhs, wsi,
-                                           (float *)xb, nullptr, info, stream, false, h->dense.wait_limit);
-        }
+        e = f64 ? trsv_pair<double>(2, 3, LU, lda, n, Bbar, ldb, nrhs, ws, ws_bytes, info, stream, *h)
+                : trsv_pair<float>(2, 3, LU, lda, n, Bbar, ldb, nrhs, ws, ws_bytes, info, stream, *h);
     } else {
         e = f64 ? ebv::batch_solve<double>(true, (const double *)LU, lda, (int)n, strideLU, (double *)Bbar, ldb, strideB, (int)nrhs, batch, stream)
                 : ebv::batch_solve<float>(true, (const float *)LU, lda, (int)n, strideLU, (float *)Bbar, ldb, strideB, (int)nrhs, batch, stream);
@@ -1195,7 +1195,10 @@ int ebv_lu_solve_mixed(ebv_handle h, int64_t n, int64_t nrhs, const double *A, i
     int st = ebv_init();
     if (st != EBV_OK)
         return st;
-    const MixedLayout lay(n, nrhs);
+    int chunks = ebv::trsv_chunks(nrhs);
+    while (chunks > 1 && ws_bytes < MixedLayout(n, nrhs, chunks).total)
+        --chunks;
+    const MixedLayout lay(n, nrhs, chunks);
     if (!ws_ok(ws, ws_bytes, lay.total))
         return EBV_ERR_WORKSPACE;
     char *w = (char *)ws;
@@ -1226,8 +1229,10 @@ int ebv_lu_solve_mixed(ebv_handle h, int64_t n, int64_t nrhs, const double *A, i
     EBV_TRY(ebv::dense_factor<float>(A32, n, ni, info, (void *)(w + lay.dtile), h->dense, nullptr, stream));
     EBV_TRY((ebv::convert<double, float>(ni, nr, B, ldb, R32, nrhs, nullptr, stream)));
     for (int it = 0; it <= max_iter; ++it) {
-        EBV_TRY(ebv::dense_trsv<float>(0, A32, n, ni, R32, nrhs, nr, wsi, XB, conv, nullptr, stream, false, h->dense.wait_limit));
-        EBV_TRY(ebv::dense_trsv<float>(1, A32, n, ni, R32, nrhs, nr, wsi, XB, conv, nullptr, stream, false, h->dense.wait_limit));
+        EBV_TRY(ebv::dense_trsv<float>(0, A32, n, ni, R32, nrhs, nr, wsi, XB, chunks, conv, nullptr, stream, ebv::TrsvStart::running,
+                                       h->dense.wait_limit));
+        EBV_TRY(ebv::dense_trsv<float>(1, A32, n, ni, R32, nrhs, nr, wsi, XB, chunks, conv, nullptr, stream, ebv::TrsvStart::running,
+                                       h->dense.wait_limit));
         EBV_TRY(ebv::mixed_xupdate(ni, nr, X, ldx, R32, nrhs, it == 0, xbits, conv, stream));
         EBV_TRY(ebv::mixed_residual(ni, nr, A, lda, B, ldb, X, ldx, R64, nrhs, rbits, conv, stream));
         EBV_TRY(ebv::mixed_check(nr, rbits, xbits, mbits, tol, it, iters, ferr, conv, stream));

@@ -62,6 +62,14 @@ constexpr size_t trsv_xb_bytes(size_t elem, int64_t n)
     const int64_t nb = (n + 63) / 64;
     return ((size_t)(kTrsvHelpers + 1) * nb * 64 * 16 * elem + 255) / 256 * 256;
 }
+/* Chunks of 16 right-hand sides solved side by side: what a workspace is sized
+ * for (four chains of n = 4096 and three workgroups a block put 768 workgroups
+ * on 256 compute units; more would only queue). */
+constexpr int kTrsvChunks = 4;
+constexpr int trsv_chunks(int64_t nrhs)
+{
+    return nrhs <= 16 ? 1 : (int)((nrhs + 15) / 16 < kTrsvChunks ? (nrhs + 15) / 16 : kTrsvChunks);
+}
 
 /* Explicit inverse from the factors: P receives the inverse packs of the
  * diagonal tiles (ceil(n/64) * 64 * 64 elements), X (n x n, pitch ldx) the
@@ -103,18 +111,22 @@ template <typename T>
 hipError_t dense_factor(T *A, int64_t lda, int n, int32_t *info, void *ws, const DenseTuning &tun, UpdateProfile *prof,
                         hipStream_t st, T *B = nullptr, int64_t ldb = 0, int nrhs = 0, bool prefilled = false);
 /* Factor + backward substitution on a workspace of factor_ws_bytes followed
- * by trsv_xb_bytes (B riding along in the factor). */
+ * by `chunks` (>= 1) times trsv_xb_bytes (B riding along in the factor). */
 template <typename T>
-hipError_t factor_solve(T *A, int64_t lda, int n, int32_t *info, void *ws, const DenseTuning &tun, UpdateProfile *prof,
-                        hipStream_t st, T *B, int64_t ldb, int nrhs);
-/* Multi-workgroup triangular solve: wsi = status, ticket counter, solved
- * counter (kCtlHead ints); xb = exchange buffer of trsv_xb_bytes(sizeof(T), n);
- * prefilled: the counters are zero and xb is marked for the first launch;
+hipError_t factor_solve(T *A, int64_t lda, int n, int32_t *info, void *ws, int chunks, const DenseTuning &tun,
+                        UpdateProfile *prof, hipStream_t st, T *B, int64_t ldb, int nrhs);
+/* Multi-workgroup triangular solve: wsi = status, ticket counter, a solved
+ * counter per chunk of 16 right-hand sides; xb = `chunks` (>= 1) exchange
+ * buffers of trsv_xb_bytes(sizeof(T), n), as many chunks run side by side;
  * info (or NULL): receives -status at the end of each launch when the status
- * word is nonzero. */
+ * word is nonzero.  start: what the first launch finds -- fresh: nothing
+ * (status, info and counters are cleared, xb marked), running: the status of
+ * earlier launches, which is kept, ready: with up to 16 right-hand sides (or
+ * chunks = 1) also cleared counters and marked rows. */
+enum class TrsvStart { fresh, running, ready };
 template <typename T>
 hipError_t dense_trsv(int mode, const T *LU, int64_t lda, int n, T *B, int64_t ldb, int nrhs, int *wsi, T *xb,
-                      const int *skip, int32_t *info, hipStream_t st, bool prefilled = false,
+                      int chunks, const int *skip, int32_t *info, hipStream_t st, TrsvStart start,
                       long long wait_limit = 0);
 template <typename T>
 hipError_t batch_factor(T *A, int64_t lda, int n, int64_t batch, int64_t strideA, int32_t *info, hipStream_t st);

@@ -81,21 +81,6 @@ hipError_t fold_status(const int *status, int32_t *info, hipStream_t st)
     return hipGetLastError();
 }
 
-/* Fill count elements of an exchange buffer with the unsolved mark (as raw
- * bits: the mark never passes through floating-point registers). */
-template <typename T> static hipError_t fill_unsolved(T *p, int64_t count, hipStream_t st)
-{
-    if (count <= 0)
-        return hipSuccess;
-    if (sizeof(T) == 8) {
-        const int grid = (int)std::min<int64_t>((count + 255) / 256, 1024);
-        hipLaunchKernelGGL(k_fill_u64, dim3(grid), dim3(256), 0, st, reinterpret_cast<unsigned long long *>(p),
-                           count, kUnsolvedMark64);
-        return hipGetLastError();
-    }
-    return fill_i32(reinterpret_cast<int *>(p), count, (int)kUnsolvedMark32, st);
-}
-
 /* ------------------------------------------------------- dense factor --- */
 
 /* LDS of the workgroup that factors a diagonal tile: the tile, the packed
@@ -882,10 +867,10 @@ hipError_t dense_factor(T *A, int64_t lda, int n, int32_t *info, void *ws, const
     return factor_phases(A, lda, n, info, Pg, tun, pr, st, B, ldb, nrhs);
 }
 
-/* Start of a factor + solve: the control words and info cleared and the
- * backward substitution's exchange rows marked unsolved, in one launch. */
+/* Start of a solve (or a factor + solve): control words and info cleared and
+ * the substitution's exchange rows marked unsolved, in one launch. */
 template <typename T>
-__global__ void k_init_factor_solve(int *ctl, int nctl, int32_t *info, T *xb, int64_t nxb)
+__global__ void k_solve_init(int *ctl, int nctl, int32_t *info, T *xb, int64_t nxb)
 {
     const int64_t i0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, step = (int64_t)gridDim.x * blockDim.x;
     for (int64_t i = i0; i < nctl; i += step)
@@ -904,16 +889,24 @@ __global__ void k_init_factor_solve(int *ctl, int nctl, int32_t *info, T *xb, in
 }
 
 template <typename T>
-hipError_t factor_solve(T *A, int64_t lda, int n, int32_t *info, void *ws, const DenseTuning &tun, UpdateProfile *pr,
-                        hipStream_t st, T *B, int64_t ldb, int nrhs)
+static hipError_t solve_init(int *ctl, int nctl, int32_t *info, T *xb, int64_t nxb, hipStream_t st)
+{
+    const int grid = (int)std::min<int64_t>((nxb + 255) / 256 + 1, 1024);
+    hipLaunchKernelGGL((k_solve_init<T>), dim3(grid), dim3(256), 0, st, ctl, nctl, info, xb, nxb);
+    return hipGetLastError();
+}
+
+template <typename T>
+hipError_t factor_solve(T *A, int64_t lda, int n, int32_t *info, void *ws, int chunks, const DenseTuning &tun,
+                        UpdateProfile *pr, hipStream_t st, T *B, int64_t ldb, int nrhs)
 {
     const int nb = (n + TB - 1) / TB;
     int *ctl = static_cast<int *>(ws);
     T *xb = reinterpret_cast<T *>(static_cast<char *>(ws) + factor_ws_bytes(sizeof(T), n));
-    const int64_t nxb = nrhs > 0 ? (int64_t)(kTrsvHelpers + 1) * nb * TB * 16 : 0;
-    const int grid = (int)std::min<int64_t>((nxb + 255) / 256 + 1, 1024);
-    hipLaunchKernelGGL((k_init_factor_solve<T>), dim3(grid), dim3(256), 0, st, ctl, kCtlHead + 2 * nb, info, xb, nxb);
-    hipError_t e = hipGetLastError();
+    /* the exchange rows are marked here when one chunk at a time uses them */
+    const bool mark = nrhs > 0 && (chunks == 1 || nrhs <= 16);
+    const int64_t nxb = mark ? (int64_t)(kTrsvHelpers + 1) * nb * TB * 16 : 0;
+    hipError_t e = solve_init<T>(ctl, kCtlHead + 2 * nb, info, xb, nxb, st);
     if (e == hipSuccess)
         e = dense_factor<T>(A, lda, n, info, ws, tun, pr, st, B, ldb, nrhs, true);
     if (e != hipSuccess)
@@ -921,7 +914,8 @@ hipError_t factor_solve(T *A, int64_t lda, int n, int32_t *info, void *ws, const
     /* the backward substitution reports the status word into info at its
      * end; without right-hand sides a separate launch does */
     if (nrhs > 0)
-        return dense_trsv<T>(TRI_U, A, lda, n, B, ldb, nrhs, ctl, xb, nullptr, info, st, true, tun.wait_limit);
+        return dense_trsv<T>(TRI_U, A, lda, n, B, ldb, nrhs, ctl, xb, chunks, nullptr, info, st, TrsvStart::ready,
+                             tun.wait_limit);
     return fold_status(ctl, info, st);
 }
 
@@ -942,9 +936,13 @@ hipError_t factor_solve(T *A, int64_t lda, int n, int32_t *info, void *ws, const
  *     z = D^{-1} r;
  * so that each of the two last blocks costs one product in registers as it
  * arrives: y = z - W_{j1} y_{j1} - W_{j2} y_{j2} (the two products in an
- * accumulator of their own, so neither waits for z).  Up to 16 right-hand
- * sides per launch (the 16 columns of the matrix-core products); wave w
- * owns rows 16w..16w+15 of the block.
+ * accumulator of their own, so neither waits for z).  The 16 columns of the
+ * matrix-core products are 16 right-hand sides; further ones go in chunks of
+ * 16, up to kTrsvChunks of them side by side in one launch, each a chain of
+ * its own (the launch is bound by the chain's latency, 2.2 us a block, not by
+ * the compute units: 47 blocks and 40 right-hand sides, forward and backward,
+ * 656 us in three launches each, one after the other).  Wave w owns rows
+ * 16w..16w+15 of the block.
  * Solved blocks are exchanged through XB (n rounded up to 64 rows, pitch 16,
  * filled with the unsolved mark before the launch): a workgroup stores its
  * block there with coherent stores and, without waiting for them, raises
@@ -957,22 +955,22 @@ hipError_t factor_solve(T *A, int64_t lda, int n, int32_t *info, void *ws, const
  */
 template <typename T, int MODE>
 __global__ __launch_bounds__(NT) void k_trsv(const T *__restrict__ LU, int64_t lda, int n, T *__restrict__ B,
-                                             int64_t ldb, int nrhs_here, int *wsi, T *__restrict__ XB, const int *skip,
-                                             int32_t *info, long wlim)
+                                             int64_t ldb, int nrhs, int nch, int *wsi, T *__restrict__ XB,
+                                             const int *skip, int32_t *info, long wlim)
 {
     typedef typename vec4<T>::type V;
     if (skip && *skip)
         return;
     __shared__ TileSmem<T> sm;
     __shared__ T wls[2][16][NT]; /* -W of the last two blocks, A-operand order per thread */
-    int *status = wsi, *ctr = wsi + 1, *solved = wsi + 2;
+    int *status = wsi, *ctr = wsi + 1;
     if (threadIdx.x == 0) {
         sm.ticket = atomicAdd(ctr, 1);
         sm.avail = 0;
     }
     __syncthreads();
     const int nb = (n + TB - 1) / TB;
-    if (sm.ticket >= (kTrsvHelpers + 1) * nb) { /* counter not reset: refuse rather than index out of range */
+    if (sm.ticket >= (kTrsvHelpers + 1) * nb * nch) { /* counter not reset: refuse rather than index out of range */
         if (threadIdx.x == 0)
             atomicOr(status, 2);
         return;
@@ -980,8 +978,14 @@ __global__ __launch_bounds__(NT) void k_trsv(const T *__restrict__ LU, int64_t l
     constexpr bool FWD = tri_forward(MODE), TR = tri_trans(MODE), UNITL = (MODE == TRI_L || MODE == TRI_LT);
     /* kTrsvHelpers helpers, then the block's own workgroup, per position:
      * a workgroup only ever waits for lower tickets */
-    const int pos = sm.ticket / (kTrsvHelpers + 1), role = sm.ticket % (kTrsvHelpers + 1);
+    const int item = sm.ticket / (kTrsvHelpers + 1), role = sm.ticket % (kTrsvHelpers + 1);
+    const int pos = item / nch, ch = item - pos * nch;
     const bool helper = role < kTrsvHelpers;
+    /* this chunk's columns, exchange rows and counter */
+    const int nrhs_here = min(16, nrhs - 16 * ch);
+    int *solved = wsi + 2 + ch;
+    B += 16 * ch;
+    XB += (int64_t)ch * (kTrsvHelpers + 1) * nb * TB * 16;
     const int blk = FWD ? pos : nb - 1 - pos;
     const int ndep = pos; /* blocks solved before this one */
     const int t = threadIdx.x, w = wave_id(), l = t & 63, lr = l & 15, lk = l >> 4;
@@ -1271,21 +1275,22 @@ __global__ __launch_bounds__(NT) void k_trsv(const T *__restrict__ LU, int64_t l
 }
 
 template <typename T, int MODE>
-static hipError_t trsv_mode(const T *LU, int64_t lda, int n, T *B, int64_t ldb, int nrhs, int *wsi, T *xb,
-                            const int *skip, int32_t *info, hipStream_t st, bool prefilled, long wlim)
+static hipError_t trsv_mode(const T *LU, int64_t lda, int n, T *B, int64_t ldb, int nrhs, int *wsi, T *xb, int chunks,
+                            const int *skip, int32_t *info, hipStream_t st, TrsvStart start, long wlim)
 {
     const int nb = (n + TB - 1) / TB;
+    const int64_t nx = (int64_t)(kTrsvHelpers + 1) * nb * TB * 16;
     hipError_t e = hipSuccess;
-    for (int c0 = 0; c0 < nrhs; c0 += 16) {
-        const int nh = min(16, nrhs - c0);
-        if (!(prefilled && c0 == 0)) { /* counters cleared, exchange rows marked */
-            if ((e = fill_i32(wsi + 1, kCtlHead - 1, 0, st)) != hipSuccess)
-                return e;
-            if ((e = fill_unsolved(xb, (int64_t)(kTrsvHelpers + 1) * nb * TB * 16, st)) != hipSuccess)
+    for (int c0 = 0; c0 < nrhs; c0 += 16 * chunks) {
+        const int nc = min(16 * chunks, nrhs - c0), nch = (nc + 15) / 16;
+        if (c0 > 0 || start != TrsvStart::ready || nch > 1) { /* counters cleared, exchange rows marked */
+            const bool all = c0 == 0 && start == TrsvStart::fresh;
+            if ((e = solve_init<T>(wsi + (all ? 0 : 1), (all ? 2 : 1) + nch, all ? info : nullptr, xb, nch * nx, st)) !=
+                hipSuccess)
                 return e;
         }
-        hipLaunchKernelGGL((k_trsv<T, MODE>), dim3((kTrsvHelpers + 1) * nb), dim3(NT), 0, st, LU, lda, n, B + c0, ldb,
-                           nh, wsi, xb, skip, info, wlim);
+        hipLaunchKernelGGL((k_trsv<T, MODE>), dim3((kTrsvHelpers + 1) * nb * nch), dim3(NT), 0, st, LU, lda, n, B + c0,
+                           ldb, nc, nch, wsi, xb, skip, info, wlim);
         if ((e = hipGetLastError()) != hipSuccess)
             return e;
     }
@@ -1294,14 +1299,14 @@ static hipError_t trsv_mode(const T *LU, int64_t lda, int n, T *B, int64_t ldb, 
 
 template <typename T>
 hipError_t dense_trsv(int mode, const T *LU, int64_t lda, int n, T *B, int64_t ldb, int nrhs, int *wsi, T *xb,
-                      const int *skip, int32_t *info, hipStream_t st, bool prefilled, long long wait_limit)
+                      int chunks, const int *skip, int32_t *info, hipStream_t st, TrsvStart start, long long wait_limit)
 {
     const long wl = wait_limit > 0 ? (long)wait_limit : 1L << 22;
     switch (mode) {
-    case TRI_L: return trsv_mode<T, TRI_L>(LU, lda, n, B, ldb, nrhs, wsi, xb, skip, info, st, prefilled, wl);
-    case TRI_U: return trsv_mode<T, TRI_U>(LU, lda, n, B, ldb, nrhs, wsi, xb, skip, info, st, prefilled, wl);
-    case TRI_UT: return trsv_mode<T, TRI_UT>(LU, lda, n, B, ldb, nrhs, wsi, xb, skip, info, st, prefilled, wl);
-    default: return trsv_mode<T, TRI_LT>(LU, lda, n, B, ldb, nrhs, wsi, xb, skip, info, st, prefilled, wl);
+    case TRI_L: return trsv_mode<T, TRI_L>(LU, lda, n, B, ldb, nrhs, wsi, xb, chunks, skip, info, st, start, wl);
+    case TRI_U: return trsv_mode<T, TRI_U>(LU, lda, n, B, ldb, nrhs, wsi, xb, chunks, skip, info, st, start, wl);
+    case TRI_UT: return trsv_mode<T, TRI_UT>(LU, lda, n, B, ldb, nrhs, wsi, xb, chunks, skip, info, st, start, wl);
+    default: return trsv_mode<T, TRI_LT>(LU, lda, n, B, ldb, nrhs, wsi, xb, chunks, skip, info, st, start, wl);
     }
 }
 
@@ -3525,14 +3530,14 @@ template hipError_t dense_factor<double>(double *, int64_t, int, int32_t *, void
                                         hipStream_t, double *, int64_t, int, bool);
 template hipError_t dense_factor<float>(float *, int64_t, int, int32_t *, void *, const DenseTuning &, UpdateProfile *,
                                        hipStream_t, float *, int64_t, int, bool);
-template hipError_t factor_solve<double>(double *, int64_t, int, int32_t *, void *, const DenseTuning &, UpdateProfile *,
+template hipError_t factor_solve<double>(double *, int64_t, int, int32_t *, void *, int, const DenseTuning &, UpdateProfile *,
                                          hipStream_t, double *, int64_t, int);
-template hipError_t factor_solve<float>(float *, int64_t, int, int32_t *, void *, const DenseTuning &, UpdateProfile *,
+template hipError_t factor_solve<float>(float *, int64_t, int, int32_t *, void *, int, const DenseTuning &, UpdateProfile *,
                                         hipStream_t, float *, int64_t, int);
-template hipError_t dense_trsv<double>(int, const double *, int64_t, int, double *, int64_t, int, int *, double *,
-                                       const int *, int32_t *, hipStream_t, bool, long long);
-template hipError_t dense_trsv<float>(int, const float *, int64_t, int, float *, int64_t, int, int *, float *,
-                                      const int *, int32_t *, hipStream_t, bool, long long);
+template hipError_t dense_trsv<double>(int, const double *, int64_t, int, double *, int64_t, int, int *, double *, int,
+                                       const int *, int32_t *, hipStream_t, TrsvStart, long long);
+template hipError_t dense_trsv<float>(int, const float *, int64_t, int, float *, int64_t, int, int *, float *, int,
+                                      const int *, int32_t *, hipStream_t, TrsvStart, long long);
 template hipError_t batch_factor<double>(double *, int64_t, int, int64_t, int64_t, int32_t *, hipStream_t);
 template hipError_t batch_factor<float>(float *, int64_t, int, int64_t, int64_t, int32_t *, hipStream_t);
 template hipError_t batch_solve<double>(bool, const double *, int64_t, int, int64_t, double *, int64_t, int64_t, int, int64_t, hipStream_t);
