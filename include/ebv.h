@@ -137,10 +137,9 @@ size_t ebv_workspace_status_offset(void);
 size_t ebv_workspace_size(int op, ebv_dtype dtype, int64_t n, int64_t nrhs, int64_t batch);
 
 /* Tuning of the single-system factor (ebv_lu_factor with batch = 1 and
- * ebv_lu_factor_solve) held by handle h.  small_update_below: look-ahead
- * update tiles are 128 x 64 while the trailing block is larger than this,
- * else 64 x 64 (default 0; the launch-per-phase scheme uses 128 x 128 and
- * 64 x 64).  lookahead: 1 (default) runs one launch per 64-wide block step,
+ * ebv_lu_factor_solve) held by handle h.  small_update_below: the FP32
+ * factor's update tiles are 128 x 64 while the trailing block is larger than
+ * this, else 64 x 64 (default 0; FP64 update tiles are 64 x 64).  lookahead: 1 (default) runs one launch per 64-wide block step,
  * in which the next diagonal tile and panel are formed while the trailing
  * update of the current step runs; 0 runs the panel and the update as
  * separate launches.  defer_group G (1..4, default 3) and defer_above

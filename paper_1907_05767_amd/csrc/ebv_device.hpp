@@ -198,29 +198,7 @@ __device__ __forceinline__ void stage64(T *S, const T *__restrict__ G, int64_t l
                  });
 }
 
-/* Two stage64 transfers (non-transposed) with all loads of both issued
- * before any store: one memory latency for the pair. */
-template <typename T>
-__device__ __forceinline__ void stage64x2(T *S1, const T *__restrict__ G1, int64_t ld1, int nr1, int nc1, T *S2,
-                                          const T *__restrict__ G2, int64_t ld2, int nr2, int nc2)
-{
-    const int c = launder((int)threadIdx.x & 63), r0 = launder((int)threadIdx.x >> 6);
-    T v1[16], v2[16];
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-        const int r = r0 + 4 * i;
-        v1[i] = (r < nr1 && c < nc1) ? G1[(int64_t)r * ld1 + c] : T(0);
-        v2[i] = (r < nr2 && c < nc2) ? G2[(int64_t)r * ld2 + c] : T(0);
-    }
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-        const int r = r0 + 4 * i;
-        S1[r * LDT + c] = v1[i];
-        S2[r * LDT + c] = v2[i];
-    }
-}
-
-/* Dense C addressing for wg_gemm64: element (r, c) of an nr x nc tile. */
+/* Address map of a tile in memory: element (r, c) of an nr x nc tile. */
 template <typename T> struct DenseC {
     T *C;
     int64_t ldc;
@@ -230,57 +208,6 @@ template <typename T> struct DenseC {
         return (r < nr && c < nc) ? C + (int64_t)r * ldc + c : nullptr;
     }
 };
-
-/*
- * C(64x64 tile) -= A * B with A^T and B staged in LDS (pitch LDT, K = 64,
- * zero-padded): the trailing rank-64 update of Eq. 6-c applied 64 elimination
- * steps at a time, on the matrix cores.  `cref(r, c)` returns the address of
- * C's element (r, c), or nullptr for elements outside the tile's valid part.
- * Wave w computes the 32x32 quadrant (w / 2, w % 2).
- */
-template <typename T, typename CRef>
-__device__ __forceinline__ void wg_gemm64(const CRef &cref, const T *sAT, const T *sB)
-{
-    typedef typename vec4<T>::type V;
-    const int w = wave_id(), l = threadIdx.x & 63;
-    const int wm = (w >> 1) * 32, wn = (w & 1) * 32;
-    const int lr = l & 15, lk = l >> 4;
-    V acc[2][2];
-#pragma unroll
-    for (int bi = 0; bi < 2; ++bi)
-#pragma unroll
-        for (int bj = 0; bj < 2; ++bj)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const T *p = cref(wm + 16 * bi + acc_row<T>(lk, r), wn + 16 * bj + lr);
-                acc[bi][bj][r] = p ? *p : T(0);
-            }
-#pragma unroll 4
-    for (int k = 0; k < TB; k += 4) {
-        T a[2], b[2];
-#pragma unroll
-        for (int bi = 0; bi < 2; ++bi)
-            a[bi] = -sAT[(k + lk) * LDT + wm + 16 * bi + lr];
-#pragma unroll
-        for (int bj = 0; bj < 2; ++bj)
-            b[bj] = sB[(k + lk) * LDT + wn + 16 * bj + lr];
-#pragma unroll
-        for (int bi = 0; bi < 2; ++bi)
-#pragma unroll
-            for (int bj = 0; bj < 2; ++bj)
-                acc[bi][bj] = mfma16(a[bi], b[bj], acc[bi][bj]);
-    }
-#pragma unroll
-    for (int bi = 0; bi < 2; ++bi)
-#pragma unroll
-        for (int bj = 0; bj < 2; ++bj)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                T *p = cref(wm + 16 * bi + acc_row<T>(lk, r), wn + 16 * bj + lr);
-                if (p)
-                    *p = acc[bi][bj][r];
-            }
-}
 
 /* --------------------------------------------- blocked tile factor --- */
 
@@ -398,6 +325,8 @@ template <int K> __device__ __forceinline__ void row_step8(float (&x)[8], float 
     asm(EBV_ROW_STEP8("f32") : EBV_ROW_ARGS8(x) : [f] "v"(f), [k] "i"(K));
 }
 
+constexpr int DBP = 17; /* pitch of the four diagonal blocks packed by themselves */
+
 /* Compile-time loop: f(integral_constant<int, I>) for I = 0 .. N - 1. */
 template <int I, int N, typename F> __device__ __forceinline__ void static_for(F &&f)
 {
@@ -426,8 +355,10 @@ struct NoStripHook {
  * What bounds it is the chain: per step a broadcast pivot, its reciprocal and
  * about 16 fused multiply-adds.
  *
- * P (pitch LDT) receives the inverses of the four diagonal blocks as
- * tile_inv16 packs them (L^{-1} strictly lower, U^{-1} upper), rinv 1/U_kk.
+ * P receives the inverses of the four diagonal blocks as tile_inv16 packs them
+ * (L^{-1} strictly lower, U^{-1} upper): element (r, c) of block p at
+ * P[(16p + r) LDT + 16p + c], or with PACKED, where nothing else goes there,
+ * at P[(16p + r) DBP + c]; rinv (if not null) 1/U_kk.
  * Rows and columns past nvalid must hold the identity, which is kept.
  * Returns 0 or k+1 for the first exactly-zero pivot k < nvalid (the same in
  * every thread).  strip(p, 0) is called by every thread once strip p of S, its
@@ -442,17 +373,17 @@ struct NoStripHook {
  * each).  A form with the chain on one wave, two pivots at a time over LDS
  * broadcasts, and the inverses after it took 46k (FP32 47k).
  */
-template <typename T, typename Strip = NoStripHook>
+template <typename T, bool PACKED = false, typename Strip = NoStripHook>
 __device__ __forceinline__ int tile_lu64(T *S, T *P, T *rinv, int nvalid, int *zflag, Strip &&strip = Strip())
 {
     typedef typename vec4<T>::type V;
+    constexpr int PP = PACKED ? DBP : LDT; /* pitch of P */
     S = launder(S);
     P = launder(P);
-    rinv = launder(rinv);
     const int t = threadIdx.x, w = wave_id(), l = launder(t & 63), i = l & 15, g = l >> 4;
     const bool lside = w & 1; /* transposed: L below the block */
     const int half = w >> 1, q = 4 * half + g; /* this lane's chunk of eight carried columns */
-    const int ks = lside ? LDT : 1; /* LDS step from one carried column (row) to the next */
+    const int ks = lside ? (q < 6 ? LDT : PP) : 1; /* LDS step from one carried column (row) to the next */
     if (t == 0)
         *zflag = 0;
 #pragma unroll 1
@@ -464,9 +395,10 @@ __device__ __forceinline__ int tile_lu64(T *S, T *P, T *rinv, int nvalid, int *z
          * goes to P (lim of the lane's eight), the rest to the pad column */
         const int e0 = q < 6 ? 16 + 8 * q : 8 * (q - 6);
         const bool tile = q < 6 - 2 * p;
-        T *E = (q < 6 ? S : P) + c0 * LDT + c0 + (lside ? e0 * LDT + i : i * LDT + e0);
+        T *E = q < 6 ? D + (lside ? e0 * LDT + i : i * LDT + e0)
+                     : P + c0 * PP + (PACKED ? 0 : c0) + (lside ? e0 * PP + i : i * PP + e0);
         const int lim = q < 6 ? (tile ? 8 : 0) : i - e0 + (lside ? 1 : 0);
-        T *pad = P + l * LDT + TB;
+        T *pad = P + l * PP + (PACKED ? 16 : TB);
         T a[16], x[8], rv = T(0);
 #pragma unroll
         for (int j = 0; j < 16; ++j)
@@ -499,7 +431,7 @@ __device__ __forceinline__ int tile_lu64(T *S, T *P, T *rinv, int nvalid, int *z
 #pragma unroll
             for (int j = 0; j < 8; ++j)
                 D[i * LDT + 8 * half + j] = half ? a[8 + j] : a[j];
-            if (half == 0)
+            if (half == 0 && rinv)
                 rinv[c0 + i] = rv;
         }
         __syncthreads();

@@ -172,108 +172,207 @@ __global__ __launch_bounds__(NT) void k_panel(T *__restrict__ A, int64_t lda, in
 }
 
 /*
- * Trailing update A22 -= L21 U12 of one BM x BN tile (rows r0.., columns
- * c0.., K = kw <= 64 columns of the panel at k0): the rank-kw update of
- * Eq. 6-c on the matrix cores.  The tile is held in registers for the whole
- * K loop (read once, written once); 4 waves, each a (BM/2) x (BN/2) block of
- * 16x16 matrix-core tiles.  K runs in BK-deep chunks through double-buffered
- * LDS: the next chunk's global loads are in flight while the current one
- * feeds the matrix cores.  L21 is kept row-major in LDS with an odd pitch
- * (conflict-free column reads), U12 row-major.  The top-left skip x skip
- * corner of the tile is not stored (it belongs to another workgroup).
+ * Product of a BM x K and a K x BN block of a matrix in memory (K a multiple
+ * of 16) into the accumulators of four waves, each a 16 MB x 16 NB part of the
+ * BM x BN tile: acc += A B, or with NEG acc -= A B, the rank-K update of Eq.
+ * 6-c.  K runs in 16-deep chunks through double-buffered LDS: the next chunk's
+ * global loads are in flight while the current one feeds the matrix cores.
+ * Both operands are read row by row in 16-byte vectors (at any alignment of
+ * the leading dimension), with nothing but two pointer increments per chunk
+ * between them and no branch, so that the waits count single loads.  A lies in
+ * LDS by rows, pitch 16 + one vector, so that a lane reads two (four) inner
+ * indices of its row at once and lane group lk supplies the indices 2 lk, 2 lk
+ * + 1 (4 lk ..) of each eight (sixteen); B by rows, the pitch spreading those
+ * indices' rows over the banks.
+ * EDGE: only nr rows of A and nc columns of B exist; past them the last one is
+ * read instead, and what that gives is the caller's to drop.  tail() is called
+ * before the last chunk's products: loads issued there are covered by them.
+ * No barrier follows the last reads of `lds`.
+ *
+ * Measured alone on 3840 x 1280 with K = 192 (600 tiles of 128 x 64, 1200 of
+ * 64 x 64): 31 TFLOP/s in FP64 with a bounds check per element, scalar LDS
+ * traffic and 128-row tiles, 39 as written here, 48 with 64-row tiles and
+ * three workgroups per compute unit, which leave less of the chip idle at the
+ * end; in FP32, 128 x 64 on 15360 x 4096 with K = 256, 54 -> 104.
  */
-template <typename T, int BM, int BN, int BK> struct UpdateTile {
-    static constexpr int PA = BK + 1, PB = BN + 4;
+template <typename T, int MB, int NB> struct TileGemm {
+    static constexpr int BM = 32 * MB, BN = 32 * NB, BK = 16;
+    static constexpr int W = 16 / sizeof(T); /* elements of a 16-byte vector */
+    static constexpr int PA = BK + W, PB = BN + (sizeof(T) == 8 ? 8 : 4);
     static constexpr size_t LDS = sizeof(T) * 2 * (BM * PA + BK * PB);
 };
 
-template <typename T, int BM, int BN, int BK>
-__device__ __forceinline__ void update_tile(T *__restrict__ A, int64_t lda, int n, int k0, int kw, int r0, int c0,
-                                            int skip, char *lds_raw)
+template <typename T, int MB, int NB, bool NEG, bool EDGE, typename Tail>
+__device__ __forceinline__ void tile_gemm(typename vec4<T>::type (&acc)[MB][NB], const T *A, int64_t lda, int nr,
+                                          const T *B, int64_t ldb, int nc, int K, char *lds, Tail &&tail)
 {
-    typedef typename vec4<T>::type V;
-    constexpr int WM = BM / 2, WN = BN / 2, MB = WM / 16, NB = WN / 16;
-    constexpr int PA = UpdateTile<T, BM, BN, BK>::PA, PB = UpdateTile<T, BM, BN, BK>::PB;
-    constexpr int EA = BM * BK / NT, EB = BK * BN / NT; /* elements per thread per chunk */
-    static_assert(BK % EA == 0 && BN % EB == 0, "chunk split");
-    T(*sA)[BM * PA] = reinterpret_cast<T(*)[BM * PA]>(lds_raw);
-    T(*sB)[BK * PB] = reinterpret_cast<T(*)[BK * PB]>(lds_raw + sizeof(T) * 2 * BM * PA);
-    const int nr = min(BM, n - r0), nc = min(BN, n - c0);
-
+    typedef TileGemm<T, MB, NB> G;
+    constexpr int BM = G::BM, BN = G::BN, BK = G::BK, W = G::W, PA = G::PA, PB = G::PB;
+    constexpr int EA = BM * BK / NT, EB = BK * BN / NT; /* elements per thread and chunk */
+    typedef T VW __attribute__((ext_vector_type(W)));
+    T *sA = reinterpret_cast<T *>(lds), *sB = sA + 2 * BM * PA;
     const int t = threadIdx.x, w = wave_id(), l = t & 63, lr = l & 15, lk = l >> 4;
-    const int wm = (w >> 1) * WM, wn = (w & 1) * WN;
-
-    /* this thread's share of a chunk: A rows ar, k offset ak..ak+EA; B row bk, cols bc..bc+EB */
+    const int wm = (w >> 1) * 16 * MB, wn = (w & 1) * 16 * NB;
+    /* this thread's share of a chunk: A row ar, columns ak.., B row bk, columns bc.. */
     const int ar = t / (BK / EA), ak = (t % (BK / EA)) * EA;
     const int bk = t / (BN / EB), bc = (t % (BN / EB)) * EB;
+    const T *pa = A + (int64_t)(EDGE ? min(ar, nr - 1) : ar) * lda + ak;
+    const T *pb = B + (int64_t)bk * ldb;
     T ra[EA], rb[EB];
-    auto fetch = [&](int kc) {
-#pragma unroll
-        for (int e = 0; e < EA; ++e) {
-            const int kk = kc + ak + e;
-            ra[e] = (ar < nr && kk < kw) ? A[(int64_t)(r0 + ar) * lda + k0 + kk] : T(0);
-        }
-#pragma unroll
-        for (int e = 0; e < EB; ++e) {
-            const int kk = kc + bk;
-            rb[e] = (bc + e < nc && kk < kw) ? A[(int64_t)(k0 + kk) * lda + c0 + bc + e] : T(0);
-        }
-    };
-    auto park = [&](int buf) {
+    auto fetch = [&]() __attribute__((always_inline)) {
 #pragma unroll
         for (int e = 0; e < EA; ++e)
-            sA[buf][ar * PA + ak + e] = ra[e];
+            ra[e] = pa[e];
 #pragma unroll
         for (int e = 0; e < EB; ++e)
-            sB[buf][bk * PB + bc + e] = rb[e];
+            rb[e] = pb[EDGE ? min(bc + e, nc - 1) : bc + e];
+        pa += BK;
+        pb += (int64_t)BK * ldb;
     };
-
-    fetch(0);
-    V acc[MB][NB];
+    auto park = [&](int buf) __attribute__((always_inline)) {
+        T *da = sA + buf * BM * PA + ar * PA + ak, *db = sB + buf * BK * PB + bk * PB + bc;
 #pragma unroll
-    for (int bi = 0; bi < MB; ++bi)
+        for (int e = 0; e < EA; e += W)
+            *reinterpret_cast<VW *>(da + e) = *reinterpret_cast<VW *>(ra + e);
 #pragma unroll
-        for (int bj = 0; bj < NB; ++bj)
+        for (int e = 0; e < EB; e += W)
+            *reinterpret_cast<VW *>(db + e) = *reinterpret_cast<VW *>(rb + e);
+    };
+    const T *ua = sA + (wm + lr) * PA + W * lk, *ub = sB + W * lk * PB + wn + lr;
+    auto multiply = [&](int buf) __attribute__((always_inline)) {
+        const T *xa = ua + buf * BM * PA, *xb = ub + buf * BK * PB;
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int row = wm + 16 * bi + acc_row<T>(lk, r), col = wn + 16 * bj + lr;
-                acc[bi][bj][r] = (row < nr && col < nc) ? A[(int64_t)(r0 + row) * lda + c0 + col] : T(0);
-            }
-    park(0);
-    __syncthreads();
-    const int nchunks = (kw + BK - 1) / BK;
-    for (int c = 0; c < nchunks; ++c) {
-        const int buf = c & 1;
-        if (c + 1 < nchunks)
-            fetch((c + 1) * BK);
-#pragma unroll
-        for (int kk = 0; kk < BK; kk += 4) {
-            T av[MB], bv[NB];
+        for (int h = 0; h < BK; h += 4 * W) {
+            VW av[MB];
+            T bv[NB][W];
 #pragma unroll
             for (int bi = 0; bi < MB; ++bi)
-                av[bi] = -sA[buf][(wm + 16 * bi + lr) * PA + kk + lk];
+                av[bi] = *reinterpret_cast<const VW *>(xa + 16 * bi * PA + h);
 #pragma unroll
             for (int bj = 0; bj < NB; ++bj)
-                bv[bj] = sB[buf][(kk + lk) * PB + wn + 16 * bj + lr];
 #pragma unroll
-            for (int bi = 0; bi < MB; ++bi)
+                for (int k = 0; k < W; ++k)
+                    bv[bj][k] = xb[(h + k) * PB + 16 * bj];
 #pragma unroll
-                for (int bj = 0; bj < NB; ++bj)
-                    acc[bi][bj] = mfma16(av[bi], bv[bj], acc[bi][bj]);
+            for (int k = 0; k < W; ++k)
+#pragma unroll
+                for (int bi = 0; bi < MB; ++bi)
+#pragma unroll
+                    for (int bj = 0; bj < NB; ++bj)
+                        acc[bi][bj] = mfma16(NEG ? -av[bi][k] : av[bi][k], bv[bj][k], acc[bi][bj]);
         }
-        if (c + 1 < nchunks)
-            park(buf ^ 1);
+    };
+    fetch();
+    park(0);
+    __syncthreads();
+    const int nch = K / BK;
+#pragma unroll 1
+    for (int c = 0; c + 1 < nch; ++c) {
+        fetch();
+        multiply(c & 1);
+        park((c & 1) ^ 1);
         __syncthreads();
     }
+    tail();
+    multiply((nch - 1) & 1);
+}
+
+/* Trailing update A22 -= L21 U12 of the tile at (r0, c0) by the kw columns
+ * from k0: the product first, the tile's own elements loaded under its last
+ * chunk.  The top-left skip x skip corner is not stored (it belongs to
+ * another workgroup). */
+template <typename T, int MB, int NB, bool EDGE>
+__device__ __forceinline__ void update_tile_part(T *__restrict__ A, int64_t lda, int nr, int nc, int k0, int kw, int r0,
+                                                 int c0, int skip, char *lds)
+{
+    typedef typename vec4<T>::type V;
+    const int w = wave_id(), l = threadIdx.x & 63, lr = l & 15, lk = l >> 4;
+    const int wm = (w >> 1) * 16 * MB + acc_row<T>(lk, 0), wn = (w & 1) * 16 * NB + lr;
+    T *C = A + (int64_t)r0 * lda + c0;
+    auto row = [&](int bi, int r) { return wm + 16 * bi + acc_row<T>(0, r); };
+    V acc[MB][NB], cv[MB][NB];
+#pragma unroll
+    for (int bi = 0; bi < MB; ++bi)
+#pragma unroll
+        for (int bj = 0; bj < NB; ++bj)
+            acc[bi][bj] = V{0, 0, 0, 0};
+    tile_gemm<T, MB, NB, false, EDGE>(acc, A + (int64_t)r0 * lda + k0, lda, nr, A + (int64_t)k0 * lda + c0, lda, nc, kw,
+                                      lds, [&]() __attribute__((always_inline)) {
+#pragma unroll
+                                          for (int bi = 0; bi < MB; ++bi)
+#pragma unroll
+                                              for (int bj = 0; bj < NB; ++bj)
+#pragma unroll
+                                                  for (int r = 0; r < 4; ++r) {
+                                                      const int i = row(bi, r), j = wn + 16 * bj;
+                                                      cv[bi][bj][r] = EDGE ? C[(int64_t)min(i, nr - 1) * lda + min(j, nc - 1)]
+                                                                           : C[(int64_t)i * lda + j];
+                                                  }
+                                      });
 #pragma unroll
     for (int bi = 0; bi < MB; ++bi)
 #pragma unroll
         for (int bj = 0; bj < NB; ++bj)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                const int row = wm + 16 * bi + acc_row<T>(lk, r), col = wn + 16 * bj + lr;
-                if (row < nr && col < nc && !(row < skip && col < skip))
-                    A[(int64_t)(r0 + row) * lda + c0 + col] = acc[bi][bj][r];
+                const int i = row(bi, r), j = wn + 16 * bj;
+                if ((!EDGE || (i < nr && j < nc)) && !(i < skip && j < skip))
+                    C[(int64_t)i * lda + j] = cv[bi][bj][r] - acc[bi][bj][r];
+            }
+}
+
+template <typename T, int MB, int NB>
+__device__ __forceinline__ void update_tile(T *__restrict__ A, int64_t lda, int n, int k0, int kw, int r0, int c0,
+                                            int skip, char *lds)
+{
+    typedef TileGemm<T, MB, NB> G;
+    const int nr = min(G::BM, n - r0), nc = min(G::BN, n - c0);
+    if (nr == G::BM && nc == G::BN)
+        update_tile_part<T, MB, NB, false>(A, lda, nr, nc, k0, kw, r0, c0, skip, lds);
+    else
+        update_tile_part<T, MB, NB, true>(A, lda, nr, nc, k0, kw, r0, c0, skip, lds);
+}
+
+/* A 64 x 64 tile's pending update: acc = C - A B (nr rows, nc columns of it
+ * exist; the rest of the accumulators is the caller's to drop). */
+template <typename T>
+__device__ __forceinline__ void tile_pending(Acc64<T> &acc, const T *C, int64_t ldc, const T *A, int64_t lda, int nr,
+                                             const T *B, int64_t ldb, int nc, int K, char *lds)
+{
+    const int w = wave_id(), l = threadIdx.x & 63, lr = l & 15, lk = l >> 4;
+    const int wm = (w >> 1) * 32, wn = (w & 1) * 32;
+#pragma unroll
+    for (int bi = 0; bi < 2; ++bi)
+#pragma unroll
+        for (int bj = 0; bj < 2; ++bj)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                acc.v[bi][bj][r] = C[(int64_t)min(wm + 16 * bi + acc_row<T>(lk, r), nr - 1) * ldc +
+                                     min(wn + 16 * bj + lr, nc - 1)];
+    auto none = []() {};
+    if (K == 0)
+        return;
+    if (nr == TB && nc == TB)
+        tile_gemm<T, 2, 2, true, false>(acc.v, A, lda, nr, B, ldb, nc, K, lds, none);
+    else
+        tile_gemm<T, 2, 2, true, true>(acc.v, A, lda, nr, B, ldb, nc, K, lds, none);
+}
+
+/* acc64_store to an LDS tile (pitch LDT) of the nr x nc elements that exist,
+ * the rest zero or (IDENTITY) the identity. */
+template <typename T>
+__device__ __forceinline__ void acc64_to_lds(const Acc64<T> &acc, T *S, int nr, int nc, bool identity)
+{
+    const int w = wave_id(), l = threadIdx.x & 63, lr = l & 15, lk = l >> 4;
+    const int wm = (w >> 1) * 32, wn = (w & 1) * 32;
+#pragma unroll
+    for (int bi = 0; bi < 2; ++bi)
+#pragma unroll
+        for (int bj = 0; bj < 2; ++bj)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int i = wm + 16 * bi + acc_row<T>(lk, r), j = wn + 16 * bj + lr;
+                S[i * LDT + j] = (i < nr && j < nc) ? acc.v[bi][bj][r] : (identity && i == j ? T(1) : T(0));
             }
 }
 
@@ -288,44 +387,34 @@ __device__ __forceinline__ int xcd_tile(int b, int ntiles)
 
 /*
  * One block step of the launch-per-phase factor: the trailing update of the
- * region right of and below the panel at k0 in BM x BN tiles, plus one extra
- * workgroup that updates, factors and inverts the next diagonal tile (the
- * tile workgroup covering that corner does not store it), plus (with
- * right-hand sides) workgroups for B_i -= L_ik Y_k.
+ * region right of and below the panel at k0 in tiles, plus one extra workgroup
+ * that updates, factors and inverts the next diagonal tile (the tile
+ * workgroup covering that corner does not store it), plus (with right-hand
+ * sides) workgroups for B_i -= L_ik Y_k.
  */
-template <typename T, int BM, int BN, int BK>
+template <typename T, int MB, int NB>
 __global__ __launch_bounds__(NT, 2) void k_update(T *__restrict__ A, int64_t lda, int n, int k0, int kw,
                                                   int32_t *info, T *__restrict__ Pg, T *__restrict__ B,
                                                   int64_t ldb, int nrhs)
 {
-    constexpr size_t GEMM_LDS = UpdateTile<T, BM, BN, BK>::LDS;
-    constexpr size_t LDS_BYTES = GEMM_LDS > sizeof(DiagSmem<T>) ? GEMM_LDS : sizeof(DiagSmem<T>);
-    __shared__ __attribute__((aligned(16))) char lds_raw[LDS_BYTES];
+    typedef TileGemm<T, MB, NB> G;
+    constexpr size_t GEMM_LDS = std::max(G::LDS, TileGemm<T, 2, 2>::LDS);
+    __shared__ __attribute__((aligned(16))) char lds_raw[std::max(GEMM_LDS, sizeof(DiagSmem<T>))];
 
     const int i0 = k0 + kw, m = n - i0;
-    const int tiles_n = (m + BN - 1) / BN;
-    const int ntiles = ((m + BM - 1) / BM) * tiles_n;
+    const int tiles_n = (m + G::BN - 1) / G::BN;
+    const int ntiles = ((m + G::BM - 1) / G::BM) * tiles_n;
     const int b = blockIdx.x;
     const int dw = min(TB, m); /* next diagonal tile: rows/cols i0..i0+dw */
     if (b == ntiles) {
-        /* the extra workgroup: update the next diagonal tile itself (in
-         * registers, then LDS) and factor it in place (the next block step's
-         * diagonal tile); the tile workgroup covering it does not store that
-         * corner */
+        /* the extra workgroup: the next diagonal tile updated in registers,
+         * then factored in place in LDS */
         DiagSmem<T> &sm = *reinterpret_cast<DiagSmem<T> *>(lds_raw);
-        const DenseC<T> C{A + (int64_t)i0 * lda + i0, lda, dw, dw};
         Acc64<T> acc;
-        acc64_load(acc, C);
-        stage64<T, false>(sm.S, A + (int64_t)i0 * lda + k0, lda, dw, kw);
-        stage64<T, false>(sm.P, A + (int64_t)k0 * lda + i0, lda, kw, dw);
+        tile_pending(acc, A + (int64_t)i0 * lda + i0, lda, A + (int64_t)i0 * lda + k0, lda, dw,
+                     A + (int64_t)k0 * lda + i0, lda, dw, kw, lds_raw);
         __syncthreads();
-        acc64_mma<T, true>(acc, [&](int r, int k) { return sm.S[r * LDT + k]; },
-                           [&](int k, int c) { return sm.P[k * LDT + c]; });
-        __syncthreads();
-        acc64_store(acc, LdsTile<T>{sm.S});
-        __syncthreads();
-        if (threadIdx.x < TB && threadIdx.x >= dw) /* identity padding of a partial last tile */
-            sm.S[threadIdx.x * (LDT + 1)] = T(1);
+        acc64_to_lds(acc, sm.S, dw, dw, true);
         __syncthreads();
         diag_tile(A, lda, n, i0, info, Pg, sm, B != nullptr);
         return;
@@ -333,32 +422,31 @@ __global__ __launch_bounds__(NT, 2) void k_update(T *__restrict__ A, int64_t lda
     if (b > ntiles) {
         /* right-hand-side workgroups: B_i -= L_ik Y_k for one 64-row block
          * below the panel and one 64-column chunk of B */
-        DiagSmem<T> &sm = *reinterpret_cast<DiagSmem<T> *>(lds_raw);
         const int nbc = (nrhs + TB - 1) / TB, q = b - ntiles - 1;
         const int r0 = i0 + (q / nbc) * TB, c0 = (q % nbc) * TB;
         const int nr = min(TB, n - r0), nc = min(TB, nrhs - c0);
-        stage64<T, true>(sm.S, A + (int64_t)r0 * lda + k0, lda, nr, kw);
-        stage64<T, false>(sm.P, B + (int64_t)k0 * ldb + c0, ldb, kw, nc);
-        __syncthreads();
-        wg_gemm64(DenseC<T>{B + (int64_t)r0 * ldb + c0, ldb, nr, nc}, sm.S, sm.P);
+        T *C = B + (int64_t)r0 * ldb + c0;
+        Acc64<T> acc;
+        tile_pending(acc, C, ldb, A + (int64_t)r0 * lda + k0, lda, nr, B + (int64_t)k0 * ldb + c0, ldb, nc, kw, lds_raw);
+        acc64_store(acc, DenseC<T>{C, ldb, nr, nc});
         return;
     }
     const int tile = xcd_tile(b, ntiles);
-    const int r0 = i0 + (tile / tiles_n) * BM, c0 = i0 + (tile % tiles_n) * BN;
-    update_tile<T, BM, BN, BK>(A, lda, n, k0, kw, r0, c0, (r0 == i0 && c0 == i0) ? dw : 0, lds_raw);
+    const int r0 = i0 + (tile / tiles_n) * G::BM, c0 = i0 + (tile % tiles_n) * G::BN;
+    update_tile<T, MB, NB>(A, lda, n, k0, kw, r0, c0, (r0 == i0 && c0 == i0) ? dw : 0, lds_raw);
 }
 
 /* Strip q of a tile being factored (tile_lu64: S the tile, P its diagonal
- * blocks' inverses), sent to the workgroups that solve against it: by all
+ * blocks' inverses, pitch PP), sent to the workgroups that solve against it: by all
  * threads, the inverses of the diagonal block to Pg (64 x 64, pitch 64), the
  * L part below it and the U part right of it to the tile D (pitch ldd) with
  * device-coherent stores, the block itself (read by nobody else) plainly.
  * Nothing past the tile's n valid rows and columns is stored to D. */
-template <typename T>
+template <int PP, typename T>
 __device__ __forceinline__ void publish_strip(const T *S, const T *P, int q, T *Pg, T *D, int64_t ldd, int n)
 {
     const int t = launder((int)threadIdx.x), r = t >> 4, c = t & 15, b0 = 16 * q;
-    store_coherent(Pg + (b0 + r) * TB + b0 + c, P[(b0 + r) * LDT + b0 + c]);
+    store_coherent(Pg + (b0 + r) * TB + b0 + c, P[(b0 + r) * PP + (PP == LDT ? b0 : 0) + c]);
     if (b0 + r < n && b0 + c < n)
         D[(int64_t)(b0 + r) * ldd + b0 + c] = S[(b0 + r) * LDT + b0 + c];
     for (int a = b0 + 16 + r; a < TB; a += 16) {
@@ -413,17 +501,24 @@ __device__ __forceinline__ void count_strip(int *flag)
  * the flag are exchanged with device-coherent operations (store_coherent /
  * load_coherent, wait_solved).
  */
-template <typename T, int BM, int BN, int BK>
-__global__ __launch_bounds__(NT, 2) void k_step(T *__restrict__ A, int64_t lda, int n, int s, int G, int upd,
-                                                int pendp, int first_wave, int32_t *info, T *__restrict__ Pg,
-                                                T *__restrict__ B, int64_t ldb, int nrhs, int *ctl, long wlim)
+template <typename T> struct StepSmem {
+    T S[TB * LDT]; /* the diagonal or panel tile */
+    T P[TB * DBP]; /* its diagonal blocks' inverses, or a strip of the pack */
+};
+constexpr int kStepPerCu = 3; /* workgroups per compute unit that k_step's LDS and registers admit */
+
+template <typename T, int MB>
+__global__ __launch_bounds__(NT, kStepPerCu) void k_step(T *__restrict__ A, int64_t lda, int n, int s, int G, int upd,
+                                                         int pendp, int first_wave, int32_t *info, T *__restrict__ Pg,
+                                                         T *__restrict__ B, int64_t ldb, int nrhs, int *ctl, long wlim)
 {
-    static_assert(BN == TB, "one block column per update tile (one class)");
-    constexpr size_t GEMM_LDS = UpdateTile<T, BM, BN, BK>::LDS;
-    constexpr size_t LDS_BYTES = GEMM_LDS > sizeof(DiagSmem<T>) ? GEMM_LDS : sizeof(DiagSmem<T>);
-    __shared__ __attribute__((aligned(16))) char lds_raw[LDS_BYTES];
-    __shared__ int s_ticket, s_avail;
-    DiagSmem<T> &sm = *reinterpret_cast<DiagSmem<T> *>(lds_raw);
+    constexpr int BM = TileGemm<T, MB, 2>::BM;
+    static_assert(TileGemm<T, MB, 2>::BN == TB, "one block column per update tile (one class)");
+    __shared__ __attribute__((aligned(16))) char
+        lds_raw[std::max(std::max(TileGemm<T, MB, 2>::LDS, TileGemm<T, 2, 2>::LDS), sizeof(StepSmem<T>))];
+    static_assert(kStepPerCu * (sizeof(lds_raw) + 256) <= 160 * 1024, "workgroups per compute unit");
+    __shared__ int s_ticket, s_avail, s_zero;
+    StepSmem<T> &sm = *reinterpret_cast<StepSmem<T> *>(lds_raw);
 
     const int d0 = s * TB, dw = min(TB, n - d0);
     /* pending rank of block column J (a multiple of 64) */
@@ -447,154 +542,113 @@ __global__ __launch_bounds__(NT, 2) void k_step(T *__restrict__ A, int64_t lda, 
         s_avail = 0;
     }
     __syncthreads();
-    int q = s_ticket;
+    int q = __builtin_amdgcn_readfirstlane(s_ticket);
     if (q >= 1 + nt2 + nb2 + npan) { /* counter not reset: refuse */
         if (threadIdx.x == 0)
             atomicOr(status, 2);
         return;
     }
 
-    if (q == 0) { /* the diagonal tile */
-        const int kw = kw_of(s), k0 = d0 - kw;
-        if (kw > 0) {
-            /* its update in registers, K in 64-wide chunks staged in S (L) and P (U) */
-            const DenseC<T> C{A + (int64_t)d0 * lda + d0, lda, dw, dw};
-            Acc64<T> acc;
-            acc64_load(acc, C);
-            for (int h = 0; h < kw; h += TB) {
-                stage64x2<T>(sm.S, A + (int64_t)d0 * lda + k0 + h, lda, dw, TB, sm.P, A + (int64_t)(k0 + h) * lda + d0,
-                             lda, TB, dw);
-                __syncthreads();
-                acc64_mma<T, true>(acc, [&](int r, int k) { return sm.S[r * LDT + k]; },
-                                   [&](int k, int c) { return sm.P[k * LDT + c]; });
-                __syncthreads();
-            }
-            acc64_store(acc, LdsTile<T>{sm.S});
-            __syncthreads();
-            if (threadIdx.x < TB && threadIdx.x >= dw) /* identity padding of a partial last tile */
-                sm.S[threadIdx.x * (LDT + 1)] = T(1);
-            __syncthreads();
-        } else {
-            stage_tile_identity(sm.S, A + (int64_t)d0 * lda + d0, lda, dw, dw);
-            __syncthreads();
-        }
-        T *Add = A + (int64_t)d0 * lda + d0;
-        const bool pub = nr2 > 0 || nbc > 0;
-        /* what the panel items read, published a strip at a time as it is
-         * factored (publish_strip); the waves' stores of strip q are counted
-         * in the flag a little later, the last strip's at the end */
-        const int z = tile_lu64(sm.S, sm.P, sm.rinv, dw, &sm.zflag, [&](int q, int stage) __attribute__((always_inline)) {
-            if (!pub)
-                return;
-            if (stage == 0)
-                publish_strip(sm.S, sm.P, q, Pg, Add, lda, dw);
-            else
-                count_strip(flag);
-        });
-        if (threadIdx.x == 0 && info && z && *info == 0)
-            *info = d0 + z;
-        if (pub)
-            count_strip(flag);
-        else
-            lds_store_tile(sm.S, Add, lda, dw, dw);
-        return;
-    }
-    q -= 1;
-    /* panel tile p of step s: 0..nr2-1 U tiles, nr2..2nr2-1 L tiles, then the
-     * right-hand-side chunks of block row s */
-    int kind, r0, c0, nr, nc, kw;
-    T *G_;
-    int64_t ldg;
-    auto panel_tile = [&](int p) {
-        if (p < nr2) {
-            kind = 0;
-            r0 = d0, c0 = e0 + p * TB;
-            nr = dw, nc = min(TB, n - c0);
-            G_ = A + (int64_t)r0 * lda + c0, ldg = lda;
-            kw = kw_of(J0 + p);
-        } else if (p < 2 * nr2) {
-            kind = 1;
-            r0 = e0 + (p - nr2) * TB, c0 = d0;
-            nr = min(TB, n - r0), nc = dw;
-            G_ = A + (int64_t)r0 * lda + c0, ldg = lda;
-            kw = kw_of(s);
-        } else {
-            kind = 2;
-            r0 = d0, c0 = (p - 2 * nr2) * TB;
-            nr = dw, nc = min(TB, nrhs - c0);
-            G_ = B + (int64_t)r0 * ldb + c0, ldg = ldb;
-            kw = kwB;
-        }
-    };
     /* after the diagonal tile: the first wave of region tiles (first_wave of
      * them), then the panel tiles, then the other region tiles and the B
      * rows: the panel tiles start as soon as the first region tiles finish
      * instead of after all of them */
     const int n1 = min(nt2, first_wave);
-    if (q >= n1 && q < n1 + npan) {
-        q -= n1;
-        goto panel;
-    }
-    if (q >= n1)
-        q -= npan;
-    if (q < nt2) { /* trailing tile of an updated class, update only */
-        const int tile = xcd_tile(q, nt2);
-        const int jc = jfirst + jstep * (tile % ncu);
-        const int r0 = e0 + (tile / ncu) * BM, c0 = e0 + jc * TB;
-        const int kw = kw_of(J0 + jc);
-        update_tile<T, BM, BN, BK>(A, lda, n, d0 - kw, kw, r0, c0, 0, lds_raw);
-        return;
-    }
-    q -= nt2;
-    { /* B_i -= L_{i,s-1} Y_{s-1} for a 64-row block below block row s */
-        const int r0 = e0 + (q / nbc) * TB, c0 = (q % nbc) * TB;
-        const int nr = min(TB, n - r0), nc = min(TB, nrhs - c0);
-        const int k0 = d0 - kwB;
-        const DenseC<T> C{B + (int64_t)r0 * ldb + c0, ldb, nr, nc};
-        Acc64<T> acc;
-        acc64_load(acc, C);
-        for (int h = 0; h < kwB; h += TB) {
-            stage64x2<T>(sm.S, A + (int64_t)r0 * lda + k0 + h, lda, nr, TB, sm.P, B + (int64_t)(k0 + h) * ldb + c0, ldb,
-                         TB, nc);
-            __syncthreads();
-            acc64_mma<T, true>(acc, [&](int r, int k) { return sm.S[r * LDT + k]; },
-                               [&](int k, int c) { return sm.P[k * LDT + c]; });
-            __syncthreads();
+    enum { U_TILE, L_TILE, RHS_TILE, RHS_ROWS, DIAGONAL } kind;
+    int r0, c0, nr, nc, kw;
+    T *C;
+    int64_t ldc = lda;
+    if (q == 0) {
+        kind = DIAGONAL;
+        r0 = c0 = d0;
+        nr = nc = dw;
+        kw = kw_of(s);
+        /* the launch's longest chain: ahead of its compute unit's other waves */
+        __builtin_amdgcn_s_setprio(3);
+    } else if (q - 1 >= n1 && q - 1 < n1 + npan) { /* a panel tile of step s */
+        const int p = q - 1 - n1;
+        if (p < nr2) {
+            kind = U_TILE;
+            r0 = d0, c0 = e0 + p * TB;
+            nr = dw, nc = min(TB, n - c0);
+            kw = kw_of(J0 + p);
+        } else if (p < 2 * nr2) {
+            kind = L_TILE;
+            r0 = e0 + (p - nr2) * TB, c0 = d0;
+            nr = min(TB, n - r0), nc = dw;
+            kw = kw_of(s);
+        } else {
+            kind = RHS_TILE;
+            r0 = d0, c0 = (p - 2 * nr2) * TB;
+            nr = dw, nc = min(TB, nrhs - c0);
+            kw = kwB;
         }
-        acc64_store(acc, C);
-        return;
+    } else {
+        q = q - 1 < n1 ? q - 1 : q - 1 - npan;
+        if (q < nt2) { /* trailing tile of an updated class, update only */
+            const int tile = xcd_tile(q, nt2);
+            const int jc = jfirst + jstep * (tile % ncu);
+            const int kwj = kw_of(J0 + jc);
+            update_tile<T, MB, 2>(A, lda, n, d0 - kwj, kwj, e0 + (tile / ncu) * BM, e0 + jc * TB, 0, lds_raw);
+            return;
+        }
+        /* B_i -= L_{i,s-1} Y_{s-1} for a 64-row block below block row s */
+        q -= nt2;
+        kind = RHS_ROWS;
+        r0 = e0 + (q / nbc) * TB, c0 = (q % nbc) * TB;
+        nr = min(TB, n - r0), nc = min(TB, nrhs - c0);
+        kw = kwB;
     }
-panel:
-    /* a panel tile: its own pending update, then the solve against the
-     * factored diagonal tile */
-    panel_tile(q);
+    /* the tile's own pending update: C -= L_{r0,pending} (U_{pending,c0} or
+     * Y_{pending}) */
+    const T *Bop = A;
+    if (kind == RHS_TILE || kind == RHS_ROWS) {
+        Bop = B;
+        ldc = ldb;
+    }
+    C = const_cast<T *>(Bop) + (int64_t)r0 * ldc + c0;
     const int k0 = d0 - kw;
     Acc64<T> acc;
-    acc64_load(acc, DenseC<T>{G_, ldg, nr, nc});
-    for (int h = 0; h < kw; h += TB) {
-        /* tile -= L_{r0,pending} * (U_{pending,c0} or Y_{pending}) */
-        if (kind == 2)
-            stage64x2<T>(sm.S, A + (int64_t)r0 * lda + k0 + h, lda, nr, TB, sm.P, B + (int64_t)(k0 + h) * ldb + c0, ldb,
-                         TB, nc);
-        else
-            stage64x2<T>(sm.S, A + (int64_t)r0 * lda + k0 + h, lda, nr, TB, sm.P, A + (int64_t)(k0 + h) * lda + c0, lda,
-                         TB, nc);
-        __syncthreads();
-        acc64_mma<T, true>(acc, [&](int r, int k) { return sm.S[r * LDT + k]; },
-                           [&](int k, int c) { return sm.P[k * LDT + c]; });
-        __syncthreads();
+    tile_pending(acc, C, ldc, A + (int64_t)r0 * lda + k0, lda, nr, Bop + (int64_t)k0 * ldc + c0, ldc, nc, kw, lds_raw);
+    if (kind == RHS_ROWS) {
+        acc64_store(acc, DenseC<T>{C, ldc, nr, nc});
+        return;
     }
-    acc64_store(acc, LdsTile<T>{sm.S});
+    __syncthreads(); /* the product's last operand reads */
+    acc64_to_lds(acc, sm.S, nr, nc, kind == DIAGONAL);
     __syncthreads();
+    if (kind == DIAGONAL) {
+        const bool pub = nr2 > 0 || nbc > 0;
+        /* what the panel items read, published a strip at a time as it is
+         * factored (publish_strip); the waves' stores of strip q are counted
+         * in the flag a little later, the last strip's at the end */
+        const int z = tile_lu64<T, true>(sm.S, sm.P, (T *)nullptr, dw, &s_zero,
+                                         [&](int p, int stage) __attribute__((always_inline)) {
+                                             if (!pub)
+                                                 return;
+                                             if (stage == 0)
+                                                 publish_strip<DBP>(sm.S, sm.P, p, Pg, C, lda, dw);
+                                             else
+                                                 count_strip(flag);
+                                         });
+        if (threadIdx.x == 0 && info && z && *info == 0)
+            *info = d0 + z;
+        if (pub)
+            count_strip(flag);
+        else
+            lds_store_tile(sm.S, C, lda, dw, dw);
+        return;
+    }
     /* the solve against the factored diagonal tile, block step p as soon as
      * strip p of its pack is published (its flag counts 4 per strip): each
      * wave keeps its 16-wide slab of the tile in accumulators (transposed for
-     * the L tiles, X = A U^{-1} solved as U^T X^T = A^T) and runs step p
-     * with the strip staged in P: the diagonal block times the inverse of the
-     * strip's diagonal block, then its contribution removed from the blocks
-     * after it, each product taking the finished block as its B operand */
+     * the L tiles, X = A U^{-1} solved as U^T X^T = A^T) and runs step p with
+     * the strip staged in P, by rows of the lower operator (for the L tiles
+     * U^T: its columns): the diagonal block times the inverse of the strip's
+     * diagonal block, then its contribution removed from the blocks after it,
+     * each product taking the finished block as its B operand */
     typedef typename vec4<T>::type V;
-    const bool right = kind == 1;
+    const bool right = kind == L_TILE;
     const int w = wave_id(), l = threadIdx.x & 63, lr = l & 15, lk = l >> 4;
     const T *Add = A + (int64_t)d0 * lda + d0;
     V a[4];
@@ -608,8 +662,8 @@ panel:
     for (int p = 0; p < 4; ++p) {
         wait_solved(flag, 4 * p + 3, &s_avail, status, wlim);
         /* strip p: rows 16p.. of columns 16p..16p+15 (lower), or columns
-         * 16p.. of rows 16p..16p+15 (right); diagonal block from Pg,
-         * identity past the matrix end */
+         * 16p.. of rows 16p..16p+15 (right); diagonal block from Pg, zero
+         * past the matrix end */
         const int len = 64 - 16 * p;
         T v[4];
 #pragma unroll
@@ -625,38 +679,22 @@ panel:
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const int idx = threadIdx.x + NT * i;
-            const int r = right ? 16 * p + idx / len : 16 * p + (idx >> 4);
-            const int c = right ? 16 * p + idx % len : 16 * p + (idx & 15);
             if (idx < len * 16)
-                sm.P[r * LDT + c] = v[i];
+                sm.P[right ? (16 * p + idx % len) * DBP + idx / len : (16 * p + (idx >> 4)) * DBP + (idx & 15)] = v[i];
         }
         __syncthreads();
         V x = {0, 0, 0, 0};
-        if (right) {
-            wave_mma16_acc<T>(
-                x,
-                [&](int r, int k) {
-                    const T u = sm.P[(16 * p + k) * LDT + 16 * p + r];
-                    return k <= r ? u : T(0);
-                },
-                a[p]);
-            a[p] = x;
+        wave_mma16_acc<T>(
+            x,
+            [&](int r, int k) {
+                const T u = sm.P[(16 * p + r) * DBP + k];
+                return r > k ? u : (r == k ? (right ? u : T(1)) : T(0));
+            },
+            a[p]);
+        a[p] = x;
 #pragma unroll
-            for (int q2 = p + 1; q2 < 4; ++q2)
-                wave_mma16_acc<T>(a[q2], [&](int r, int k) { return -sm.P[(16 * p + k) * LDT + 16 * q2 + r]; }, a[p]);
-        } else {
-            wave_mma16_acc<T>(
-                x,
-                [&](int r, int k) {
-                    const T u = sm.P[(16 * p + r) * LDT + 16 * p + k];
-                    return r > k ? u : (r == k ? T(1) : T(0));
-                },
-                a[p]);
-            a[p] = x;
-#pragma unroll
-            for (int q2 = p + 1; q2 < 4; ++q2)
-                wave_mma16_acc<T>(a[q2], [&](int r, int k) { return -sm.P[(16 * q2 + r) * LDT + 16 * p + k]; }, a[p]);
-        }
+        for (int q2 = p + 1; q2 < 4; ++q2)
+            wave_mma16_acc<T>(a[q2], [&](int r, int k) { return -sm.P[(16 * q2 + r) * DBP + k]; }, a[p]);
     }
     __syncthreads();
 #pragma unroll
@@ -669,7 +707,7 @@ panel:
                 sm.S[(16 * q2 + acc_row<T>(lk, r)) * LDT + 16 * w + lr] = a[q2][r];
         }
     __syncthreads();
-    lds_store_tile(sm.S, G_, ldg, nr, nc);
+    lds_store_tile(sm.S, C, ldc, nr, nc);
 }
 
 /* ----------------------------------------- update-kernel measurement --- */
@@ -724,6 +762,17 @@ static bool profile_slot(UpdateProfile *p, hipStream_t st, double flops, int &sl
     return true;
 }
 
+/* Rows of an update tile: 64 in FP64, where the matrix cores are busy enough
+ * with them and more tiles fill the last wave of workgroups (48 against 39
+ * TFLOP/s, tile_gemm); 128 in FP32 while the region is larger than
+ * small_update_below, half the operand traffic per product (104 against 99
+ * TFLOP/s at 15360 x 4096, K = 256). */
+template <typename T> constexpr int kTallBlocks = sizeof(T) == 8 ? 2 : 4;
+template <typename T> static int update_rows(const DenseTuning &tun, int m)
+{
+    return m > tun.small_update_below ? 32 * kTallBlocks<T> : 64;
+}
+
 /* Launch-per-phase factor: k_diag, then per block step k_panel + k_update. */
 template <typename T>
 static hipError_t factor_phases(T *A, int64_t lda, int n, int32_t *info, T *Pg, const DenseTuning &tun,
@@ -748,15 +797,14 @@ static hipError_t factor_phases(T *A, int64_t lda, int n, int32_t *info, T *Pg, 
         const int nbr = (m + TB - 1) / TB;
         int pslot = -1;
         const bool prof = profile_slot(pr, st, 2.0 * (double)m * (double)m * (double)kw, pslot);
-        if (m > tun.small_update_below) {
-            const int nt = ((m + 127) / 128) * ((m + 127) / 128);
-            hipLaunchKernelGGL((k_update<T, 128, 128, 16>), dim3(nt + 1 + nbr * nbc), dim3(NT), 0, st, A, lda, n,
+        const int bm = update_rows<T>(tun, m);
+        const int nt = ((m + bm - 1) / bm) * ((m + 63) / 64);
+        if (bm == 128)
+            hipLaunchKernelGGL((k_update<T, kTallBlocks<T>, 2>), dim3(nt + 1 + nbr * nbc), dim3(NT), 0, st, A, lda, n,
                                k0, kw, info, Pg, B, ldb, nrhs);
-        } else {
-            const int nt = ((m + 63) / 64) * ((m + 63) / 64);
-            hipLaunchKernelGGL((k_update<T, 64, 64, 16>), dim3(nt + 1 + nbr * nbc), dim3(NT), 0, st, A, lda, n,
-                               k0, kw, info, Pg, B, ldb, nrhs);
-        }
+        else
+            hipLaunchKernelGGL((k_update<T, 2, 2>), dim3(nt + 1 + nbr * nbc), dim3(NT), 0, st, A, lda, n, k0, kw, info,
+                               Pg, B, ldb, nrhs);
         if ((e = hipGetLastError()) != hipSuccess)
             return e;
         if (prof)
@@ -784,13 +832,13 @@ static hipError_t factor_lookahead(T *A, int64_t lda, int n, int32_t *info, T *P
     const int G = max(1, min(4, sizeof(T) == 4 ? tun.defer_group_f32 : tun.defer_group));
     hipError_t e = hipSuccess;
     (void)prefilled;
-    /* workgroups resident at once (two per compute unit), less the diagonal
+    /* workgroups resident at once, less the diagonal
      * tile's: the size of the first wave of region tiles */
     int dev = 0, cus = 0;
     if ((e = hipGetDevice(&dev)) != hipSuccess ||
         (e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev)) != hipSuccess)
         return e;
-    const int first_wave = max(1, 2 * cus - 1);
+    const int first_wave = max(1, kStepPerCu * cus - 1);
     const long wlim = tun.wait_limit > 0 ? (long)tun.wait_limit : 1L << 24;
     int applied[4] = {0, 0, 0, 0};
     for (int s = 0; s < nb; ++s) {
@@ -803,8 +851,7 @@ static hipError_t factor_lookahead(T *A, int64_t lda, int n, int32_t *info, T *P
         }
         /* updated classes: none in the first launch, one while split, else all */
         const int upd = s == 0 ? -2 : (G > 1 && m2 > tun.defer_above && s + 1 < nb) ? (s + 1) % G : -1;
-        const bool tall = m2 > tun.small_update_below;
-        const int bm = tall ? 128 : 64;
+        const int bm = update_rows<T>(tun, m2);
         const int jfirst = upd < 0 ? 0 : ((upd - J0 % G) % G + G) % G, jstep = upd < 0 ? 1 : G;
         const int ncu = upd == -2 || jfirst >= nr2 ? 0 : (nr2 - jfirst + jstep - 1) / jstep;
         const int nt2 = ((m2 + bm - 1) / bm) * ncu;
@@ -825,12 +872,12 @@ static hipError_t factor_lookahead(T *A, int64_t lda, int n, int32_t *info, T *P
         }
         int pslot = -1;
         const bool prof = s > 0 && profile_slot(pr, st, fl, pslot);
-        if (tall)
-            hipLaunchKernelGGL((k_step<T, 128, 64, 16>), dim3(grid), dim3(NT), 0, st, A, lda, n, s, G, upd, pendp,
+        if (bm == 128)
+            hipLaunchKernelGGL((k_step<T, kTallBlocks<T>>), dim3(grid), dim3(NT), 0, st, A, lda, n, s, G, upd, pendp,
                                first_wave, info, Pg, B, ldb, nrhs, ctl, wlim);
         else
-            hipLaunchKernelGGL((k_step<T, 64, 64, 16>), dim3(grid), dim3(NT), 0, st, A, lda, n, s, G, upd, pendp,
-                               first_wave, info, Pg, B, ldb, nrhs, ctl, wlim);
+            hipLaunchKernelGGL((k_step<T, 2>), dim3(grid), dim3(NT), 0, st, A, lda, n, s, G, upd, pendp, first_wave,
+                               info, Pg, B, ldb, nrhs, ctl, wlim);
         if ((e = hipGetLastError()) != hipSuccess)
             return e;
         if (prof)
@@ -2865,7 +2912,7 @@ __global__ __launch_bounds__(NT) void k_sky_step(SkyPlan pl, double *__restrict_
             if (!pub)
                 return;
             if (stage == 0)
-                publish_strip(sm.t0, sm.t1, p, P, D, TB, kJ);
+                publish_strip<LDT>(sm.t0, sm.t1, p, P, D, TB, kJ);
             else
                 count_strip(flag);
         });
