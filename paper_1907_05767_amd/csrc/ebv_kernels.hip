@@ -175,8 +175,11 @@ __global__ __launch_bounds__(NT) void k_panel(T *__restrict__ A, int64_t lda, in
  * Product of a BM x K and a K x BN block of a matrix in memory (K a multiple
  * of 16) into the accumulators of four waves, each a 16 MB x 16 NB part of the
  * BM x BN tile: acc += A B, or with NEG acc -= A B, the rank-K update of Eq.
- * 6-c.  K runs in 16-deep chunks through double-buffered LDS: the next chunk's
- * global loads are in flight while the current one feeds the matrix cores.
+ * 6-c.  K runs in 16-deep chunks through double-buffered LDS: the loads of the
+ * next AHEAD (1 or 2) chunks are in flight while the current one feeds the
+ * matrix cores -- two where a workgroup may have its compute unit to itself
+ * and a chunk's products (0.4 us) do not cover a load, one where three
+ * workgroups do that for each other.
  * Both operands are read row by row in 16-byte vectors (at any alignment of
  * the leading dimension), with nothing but two pointer increments per chunk
  * between them and no branch, so that the waits count single loads.  A lies in
@@ -184,8 +187,9 @@ __global__ __launch_bounds__(NT) void k_panel(T *__restrict__ A, int64_t lda, in
  * indices of its row at once and lane group lk supplies the indices 2 lk, 2 lk
  * + 1 (4 lk ..) of each eight (sixteen); B by rows, the pitch spreading those
  * indices' rows over the banks.
- * EDGE: only nr rows of A and nc columns of B exist; past them the last one is
- * read instead, and what that gives is the caller's to drop.  tail() is called
+ * EDGE 1: only nr rows of A and nc columns of B exist; past them the last one
+ * is read instead, and what that gives is the caller's to drop.  EDGE 2: K may
+ * also be any positive number (A's elements past it count as zero).  tail() is called
  * before the last chunk's products: loads issued there are covered by them.
  * No barrier follows the last reads of `lds`.
  *
@@ -202,41 +206,68 @@ template <typename T, int MB, int NB> struct TileGemm {
     static constexpr size_t LDS = sizeof(T) * 2 * (BM * PA + BK * PB);
 };
 
-template <typename T, int MB, int NB, bool NEG, bool EDGE, typename Tail>
+template <typename T, int MB, int NB, bool NEG, int EDGE, int AHEAD, typename Tail>
 __device__ __forceinline__ void tile_gemm(typename vec4<T>::type (&acc)[MB][NB], const T *A, int64_t lda, int nr,
                                           const T *B, int64_t ldb, int nc, int K, char *lds, Tail &&tail)
 {
     typedef TileGemm<T, MB, NB> G;
     constexpr int BM = G::BM, BN = G::BN, BK = G::BK, W = G::W, PA = G::PA, PB = G::PB;
     constexpr int EA = BM * BK / NT, EB = BK * BN / NT; /* elements per thread and chunk */
+    constexpr int WB = W < EB ? W : EB;
     typedef T VW __attribute__((ext_vector_type(W)));
+    typedef T VB __attribute__((ext_vector_type(WB)));
     T *sA = reinterpret_cast<T *>(lds), *sB = sA + 2 * BM * PA;
     const int t = threadIdx.x, w = wave_id(), l = t & 63, lr = l & 15, lk = l >> 4;
     const int wm = (w >> 1) * 16 * MB, wn = (w & 1) * 16 * NB;
     /* this thread's share of a chunk: A row ar, columns ak.., B row bk, columns bc.. */
     const int ar = t / (BK / EA), ak = (t % (BK / EA)) * EA;
     const int bk = t / (BN / EB), bc = (t % (BN / EB)) * EB;
-    const T *pa = A + (int64_t)(EDGE ? min(ar, nr - 1) : ar) * lda + ak;
-    const T *pb = B + (int64_t)bk * ldb;
-    T ra[EA], rb[EB];
-    auto fetch = [&]() __attribute__((always_inline)) {
+    const T *pa = A + (int64_t)(EDGE ? min(ar, nr - 1) : ar) * lda + (EDGE == 2 ? 0 : ak);
+    const T *pb = B + (EDGE == 2 ? 0 : (int64_t)bk * ldb) + (EDGE ? 0 : bc);
+    int ob[EB]; /* columns of B past the last one: it again */
+#pragma unroll
+    for (int e = 0; e < EB; ++e)
+        ob[e] = EDGE ? min(bc + e, nc - 1) : e;
+    const int nch = EDGE == 2 ? (K + BK - 1) / BK : K / BK;
+    struct Chunk {
+        T a[EA], b[EB];
+    };
+    int fetched = 0; /* chunks requested; past the last one it again, from the cache */
+    const int64_t bstep = (int64_t)BK * ldb;
+    auto fetch = [&](Chunk &x) __attribute__((always_inline)) {
+        if (EDGE == 2) {
+            const int kc = min(fetched, nch - 1) * BK;
+            const T *row = pb + (int64_t)min(kc + bk, K - 1) * ldb;
+#pragma unroll
+            for (int e = 0; e < EA; ++e) {
+                const T v = pa[min(kc + ak + e, K - 1)];
+                x.a[e] = kc + ak + e < K ? v : T(0);
+            }
+#pragma unroll
+            for (int e = 0; e < EB; ++e)
+                x.b[e] = row[ob[e]];
+            ++fetched;
+            return;
+        }
 #pragma unroll
         for (int e = 0; e < EA; ++e)
-            ra[e] = pa[e];
+            x.a[e] = pa[e];
 #pragma unroll
         for (int e = 0; e < EB; ++e)
-            rb[e] = pb[EDGE ? min(bc + e, nc - 1) : bc + e];
-        pa += BK;
-        pb += (int64_t)BK * ldb;
+            x.b[e] = pb[ob[e]];
+        ++fetched;
+        const bool more = AHEAD == 1 || fetched < nch;
+        pa += more ? BK : 0;
+        pb += more ? bstep : 0;
     };
-    auto park = [&](int buf) __attribute__((always_inline)) {
+    auto park = [&](const Chunk &x, int buf) __attribute__((always_inline)) {
         T *da = sA + buf * BM * PA + ar * PA + ak, *db = sB + buf * BK * PB + bk * PB + bc;
 #pragma unroll
         for (int e = 0; e < EA; e += W)
-            *reinterpret_cast<VW *>(da + e) = *reinterpret_cast<VW *>(ra + e);
+            *reinterpret_cast<VW *>(da + e) = *reinterpret_cast<const VW *>(x.a + e);
 #pragma unroll
-        for (int e = 0; e < EB; e += W)
-            *reinterpret_cast<VW *>(db + e) = *reinterpret_cast<VW *>(rb + e);
+        for (int e = 0; e < EB; e += WB)
+            *reinterpret_cast<VB *>(db + e) = *reinterpret_cast<const VB *>(x.b + e);
     };
     const T *ua = sA + (wm + lr) * PA + W * lk, *ub = sB + W * lk * PB + wn + lr;
     auto multiply = [&](int buf) __attribute__((always_inline)) {
@@ -262,16 +293,38 @@ __device__ __forceinline__ void tile_gemm(typename vec4<T>::type (&acc)[MB][NB],
                         acc[bi][bj] = mfma16(NEG ? -av[bi][k] : av[bi][k], bv[bj][k], acc[bi][bj]);
         }
     };
-    fetch();
-    park(0);
+    Chunk x0, x1;
+    fetch(x0);
+    if (AHEAD == 2)
+        fetch(x1);
+    park(x0, 0);
     __syncthreads();
-    const int nch = K / BK;
+    if (AHEAD == 1) {
 #pragma unroll 1
-    for (int c = 0; c + 1 < nch; ++c) {
-        fetch();
-        multiply(c & 1);
-        park((c & 1) ^ 1);
-        __syncthreads();
+        for (int c = 0; c + 1 < nch; ++c) {
+            fetch(x0);
+            multiply(c & 1);
+            park(x0, (c & 1) ^ 1);
+            __syncthreads();
+        }
+    } else {
+        int c = 0;
+#pragma unroll 1
+        for (; c + 2 < nch; c += 2) {
+            fetch(x0);
+            multiply(0);
+            park(x1, 1);
+            __syncthreads();
+            fetch(x1);
+            multiply(1);
+            park(x0, 0);
+            __syncthreads();
+        }
+        if (c + 1 < nch) {
+            multiply(0);
+            park(x1, 1);
+            __syncthreads();
+        }
     }
     tail();
     multiply((nch - 1) & 1);
@@ -281,7 +334,7 @@ __device__ __forceinline__ void tile_gemm(typename vec4<T>::type (&acc)[MB][NB],
  * from k0: the product first, the tile's own elements loaded under its last
  * chunk.  The top-left skip x skip corner is not stored (it belongs to
  * another workgroup). */
-template <typename T, int MB, int NB, bool EDGE>
+template <typename T, int MB, int NB, int EDGE>
 __device__ __forceinline__ void update_tile_part(T *__restrict__ A, int64_t lda, int nr, int nc, int k0, int kw, int r0,
                                                  int c0, int skip, char *lds)
 {
@@ -296,7 +349,7 @@ __device__ __forceinline__ void update_tile_part(T *__restrict__ A, int64_t lda,
 #pragma unroll
         for (int bj = 0; bj < NB; ++bj)
             acc[bi][bj] = V{0, 0, 0, 0};
-    tile_gemm<T, MB, NB, false, EDGE>(acc, A + (int64_t)r0 * lda + k0, lda, nr, A + (int64_t)k0 * lda + c0, lda, nc, kw,
+    tile_gemm<T, MB, NB, false, EDGE, 1>(acc, A + (int64_t)r0 * lda + k0, lda, nr, A + (int64_t)k0 * lda + c0, lda, nc, kw,
                                       lds, [&]() __attribute__((always_inline)) {
 #pragma unroll
                                           for (int bi = 0; bi < MB; ++bi)
@@ -328,52 +381,75 @@ __device__ __forceinline__ void update_tile(T *__restrict__ A, int64_t lda, int 
     typedef TileGemm<T, MB, NB> G;
     const int nr = min(G::BM, n - r0), nc = min(G::BN, n - c0);
     if (nr == G::BM && nc == G::BN)
-        update_tile_part<T, MB, NB, false>(A, lda, nr, nc, k0, kw, r0, c0, skip, lds);
+        update_tile_part<T, MB, NB, 0>(A, lda, nr, nc, k0, kw, r0, c0, skip, lds);
     else
-        update_tile_part<T, MB, NB, true>(A, lda, nr, nc, k0, kw, r0, c0, skip, lds);
+        update_tile_part<T, MB, NB, 1>(A, lda, nr, nc, k0, kw, r0, c0, skip, lds);
 }
 
-/* A 64 x 64 tile's pending update: acc = C - A B (nr rows, nc columns of it
- * exist; the rest of the accumulators is the caller's to drop). */
-template <typename T>
-__device__ __forceinline__ void tile_pending(Acc64<T> &acc, const T *C, int64_t ldc, const T *A, int64_t lda, int nr,
-                                             const T *B, int64_t ldb, int nc, int K, char *lds)
+/* Chunks in flight of a product whose workgroup may be alone on its compute
+ * unit (FP32: measured 3 % slower with two). */
+template <typename T> constexpr int kAhead = sizeof(T) == 8 ? 2 : 1;
+
+/* A 64 x (32 NB) tile's accumulators, as tile_gemm deals it to the waves:
+ * f(bi, bj, r, i, j) for each element, (i, j) its place in the tile. */
+template <typename T, int NB, typename F> __device__ __forceinline__ void for_tile(F &&f)
 {
     const int w = wave_id(), l = threadIdx.x & 63, lr = l & 15, lk = l >> 4;
-    const int wm = (w >> 1) * 32, wn = (w & 1) * 32;
+    const int wm = (w >> 1) * 32 + acc_row<T>(lk, 0), wn = (w & 1) * 16 * NB + lr;
 #pragma unroll
     for (int bi = 0; bi < 2; ++bi)
 #pragma unroll
-        for (int bj = 0; bj < 2; ++bj)
+        for (int bj = 0; bj < NB; ++bj)
 #pragma unroll
             for (int r = 0; r < 4; ++r)
-                acc.v[bi][bj][r] = C[(int64_t)min(wm + 16 * bi + acc_row<T>(lk, r), nr - 1) * ldc +
-                                     min(wn + 16 * bj + lr, nc - 1)];
+                f(bi, bj, r, wm + 16 * bi + acc_row<T>(0, r), wn + 16 * bj);
+}
+
+/* acc -= A B for such a tile, whole or at the edge; KEDGE: K need not be a
+ * multiple of 16. */
+template <typename T, int NB, bool KEDGE = false>
+__device__ __forceinline__ void tile_minus(typename vec4<T>::type (&acc)[2][NB], const T *A, int64_t lda, int nr,
+                                           const T *B, int64_t ldb, int nc, int K, char *lds)
+{
     auto none = []() {};
     if (K == 0)
         return;
-    if (nr == TB && nc == TB)
-        tile_gemm<T, 2, 2, true, false>(acc.v, A, lda, nr, B, ldb, nc, K, lds, none);
+    if (nr == TB && nc == 32 * NB && (!KEDGE || K % 16 == 0))
+        tile_gemm<T, 2, NB, true, 0, kAhead<T>>(acc, A, lda, nr, B, ldb, nc, K, lds, none);
     else
-        tile_gemm<T, 2, 2, true, true>(acc.v, A, lda, nr, B, ldb, nc, K, lds, none);
+        tile_gemm<T, 2, NB, true, KEDGE ? 2 : 1, kAhead<T>>(acc, A, lda, nr, B, ldb, nc, K, lds, none);
 }
 
-/* acc64_store to an LDS tile (pitch LDT) of the nr x nc elements that exist,
- * the rest zero or (IDENTITY) the identity. */
-template <typename T>
-__device__ __forceinline__ void acc64_to_lds(const Acc64<T> &acc, T *S, int nr, int nc, bool identity)
+/* The tile's pending update: acc = C - A B (nr rows, nc columns of it exist;
+ * the rest of the accumulators is the caller's to drop). */
+template <typename T, int NB, bool KEDGE = false>
+__device__ __forceinline__ void tile_pending(typename vec4<T>::type (&acc)[2][NB], const T *C, int64_t ldc, const T *A,
+                                             int64_t lda, int nr, const T *B, int64_t ldb, int nc, int K, char *lds)
 {
-    const int w = wave_id(), l = threadIdx.x & 63, lr = l & 15, lk = l >> 4;
-    const int wm = (w >> 1) * 32, wn = (w & 1) * 32;
-#pragma unroll
-    for (int bi = 0; bi < 2; ++bi)
-#pragma unroll
-        for (int bj = 0; bj < 2; ++bj)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int i = wm + 16 * bi + acc_row<T>(lk, r), j = wn + 16 * bj + lr;
-                S[i * LDT + j] = (i < nr && j < nc) ? acc.v[bi][bj][r] : (identity && i == j ? T(1) : T(0));
-            }
+    for_tile<T, NB>([&](int bi, int bj, int r, int i, int j) {
+        acc[bi][bj][r] = C[(int64_t)min(i, nr - 1) * ldc + min(j, nc - 1)];
+    });
+    tile_minus<T, NB, KEDGE>(acc, A, lda, nr, B, ldb, nc, K, lds);
+}
+
+template <typename T, int NB>
+__device__ __forceinline__ void tile_store(const typename vec4<T>::type (&acc)[2][NB], T *C, int64_t ldc, int nr, int nc)
+{
+    for_tile<T, NB>([&](int bi, int bj, int r, int i, int j) {
+        if (i < nr && j < nc)
+            C[(int64_t)i * ldc + j] = acc[bi][bj][r];
+    });
+}
+
+/* The tile to LDS (pitch LDT): the nr x nc elements that exist, the rest zero
+ * or the identity. */
+template <typename T, int NB>
+__device__ __forceinline__ void tile_to_lds(const typename vec4<T>::type (&acc)[2][NB], T *S, int nr, int nc,
+                                            bool identity)
+{
+    for_tile<T, NB>([&](int bi, int bj, int r, int i, int j) {
+        S[i * LDT + j] = (i < nr && j < nc) ? acc[bi][bj][r] : (identity && i == j ? T(1) : T(0));
+    });
 }
 
 /* Tile index -> position: tiles are dealt to the 8 XCDs in contiguous runs
@@ -411,10 +487,10 @@ __global__ __launch_bounds__(NT, 2) void k_update(T *__restrict__ A, int64_t lda
          * then factored in place in LDS */
         DiagSmem<T> &sm = *reinterpret_cast<DiagSmem<T> *>(lds_raw);
         Acc64<T> acc;
-        tile_pending(acc, A + (int64_t)i0 * lda + i0, lda, A + (int64_t)i0 * lda + k0, lda, dw,
+        tile_pending<T, 2>(acc.v, A + (int64_t)i0 * lda + i0, lda, A + (int64_t)i0 * lda + k0, lda, dw,
                      A + (int64_t)k0 * lda + i0, lda, dw, kw, lds_raw);
         __syncthreads();
-        acc64_to_lds(acc, sm.S, dw, dw, true);
+        tile_to_lds<T, 2>(acc.v, sm.S, dw, dw, true);
         __syncthreads();
         diag_tile(A, lda, n, i0, info, Pg, sm, B != nullptr);
         return;
@@ -427,8 +503,9 @@ __global__ __launch_bounds__(NT, 2) void k_update(T *__restrict__ A, int64_t lda
         const int nr = min(TB, n - r0), nc = min(TB, nrhs - c0);
         T *C = B + (int64_t)r0 * ldb + c0;
         Acc64<T> acc;
-        tile_pending(acc, C, ldb, A + (int64_t)r0 * lda + k0, lda, nr, B + (int64_t)k0 * ldb + c0, ldb, nc, kw, lds_raw);
-        acc64_store(acc, DenseC<T>{C, ldb, nr, nc});
+        tile_pending<T, 2>(acc.v, C, ldb, A + (int64_t)r0 * lda + k0, lda, nr, B + (int64_t)k0 * ldb + c0, ldb, nc, kw,
+                           lds_raw);
+        tile_store<T, 2>(acc.v, C, ldb, nr, nc);
         return;
     }
     const int tile = xcd_tile(b, ntiles);
@@ -609,13 +686,14 @@ __global__ __launch_bounds__(NT, kStepPerCu) void k_step(T *__restrict__ A, int6
     C = const_cast<T *>(Bop) + (int64_t)r0 * ldc + c0;
     const int k0 = d0 - kw;
     Acc64<T> acc;
-    tile_pending(acc, C, ldc, A + (int64_t)r0 * lda + k0, lda, nr, Bop + (int64_t)k0 * ldc + c0, ldc, nc, kw, lds_raw);
+    tile_pending<T, 2>(acc.v, C, ldc, A + (int64_t)r0 * lda + k0, lda, nr, Bop + (int64_t)k0 * ldc + c0, ldc, nc, kw,
+                       lds_raw);
     if (kind == RHS_ROWS) {
-        acc64_store(acc, DenseC<T>{C, ldc, nr, nc});
+        tile_store<T, 2>(acc.v, C, ldc, nr, nc);
         return;
     }
     __syncthreads(); /* the product's last operand reads */
-    acc64_to_lds(acc, sm.S, nr, nc, kind == DIAGONAL);
+    tile_to_lds<T, 2>(acc.v, sm.S, nr, nc, kind == DIAGONAL);
     __syncthreads();
     if (kind == DIAGONAL) {
         const bool pub = nr2 > 0 || nbc > 0;
@@ -2665,98 +2743,141 @@ __global__ __launch_bounds__(NT) void k_diag_packs(const T *__restrict__ LU, int
  * Explicit inverse X = A^{-1} = U^{-1} L^{-1} from the factors (Eq. 4-c: the
  * elementary upper factors times the elementary lower factors), as two
  * right-looking blocked triangular solves on the identity, one launch per
- * 64-wide block step, one workgroup per 64 x 64 tile of the result:
- *   forward, W = L^{-1} (block lower triangular): step k takes the tiles
- *     (r, c), r > k, c <= k, and subtracts L_rk W_kc (a tile first touched
- *     here starts from zero); the workgroup of block row k + 1 then has its
- *     last update and applies L_{k+1,k+1}^{-1} at once; one more workgroup
- *     writes the diagonal tile W_{k+1,k+1} = L_{k+1,k+1}^{-1};
- *   backward, X = U^{-1} W (dense): the tiles of row r < k take the terms
- *     U_rs X_sc of the steps s >= k G = kInvGroup steps at a time: launch
- *     k updates the rows r = k-1, k-1-G, ... with the terms of steps k ..
- *     k+G-1 (one stream with K = 64 G over contiguous columns of U and rows
- *     of X; fewer at the first such launch), so a tile is read and written
- *     once per G steps; the tiles above W's diagonal start from zero at
- *     their first update; block row k - 1 has then received every term and
- *     applies U_{k-1,k-1}^{-1}.
+ * 64-wide block step, one workgroup per 64 x 64 tile of the result.  A tile
+ * takes the terms of G = kInvGroup steps at a time, so that it is read and
+ * written once per G steps and its product is G times as deep:
+ *   forward, W = L^{-1} (block lower triangular): launch k takes the rows r =
+ *     k+1, k+1+G, ... and subtracts L_rs W_sc of the steps s = k-G+1 .. k
+ *     (those >= c: W_sc is zero before; a tile first touched here starts from
+ *     zero); row k + 1 then has its last term and is multiplied by
+ *     L_{k+1,k+1}^{-1} at once; one more workgroup writes the diagonal tile
+ *     W_{k+1,k+1} = L_{k+1,k+1}^{-1};
+ *   backward, X = U^{-1} W (dense): launch k takes the rows r = k-1, k-1-G,
+ *     ... and subtracts U_rs X_sc of the steps s = k .. k+G-1 (fewer at the
+ *     first launches); the tiles above W's diagonal start from zero at their
+ *     first update; row k - 1 has then received every term and is multiplied
+ *     by U_{k-1,k-1}^{-1}.
  * W is kept in X's storage and overwritten in place.  The inverses of the
- * diagonal tiles come from their packs (k_diag_packs).
+ * diagonal tiles come from their packs (k_diag_packs), read as the products'
+ * left operand straight from memory.
+ * What bounds it is the product's rate and, where a launch has fewer tiles
+ * than the chip holds, one tile's own length.  n = 4096, forward | backward
+ * launches on average: one step a tile, operands streamed without LDS, 26 | 58
+ * us, two steps backward 26 | 54, tile_gemm and four steps 17 | 29.
  */
-constexpr int kInvGroup = 2; /* backward steps applied per tile update */
+constexpr int kInvGroup = 4;
 
-template <typename T, bool FWD>
-__global__ __launch_bounds__(NT, 2) void k_inv_step(const T *__restrict__ LU, int64_t lda, int n,
+template <typename T, bool FWD, int NB>
+__global__ __launch_bounds__(NT, 3) void k_inv_step(const T *__restrict__ LU, int64_t lda, int n,
                                                     const T *__restrict__ P, T *__restrict__ X, int64_t ldx, int k)
 {
-    __shared__ TileSmem<T> sm;
-    const int nt = (n + TB - 1) / TB, b = blockIdx.x;
-    int r, c;
-    bool diag_only = false;
+    typedef typename vec4<T>::type V;
+    constexpr int G = kInvGroup, H = 2 / NB; /* H workgroups per 64 x 64 tile */
+    __shared__ __attribute__((aligned(16))) char lds_raw[std::max(TileGemm<T, 2, NB>::LDS, sizeof(T) * TB * LDT)];
+    T *S = reinterpret_cast<T *>(lds_raw);
+    const int nt = (n + TB - 1) / TB, b = blockIdx.x / H, h0 = blockIdx.x % H * 32;
+    int r, c, s0, K; /* the tile, the first step of its terms and their inner length */
+    bool fresh;
     if (FWD) {
-        const int cols = k + 1, nupd = (nt - 1 - k) * cols;
-        if (b < nupd) {
-            r = k + 1 + b / cols;
-            c = b % cols;
-        } else {
-            r = c = k + 1; /* W_{k+1,k+1} = L_{k+1,k+1}^{-1} */
-            diag_only = true;
+        const int cols = k + 1, nupd = (nt - 1 - k + G - 1) / G * cols;
+        if (b >= nupd) { /* W_{k+1,k+1} = L_{k+1,k+1}^{-1} */
+            const int d0 = (k + 1) * TB, nd = min(TB, n - d0);
+            const T *Pr = P + (int64_t)(k + 1) * TB * TB;
+            T *C = X + (int64_t)d0 * ldx + d0;
+            tile_xfer<T>(
+                [&](int rr, int cc) {
+                    const T v = Pr[rr * TB + cc];
+                    return rr > cc ? v : (rr == cc ? T(1) : T(0));
+                },
+                [&](int rr, int cc, T v) {
+                    if (rr < nd && cc < nd && (H == 1 || cc >> 5 == h0 >> 5))
+                        C[(int64_t)rr * ldx + cc] = v;
+                });
+            return;
         }
+        r = k + 1 + G * (b / cols);
+        c = b % cols;
+        s0 = max(c, k + 1 - G);
+        K = (k + 1 - s0) * TB;
+        fresh = c > k - G;
+    } else if (k == nt) { /* the last block row: no terms */
+        r = nt - 1;
+        c = b;
+        s0 = K = 0;
+        fresh = false;
     } else {
-        if (k == nt) { /* the last block row: only its inverse product */
-            r = nt - 1;
-            c = b;
-            diag_only = true;
-        } else { /* rows k-1, k-1-G, ...: the terms of steps k .. k+G-1 */
-            r = k - 1 - kInvGroup * (b / nt);
-            c = b % nt;
+        r = k - 1 - G * (b / nt);
+        c = b % nt;
+        s0 = k;
+        K = min(G * TB, n - k * TB);
+        fresh = r < c && k + G >= nt;
+    }
+    const int nr = min(TB, n - r * TB), nc = min(32 * NB, n - c * TB - h0);
+    if (nc <= 0)
+        return;
+    T *C = X + (int64_t)r * TB * ldx + (int64_t)c * TB + h0;
+    const T *Ap = LU + (int64_t)r * TB * lda + (int64_t)s0 * TB, *Bp = X + (int64_t)s0 * TB * ldx + (int64_t)c * TB + h0;
+    V acc[2][NB];
+    if (fresh) {
+        for_tile<T, NB>([&](int bi, int bj, int rr, int, int) { acc[bi][bj][rr] = T(0); });
+        tile_minus<T, NB, true>(acc, Ap, lda, nr, Bp, ldx, nc, K, lds_raw);
+    } else {
+        tile_pending<T, NB, true>(acc, C, ldx, Ap, lda, nr, Bp, ldx, nc, K, lds_raw);
+    }
+    if (r != (FWD ? k + 1 : k - 1)) {
+        tile_store<T, NB>(acc, C, ldx, nr, nc);
+        return;
+    }
+    /* the row is complete: times its diagonal tile's inverse, the triangle's
+     * zero half of inner indices left out */
+    __syncthreads();
+    tile_to_lds<T, NB>(acc, S, nr, nc, false);
+    const T *Pr = P + (int64_t)r * TB * TB;
+    const int w = wave_id(), l = threadIdx.x & 63, lr = l & 15, lk = l >> 4;
+    const int wm = (w >> 1) * 32, wn = (w & 1) * 16 * NB;
+    V x[2][NB];
+#pragma unroll
+    for (int bi = 0; bi < 2; ++bi)
+#pragma unroll
+        for (int bj = 0; bj < NB; ++bj)
+            x[bi][bj] = V{0, 0, 0, 0};
+    __syncthreads();
+#pragma unroll 1
+    for (int kc = FWD ? 0 : wm; kc < (FWD ? wm + 32 : TB); kc += 32) {
+        T a[2][8];
+#pragma unroll
+        for (int bi = 0; bi < 2; ++bi)
+#pragma unroll
+            for (int ks = 0; ks < 8; ++ks)
+                a[bi][ks] = Pr[(wm + 16 * bi + lr) * TB + kc + 4 * ks + lk];
+#pragma unroll
+        for (int ks = 0; ks < 8; ++ks) {
+            const int kk = kc + 4 * ks + lk;
+#pragma unroll
+            for (int bi = 0; bi < 2; ++bi) {
+                const int rr = wm + 16 * bi + lr;
+                const T av = FWD ? (rr > kk ? a[bi][ks] : (rr == kk ? T(1) : T(0))) : (rr <= kk ? a[bi][ks] : T(0));
+#pragma unroll
+                for (int bj = 0; bj < NB; ++bj)
+                    x[bi][bj] = mfma16(av, S[kk * LDT + wn + 16 * bj + lr], x[bi][bj]);
+            }
         }
     }
-    const int next = FWD ? k + 1 : k - 1;
-    const int nr = min(TB, n - r * TB), nc = min(TB, n - c * TB);
-    T *C = X + (int64_t)r * TB * ldx + (int64_t)c * TB;
-    const T *Pr = P + (int64_t)r * TB * TB;
-    if (FWD && diag_only) {
-        tile_xfer<T>(
-            [&](int rr, int cc) {
-                const T v = Pr[rr * TB + cc];
-                return rr > cc ? v : (rr == cc ? T(1) : T(0));
-            },
-            [&](int rr, int cc, T v) {
-                if (rr < nr && cc < nc)
-                    C[(int64_t)rr * ldx + cc] = v;
-            });
-        return;
-    }
-    Acc64<T> acc;
-    /* the running value: zero where the tile is first touched (forward: the
-     * column being eliminated; backward: above W's diagonal, at the row's
-     * first update, launch nt - 1 or nt - 2) */
-    const bool fresh = FWD ? c == k : (r < c && k + kInvGroup >= nt);
-    if (fresh)
-        acc64_zero(acc);
+    tile_store<T, NB>(x, C, ldx, nr, nc);
+}
+
+template <typename T, bool FWD>
+static hipError_t inv_step(int tiles, const T *LU, int64_t lda, int n, const T *P, T *X, int64_t ldx, int k,
+                           hipStream_t st)
+{
+    /* up to 384 tiles: halves of 32 columns, which fill the chip's 768 places
+     * once and finish in half the time; more: whole tiles, half the operand
+     * traffic (n = 4096: 264 tiles 21 -> 18 us, 1024 tiles 43 us) */
+    if (tiles <= 384)
+        hipLaunchKernelGGL((k_inv_step<T, FWD, 1>), dim3(2 * tiles), dim3(NT), 0, st, LU, lda, n, P, X, ldx, k);
     else
-        acc64_load(acc, DenseC<T>{C, ldx, nr, nc});
-    if (!diag_only) {
-        /* backward: steps k .. k + G - 1, those that exist */
-        const int kw = min(FWD ? TB : kInvGroup * TB, n - k * TB);
-        acc64_stream<T, true>(acc, LU + (int64_t)r * TB * lda + (int64_t)k * TB, lda,
-                              X + (int64_t)k * TB * ldx + (int64_t)c * TB, ldx, nr, nc, kw);
-    }
-    if (r != next) {
-        acc64_store(acc, DenseC<T>{C, ldx, nr, nc});
-        return;
-    }
-    /* block row `next` is complete: times its diagonal tile's inverse */
-    acc64_store(acc, LdsTile<T>{sm.t0});
-    tile_xfer<T>([&](int rr, int cc) { return Pr[rr * TB + cc]; },
-                 [&](int rr, int cc, T v) { sm.t1[rr * LDT + cc] = v; });
-    __syncthreads();
-    if (FWD)
-        wg_gemm64f<T, true>(DenseC<T>{C, ldx, nr, nc}, InvL<T>{sm.t1},
-                            [&](int kk, int cc) { return sm.t0[kk * LDT + cc]; });
-    else
-        wg_gemm64f<T, true>(DenseC<T>{C, ldx, nr, nc}, InvUFull<T>{sm.t1},
-                            [&](int kk, int cc) { return sm.t0[kk * LDT + cc]; });
+        hipLaunchKernelGGL((k_inv_step<T, FWD, 2>), dim3(tiles), dim3(NT), 0, st, LU, lda, n, P, X, ldx, k);
+    return hipGetLastError();
 }
 
 template <typename T>
@@ -2765,16 +2886,10 @@ hipError_t lu_inverse(const T *LU, int64_t lda, int n, T *X, int64_t ldx, T *P, 
     const int nt = (n + TB - 1) / TB;
     hipLaunchKernelGGL(k_diag_packs<T>, dim3(nt), dim3(NT), 0, st, LU, lda, n, P);
     hipError_t e = hipGetLastError();
-    for (int k = -1; k + 1 < nt && e == hipSuccess; ++k) {
-        const int grid = (nt - 1 - k) * (k + 1) + 1;
-        hipLaunchKernelGGL((k_inv_step<T, true>), dim3(grid), dim3(NT), 0, st, LU, lda, n, (const T *)P, X, ldx, k);
-        e = hipGetLastError();
-    }
-    for (int k = nt; k > 0 && e == hipSuccess; --k) {
-        const int grid = k == nt ? nt : (k + kInvGroup - 1) / kInvGroup * nt; /* rows k-1, k-1-G, ... */
-        hipLaunchKernelGGL((k_inv_step<T, false>), dim3(grid), dim3(NT), 0, st, LU, lda, n, (const T *)P, X, ldx, k);
-        e = hipGetLastError();
-    }
+    for (int k = -1; k + 1 < nt && e == hipSuccess; ++k) /* rows k+1, k+1+G, ... and the diagonal tile */
+        e = inv_step<T, true>((nt - 1 - k + kInvGroup - 1) / kInvGroup * (k + 1) + 1, LU, lda, n, P, X, ldx, k, st);
+    for (int k = nt; k > 0 && e == hipSuccess; --k) /* rows k-1, k-1-G, ... */
+        e = inv_step<T, false>(k == nt ? nt : (k + kInvGroup - 1) / kInvGroup * nt, LU, lda, n, P, X, ldx, k, st);
     return e;
 }
 
