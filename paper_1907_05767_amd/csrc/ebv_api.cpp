@@ -95,7 +95,7 @@ int trsv_fit(size_t bytes, size_t elem, int64_t n, int64_t nrhs)
 
 /* Mixed precision (dense): [factor workspace: control words + diagonal
  * tile][exchange rows][conv int, margin u64][rbits u64[nrhs]][xbits u64[nrhs]]
- * [A32 n*n floats][R32 n*nrhs floats][R64 n*nrhs doubles] */
+ * [A32 n*n floats][R32 n*nrhs floats][n*nrhs doubles, unused] */
 struct MixedLayout {
     size_t trsv, dtile, xb, conv, mbits, rbits, xbits, a32, r32, r64, total;
     MixedLayout(int64_t n, int64_t nrhs, int chunks)
@@ -1210,7 +1210,6 @@ int ebv_lu_solve_mixed(ebv_handle h, int64_t n, int64_t nrhs, const double *A, i
     float *A32 = (float *)(w + lay.a32);
     float *XB = (float *)(w + lay.xb);
     float *R32 = (float *)(w + lay.r32);
-    double *R64 = (double *)(w + lay.r64);
     const int ni = (int)n, nr = (int)nrhs;
     hipError_t e;
 #define EBV_TRY(x)                                                                                                     \
@@ -1218,26 +1217,23 @@ int ebv_lu_solve_mixed(ebv_handle h, int64_t n, int64_t nrhs, const double *A, i
         if ((e = (x)) != hipSuccess)                                                                                   \
             return EBV_ERR_HIP;                                                                                        \
     } while (0)
-    EBV_TRY(ebv::fill_i32(wsi, 1, 0, stream));
-    EBV_TRY(ebv::fill_i32(conv, 1, 0, stream));
-    EBV_TRY(ebv::fill_u64(mbits, 1, 0x7FF0000000000000ull, stream)); /* +inf */
-    EBV_TRY(ebv::fill_u64(rbits, nrhs, 0, stream));
-    EBV_TRY(ebv::fill_u64(xbits, nrhs, 0, stream));
-    if (iters)
-        EBV_TRY(ebv::fill_i32(iters, nrhs, -1, stream));
+    EBV_TRY(ebv::mixed_init(ni, nr, wsi, info, conv, mbits, rbits, xbits, iters, XB, stream));
     EBV_TRY(ebv::convert_margin(ni, A, lda, A32, n, mbits, stream));
-    EBV_TRY(ebv::dense_factor<float>(A32, n, ni, info, (void *)(w + lay.dtile), h->dense, nullptr, stream));
+    EBV_TRY(ebv::dense_factor<float>(A32, n, ni, info, (void *)(w + lay.dtile), h->dense, nullptr, stream, nullptr, 0, 0,
+                                     true));
     EBV_TRY((ebv::convert<double, float>(ni, nr, B, ldb, R32, nrhs, nullptr, stream)));
     for (int it = 0; it <= max_iter; ++it) {
-        EBV_TRY(ebv::dense_trsv<float>(0, A32, n, ni, R32, nrhs, nr, wsi, XB, chunks, conv, nullptr, stream, ebv::TrsvStart::running,
+        /* the counters of further chunks lie among the factor's control words */
+        const ebv::TrsvStart start =
+            it > 0 || chunks == 1 ? ebv::TrsvStart::ready : ebv::TrsvStart::running;
+        EBV_TRY(ebv::dense_trsv<float>(0, A32, n, ni, R32, nrhs, nr, wsi, XB, chunks, conv, nullptr, stream, start,
                                        h->dense.wait_limit));
-        EBV_TRY(ebv::dense_trsv<float>(1, A32, n, ni, R32, nrhs, nr, wsi, XB, chunks, conv, nullptr, stream, ebv::TrsvStart::running,
-                                       h->dense.wait_limit));
+        EBV_TRY(ebv::dense_trsv<float>(1, A32, n, ni, R32, nrhs, nr, wsi, XB, chunks, conv, nullptr, stream,
+                                       ebv::TrsvStart::running, h->dense.wait_limit));
         EBV_TRY(ebv::mixed_xupdate(ni, nr, X, ldx, R32, nrhs, it == 0, xbits, conv, stream));
-        EBV_TRY(ebv::mixed_residual(ni, nr, A, lda, B, ldb, X, ldx, R64, nrhs, rbits, conv, stream));
-        EBV_TRY(ebv::mixed_check(nr, rbits, xbits, mbits, tol, it, iters, ferr, conv, stream));
-        if (it < max_iter)
-            EBV_TRY((ebv::convert<double, float>(ni, nr, R64, nrhs, R32, nrhs, conv, stream)));
+        EBV_TRY(ebv::mixed_residual(ni, nr, A, lda, B, ldb, X, ldx, R32, nrhs, rbits, conv, stream));
+        EBV_TRY(ebv::mixed_check(ni, nr, rbits, xbits, mbits, tol, it, iters, ferr, conv, wsi, XB, chunks,
+                                 it == max_iter, stream));
     }
     EBV_TRY(ebv::fold_status(wsi, info, stream));
 #undef EBV_TRY

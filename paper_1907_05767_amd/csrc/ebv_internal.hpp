@@ -121,8 +121,8 @@ hipError_t factor_solve(T *A, int64_t lda, int n, int32_t *info, void *ws, int c
  * info (or NULL): receives -status at the end of each launch when the status
  * word is nonzero.  start: what the first launch finds -- fresh: nothing
  * (status, info and counters are cleared, xb marked), running: the status of
- * earlier launches, which is kept, ready: with up to 16 right-hand sides (or
- * chunks = 1) also cleared counters and marked rows. */
+ * earlier launches, which is kept, ready: also its chunks' counters cleared
+ * and their rows marked. */
 enum class TrsvStart { fresh, running, ready };
 template <typename T>
 hipError_t dense_trsv(int mode, const T *LU, int64_t lda, int n, T *B, int64_t ldb, int nrhs, int *wsi, T *xb,
@@ -164,18 +164,25 @@ hipError_t convert(int rows, int cols, const TI *S, int64_t lds, TO *D, int64_t 
  * bit patterns, which every *bits word below relies on. */
 hipError_t convert_margin(int n, const double *A, int64_t lda, float *D, int64_t ldd, unsigned long long *mbits,
                           hipStream_t st);
-/* R = B - A X and max_i |r_ic| into rbits[c]. */
+/* One launch ahead of everything: status, info and the factor's control words
+ * cleared, the words below set up, iters (or NULL) to -1, and the exchange rows
+ * of the first forward substitution (one chunk) marked. */
+hipError_t mixed_init(int n, int nrhs, int *ctl, int32_t *info, int *conv, unsigned long long *mbits,
+                      unsigned long long *rbits, unsigned long long *xbits, int32_t *iters, float *xb, hipStream_t st);
+/* R = float(B - A X), the next correction's right-hand sides, and
+ * max_i |r_ic| into rbits[c]. */
 hipError_t mixed_residual(int n, int nrhs, const double *A, int64_t lda, const double *B, int64_t ldb, const double *X,
-                          int64_t ldx, double *R, int64_t ldr, unsigned long long *rbits, const int *skip, hipStream_t st);
+                          int64_t ldx, float *R, int64_t ldr, unsigned long long *rbits, const int *skip, hipStream_t st);
 /* Stopping test after refinement step `it`: column c has converged when its
  * forward-error bound max_i|r_ic| / (margin * max_i|x_ic|) <= tol; every
- * column's bound goes to ferr[c]. */
-hipError_t mixed_check(int nrhs, unsigned long long *rbits, unsigned long long *xbits, const unsigned long long *mbits,
-                       double tol, int it, int32_t *iters, double *ferr, int *conv, hipStream_t st);
+ * column's bound goes to ferr[c].  Unless last, the launch also readies the
+ * next forward substitution (TrsvStart::ready, up to `chunks` chunks). */
+hipError_t mixed_check(int n, int nrhs, unsigned long long *rbits, unsigned long long *xbits,
+                       const unsigned long long *mbits, double tol, int it, int32_t *iters, double *ferr, int *conv,
+                       int *ctl, float *xb, int chunks, bool last, hipStream_t st);
 /* X (+)= D, and max_i |x_ic| of the result into xbits[c]. */
 hipError_t mixed_xupdate(int n, int nrhs, double *X, int64_t ldx, const float *D, int64_t ldd, int first,
                          unsigned long long *xbits, const int *skip, hipStream_t st);
-hipError_t fill_u64(unsigned long long *p, int64_t count, unsigned long long value, hipStream_t st);
 
 } /* namespace ebv */
 

@@ -48,22 +48,6 @@ hipError_t fill_i32(int *p, int64_t count, int value, hipStream_t st)
     return hipGetLastError();
 }
 
-__global__ void k_fill_u64(unsigned long long *p, int64_t count, unsigned long long value)
-{
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < count;
-         i += (int64_t)gridDim.x * blockDim.x)
-        p[i] = value;
-}
-
-hipError_t fill_u64(unsigned long long *p, int64_t count, unsigned long long value, hipStream_t st)
-{
-    if (count <= 0)
-        return hipSuccess;
-    int grid = (int)std::min<int64_t>((count + 255) / 256, 1024);
-    hipLaunchKernelGGL(k_fill_u64, dim3(grid), dim3(256), 0, st, p, count, value);
-    return hipGetLastError();
-}
-
 __global__ void k_fold_status(const int *status, int32_t *info)
 {
     if (threadIdx.x == 0) {
@@ -1039,8 +1023,8 @@ hipError_t factor_solve(T *A, int64_t lda, int n, int32_t *info, void *ws, int c
     /* the backward substitution reports the status word into info at its
      * end; without right-hand sides a separate launch does */
     if (nrhs > 0)
-        return dense_trsv<T>(TRI_U, A, lda, n, B, ldb, nrhs, ctl, xb, chunks, nullptr, info, st, TrsvStart::ready,
-                             tun.wait_limit);
+        return dense_trsv<T>(TRI_U, A, lda, n, B, ldb, nrhs, ctl, xb, chunks, nullptr, info, st,
+                             mark ? TrsvStart::ready : TrsvStart::running, tun.wait_limit);
     return fold_status(ctl, info, st);
 }
 
@@ -1408,7 +1392,7 @@ static hipError_t trsv_mode(const T *LU, int64_t lda, int n, T *B, int64_t ldb, 
     hipError_t e = hipSuccess;
     for (int c0 = 0; c0 < nrhs; c0 += 16 * chunks) {
         const int nc = min(16 * chunks, nrhs - c0), nch = (nc + 15) / 16;
-        if (c0 > 0 || start != TrsvStart::ready || nch > 1) { /* counters cleared, exchange rows marked */
+        if (c0 > 0 || start != TrsvStart::ready) { /* counters cleared, exchange rows marked */
             const bool all = c0 == 0 && start == TrsvStart::fresh;
             if ((e = solve_init<T>(wsi + (all ? 0 : 1), (all ? 2 : 1) + nch, all ? info : nullptr, xb, nch * nx, st)) !=
                 hipSuccess)
@@ -3516,6 +3500,12 @@ hipError_t convert(int rows, int cols, const TI *S, int64_t lds, TO *D, int64_t 
     return hipGetLastError();
 }
 
+/* The larger of two magnitudes, a NaN above all (as their bits compare). */
+__device__ __forceinline__ double max_nan(double a, double b)
+{
+    return (unsigned long long)__double_as_longlong(a) < (unsigned long long)__double_as_longlong(b) ? b : a;
+}
+
 /* float(A) and the dominance margin, one wave per row: lanes split the row,
  * convert it and sum |a_ij| off the diagonal; the row's margin
  * |a_ii| - sum, clamped at 0, goes into *mbits by atomic minimum. */
@@ -3548,48 +3538,77 @@ __global__ __launch_bounds__(NT) void k_convert_margin(int n, const double *__re
         atomicMin(mbits, (unsigned long long)__double_as_longlong(mloc));
 }
 
-/* R = B - A X for NR <= 8 columns, one workgroup per row; max |r_ic| into bits[c]. */
-template <int NR>
+/* R = float(B - A X) for NR <= 8 columns, the right-hand sides of the next
+ * correction; max |r_ic| (in double) into bits[c].  RR rows per workgroup, a
+ * thread every 256th column of them, so that X is read once per RR rows: one
+ * row per workgroup read four times as many bytes of X, from L2, as of A
+ * (n = 16384, 4 columns: 1.46 ms; A alone at the copy's rate 0.45 ms).  Two
+ * columns' loads are issued before either is used. */
+template <int NR, int RR>
 __global__ __launch_bounds__(NT) void k_residual(int n, int nrhs, const double *__restrict__ A, int64_t lda,
                                                  const double *__restrict__ B, int64_t ldb, const double *__restrict__ X,
-                                                 int64_t ldx, double *__restrict__ R, int64_t ldr,
+                                                 int64_t ldx, float *__restrict__ R, int64_t ldr,
                                                  unsigned long long *bits, const int *skip)
 {
     if (skip && *skip)
         return;
-    __shared__ double red[4][NR];
-    const int t = threadIdx.x;
-    for (int i = blockIdx.x; i < n; i += gridDim.x) {
-        double acc[NR];
+    __shared__ double red[4][RR][NR];
+    const int t = threadIdx.x, i0 = blockIdx.x * RR;
+    double acc[RR][NR];
+#pragma unroll
+    for (int u = 0; u < RR; ++u)
 #pragma unroll
         for (int c = 0; c < NR; ++c)
-            acc[c] = 0.0;
-        const double *ai = A + (int64_t)i * lda;
-        for (int j = t; j < n; j += NT) {
-            const double a = ai[j];
+            acc[u][c] = 0.0;
+    /* rows past the last one read it again */
+    const double *ai[RR];
+#pragma unroll
+    for (int u = 0; u < RR; ++u)
+        ai[u] = A + (int64_t)min(i0 + u, n - 1) * lda;
+    auto load = [&](int j, double(&a)[RR], double(&x)[NR]) __attribute__((always_inline)) {
+        const int jc = min(j, n - 1);
+#pragma unroll
+        for (int u = 0; u < RR; ++u)
+            a[u] = ai[u][jc];
+#pragma unroll
+        for (int c = 0; c < NR; ++c)
+            x[c] = X[(int64_t)jc * ldx + min(c, nrhs - 1)];
+    };
+    auto add = [&](int j, const double(&a)[RR], const double(&x)[NR]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < RR; ++u) {
+            const double v = j < n ? a[u] : 0.0;
 #pragma unroll
             for (int c = 0; c < NR; ++c)
-                if (c < nrhs)
-                    acc[c] += a * X[(int64_t)j * ldx + c];
+                acc[u][c] = __builtin_fma(v, x[c], acc[u][c]);
         }
+    };
+    for (int j = t; j < n; j += 2 * NT) {
+        double a0[RR], a1[RR], x0[NR], x1[NR];
+        load(j, a0, x0);
+        load(j + NT, a1, x1);
+        add(j, a0, x0);
+        add(j + NT, a1, x1);
+    }
+#pragma unroll
+    for (int u = 0; u < RR; ++u)
 #pragma unroll
         for (int c = 0; c < NR; ++c) {
 #pragma unroll
             for (int o = 32; o > 0; o >>= 1)
-                acc[c] += __shfl_xor(acc[c], o);
+                acc[u][c] += __shfl_xor(acc[u][c], o);
+            if ((t & 63) == 0)
+                red[t >> 6][u][c] = acc[u][c];
         }
-        if ((t & 63) == 0)
-#pragma unroll
-            for (int c = 0; c < NR; ++c)
-                red[t >> 6][c] = acc[c];
-        __syncthreads();
-        if (t < nrhs && t < NR) {
-            const double s = red[0][t] + red[1][t] + red[2][t] + red[3][t];
-            const double r = B[(int64_t)i * ldb + t] - s;
-            R[(int64_t)i * ldr + t] = r;
-            atomicMax(bits + t, (unsigned long long)__double_as_longlong(fabs(r)));
+    __syncthreads();
+    if (t < NR && t < nrhs) {
+        double m = 0.0;
+        for (int u = 0; u < RR && i0 + u < n; ++u) {
+            const double r = B[(int64_t)(i0 + u) * ldb + t] - ((red[0][u][t] + red[1][u][t]) + (red[2][u][t] + red[3][u][t]));
+            R[(int64_t)(i0 + u) * ldr + t] = (float)r;
+            m = max_nan(m, fabs(r));
         }
-        __syncthreads();
+        atomicMax(bits + t, (unsigned long long)__double_as_longlong(m));
     }
 }
 
@@ -3597,11 +3616,10 @@ __global__ __launch_bounds__(NT) void k_residual(int n, int nrhs, const double *
  * m = min_i (|a_ii| - sum_{j != i} |a_ij|) > 0 the inverse is bounded,
  * ||A^{-1}||_inf <= 1/m, so the forward error of column c is at most
  * ||r_c||_inf / m; relative to the solution, ||r_c|| / (m ||x_c||). */
-__global__ void k_check(int nrhs, unsigned long long *rbits, unsigned long long *xbits,
-                        const unsigned long long *mbits, double tol, int it, int32_t *iters, double *ferr, int *conv)
+__device__ __forceinline__ void mixed_test(int nrhs, unsigned long long *rbits, unsigned long long *xbits,
+                                           const unsigned long long *mbits, double tol, int it, int32_t *iters,
+                                           double *ferr, int *conv)
 {
-    if (threadIdx.x != 0 || blockIdx.x != 0 || *conv)
-        return;
     const double m = __longlong_as_double((long long)*mbits);
     bool all = true;
     for (int c = 0; c < nrhs; ++c) {
@@ -3624,19 +3642,71 @@ __global__ void k_check(int nrhs, unsigned long long *rbits, unsigned long long 
         *conv = 1;
 }
 
-/* X (+)= D for the mixed-precision update; max |x_ic| of the result into xbits[c]. */
+/* The test, and (nctl > 0) the start of the next correction's forward
+ * substitution: its counters cleared and its exchange rows marked, in the one
+ * launch.  Workgroups that do not see the test's outcome yet mark rows that
+ * nobody reads. */
+__global__ void k_check(int nrhs, unsigned long long *rbits, unsigned long long *xbits,
+                        const unsigned long long *mbits, double tol, int it, int32_t *iters, double *ferr, int *conv,
+                        int *ctl, int nctl, unsigned int *xb, int64_t nxb)
+{
+    if (*conv)
+        return;
+    const int64_t i0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, step = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t i = i0; i < nctl; i += step)
+        ctl[i] = 0;
+    for (int64_t i = i0; i < nxb; i += step)
+        xb[i] = kUnsolvedMark32;
+    if (i0 == 0)
+        mixed_test(nrhs, rbits, xbits, mbits, tol, it, iters, ferr, conv);
+}
+
+/* Start of a mixed-precision solve: status, control words, info, the stopping
+ * test's state and the first forward substitution's exchange rows. */
+__global__ void k_mixed_init(int *ctl, int nctl, int32_t *info, int *conv, unsigned long long *mbits,
+                             unsigned long long *rbits, unsigned long long *xbits, int32_t *iters, int nrhs,
+                             unsigned int *xb, int64_t nxb)
+{
+    const int64_t i0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, step = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t i = i0; i < nctl; i += step)
+        ctl[i] = 0;
+    for (int64_t i = i0; i < nxb; i += step)
+        xb[i] = kUnsolvedMark32;
+    for (int64_t c = i0; c < nrhs; c += step) {
+        rbits[c] = xbits[c] = 0ull;
+        if (iters)
+            iters[c] = -1;
+    }
+    if (i0 == 0) {
+        *conv = 0;
+        *mbits = 0x7FF0000000000000ull; /* +inf */
+        if (info)
+            *info = 0;
+    }
+}
+
+/* X (+)= D for the mixed-precision update; max |x_ic| of the result into
+ * xbits[c], one atomic per wave and column (one per element, all to the same
+ * words, took 180 us for 65536 of them). */
 __global__ void k_xupdate(int n, int nrhs, double *__restrict__ X, int64_t ldx, const float *__restrict__ D,
                           int64_t ldd, int first, unsigned long long *xbits, const int *skip)
 {
     if (skip && *skip)
         return;
-    const int64_t total = (int64_t)n * nrhs;
-    for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t i = e / nrhs, c = e % nrhs;
-        const double d = (double)D[i * ldd + c];
-        const double x = first ? d : X[i * ldx + c] + d;
-        X[i * ldx + c] = x;
-        atomicMax(xbits + c, (unsigned long long)__double_as_longlong(fabs(x)));
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    for (int c = 0; c < nrhs; ++c) {
+        double m = 0.0;
+        if (i < n) {
+            const double d = (double)D[i * ldd + c];
+            const double x = first ? d : X[i * ldx + c] + d;
+            X[i * ldx + c] = x;
+            m = fabs(x);
+        }
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1)
+            m = max_nan(m, __shfl_xor(m, o));
+        if ((threadIdx.x & 63) == 0)
+            atomicMax(xbits + c, (unsigned long long)__double_as_longlong(m));
     }
 }
 
@@ -3648,41 +3718,54 @@ hipError_t convert_margin(int n, const double *A, int64_t lda, float *D, int64_t
     return hipGetLastError();
 }
 
-hipError_t mixed_residual(int n, int nrhs, const double *A, int64_t lda, const double *B, int64_t ldb, const double *X,
-                          int64_t ldx, double *R, int64_t ldr, unsigned long long *bits, const int *skip, hipStream_t st)
+template <int NR, int RR>
+static void residual_launch(int n, int nh, const double *A, int64_t lda, const double *B, int64_t ldb, const double *X,
+                            int64_t ldx, float *R, int64_t ldr, unsigned long long *bits, const int *skip, hipStream_t st)
 {
-    const int grid = min(n, 16384);
-    for (int c0 = 0; c0 < nrhs; c0 += 8) {
+    hipLaunchKernelGGL((k_residual<NR, RR>), dim3((n + RR - 1) / RR), dim3(NT), 0, st, n, nh, A, lda, B, ldb, X, ldx, R,
+                       ldr, bits, skip);
+}
+hipError_t mixed_residual(int n, int nrhs, const double *A, int64_t lda, const double *B, int64_t ldb, const double *X,
+                          int64_t ldx, float *R, int64_t ldr, unsigned long long *bits, const int *skip, hipStream_t st)
+{
+    hipError_t e = hipSuccess;
+    for (int c0 = 0; c0 < nrhs && e == hipSuccess; c0 += 8) {
         const int nh = min(8, nrhs - c0);
-        if (nh == 1)
-            hipLaunchKernelGGL(k_residual<1>, dim3(grid), dim3(NT), 0, st, n, nh, A, lda, B + c0, ldb, X + c0, ldx,
-                               R + c0, ldr, bits + c0, skip);
-        else if (nh <= 4)
-            hipLaunchKernelGGL(k_residual<4>, dim3(grid), dim3(NT), 0, st, n, nh, A, lda, B + c0, ldb, X + c0, ldx,
-                               R + c0, ldr, bits + c0, skip);
-        else
-            hipLaunchKernelGGL(k_residual<8>, dim3(grid), dim3(NT), 0, st, n, nh, A, lda, B + c0, ldb, X + c0, ldx,
-                               R + c0, ldr, bits + c0, skip);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess)
-            return e;
+        auto run = nh == 1 ? residual_launch<1, 8> : nh <= 4 ? residual_launch<4, 8> : residual_launch<8, 4>;
+        run(n, nh, A, lda, B + c0, ldb, X + c0, ldx, R + c0, ldr, bits + c0, skip, st);
+        e = hipGetLastError();
     }
-    return hipSuccess;
+    return e;
 }
 
-hipError_t mixed_check(int nrhs, unsigned long long *rbits, unsigned long long *xbits, const unsigned long long *mbits,
-                       double tol, int it, int32_t *iters, double *ferr, int *conv, hipStream_t st)
+static int mark_grid(int64_t nxb) { return (int)std::min<int64_t>((nxb + 255) / 256 + 1, 1024); }
+/* Exchange rows of `chunks` chunks, and the control words ahead of them. */
+static int64_t mixed_marks(int n, int chunks) { return (int64_t)chunks * (kTrsvHelpers + 1) * ((n + TB - 1) / TB) * TB * 16; }
+
+hipError_t mixed_init(int n, int nrhs, int *ctl, int32_t *info, int *conv, unsigned long long *mbits,
+                      unsigned long long *rbits, unsigned long long *xbits, int32_t *iters, float *xb, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_check, dim3(1), dim3(64), 0, st, nrhs, rbits, xbits, mbits, tol, it, iters, ferr, conv);
+    const int64_t nxb = mixed_marks(n, 1);
+    hipLaunchKernelGGL(k_mixed_init, dim3(mark_grid(nxb)), dim3(256), 0, st, ctl, kCtlHead + 2 * ((n + TB - 1) / TB), info,
+                       conv, mbits, rbits, xbits, iters, nrhs, reinterpret_cast<unsigned int *>(xb), nxb);
+    return hipGetLastError();
+}
+
+hipError_t mixed_check(int n, int nrhs, unsigned long long *rbits, unsigned long long *xbits,
+                       const unsigned long long *mbits, double tol, int it, int32_t *iters, double *ferr, int *conv,
+                       int *ctl, float *xb, int chunks, bool last, hipStream_t st)
+{
+    const int nch = last ? 0 : min(chunks, (nrhs + 15) / 16);
+    const int64_t nxb = mixed_marks(n, nch);
+    hipLaunchKernelGGL(k_check, dim3(mark_grid(nxb)), dim3(256), 0, st, nrhs, rbits, xbits, mbits, tol, it, iters, ferr,
+                       conv, ctl + 1, last ? 0 : 1 + nch, reinterpret_cast<unsigned int *>(xb), nxb);
     return hipGetLastError();
 }
 
 hipError_t mixed_xupdate(int n, int nrhs, double *X, int64_t ldx, const float *D, int64_t ldd, int first,
                          unsigned long long *xbits, const int *skip, hipStream_t st)
 {
-    const int64_t total = (int64_t)n * nrhs;
-    const int grid = (int)std::min<int64_t>((total + 255) / 256, 4096);
-    hipLaunchKernelGGL(k_xupdate, dim3(max(grid, 1)), dim3(256), 0, st, n, nrhs, X, ldx, D, ldd, first, xbits, skip);
+    hipLaunchKernelGGL(k_xupdate, dim3((n + 255) / 256), dim3(256), 0, st, n, nrhs, X, ldx, D, ldd, first, xbits, skip);
     return hipGetLastError();
 }
 
@@ -3711,6 +3794,5 @@ template hipError_t lu_inverse<float>(const float *, int64_t, int, float *, int6
 template hipError_t outer_neg<double>(int, int, const double *, int64_t, int64_t, const double *, int64_t, int64_t, double *, int64_t, int64_t, int64_t, hipStream_t);
 template hipError_t outer_neg<float>(int, int, const float *, int64_t, int64_t, const float *, int64_t, int64_t, float *, int64_t, int64_t, int64_t, hipStream_t);
 template hipError_t convert<double, float>(int, int, const double *, int64_t, float *, int64_t, const int *, hipStream_t);
-template hipError_t convert<float, double>(int, int, const float *, int64_t, double *, int64_t, const int *, hipStream_t);
 
 } /* namespace ebv */
