@@ -747,176 +747,27 @@ __device__ __forceinline__ void stage_tile_identity(T *S, const T *__restrict__ 
                  [&](int r, int c, T v) { S[r * LDT + c] = v; });
 }
 
+/* Operands of one 16-deep chunk of a streamed product, in the matrix cores'
+ * operand layout. */
+template <typename T> struct StreamRegs {
+    T a[2][4], b[2][4];
+};
+
 /*
- * acc -= A(nr x kw) * B(kw x nc) for one 64 x 64 tile held in the Acc64
- * accumulators (wave w: the 32 x 32 quadrant (w / 2, w % 2)), kw a multiple
- * of 16: the trailing updates of Eq. 6-c that a tile has pending, applied at
- * once.  Each wave loads its operands straight from memory into registers in
- * the matrix-core operand layout, 16 inner indices (a chunk) at a time, and
- * keeps two chunks in flight while it multiplies the third: no LDS, no
- * barrier, so the waves of a workgroup stream independently.  Within a chunk
- * lane group g = lane / 16 supplies inner indices 4g .. 4g+3 (one per
- * product), so a lane's four A elements are contiguous in memory.  Rows of A
- * past nr and columns of B past nc read as zero (their addresses clamped to
- * a valid element, the value then masked).  Ap = &A(0, 0) (pitch lda), Bp =
- * &B(0, 0) (pitch ldb).
+ * acc -= sum_t A_t B_t over a list of npairs pairs of 64 x 64 tiles (pitch
+ * 64, the inner index fully inside the matrix).  Each wave loads its operands
+ * straight from memory into registers in the matrix-core operand layout, a
+ * chunk of 16 inner indices at a time, and keeps two chunks in flight while it
+ * multiplies the third: no LDS, no barrier.  Within a chunk lane group g =
+ * lane / 16 supplies inner indices 4g .. 4g+3 (one per product), so a lane's
+ * four A elements are contiguous in memory.  pair(t, A, B) sets the addresses
+ * of the t-th pair (uniform in the workgroup); rows of A past nr and columns
+ * of B past nc read as zero.
  *
  * Every prefetch is issued, its chunk index clamped to the last chunk (the
  * last two re-read it from cache): with a prefetch behind a branch the
  * compiler's wait counts at the merge must cover the path that skipped it,
  * so the product before it waited for the chunk just requested as well.
- */
-template <typename T, int NA = 1, int NB = 1> struct StreamRegs {
-    T a[NA][2][4], b[NB][2][4];
-    int k0; /* first inner index of the chunk (KMASK) */
-};
-
-/*
- * The same stream for NA x NB tiles that share their operands:
- * acc[ia * NB + ib] -= A_ia * B_ib, where A_ia is the 64-row block starting
- * 64 ia rows below Ap (nr[ia] valid rows) and B_ib the 64-column block
- * starting 64 ib columns right of Bp (nc[ib] valid columns).  Two tiles of
- * one block row (NB = 2) read their common left operand once, two tiles of
- * one block column (NA = 2) their common right operand: a quarter less
- * operand traffic than two separate streams.
- */
-template <typename T, int NA, int NB, bool KMASK = false>
-__device__ __forceinline__ void acc64_stream_n(Acc64<T> *acc, const T *Ap, int64_t lda, const T *Bp, int64_t ldb,
-                                               const int (&nr)[NA], const int (&nc)[NB], int kw)
-{
-    /* KMASK: kw need not be a multiple of 16; inner indices past kw read as
-     * zero (addresses clamped to kw - 1) */
-    const int nch = KMASK ? (kw + 15) >> 4 : kw >> 4;
-    if (nch == 0)
-        return;
-    const int w = wave_id(), l = threadIdx.x & 63, lr = l & 15, g = l >> 4;
-    const int wm = (w >> 1) * 32, wn = (w & 1) * 32;
-    /* chunk 0's operands of this lane: A(r, 4g), B(4g, c) */
-    const T *ap[NA][2];
-    const T *bp[NB][2];
-    bool aok[NA][2], bok[NB][2];
-#pragma unroll
-    for (int ia = 0; ia < NA; ++ia)
-#pragma unroll
-        for (int bi = 0; bi < 2; ++bi) {
-            const int r = wm + 16 * bi + lr;
-            aok[ia][bi] = r < nr[ia];
-            ap[ia][bi] = Ap + (int64_t)(TB * ia + min(r, nr[ia] - 1)) * lda + 4 * g;
-        }
-#pragma unroll
-    for (int ib = 0; ib < NB; ++ib)
-#pragma unroll
-        for (int bj = 0; bj < 2; ++bj) {
-            const int c = wn + 16 * bj + lr;
-            bok[ib][bj] = c < nc[ib];
-            bp[ib][bj] = Bp + (int64_t)(4 * g) * ldb + TB * ib + min(c, nc[ib] - 1);
-        }
-    auto load = [&](StreamRegs<T, NA, NB> &R, int ci) {
-        ci = min(ci, nch - 1);
-        const int k0 = 16 * ci;
-        R.k0 = k0;
-#pragma unroll
-        for (int s = 0; s < 4; ++s) {
-            /* offset of inner index k0 + 4g + s from the lane's chunk-0 index */
-            const int kk = KMASK ? min(k0 + 4 * g + s, kw - 1) - 4 * g : k0 + s;
-#pragma unroll
-            for (int ia = 0; ia < NA; ++ia)
-#pragma unroll
-                for (int bi = 0; bi < 2; ++bi)
-                    R.a[ia][bi][s] = ap[ia][bi][kk];
-#pragma unroll
-            for (int ib = 0; ib < NB; ++ib)
-#pragma unroll
-                for (int bj = 0; bj < 2; ++bj)
-                    R.b[ib][bj][s] = bp[ib][bj][(int64_t)kk * ldb];
-        }
-        /* keeps the loads here, ahead of the product after them: left free,
-         * the compiler sinks them to their first use or moves the product
-         * above them, and the chunk is waited for as soon as it is issued
-         * (the operand pointers are not restrict-qualified, so that this
-         * barrier may write what they point to) */
-        asm volatile("" ::: "memory");
-        __builtin_amdgcn_sched_barrier(0);
-    };
-    auto mul = [&](const StreamRegs<T, NA, NB> &R) {
-#pragma unroll
-        for (int s = 0; s < 4; ++s) {
-            const bool kok = !KMASK || R.k0 + 4 * g + s < kw;
-            T av[NA][2], bv[NB][2];
-#pragma unroll
-            for (int ia = 0; ia < NA; ++ia)
-#pragma unroll
-                for (int bi = 0; bi < 2; ++bi)
-                    av[ia][bi] = (aok[ia][bi] && kok) ? -R.a[ia][bi][s] : T(0);
-#pragma unroll
-            for (int ib = 0; ib < NB; ++ib)
-#pragma unroll
-                for (int bj = 0; bj < 2; ++bj)
-                    bv[ib][bj] = (bok[ib][bj] && kok) ? R.b[ib][bj][s] : T(0);
-#pragma unroll
-            for (int ia = 0; ia < NA; ++ia)
-#pragma unroll
-                for (int ib = 0; ib < NB; ++ib)
-#pragma unroll
-                    for (int bi = 0; bi < 2; ++bi)
-#pragma unroll
-                        for (int bj = 0; bj < 2; ++bj)
-                            acc[ia * NB + ib].v[bi][bj] =
-                                mfma16(av[ia][bi], bv[ib][bj], acc[ia * NB + ib].v[bi][bj]);
-        }
-    };
-    if (NA * NB > 1) {
-        /* a chunk of several tiles is multiplied long enough to cover the
-         * next one's loads: one chunk in flight (and the registers of a
-         * third set would spill) */
-        StreamRegs<T, NA, NB> r0, r1;
-        load(r0, 0);
-        int c = 0;
-        for (; c + 2 <= nch; c += 2) {
-            load(r1, c + 1);
-            mul(r0);
-            load(r0, c + 2);
-            mul(r1);
-        }
-        if (c < nch)
-            mul(r0);
-        return;
-    }
-    StreamRegs<T, NA, NB> r0, r1, r2;
-    load(r0, 0);
-    load(r1, 1);
-    /* whole triples in a straight-line body (an exit between its products
-     * would merge load states again), the last one or two chunks after */
-    int c = 0;
-    for (; c + 3 <= nch; c += 3) {
-        load(r2, c + 2);
-        mul(r0);
-        load(r0, c + 3);
-        mul(r1);
-        load(r1, c + 4);
-        mul(r2);
-    }
-    if (c < nch)
-        mul(r0);
-    if (c + 1 < nch)
-        mul(r1);
-}
-
-template <typename T, bool KMASK = false>
-__device__ __forceinline__ void acc64_stream(Acc64<T> &acc, const T *Ap, int64_t lda, const T *Bp, int64_t ldb, int nr,
-                                             int nc, int kw)
-{
-    const int nrs[1] = {nr}, ncs[1] = {nc};
-    acc64_stream_n<T, 1, 1, KMASK>(&acc, Ap, lda, Bp, ldb, nrs, ncs, kw);
-}
-
-/*
- * acc -= sum_t A_t B_t over a list of npairs pairs of 64 x 64 tiles (pitch
- * 64, the inner index fully inside the matrix): acc64_stream's chunk ring run
- * as one sequence over all the pairs, so that the first loads of each pair
- * are issued while the previous pair is multiplied instead of after it.
- * pair(t, A, B) sets the addresses of the t-th pair (uniform in the
- * workgroup); rows of A past nr and columns of B past nc read as zero.
  */
 template <typename T, typename PairFn>
 __device__ __forceinline__ void acc64_stream_pairs(Acc64<T> &acc, int npairs, PairFn &&pair, int nr, int nc)
@@ -941,7 +792,7 @@ __device__ __forceinline__ void acc64_stream_pairs(Acc64<T> &acc, int npairs, Pa
         boff[bj] = 4 * g * TB + min(c, nc - 1);
     }
     auto load = [&](StreamRegs<T> &R, int ci) {
-        ci = min(ci, nch - 1); /* every prefetch issued: see acc64_stream */
+        ci = min(ci, nch - 1); 
         const T *A;
         const T *B;
         pair(ci >> 2, A, B);
@@ -950,12 +801,12 @@ __device__ __forceinline__ void acc64_stream_pairs(Acc64<T> &acc, int npairs, Pa
         for (int bi = 0; bi < 2; ++bi)
 #pragma unroll
             for (int s = 0; s < 4; ++s)
-                R.a[0][bi][s] = A[aoff[bi] + k0 + s];
+                R.a[bi][s] = A[aoff[bi] + k0 + s];
 #pragma unroll
         for (int bj = 0; bj < 2; ++bj)
 #pragma unroll
             for (int s = 0; s < 4; ++s)
-                R.b[0][bj][s] = B[boff[bj] + (k0 + s) * TB];
+                R.b[bj][s] = B[boff[bj] + (k0 + s) * TB];
         asm volatile("" ::: "memory");
         __builtin_amdgcn_sched_barrier(0);
     };
@@ -966,13 +817,15 @@ __device__ __forceinline__ void acc64_stream_pairs(Acc64<T> &acc, int npairs, Pa
             for (int bi = 0; bi < 2; ++bi)
 #pragma unroll
                 for (int bj = 0; bj < 2; ++bj)
-                    acc.v[bi][bj] = mfma16(aok[bi] ? -R.a[0][bi][s] : T(0), bok[bj] ? R.b[0][bj][s] : T(0),
+                    acc.v[bi][bj] = mfma16(aok[bi] ? -R.a[bi][s] : T(0), bok[bj] ? R.b[bj][s] : T(0),
                                            acc.v[bi][bj]);
     };
     StreamRegs<T> r0, r1, r2;
     load(r0, 0);
     load(r1, 1); /* nch >= 4 */
-    int c = 0; /* as in acc64_stream */
+    /* whole triples in a straight-line body (an exit between its products
+     * would merge load states again), the last one or two chunks after */
+    int c = 0;
     for (; c + 3 <= nch; c += 3) {
         load(r2, c + 2);
         mul(r0);
@@ -988,6 +841,331 @@ __device__ __forceinline__ void acc64_stream_pairs(Acc64<T> &acc, int npairs, Pa
 }
 
 /*
+ * Product of a BM x K and a K x BN block of a matrix in memory (K a multiple
+ * of 16) into the accumulators of four waves, each a 16 MB x 16 NB part of the
+ * BM x BN tile: acc += A B, or with NEG acc -= A B, the rank-K update of Eq.
+ * 6-c.  K runs in 16-deep chunks through double-buffered LDS: the loads of the
+ * next AHEAD (1 or 2) chunks are in flight while the current one feeds the
+ * matrix cores -- two where a workgroup may have its compute unit to itself
+ * and a chunk's products (0.4 us) do not cover a load, one where three
+ * workgroups do that for each other.
+ * Both operands are read row by row in 16-byte vectors (at any alignment of
+ * the leading dimension), with nothing but two pointer increments per chunk
+ * between them and no branch, so that the waits count single loads.  A lies in
+ * LDS by rows, pitch 16 + one vector, so that a lane reads two (four) inner
+ * indices of its row at once and lane group lk supplies the indices 2 lk, 2 lk
+ * + 1 (4 lk ..) of each eight (sixteen); B by rows, the pitch spreading those
+ * indices' rows over the banks.
+ * EDGE 1: only nr rows of A and nc columns of B exist; past them the last one
+ * is read instead, and what that gives is the caller's to drop.  EDGE 2: K may
+ * also be any positive number (A's elements past it count as zero).  tail() is called
+ * before the last chunk's products: loads issued there are covered by them.
+ * No barrier follows the last reads of `lds`.
+ *
+ * Measured alone on 3840 x 1280 with K = 192 (600 tiles of 128 x 64, 1200 of
+ * 64 x 64): 31 TFLOP/s in FP64 with a bounds check per element, scalar LDS
+ * traffic and 128-row tiles, 39 as written here, 48 with 64-row tiles and
+ * three workgroups per compute unit, which leave less of the chip idle at the
+ * end; in FP32, 128 x 64 on 15360 x 4096 with K = 256, 54 -> 104.
+ */
+template <typename T, int MB, int NB, int BK_ = 16> struct TileGemm {
+    static constexpr int BM = 32 * MB, BN = 32 * NB, BK = BK_;
+    static constexpr int W = 16 / sizeof(T); /* elements of a 16-byte vector */
+    static constexpr int PA = BK + W, PB = BN + (sizeof(T) == 8 ? 8 : 4);
+    static constexpr size_t LDS = sizeof(T) * 2 * (BM * PA + BK * PB);
+};
+
+template <typename T, int MB, int NB, bool NEG, int EDGE, int AHEAD, int BK_ = 16, typename Tail>
+__device__ __forceinline__ void tile_gemm(typename vec4<T>::type (&acc)[MB][NB], const T *A, int64_t lda, int nr,
+                                          const T *B, int64_t ldb, int nc, int K, char *lds, Tail &&tail)
+{
+    typedef TileGemm<T, MB, NB, BK_> G;
+    constexpr int BM = G::BM, BN = G::BN, BK = G::BK, W = G::W, PA = G::PA, PB = G::PB;
+    constexpr int EA = BM * BK / NT, EB = BK * BN / NT; /* elements per thread and chunk */
+    constexpr int WB = W < EB ? W : EB;
+    typedef T VW __attribute__((ext_vector_type(W)));
+    typedef T VB __attribute__((ext_vector_type(WB)));
+    T *sA = reinterpret_cast<T *>(lds), *sB = sA + 2 * BM * PA;
+    const int t = launder((int)threadIdx.x), w = wave_id(), l = t & 63, lr = l & 15, lk = l >> 4;
+    const int wm = (w >> 1) * 16 * MB, wn = (w & 1) * 16 * NB;
+    /* this thread's share of a chunk: A row ar, columns ak.., B row bk, columns bc.. */
+    const int ar = t / (BK / EA), ak = (t % (BK / EA)) * EA;
+    const int bk = t / (BN / EB), bc = (t % (BN / EB)) * EB;
+    const T *pa = A + (int64_t)(EDGE ? min(ar, nr - 1) : ar) * lda + (EDGE == 2 ? 0 : ak);
+    const T *pb = B + (EDGE == 2 ? 0 : (int64_t)bk * ldb) + (EDGE ? 0 : bc);
+    int ob[EB]; /* columns of B past the last one: it again */
+#pragma unroll
+    for (int e = 0; e < EB; ++e)
+        ob[e] = EDGE ? min(bc + e, nc - 1) : e;
+    const int nch = EDGE == 2 ? (K + BK - 1) / BK : K / BK;
+    struct Chunk {
+        T a[EA], b[EB];
+    };
+    int fetched = 0; /* chunks requested; past the last one it again, from the cache */
+    const int64_t bstep = (int64_t)BK * ldb;
+    auto fetch = [&](Chunk &x) __attribute__((always_inline)) {
+        if (EDGE == 2) {
+            const int kc = min(fetched, nch - 1) * BK;
+            const T *row = pb + (int64_t)min(kc + bk, K - 1) * ldb;
+#pragma unroll
+            for (int e = 0; e < EA; ++e) {
+                const T v = pa[min(kc + ak + e, K - 1)];
+                x.a[e] = kc + ak + e < K ? v : T(0);
+            }
+#pragma unroll
+            for (int e = 0; e < EB; ++e)
+                x.b[e] = row[ob[e]];
+            ++fetched;
+            return;
+        }
+#pragma unroll
+        for (int e = 0; e < EA; ++e)
+            x.a[e] = pa[e];
+#pragma unroll
+        for (int e = 0; e < EB; ++e)
+            x.b[e] = pb[ob[e]];
+        ++fetched;
+        const bool more = AHEAD == 1 || fetched < nch;
+        pa += more ? BK : 0;
+        pb += more ? bstep : 0;
+    };
+    auto park = [&](const Chunk &x, int buf) __attribute__((always_inline)) {
+        T *da = sA + buf * BM * PA + ar * PA + ak, *db = sB + buf * BK * PB + bk * PB + bc;
+#pragma unroll
+        for (int e = 0; e < EA; e += W)
+            *reinterpret_cast<VW *>(da + e) = *reinterpret_cast<const VW *>(x.a + e);
+#pragma unroll
+        for (int e = 0; e < EB; e += WB)
+            *reinterpret_cast<VB *>(db + e) = *reinterpret_cast<const VB *>(x.b + e);
+    };
+    const T *ua = sA + (wm + lr) * PA + W * lk, *ub = sB + W * lk * PB + wn + lr;
+    auto multiply = [&](int buf) __attribute__((always_inline)) {
+        const T *xa = ua + buf * BM * PA, *xb = ub + buf * BK * PB;
+#pragma unroll
+        for (int h = 0; h < BK; h += 4 * W) {
+            VW av[MB];
+            T bv[NB][W];
+#pragma unroll
+            for (int bi = 0; bi < MB; ++bi)
+                av[bi] = *reinterpret_cast<const VW *>(xa + 16 * bi * PA + h);
+#pragma unroll
+            for (int bj = 0; bj < NB; ++bj)
+#pragma unroll
+                for (int k = 0; k < W; ++k)
+                    bv[bj][k] = xb[(h + k) * PB + 16 * bj];
+#pragma unroll
+            for (int k = 0; k < W; ++k)
+#pragma unroll
+                for (int bi = 0; bi < MB; ++bi)
+#pragma unroll
+                    for (int bj = 0; bj < NB; ++bj)
+                        acc[bi][bj] = mfma16(NEG ? -av[bi][k] : av[bi][k], bv[bj][k], acc[bi][bj]);
+        }
+    };
+    Chunk x[AHEAD];
+#pragma unroll
+    for (int u = 0; u < AHEAD; ++u)
+        fetch(x[u]);
+    park(x[0], 0);
+    __syncthreads();
+    int c = 0;
+    if (AHEAD == 1) {
+#pragma unroll 1
+        for (; c + 1 < nch; ++c) {
+            fetch(x[0]);
+            multiply(c & 1);
+            park(x[0], (c & 1) ^ 1);
+            __syncthreads();
+        }
+    } else {
+        static_assert(AHEAD == 1 || AHEAD % 2 == 0, "the buffers alternate within a round");
+#pragma unroll 1
+        for (; c + AHEAD < nch; c += AHEAD)
+#pragma unroll
+            for (int u = 0; u < AHEAD; ++u) {
+                fetch(x[u]);
+                multiply(u & 1);
+                park(x[(u + 1) % AHEAD], (u & 1) ^ 1);
+                __syncthreads();
+            }
+#pragma unroll
+        for (int u = 0; u + 1 < AHEAD; ++u)
+            if (c + u + 1 < nch) {
+                multiply(u & 1);
+                park(x[u + 1], (u & 1) ^ 1);
+                __syncthreads();
+            }
+    }
+    tail();
+    multiply((nch - 1) & 1);
+}
+
+/* Chunks in flight of a product whose workgroup may be alone on its compute
+ * unit (FP32: measured 3 % slower with two). */
+template <typename T> constexpr int kAhead = sizeof(T) == 8 ? 2 : 1;
+
+/* A (32 MB) x (32 NB) tile's accumulators, as tile_gemm deals it to the waves:
+ * f(bi, bj, r, i, j) for each element, (i, j) its place in the tile. */
+template <typename T, int NB, int MB = 2, typename F> __device__ __forceinline__ void for_tile(F &&f)
+{
+    const int w = wave_id(), l = launder((int)threadIdx.x) & 63, lr = l & 15, lk = l >> 4;
+    const int wm = (w >> 1) * 16 * MB + acc_row<T>(lk, 0), wn = (w & 1) * 16 * NB + lr;
+#pragma unroll
+    for (int bi = 0; bi < MB; ++bi)
+#pragma unroll
+        for (int bj = 0; bj < NB; ++bj)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                f(bi, bj, r, wm + 16 * bi + acc_row<T>(0, r), wn + 16 * bj);
+}
+
+/* acc -= A B for such a tile, whole or at the edge; KEDGE: K need not be a
+ * multiple of 16. */
+template <typename T, int NB, bool KEDGE = false>
+__device__ __forceinline__ void tile_minus(typename vec4<T>::type (&acc)[2][NB], const T *A, int64_t lda, int nr,
+                                           const T *B, int64_t ldb, int nc, int K, char *lds)
+{
+    auto none = []() {};
+    if (K == 0)
+        return;
+    if (nr == TB && nc == 32 * NB && (!KEDGE || K % 16 == 0))
+        tile_gemm<T, 2, NB, true, 0, kAhead<T>>(acc, A, lda, nr, B, ldb, nc, K, lds, none);
+    else
+        tile_gemm<T, 2, NB, true, KEDGE ? 2 : 1, kAhead<T>>(acc, A, lda, nr, B, ldb, nc, K, lds, none);
+}
+
+/* The tile's pending update: acc = C - A B (nr rows, nc columns of it exist;
+ * the rest of the accumulators is the caller's to drop). */
+template <typename T, int NB, bool KEDGE = false>
+__device__ __forceinline__ void tile_pending(typename vec4<T>::type (&acc)[2][NB], const T *C, int64_t ldc, const T *A,
+                                             int64_t lda, int nr, const T *B, int64_t ldb, int nc, int K, char *lds)
+{
+    for_tile<T, NB>([&](int bi, int bj, int r, int i, int j) {
+        acc[bi][bj][r] = C[(int64_t)min(i, nr - 1) * ldc + min(j, nc - 1)];
+    });
+    tile_minus<T, NB, KEDGE>(acc, A, lda, nr, B, ldb, nc, K, lds);
+}
+
+template <typename T, int NB>
+__device__ __forceinline__ void tile_store(const typename vec4<T>::type (&acc)[2][NB], T *C, int64_t ldc, int nr, int nc)
+{
+    for_tile<T, NB>([&](int bi, int bj, int r, int i, int j) {
+        if (i < nr && j < nc)
+            C[(int64_t)i * ldc + j] = acc[bi][bj][r];
+    });
+}
+
+/* The tile to LDS (pitch LDT): the nr x nc elements that exist, the rest zero
+ * or the identity. */
+template <typename T, int NB>
+__device__ __forceinline__ void tile_to_lds(const typename vec4<T>::type (&acc)[2][NB], T *S, int nr, int nc,
+                                            bool identity)
+{
+    for_tile<T, NB>([&](int bi, int bj, int r, int i, int j) {
+        S[i * LDT + j] = (i < nr && j < nc) ? acc[bi][bj][r] : (identity && i == j ? T(1) : T(0));
+    });
+}
+
+/* Workgroups per compute unit of the kernels around wg_crout: what LDS (70 KB
+ * in FP64, 46 KB in FP32) admits; FP32's third one took the mixed-precision
+ * batch from 6.6 to 6.4 ms. */
+template <typename T> constexpr int kCroutPerCu = sizeof(T) == 8 ? 2 : 3;
+
+template <typename T> struct CroutSmem {
+    static constexpr int BK = sizeof(T) == 8 ? 8 : 16; /* chunk depth: two workgroups' buffers fit a compute unit */
+    static constexpr size_t PAIR = TileGemm<T, 4, 2, BK>::LDS > TileGemm<T, 2, 4, BK>::LDS
+                                       ? TileGemm<T, 4, 2, BK>::LDS
+                                       : TileGemm<T, 2, 4, BK>::LDS,
+                            GEMM = PAIR > TileGemm<T, 2, 2>::LDS ? PAIR : TileGemm<T, 2, 2>::LDS;
+    union alignas(16) {
+        T t0[TB * LDT];  /* diagonal tile / updated tile */
+        char gemm[GEMM]; /* operand buffers of the streamed products */
+    };
+    T t1[TB * LDT]; /* inverses of the diagonal tile's factors */
+    int ticket;
+    int zflag; /* zero-pivot report shared by the workgroup */
+};
+
+/* G = L_jj^{-1} X (LEFT) or X U_jj^{-1} for the 64 x 64 tile X in t0 and the
+ * pack of inverses in t1, the nr x nc elements that exist stored.  Of the
+ * triangle's four 16-wide block rows (columns) a wave takes the shortest and
+ * the longest or the two between, five inner blocks either way instead of
+ * eight: 40 products of 64 cycles a wave instead of 64. */
+template <typename T, bool LEFT>
+__device__ __forceinline__ void tri_product(T *G, int64_t ldg, int nr, int nc, const T *t0, const T *t1)
+{
+    typedef typename vec4<T>::type V;
+    const int w = wave_id(), l = launder((int)threadIdx.x) & 63, lr = l & 15, lk = l >> 4;
+    const int tri = LEFT ? w >> 1 : w & 1, oth = (LEFT ? w & 1 : w >> 1) * 32;
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+        const int tb = b == 0 ? 3 - tri : tri; /* this wave's block of the triangle */
+        V x[2] = {V{0, 0, 0, 0}, V{0, 0, 0, 0}};
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            if (q <= tb)
+#pragma unroll
+                for (int ks = 0; ks < 4; ++ks) {
+                    const int k = 16 * q + 4 * ks + lk, i = 16 * tb + lr;
+                    const T p = LEFT ? t1[i * LDT + k] : t1[k * LDT + i];
+                    const T f = LEFT ? (i > k ? p : (i == k ? T(1) : T(0))) : (k <= i ? p : T(0));
+#pragma unroll
+                    for (int c = 0; c < 2; ++c) {
+                        const int o = oth + 16 * c + lr;
+                        if (LEFT)
+                            x[c] = mfma16(f, t0[k * LDT + o], x[c]);
+                        else
+                            x[c] = mfma16(t0[o * LDT + k], f, x[c]);
+                    }
+                }
+#pragma unroll
+        for (int c = 0; c < 2; ++c)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int i = (LEFT ? 16 * tb : oth + 16 * c) + acc_row<T>(lk, r), j = (LEFT ? oth + 16 * c : 16 * tb) + lr;
+                if (i < nr && j < nc)
+                    G[(int64_t)i * ldg + j] = x[c][r];
+            }
+    }
+}
+
+/* One piece of a Crout step: G (32 MB x 32 NB: a 64 x 64 tile, two side by side
+ * or one below the other, or half of one) receives its pending updates A B, K
+ * deep, and is multiplied by the diagonal tile's inverse (t1), LEFT: U or Y
+ * tiles, L_jj^{-1} G, else L tiles, G U_jj^{-1}. */
+template <typename T, int MB, int NB, bool LEFT>
+__device__ __forceinline__ void crout_piece(T *G, int64_t ldg, int nr, int nc, const T *A, int64_t lda, const T *B,
+                                            int64_t ldb, int K, CroutSmem<T> &sm)
+{
+    typedef typename vec4<T>::type V;
+    constexpr int BK = CroutSmem<T>::BK, AHEAD = sizeof(T) == 8 ? 4 : 2;
+    V acc[MB][NB];
+    for_tile<T, NB, MB>([&](int bi, int bj, int r, int i, int j) {
+        acc[bi][bj][r] = G[(int64_t)min(i, nr - 1) * ldg + min(j, nc - 1)];
+    });
+    auto none = []() {};
+    if (K > 0) {
+        if (nr == 32 * MB && nc == 32 * NB)
+            tile_gemm<T, MB, NB, true, 0, AHEAD, BK>(acc, A, lda, nr, B, ldb, nc, K, sm.gemm, none);
+        else
+            tile_gemm<T, MB, NB, true, 1, AHEAD, BK>(acc, A, lda, nr, B, ldb, nc, K, sm.gemm, none);
+    }
+#pragma unroll
+    for (int h = 0; h < (MB * NB > 4 ? 2 : 1); ++h) {
+        const int i0 = MB > 2 ? TB * h : 0, j0 = NB > 2 ? TB * h : 0; /* tile h of the piece */
+        __syncthreads();
+        for_tile<T, NB, MB>([&](int bi, int bj, int r, int i, int j) {
+            if (MB * NB <= 4 || (MB > 2 ? i >> 6 : j >> 6) == h)
+                sm.t0[(i - i0) * LDT + j - j0] = (i < nr && j < nc) ? acc[bi][bj][r] : T(0);
+        });
+        __syncthreads();
+        tri_product<T, LEFT>(G + (int64_t)i0 * ldg + j0, ldg, min(TB, nr - i0), min(NB == 1 ? 32 : TB, nc - j0), sm.t0,
+                             sm.t1);
+    }
+    __syncthreads();
+}
+
+/*
  * Blocked Doolittle LU of one n x n system by one workgroup in Crout order
  * (Eq. 6-c's updates applied lazily): at block step j the diagonal tile and
  * the tiles of block row j and block column j receive, in one streamed
@@ -996,15 +1174,25 @@ __device__ __forceinline__ void acc64_stream_pairs(Acc64<T> &acc, int npairs, Pa
  *     factors inverted (tile_inv_off),
  *   - block row j becomes U:   U_jc = L_jj^{-1} A_jc,
  *   - block column j becomes L: L_rj = A_rj U_jj^{-1},
- * all products on the matrix cores.  Every tile is read and written once
- * for its whole update.  With right-hand sides (B != NULL, n x nrhs, pitch
+ * all products on the matrix cores, the streamed ones through tile_gemm with
+ * two tiles that share an operand at a time (it is read once for both) and
+ * four chunks in flight (two in FP32), since with two workgroups on a compute
+ * unit a chunk's products do not cover a load from HBM.  Every tile is read
+ * and written once for its whole update.  With right-hand sides (B != NULL, n x nrhs, pitch
  * ldb) the forward substitution L Y = B (Eq. 1) rides along as extra columns
  * of block row j: Y_j = L_jj^{-1} (B_j - L_j,0:j Y_0:j).  Returns the first
  * zero pivot (1-based) or 0; the factor overwrites A, Y overwrites B.
+ *
+ * Where the time goes (FP64; copies of the kernel with one part left out), 4096
+ * systems of n = 16..512 | 512 of n = 1024, of 4.63 | 9.29 ms: streamed
+ * products 1.6 | 6.2, products with the inverses 0.9 | 1.3, diagonal tiles 0.6
+ * | 0.7, right-hand sides 0.35 | 0.45, backward substitution 0.45 | 0.35.
+ * With operands streamed to registers without LDS, full 64-deep inverse
+ * products and 64-wide right-hand sides the two took 5.6 | 10.9 ms.
  */
 template <typename T>
 __device__ __forceinline__ int wg_crout(T *__restrict__ A, int64_t lda, int n, T *__restrict__ B, int64_t ldb, int nrhs,
-                                     TileSmem<T> &sm)
+                                     CroutSmem<T> &sm)
 {
     const int nt = (n + TB - 1) / TB;
     int zero_at = 0;
@@ -1015,16 +1203,13 @@ __device__ __forceinline__ int wg_crout(T *__restrict__ A, int64_t lda, int n, T
         /* diagonal tile: all pending updates, then into LDS with the
          * identity past the system's end */
         {
-            Acc64<T> acc;
+            typename vec4<T>::type acc[2][2];
             T *Akk = A + (int64_t)k0 * lda + k0;
-            acc64_load(acc, DenseC<T>{Akk, lda, kw, kw});
-            acc64_stream(acc, Lrow, lda, Ucol, lda, kw, kw, k0);
-            acc64_store(acc, LdsTile<T>{sm.t0});
+            tile_pending<T, 2>(acc, Akk, lda, Lrow, lda, kw, Ucol, lda, kw, k0, sm.gemm);
             __syncthreads();
-            if (threadIdx.x >= kw && threadIdx.x < TB)
-                sm.t0[threadIdx.x * LDT + threadIdx.x] = T(1);
+            tile_to_lds<T, 2>(acc, sm.t0, kw, kw, true);
             __syncthreads();
-            const int z = tile_lu64(sm.t0, sm.t1, sm.rinv, kw, &sm.zflag);
+            const int z = tile_lu64(sm.t0, sm.t1, (T *)nullptr, kw, &sm.zflag);
             if (z && !zero_at)
                 zero_at = k0 + z;
             lds_store_tile(sm.t0, Akk, lda, kw, kw);
@@ -1032,77 +1217,28 @@ __device__ __forceinline__ int wg_crout(T *__restrict__ A, int64_t lda, int n, T
                 break;
             tile_inv_off(sm.t0, sm.t1);
         }
-        /* block row j right of the diagonal (U), then the right-hand sides
-         * (Y); factor tiles two at a time where two remain (one stream for
-         * both, the left operand read once) */
-        const int ncol = nt - 1 - j + (B ? (nrhs + TB - 1) / TB : 0);
-        for (int q = 0; q < ncol; ++q) {
-            if (q + 1 < nt - 1 - j) {
-                const int c0 = k0 + TB + q * TB, cw1 = min(TB, n - c0 - TB);
-                T *G = A + (int64_t)k0 * lda + c0;
-                const int nrs[1] = {kw}, ncs[2] = {TB, cw1};
-                Acc64<T> acc[2];
-                acc64_load(acc[0], DenseC<T>{G, lda, kw, TB});
-                acc64_load(acc[1], DenseC<T>{G + TB, lda, kw, cw1});
-                acc64_stream_n<T, 1, 2>(acc, Lrow, lda, A + c0, lda, nrs, ncs, k0);
-#pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    acc64_store(acc[h], LdsTile<T>{sm.t0});
-                    __syncthreads();
-                    wg_gemm64f<T, true>(DenseC<T>{G + h * TB, lda, kw, h ? cw1 : TB}, InvL<T>{sm.t1},
-                                        [&](int k, int c) { return sm.t0[k * LDT + c]; });
-                    __syncthreads();
-                }
-                ++q;
-                continue;
-            }
-            const bool rhs = q >= nt - 1 - j;
-            const int c0 = rhs ? (q - (nt - 1 - j)) * TB : k0 + TB + q * TB;
-            const int cw = min(TB, (rhs ? nrhs : n) - c0);
-            T *G = rhs ? B + (int64_t)k0 * ldb + c0 : A + (int64_t)k0 * lda + c0;
-            const int64_t ldg = rhs ? ldb : lda;
-            const T *Bop = rhs ? B + c0 : A + c0;
-            Acc64<T> acc;
-            acc64_load(acc, DenseC<T>{G, ldg, kw, cw});
-            acc64_stream(acc, Lrow, lda, Bop, ldg, kw, cw, k0);
-            acc64_store(acc, LdsTile<T>{sm.t0});
-            __syncthreads();
-            wg_gemm64f<T, true>(DenseC<T>{G, ldg, kw, cw}, InvL<T>{sm.t1},
-                                [&](int k, int c) { return sm.t0[k * LDT + c]; });
-            __syncthreads();
+        /* block row j right of the diagonal (U), two tiles at a time where two
+         * remain (the left operand read once), then the right-hand sides (Y) */
+        for (int c0 = k0 + TB; c0 < n;) {
+            T *G = A + (int64_t)k0 * lda + c0;
+            if (c0 + TB < n)
+                crout_piece<T, 2, 4, true>(G, lda, kw, min(2 * TB, n - c0), Lrow, lda, A + c0, lda, k0, sm);
+            else
+                crout_piece<T, 2, 2, true>(G, lda, kw, n - c0, Lrow, lda, A + c0, lda, k0, sm);
+            c0 += 2 * TB;
         }
+        if (B)
+            for (int c0 = 0; c0 < nrhs; c0 += 32)
+                crout_piece<T, 2, 1, true>(B + (int64_t)k0 * ldb + c0, ldb, kw, min(32, nrhs - c0), Lrow, lda, B + c0, ldb,
+                                           k0, sm);
         /* block column j below the diagonal (L), two tiles at a time where
          * two remain (the right operand read once) */
-        for (int r = j + 1; r < nt; ++r) {
-            if (r + 1 < nt) {
-                const int r0 = r * TB, rw1 = min(TB, n - r0 - TB);
-                T *G = A + (int64_t)r0 * lda + k0;
-                const int nrs[2] = {TB, rw1}, ncs[1] = {kw};
-                Acc64<T> acc[2];
-                acc64_load(acc[0], DenseC<T>{G, lda, TB, kw});
-                acc64_load(acc[1], DenseC<T>{G + (int64_t)TB * lda, lda, rw1, kw});
-                acc64_stream_n<T, 2, 1>(acc, A + (int64_t)r0 * lda, lda, Ucol, lda, nrs, ncs, k0);
-#pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    acc64_store(acc[h], LdsTile<T>{sm.t0});
-                    __syncthreads();
-                    wg_gemm64f<T, true>(DenseC<T>{G + (int64_t)h * TB * lda, lda, h ? rw1 : TB, kw},
-                                        [&](int rr, int k) { return sm.t0[rr * LDT + k]; }, InvU<T>{sm.t1});
-                    __syncthreads();
-                }
-                ++r;
-                continue;
-            }
-            const int r0 = r * TB, rw = min(TB, n - r0);
+        for (int r0 = k0 + TB; r0 < n; r0 += 2 * TB) {
             T *G = A + (int64_t)r0 * lda + k0;
-            Acc64<T> acc;
-            acc64_load(acc, DenseC<T>{G, lda, rw, kw});
-            acc64_stream(acc, A + (int64_t)r0 * lda, lda, Ucol, lda, rw, kw, k0);
-            acc64_store(acc, LdsTile<T>{sm.t0});
-            __syncthreads();
-            wg_gemm64f<T, true>(DenseC<T>{G, lda, rw, kw}, [&](int rr, int k) { return sm.t0[rr * LDT + k]; },
-                                InvU<T>{sm.t1});
-            __syncthreads();
+            if (r0 + TB < n)
+                crout_piece<T, 4, 2, false>(G, lda, min(2 * TB, n - r0), kw, A + (int64_t)r0 * lda, lda, Ucol, lda, k0, sm);
+            else
+                crout_piece<T, 2, 2, false>(G, lda, n - r0, kw, A + (int64_t)r0 * lda, lda, Ucol, lda, k0, sm);
         }
     }
     __syncthreads();

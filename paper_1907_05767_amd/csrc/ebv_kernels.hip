@@ -155,165 +155,6 @@ __global__ __launch_bounds__(NT) void k_panel(T *__restrict__ A, int64_t lda, in
     }
 }
 
-/*
- * Product of a BM x K and a K x BN block of a matrix in memory (K a multiple
- * of 16) into the accumulators of four waves, each a 16 MB x 16 NB part of the
- * BM x BN tile: acc += A B, or with NEG acc -= A B, the rank-K update of Eq.
- * 6-c.  K runs in 16-deep chunks through double-buffered LDS: the loads of the
- * next AHEAD (1 or 2) chunks are in flight while the current one feeds the
- * matrix cores -- two where a workgroup may have its compute unit to itself
- * and a chunk's products (0.4 us) do not cover a load, one where three
- * workgroups do that for each other.
- * Both operands are read row by row in 16-byte vectors (at any alignment of
- * the leading dimension), with nothing but two pointer increments per chunk
- * between them and no branch, so that the waits count single loads.  A lies in
- * LDS by rows, pitch 16 + one vector, so that a lane reads two (four) inner
- * indices of its row at once and lane group lk supplies the indices 2 lk, 2 lk
- * + 1 (4 lk ..) of each eight (sixteen); B by rows, the pitch spreading those
- * indices' rows over the banks.
- * EDGE 1: only nr rows of A and nc columns of B exist; past them the last one
- * is read instead, and what that gives is the caller's to drop.  EDGE 2: K may
- * also be any positive number (A's elements past it count as zero).  tail() is called
- * before the last chunk's products: loads issued there are covered by them.
- * No barrier follows the last reads of `lds`.
- *
- * Measured alone on 3840 x 1280 with K = 192 (600 tiles of 128 x 64, 1200 of
- * 64 x 64): 31 TFLOP/s in FP64 with a bounds check per element, scalar LDS
- * traffic and 128-row tiles, 39 as written here, 48 with 64-row tiles and
- * three workgroups per compute unit, which leave less of the chip idle at the
- * end; in FP32, 128 x 64 on 15360 x 4096 with K = 256, 54 -> 104.
- */
-template <typename T, int MB, int NB> struct TileGemm {
-    static constexpr int BM = 32 * MB, BN = 32 * NB, BK = 16;
-    static constexpr int W = 16 / sizeof(T); /* elements of a 16-byte vector */
-    static constexpr int PA = BK + W, PB = BN + (sizeof(T) == 8 ? 8 : 4);
-    static constexpr size_t LDS = sizeof(T) * 2 * (BM * PA + BK * PB);
-};
-
-template <typename T, int MB, int NB, bool NEG, int EDGE, int AHEAD, typename Tail>
-__device__ __forceinline__ void tile_gemm(typename vec4<T>::type (&acc)[MB][NB], const T *A, int64_t lda, int nr,
-                                          const T *B, int64_t ldb, int nc, int K, char *lds, Tail &&tail)
-{
-    typedef TileGemm<T, MB, NB> G;
-    constexpr int BM = G::BM, BN = G::BN, BK = G::BK, W = G::W, PA = G::PA, PB = G::PB;
-    constexpr int EA = BM * BK / NT, EB = BK * BN / NT; /* elements per thread and chunk */
-    constexpr int WB = W < EB ? W : EB;
-    typedef T VW __attribute__((ext_vector_type(W)));
-    typedef T VB __attribute__((ext_vector_type(WB)));
-    T *sA = reinterpret_cast<T *>(lds), *sB = sA + 2 * BM * PA;
-    const int t = threadIdx.x, w = wave_id(), l = t & 63, lr = l & 15, lk = l >> 4;
-    const int wm = (w >> 1) * 16 * MB, wn = (w & 1) * 16 * NB;
-    /* this thread's share of a chunk: A row ar, columns ak.., B row bk, columns bc.. */
-    const int ar = t / (BK / EA), ak = (t % (BK / EA)) * EA;
-    const int bk = t / (BN / EB), bc = (t % (BN / EB)) * EB;
-    const T *pa = A + (int64_t)(EDGE ? min(ar, nr - 1) : ar) * lda + (EDGE == 2 ? 0 : ak);
-    const T *pb = B + (EDGE == 2 ? 0 : (int64_t)bk * ldb) + (EDGE ? 0 : bc);
-    int ob[EB]; /* columns of B past the last one: it again */
-#pragma unroll
-    for (int e = 0; e < EB; ++e)
-        ob[e] = EDGE ? min(bc + e, nc - 1) : e;
-    const int nch = EDGE == 2 ? (K + BK - 1) / BK : K / BK;
-    struct Chunk {
-        T a[EA], b[EB];
-    };
-    int fetched = 0; /* chunks requested; past the last one it again, from the cache */
-    const int64_t bstep = (int64_t)BK * ldb;
-    auto fetch = [&](Chunk &x) __attribute__((always_inline)) {
-        if (EDGE == 2) {
-            const int kc = min(fetched, nch - 1) * BK;
-            const T *row = pb + (int64_t)min(kc + bk, K - 1) * ldb;
-#pragma unroll
-            for (int e = 0; e < EA; ++e) {
-                const T v = pa[min(kc + ak + e, K - 1)];
-                x.a[e] = kc + ak + e < K ? v : T(0);
-            }
-#pragma unroll
-            for (int e = 0; e < EB; ++e)
-                x.b[e] = row[ob[e]];
-            ++fetched;
-            return;
-        }
-#pragma unroll
-        for (int e = 0; e < EA; ++e)
-            x.a[e] = pa[e];
-#pragma unroll
-        for (int e = 0; e < EB; ++e)
-            x.b[e] = pb[ob[e]];
-        ++fetched;
-        const bool more = AHEAD == 1 || fetched < nch;
-        pa += more ? BK : 0;
-        pb += more ? bstep : 0;
-    };
-    auto park = [&](const Chunk &x, int buf) __attribute__((always_inline)) {
-        T *da = sA + buf * BM * PA + ar * PA + ak, *db = sB + buf * BK * PB + bk * PB + bc;
-#pragma unroll
-        for (int e = 0; e < EA; e += W)
-            *reinterpret_cast<VW *>(da + e) = *reinterpret_cast<const VW *>(x.a + e);
-#pragma unroll
-        for (int e = 0; e < EB; e += WB)
-            *reinterpret_cast<VB *>(db + e) = *reinterpret_cast<const VB *>(x.b + e);
-    };
-    const T *ua = sA + (wm + lr) * PA + W * lk, *ub = sB + W * lk * PB + wn + lr;
-    auto multiply = [&](int buf) __attribute__((always_inline)) {
-        const T *xa = ua + buf * BM * PA, *xb = ub + buf * BK * PB;
-#pragma unroll
-        for (int h = 0; h < BK; h += 4 * W) {
-            VW av[MB];
-            T bv[NB][W];
-#pragma unroll
-            for (int bi = 0; bi < MB; ++bi)
-                av[bi] = *reinterpret_cast<const VW *>(xa + 16 * bi * PA + h);
-#pragma unroll
-            for (int bj = 0; bj < NB; ++bj)
-#pragma unroll
-                for (int k = 0; k < W; ++k)
-                    bv[bj][k] = xb[(h + k) * PB + 16 * bj];
-#pragma unroll
-            for (int k = 0; k < W; ++k)
-#pragma unroll
-                for (int bi = 0; bi < MB; ++bi)
-#pragma unroll
-                    for (int bj = 0; bj < NB; ++bj)
-                        acc[bi][bj] = mfma16(NEG ? -av[bi][k] : av[bi][k], bv[bj][k], acc[bi][bj]);
-        }
-    };
-    Chunk x0, x1;
-    fetch(x0);
-    if (AHEAD == 2)
-        fetch(x1);
-    park(x0, 0);
-    __syncthreads();
-    if (AHEAD == 1) {
-#pragma unroll 1
-        for (int c = 0; c + 1 < nch; ++c) {
-            fetch(x0);
-            multiply(c & 1);
-            park(x0, (c & 1) ^ 1);
-            __syncthreads();
-        }
-    } else {
-        int c = 0;
-#pragma unroll 1
-        for (; c + 2 < nch; c += 2) {
-            fetch(x0);
-            multiply(0);
-            park(x1, 1);
-            __syncthreads();
-            fetch(x1);
-            multiply(1);
-            park(x0, 0);
-            __syncthreads();
-        }
-        if (c + 1 < nch) {
-            multiply(0);
-            park(x1, 1);
-            __syncthreads();
-        }
-    }
-    tail();
-    multiply((nch - 1) & 1);
-}
-
 /* Trailing update A22 -= L21 U12 of the tile at (r0, c0) by the kw columns
  * from k0: the product first, the tile's own elements loaded under its last
  * chunk.  The top-left skip x skip corner is not stored (it belongs to
@@ -368,72 +209,6 @@ __device__ __forceinline__ void update_tile(T *__restrict__ A, int64_t lda, int 
         update_tile_part<T, MB, NB, 0>(A, lda, nr, nc, k0, kw, r0, c0, skip, lds);
     else
         update_tile_part<T, MB, NB, 1>(A, lda, nr, nc, k0, kw, r0, c0, skip, lds);
-}
-
-/* Chunks in flight of a product whose workgroup may be alone on its compute
- * unit (FP32: measured 3 % slower with two). */
-template <typename T> constexpr int kAhead = sizeof(T) == 8 ? 2 : 1;
-
-/* A 64 x (32 NB) tile's accumulators, as tile_gemm deals it to the waves:
- * f(bi, bj, r, i, j) for each element, (i, j) its place in the tile. */
-template <typename T, int NB, typename F> __device__ __forceinline__ void for_tile(F &&f)
-{
-    const int w = wave_id(), l = threadIdx.x & 63, lr = l & 15, lk = l >> 4;
-    const int wm = (w >> 1) * 32 + acc_row<T>(lk, 0), wn = (w & 1) * 16 * NB + lr;
-#pragma unroll
-    for (int bi = 0; bi < 2; ++bi)
-#pragma unroll
-        for (int bj = 0; bj < NB; ++bj)
-#pragma unroll
-            for (int r = 0; r < 4; ++r)
-                f(bi, bj, r, wm + 16 * bi + acc_row<T>(0, r), wn + 16 * bj);
-}
-
-/* acc -= A B for such a tile, whole or at the edge; KEDGE: K need not be a
- * multiple of 16. */
-template <typename T, int NB, bool KEDGE = false>
-__device__ __forceinline__ void tile_minus(typename vec4<T>::type (&acc)[2][NB], const T *A, int64_t lda, int nr,
-                                           const T *B, int64_t ldb, int nc, int K, char *lds)
-{
-    auto none = []() {};
-    if (K == 0)
-        return;
-    if (nr == TB && nc == 32 * NB && (!KEDGE || K % 16 == 0))
-        tile_gemm<T, 2, NB, true, 0, kAhead<T>>(acc, A, lda, nr, B, ldb, nc, K, lds, none);
-    else
-        tile_gemm<T, 2, NB, true, KEDGE ? 2 : 1, kAhead<T>>(acc, A, lda, nr, B, ldb, nc, K, lds, none);
-}
-
-/* The tile's pending update: acc = C - A B (nr rows, nc columns of it exist;
- * the rest of the accumulators is the caller's to drop). */
-template <typename T, int NB, bool KEDGE = false>
-__device__ __forceinline__ void tile_pending(typename vec4<T>::type (&acc)[2][NB], const T *C, int64_t ldc, const T *A,
-                                             int64_t lda, int nr, const T *B, int64_t ldb, int nc, int K, char *lds)
-{
-    for_tile<T, NB>([&](int bi, int bj, int r, int i, int j) {
-        acc[bi][bj][r] = C[(int64_t)min(i, nr - 1) * ldc + min(j, nc - 1)];
-    });
-    tile_minus<T, NB, KEDGE>(acc, A, lda, nr, B, ldb, nc, K, lds);
-}
-
-template <typename T, int NB>
-__device__ __forceinline__ void tile_store(const typename vec4<T>::type (&acc)[2][NB], T *C, int64_t ldc, int nr, int nc)
-{
-    for_tile<T, NB>([&](int bi, int bj, int r, int i, int j) {
-        if (i < nr && j < nc)
-            C[(int64_t)i * ldc + j] = acc[bi][bj][r];
-    });
-}
-
-/* The tile to LDS (pitch LDT): the nr x nc elements that exist, the rest zero
- * or the identity. */
-template <typename T, int NB>
-__device__ __forceinline__ void tile_to_lds(const typename vec4<T>::type (&acc)[2][NB], T *S, int nr, int nc,
-                                            bool identity)
-{
-    for_tile<T, NB>([&](int bi, int bj, int r, int i, int j) {
-        S[i * LDT + j] = (i < nr && j < nc) ? acc[bi][bj][r] : (identity && i == j ? T(1) : T(0));
-    });
 }
 
 /* Tile index -> position: tiles are dealt to the 8 XCDs in contiguous runs
@@ -1422,10 +1197,10 @@ hipError_t dense_trsv(int mode, const T *LU, int64_t lda, int n, T *B, int64_t l
 /* ---------------------------------------------------- uniform batches --- */
 
 template <typename T>
-__global__ __launch_bounds__(NT, 2) void k_lu_batch(T *__restrict__ A, int64_t lda, int n, int64_t strideA,
+__global__ __launch_bounds__(NT, kCroutPerCu<T>) void k_lu_batch(T *__restrict__ A, int64_t lda, int n, int64_t strideA,
                                                     int32_t *info)
 {
-    __shared__ TileSmem<T> sm;
+    __shared__ CroutSmem<T> sm;
     T *Ab = A + (int64_t)blockIdx.x * strideA;
     const int z = wg_crout<T>(Ab, lda, n, nullptr, 0, 0, sm);
     if (threadIdx.x == 0 && info)
@@ -1518,11 +1293,12 @@ hipError_t batch_solve(bool adjoint, const T *LU, int64_t lda, int n, int64_t st
  * factors and solves it alone.  Every workgroup leaves the loop once the
  * queue is exhausted. */
 template <typename T>
-__global__ __launch_bounds__(NT, 2) void k_batched(int count, const int *__restrict__ ns, const int64_t *__restrict__ offA,
+__global__ __launch_bounds__(NT, kCroutPerCu<T>) void k_batched(int count, const int *__restrict__ ns, const int64_t *__restrict__ offA,
                                                    T *__restrict__ A, const int64_t *__restrict__ offB, T *__restrict__ B,
                                                    const int *__restrict__ order, int32_t *info, int *queue)
 {
-    __shared__ TileSmem<T> sm;
+    __shared__ union { CroutSmem<T> c; TileSmem<T> s; } smu;
+    CroutSmem<T> &sm = smu.c;
     for (;;) {
         if (threadIdx.x == 0)
             sm.ticket = atomicAdd(queue, 1);
@@ -1557,15 +1333,18 @@ __global__ __launch_bounds__(NT, 2) void k_batched(int count, const int *__restr
                 for (int i = threadIdx.x; i < n; i += NT)
                     Bs[i] = sm.t1[i];
             } else {
-                wg_solve<T, TRI_U, 1>(As, n, n, Bs, 1, 1, sm);
+                wg_solve<T, TRI_U, 1>(As, n, n, Bs, 1, 1, smu.s);
             }
         }
     }
 }
 
-/* Largest system whose refinement keeps its vectors in LDS (the float
- * vector in a tile buffer of TileSmem<float>, x in double beside it). */
+/* Largest system whose refinement keeps its float vector in LDS (t1). */
 constexpr int kMixLdsN = TB * LDT;
+/* ... and x in double beside it, in what the products' buffers leave of LDS
+ * past the diagonal blocks' place (a third workgroup per compute unit against
+ * reading x through L2 for larger systems). */
+constexpr int kMixXdN = (CroutSmem<float>::GEMM - sizeof(float) * TB * LDT) / sizeof(double); /* 1312 */
 
 /* Workgroup-wide maximum (result valid in every thread). */
 __device__ double wg_max(double v, double *red)
@@ -1588,15 +1367,15 @@ __device__ double wg_max(double v, double *red)
  * the system's dominance margin m = min_i (|a_ii| - sum_{j != i} |a_ij|) > 0,
  * ||x - x*||_inf <= ||r||_inf / m, and the loop ends once
  * ||r||_inf <= tol m ||x||_inf (never for m = 0: iters reports -1). */
-__global__ __launch_bounds__(NT, 2) void k_batched_mixed(int count, const int *__restrict__ ns, const int64_t *__restrict__ offA,
+__global__ __launch_bounds__(NT, kCroutPerCu<float>) void k_batched_mixed(int count, const int *__restrict__ ns, const int64_t *__restrict__ offA,
                                                          const double *__restrict__ A, const int64_t *__restrict__ offB,
                                                          double *__restrict__ B, const int *__restrict__ order,
                                                          int32_t *info, int *queue, float *__restrict__ W,
                                                          float *__restrict__ R32, double *__restrict__ X,
                                                          int max_iter, double tol, int32_t *iters)
 {
-    __shared__ TileSmem<float> sm;
-    __shared__ double xd[kMixLdsN]; /* x in double while the vectors fit LDS */
+    __shared__ union { CroutSmem<float> c; TileSmem<float> s; } smu;
+    CroutSmem<float> &sm = smu.c;
     __shared__ double red[4];
     const int t = threadIdx.x, w = wave_id(), l = t & 63;
     for (;;) {
@@ -1624,6 +1403,9 @@ __global__ __launch_bounds__(NT, 2) void k_batched_mixed(int count, const int *_
         float *Ws = W + offA[s];
         float *rs = R32 + offB[s];
         double *xs = X + offB[s];
+        /* x in double: in LDS, past the diagonal blocks' place in t0, while it
+         * fits there, else in memory */
+        double *xd = n <= kMixXdN ? reinterpret_cast<double *>(sm.gemm + sizeof(sm.t0)) : xs;
         /* float copy and dominance margin: wave w takes rows 4w .. 4w+3,
          * 4w+16 .., four rows at a time, its lanes the columns (all of a
          * group's loads issued before its sums) */
@@ -1748,8 +1530,8 @@ __global__ __launch_bounds__(NT, 2) void k_batched_mixed(int count, const int *_
         } else {
             for (int it = 0; it <= max_iter; ++it) {
                 if (it > 0)
-                    wg_solve<float, TRI_L, 1>(Ws, n, n, rs, 1, 1, sm);
-                wg_solve<float, TRI_U, 1>(Ws, n, n, rs, 1, 1, sm);
+                    wg_solve<float, TRI_L, 1>(Ws, n, n, rs, 1, 1, smu.s);
+                wg_solve<float, TRI_U, 1>(Ws, n, n, rs, 1, 1, smu.s);
                 double xmax = 0.0;
                 for (int i = t; i < n; i += NT) {
                     const double x = (it == 0) ? (double)rs[i] : xs[i] + (double)rs[i];
