@@ -311,8 +311,8 @@ int ebv_pipeline_factor_solve(ebv_handle h, ebv_dtype dtype, int64_t count, int6
  *          tiles (64 * 64 doubles each), one more per 64-row block for the
  *          inverses of the diagonal tiles' factors (the solve forms them all
  *          in parallel and applies each as one matrix-core product), then
- *          the factor's control words (rounded to 256 bytes).  The factor is right-looking, one launch per 64-wide
- *          block step: the diagonal tile (published 16 columns at a time
+ *          the control words (rounded to 256 bytes).  The factor is
+ *          right-looking, one launch per 64-wide block step: the diagonal tile (published 16 columns at a time
  *          while it is factored), the envelope tiles of its block column
  *          and row (each step of their block substitution waits, bounded,
  *          for the strip it needs), and every
@@ -321,7 +321,10 @@ int ebv_pipeline_factor_solve(ebv_handle h, ebv_dtype dtype, int64_t count, int6
  *   info   device int32 or NULL: zero pivot (1-based) or 0; for the factor
  *          -status when a bounded wait gave up (results then invalid).
  * ebv_lu_solve_skyline: forward then backward substitution (Eq. 1) on the
- * factors, B (n x nrhs, ldb >= nrhs) -> X.
+ * factors, B (n x nrhs, ldb >= nrhs) -> X.  One launch per direction and 16
+ * right-hand sides, the blocks chained through the workspace; their bounded
+ * waits take 2^24 spins or the handle's limit, whichever is more, and one that
+ * gives up leaves not-a-numbers in X.
  */
 size_t ebv_skyline_workspace_size(int64_t n, const int32_t *f_host, const int32_t *g_host);
 int ebv_lu_factor_skyline(ebv_handle h, int64_t n, const int32_t *f_host, const int32_t *g_host, const int32_t *f,

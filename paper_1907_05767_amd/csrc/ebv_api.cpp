@@ -932,10 +932,13 @@ int ebv_lu_solve_skyline(ebv_handle h, int64_t n, int64_t nrhs, const int32_t *f
     if (!ws_ok(ws, ws_bytes, skyline_ws_bytes(pl.nt, nt)))
         return EBV_ERR_WORKSPACE;
     double *tiles = (double *)ws;
+    int *ctl = (int *)((char *)ws + skyline_tiles_bytes(pl.nt, nt));
+    /* no info argument to report a give-up in: a lowered limit does not apply */
+    const long wlim = std::max<long>((long)h->dense.wait_limit, 1L << 24);
     hipError_t e = ebv::skyline_pack(pl, f, rp, const_cast<double *>(AL), g, cp, const_cast<double *>(AU), tiles,
                                      false, stream);
     if (e == hipSuccess)
-        e = ebv::skyline_solve(pl, tiles, tiles + nt * 64 * 64, B, ldb, (int)nrhs, stream);
+        e = ebv::skyline_solve(pl, tiles, tiles + nt * 64 * 64, ctl, B, ldb, (int)nrhs, wlim, stream);
     return hip_status(e);
 }
 

@@ -2944,51 +2944,35 @@ hipError_t skyline_factor(const SkyPlan &pl, double *tiles, double *P, int *ctl,
     return e;
 }
 
-/* Operator tiles of the skyline factors for solve_block (zero outside the
- * envelope). */
-template <int MODE> struct SkyOp {
-    const SkyPlan *pl;
-    const double *tiles;
-    __device__ __forceinline__ void operator()(double *S, int bi, int bj) const
-    {
-        const double *T = sky_tile(*pl, const_cast<double *>(tiles), bi, bj);
-        const int nr = min(TB, pl->n - bi * TB), nc = min(TB, pl->n - bj * TB);
-        tile_xfer<double>([&](int r, int c) { return (T && r < nr && c < nc) ? T[r * TB + c] : 0.0; },
-                          [&](int r, int c, double v) { S[r * LDT + c] = v; });
-    }
-    /* the tile's row rr, columns 16q.., read unconditionally (clamped into
-     * the tile) and masked after; a tile outside the envelope reads as zero */
-    __device__ __forceinline__ void seg(int bi, int bj, int rr, int q, double (&m)[16]) const
-    {
-        const double *T = sky_tile(*pl, const_cast<double *>(tiles), bi, bj);
-        const int nr = min(TB, pl->n - bi * TB), nc = min(TB, pl->n - bj * TB);
-        if (!T) {
-#pragma unroll
-            for (int cc = 0; cc < 16; ++cc)
-                m[cc] = 0.0;
-            return;
-        }
-        const double *row = T + min(rr, nr - 1) * TB;
-#pragma unroll
-        for (int cc = 0; cc < 16; ++cc) {
-            const int c = 16 * q + cc;
-            const double v = row[min(c, nc - 1)];
-            m[cc] = (rr < nr && c < nc) ? v : 0.0;
-        }
-    }
-};
-
 /* Inverse packs of the skyline factor's diagonal tiles, one workgroup per
  * tile (all independent): P + b * 4096 (pitch 64) receives L_bb^{-1} in its
  * strict lower part (unit diagonal implied) and U_bb^{-1} in its upper part;
- * a partial last tile is padded with the identity. */
-__global__ __launch_bounds__(NT) void k_sky_packs(SkyPlan pl, const double *__restrict__ tiles,
-                                                  double *__restrict__ P)
+ * a partial last tile is padded with the identity.  The diagonal tile is not
+ * needed any more then (a solve packs its own copy of the factors): its
+ * storage becomes the block's exchange rows of k_sky_trsv, marked unsolved
+ * here for the first chunk of right-hand sides, and the control words are
+ * cleared. */
+__device__ __forceinline__ void sky_mark(double *T)
+{
+    unsigned long long *x = reinterpret_cast<unsigned long long *>(T);
+    for (int i = threadIdx.x; i < TB * TB; i += NT)
+        x[i] = kUnsolvedMark64;
+}
+__device__ __forceinline__ void sky_clear(int *ctl, bool all)
+{
+    if (blockIdx.x == 0 && threadIdx.x < kSkyCtl && (all || threadIdx.x > 0))
+        ctl[threadIdx.x] = 0;
+}
+__global__ __launch_bounds__(NT) void k_sky_packs(SkyPlan pl, double *__restrict__ tiles, double *__restrict__ P,
+                                                  int *ctl)
 {
     __shared__ TileSmem<double> sm;
     const int b = blockIdx.x, kb = min(TB, pl.n - b * TB);
-    stage_tile_identity(sm.t0, sky_tile(pl, const_cast<double *>(tiles), b, b), TB, kb, kb);
+    double *D = sky_tile(pl, tiles, b, b);
+    stage_tile_identity(sm.t0, D, TB, kb, kb);
     __syncthreads();
+    sky_mark(D);
+    sky_clear(ctl, true);
     if (threadIdx.x < TB)
         sm.rinv[threadIdx.x] = recip(sm.t0[threadIdx.x * LDT + threadIdx.x]);
     __syncthreads();
@@ -2997,146 +2981,266 @@ __global__ __launch_bounds__(NT) void k_sky_packs(SkyPlan pl, const double *__re
     tile_xfer<double>([&](int r, int c) { return sm.t1[r * LDT + c]; },
                       [&](int r, int c, double v) { Pb[r * TB + c] = v; });
 }
-
-/* The operand values one lane contributes to a pack product (below): row
- * 16w + lr of the pack of block blk, inner indices 16q + 4lk + ks, loaded
- * raw (the triangle is selected at use). */
-__device__ __forceinline__ void sky_pack_load(const double *__restrict__ Pb, double (&pv)[16])
+/* The same marks and words for a further chunk. */
+__global__ __launch_bounds__(NT) void k_sky_marks(SkyPlan pl, double *__restrict__ tiles, int *ctl)
 {
-    const int w = wave_id(), l = threadIdx.x & 63, lr = l & 15, lk = l >> 4, row = 16 * w + lr;
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
-#pragma unroll
-        for (int ks = 0; ks < 4; ++ks)
-            pv[4 * q + ks] = Pb[row * TB + 16 * q + 4 * lk + ks];
-}
-
-/* Block blk of a substitution with all its updates applied, its right-hand
- * sides staged in LDS (Ys, 64 x 16, pitch 17, zero past n and nrhs_here):
- * times the inverse of the diagonal tile's unit lower (LOWER) or upper
- * factor from its pack (pv, from sky_pack_load), one matrix-core product
- * (wave w the rows 16w..16w+15), the result stored in B. */
-template <bool LOWER>
-__device__ __forceinline__ void sky_pack_product(const double (&pv)[16], const double *Ys, int n, double *B,
-                                                 int64_t ldb, int nrhs_here, int blk)
-{
-    constexpr int YP = 17;
-    const int b0 = blk * TB;
-    const int w = wave_id(), l = threadIdx.x & 63, lr = l & 15, lk = l >> 4, row = 16 * w + lr;
-    d4 x = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
-#pragma unroll
-        for (int ks = 0; ks < 4; ++ks) {
-            const int k = 16 * q + 4 * lk + ks;
-            const double other = (LOWER && row == k) ? 1.0 : 0.0;
-            const bool keep = LOWER ? row > k : row <= k;
-            x = mfma16(keep ? pv[4 * q + ks] : other, Ys[k * YP + lr], x);
-        }
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        const int rb = b0 + 16 * w + acc_row<double>(lk, r);
-        if (rb < n && lr < nrhs_here)
-            B[(int64_t)rb * ldb + lr] = x[r];
-    }
+    sky_mark(sky_tile(pl, tiles, blockIdx.x, blockIdx.x));
+    sky_clear(ctl, false);
 }
 
 /*
- * One step of the skyline substitutions (Eq. 1), FWD: L Y = B (block order
- * 0, 1, ...), else U X = Y (block order nt-1, nt-2, ...).  Block J is solved
- * already; each workgroup takes one envelope tile of block column J -- the
- * lower tiles (R, J), R > J, forward; the upper tiles (I, J), I < J, backward
- * -- and subtracts its product with block J's solution from its block row's
- * right-hand sides (distinct rows per workgroup).  The block solved next
- * (J + 1 forward, J - 1 backward) then has all its updates: the workgroup
- * that updated it (or the extra last workgroup when block J has no tile in
- * that row) solves its diagonal triangle right away, from the updated rows
- * kept in LDS and the pack's operands loaded at the start.  J = -1 (forward)
- * or nt (backward) only solves the first block.
+ * Skyline substitution (Eq. 1) of up to 16 right-hand sides in one launch,
+ * FWD: L Y = B (block order 0, 1, ...), else U X = Y (block order nt-1, ...),
+ * chained like the dense one (k_trsv): workgroups take tickets in solve order,
+ * per block one helper and the block's own; solved blocks and the helpers'
+ * partial sums travel through marked exchange rows.  A block depends on the
+ * envelope tiles of its own row: forward J = F .. blk-1, backward the J > blk
+ * whose columns reach it, oldest first.  All but the last three are shared
+ * with the helper and read through the caches once the solved-blocks counter
+ * has passed them; the last three are polled, and the last two, as D^{-1} M_j
+ * formed while waiting, cost one product in registers each as they arrive:
+ *   y = D^{-1} (b - sum_j M_j y_j) - W_1 y_1 - W_2 y_2.
+ * Operand tiles are read as the matrix cores' left operand, four contiguous
+ * inner indices a lane.  What bounds it is the chain of blocks: 560 us a
+ * direction at n = 16384, 2.2 us a block; one launch per block and direction,
+ * its updates spread over as many workgroups as the block column has tiles,
+ * took 2.9 ms (11.3 us a block).
  */
-template <int NR, bool FWD>
-__global__ __launch_bounds__(NT) void k_sky_sweep(SkyPlan pl, const double *__restrict__ tiles,
-                                                  const double *__restrict__ P, double *B, int64_t ldb,
-                                                  int nrhs_here, int J, int ntarget)
+template <bool FWD>
+__global__ __launch_bounds__(NT) void k_sky_trsv(SkyPlan pl, double *__restrict__ tiles, const double *__restrict__ P,
+                                                 double *__restrict__ B, int64_t ldb, int nrhs_here, int *ctl, long wlim)
 {
-    constexpr int MODE = FWD ? TRI_L : TRI_U;
-    constexpr int YP = 17;
+    constexpr int ROLES = 2; /* the helper, then the block's own */
     __shared__ TileSmem<double> sm;
-    const int nt = pl.nt, n = pl.n, b = blockIdx.x;
-    const int t = threadIdx.x, rr = t >> 2, q = t & 3;
-    const SkyOp<MODE> op{&pl, tiles};
-    const int next = FWD ? J + 1 : J - 1;
-    int target = -1;
-    if (b < ntarget) /* forward: the b-th block row below J reaching column J; backward: rows G_J.. */
-        target = FWD ? sky_nth(pl.F, J + 1, nt, J, b) : pl.G[J] + b;
-    else
-        target = next; /* no tile of block column J in the next block's row */
-    const bool solves = target == next && next >= 0 && next < nt;
-    double pv[16]; /* loaded by every workgroup (block index clamped): no branch around loads */
-    sky_pack_load(P + (int64_t)min(max(next, 0), nt - 1) * TB * TB, pv);
-    double *Ys = sm.t0; /* the next block's right-hand sides for its pack product */
-    if (b < ntarget) {
-        double *Y = sm.t1;
-        const int kJ = min(TB, n - J * TB);
-        for (int idx = t; idx < TB * NR; idx += NT) {
-            const int r = idx / NR, c = idx % NR;
-            const double v = B[(int64_t)(J * TB + min(r, kJ - 1)) * ldb + min(c, nrhs_here - 1)];
-            Y[r * NR + c] = (r < kJ && c < nrhs_here) ? v : 0.0;
-        }
-        double m[16];
-        op.seg(target, J, rr, q, m);
-        const int rows = min(TB, n - target * TB);
-        double bo[NR]; /* row rr's right-hand sides (address clamped) */
-        {
-            const double *brow = B + (int64_t)(target * TB + min(rr, rows - 1)) * ldb;
-#pragma unroll
-            for (int c = 0; c < NR; ++c)
-                bo[c] = brow[min(c, nrhs_here - 1)];
-        }
-        __syncthreads();
-        double acc[NR];
-#pragma unroll
-        for (int c = 0; c < NR; ++c)
-            acc[c] = 0.0;
-#pragma unroll
-        for (int cc = 0; cc < 16; ++cc)
-#pragma unroll
-            for (int c = 0; c < NR; ++c)
-                acc[c] = __builtin_fma(m[cc], Y[(16 * q + cc) * NR + c], acc[c]);
-#pragma unroll
-        for (int c = 0; c < NR; ++c) {
-            acc[c] += __shfl_xor(acc[c], 1);
-            acc[c] += __shfl_xor(acc[c], 2);
-        }
-        if (q == 0) {
-            if (solves) {
-#pragma unroll
-                for (int c = 0; c < 16; ++c)
-                    Ys[rr * YP + c] = (c < NR && rr < rows && c < nrhs_here) ? bo[min(c, NR - 1)] - acc[min(c, NR - 1)]
-                                                                            : 0.0;
-            } else if (rr < rows) {
-#pragma unroll
-                for (int c = 0; c < NR; ++c)
-                    if (c < nrhs_here)
-                        B[(int64_t)(target * TB + rr) * ldb + c] = bo[c] - acc[c];
-            }
-        }
-        __syncthreads();
-    } else if (solves) {
-        /* no update of the next block in this step: its rows as they are */
-        const int b0 = next * TB;
-        if (q == 0) {
-            const double *brow = B + (int64_t)min(b0 + rr, n - 1) * ldb;
-#pragma unroll
-            for (int c = 0; c < 16; ++c) {
-                const double v = brow[min(c, nrhs_here - 1)];
-                Ys[rr * YP + c] = (b0 + rr < n && c < nrhs_here) ? v : 0.0;
-            }
-        }
-        __syncthreads();
+    __shared__ double wls[2][16][NT]; /* -W of the last two blocks, operand order per thread */
+    __shared__ int16_t dl[kSkyMaxBlocks];
+    int *status = ctl, *ctr = ctl + (FWD ? 1 : 3), *solved = ctr + 1;
+    const int n = pl.n, nt = pl.nt;
+    if (threadIdx.x == 0) {
+        sm.ticket = atomicAdd(ctr, 1);
+        sm.avail = 0;
     }
-    if (solves)
-        sky_pack_product<FWD>(pv, Ys, n, B, ldb, nrhs_here, next);
+    __syncthreads();
+    if (sm.ticket >= ROLES * nt) { /* counter not reset: refuse rather than index out of range */
+        if (threadIdx.x == 0)
+            atomicOr(status, 2);
+        return;
+    }
+    const int pos = __builtin_amdgcn_readfirstlane(sm.ticket / ROLES), role = sm.ticket % ROLES;
+    const int blk = FWD ? pos : nt - 1 - pos;
+    const int t = threadIdx.x, w = wave_id(), l = t & 63, lr = l & 15, lk = l >> 4;
+    const int r0 = blk * TB, nr = min(TB, n - r0);
+    /* dependencies, oldest first */
+    int nd = 0;
+    if (FWD) {
+        nd = blk - pl.F[blk];
+        for (int d = t; d < nd; d += NT)
+            dl[d] = (int16_t)(pl.F[blk] + d);
+    } else {
+        for (int base = blk + 1 + (nt - blk - 2) / 64 * 64; base > blk; base -= 64) {
+            const int J = base + l;
+            const bool dep = J < nt && pl.G[min(J, nt - 1)] <= blk;
+            const unsigned long long m = __ballot(dep);
+            if (w == 0 && dep)
+                dl[nd + __popcll(m & ~((2ull << l) - 1))] = (int16_t)J;
+            nd += __popcll(m);
+        }
+    }
+    __syncthreads();
+    auto dep_blk = [&](int d) { return __builtin_amdgcn_readfirstlane((int)dl[d]); };
+    auto dep_pos = [&](int bj) { return FWD ? bj : nt - 1 - bj; };
+    /* exchange rows of block b (64 x 16), then the helper's partial sums */
+    auto rows = [&](int b) { return sky_tile(pl, tiles, b, b) + (FWD ? 0 : 2 * TB * 16); };
+    auto load_a = [&](int bj, double(&a)[16]) {
+        const double *T = sky_tile(pl, tiles, blk, bj) + (16 * w + lr) * TB + 4 * lk;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const d4 v = *reinterpret_cast<const d4 *>(T + 16 * q);
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks)
+                a[4 * q + ks] = v[ks];
+        }
+    };
+    auto row_of = [&](int i) { return 16 * (i >> 2) + 4 * lk + (i & 3); }; /* inner index of operand value i */
+    auto fetch_y = [&](int bj, double(&y)[16]) {
+        const double *X = rows(bj);
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+            y[i] = load_coherent(X + row_of(i) * 16 + lr);
+    };
+    auto fetch_y_cached = [&](int bj, double(&y)[16]) {
+        const double *X = rows(bj);
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+            y[i] = X[row_of(i) * 16 + lr];
+    };
+    auto has_mark = [&](const double(&y)[16]) {
+        bool miss = false;
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+            miss = miss || is_unsolved_mark(y[i]);
+        return miss;
+    };
+    auto load_y = [&](int bj, double(&y)[16]) {
+        for (long spins = 0;; ++spins) {
+            fetch_y(bj, y);
+            if (!__any(has_mark(y)))
+                break;
+            if (wait_give_up(status, spins, wlim))
+                break;
+            __builtin_amdgcn_s_sleep(1);
+        }
+    };
+    const int K = nd - 2;  /* dependencies before the last two */
+    const int KP = K - 1;  /* ... of which those taken in passes; the next one is polled */
+    d4 acc = {0, 0, 0, 0}, acc2 = {0, 0, 0, 0};
+    auto pass = [&](int d, const double(&cur)[16], double(&nxt)[16], d4 &ac) __attribute__((always_inline)) {
+        const int bd = dep_blk(d);
+        wait_solved(solved, dep_pos(bd), &sm.avail, status, wlim);
+        double y[16];
+        fetch_y_cached(bd, y);
+        __builtin_amdgcn_sched_barrier(0);
+        load_a(dep_blk(min(d + ROLES, KP - 1)), nxt);
+        __builtin_amdgcn_sched_barrier(0);
+        if (__any(has_mark(y)))
+            load_y(bd, y);
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+            ac = mfma16(cur[i], y[i], ac);
+    };
+    auto passes = [&]() __attribute__((always_inline)) {
+        if (role < KP) {
+            double a0[16], a1[16];
+            load_a(dep_blk(role), a0);
+            for (int d = role; d < KP; d += 2 * ROLES) {
+                pass(d, a0, a1, acc);
+                if (d + ROLES < KP)
+                    pass(d + ROLES, a1, a0, acc2);
+            }
+        }
+    };
+    double *PB = rows(blk) + TB * 16 + 4 * t; /* the helper's sums, accumulator layout */
+    if (role == 0) {
+        if (KP <= 0)
+            return; /* nothing to share: the block's own does not wait for it */
+        passes();
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+            store_coherent(PB + r, acc[r] + acc2[r]);
+        return;
+    }
+    d4 rhs;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int row = 16 * w + acc_row<double>(lk, r);
+        rhs[r] = (row < nr && lr < nrhs_here) ? B[(int64_t)(r0 + row) * ldb + lr] : 0.0;
+    }
+    /* the diagonal tile's inverse, operand order */
+    double dA[16];
+    {
+        const double *Pb = P + (int64_t)blk * TB * TB + (16 * w + lr) * TB;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            const int r = 16 * w + lr, k = row_of(i);
+            const double v = Pb[k];
+            dA[i] = FWD ? (r > k ? v : (r == k ? 1.0 : 0.0)) : (r <= k ? v : 0.0);
+        }
+    }
+    auto form_w = [&](int bj, int slot) {
+        const double *T = sky_tile(pl, tiles, blk, bj);
+        tile_xfer<double>([&](int r, int c) { return T[r * TB + c]; },
+                          [&](int r, int c, double v) { sm.t0[r * LDT + c] = v; });
+        __syncthreads();
+        d4 wacc[4];
+#pragma unroll
+        for (int cb = 0; cb < 4; ++cb) {
+            wacc[cb] = d4{0, 0, 0, 0};
+#pragma unroll
+            for (int i = 0; i < 16; ++i)
+                wacc[cb] = mfma16(dA[i], sm.t0[row_of(i) * LDT + 16 * cb + lr], wacc[cb]);
+        }
+        __syncthreads();
+#pragma unroll
+        for (int cb = 0; cb < 4; ++cb)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                sm.t0[(16 * w + acc_row<double>(lk, r)) * LDT + 16 * cb + lr] = wacc[cb][r];
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+            wls[slot][i][t] = -sm.t0[(16 * w + lr) * LDT + row_of(i)];
+        __syncthreads();
+    };
+    if (nd >= 1)
+        form_w(dep_blk(nd - 1), 0);
+    if (nd >= 2)
+        form_w(dep_blk(nd - 2), 1);
+    if (K > 0) {
+        double al[16], y[16];
+        load_a(dep_blk(K - 1), al);
+        passes();
+        load_y(dep_blk(K - 1), y);
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+            acc = mfma16(al[i], y[i], acc);
+        if (KP > 0) { /* the helper's sums, re-read until none is the mark */
+            double pv[4];
+            for (long spins = 0;; ++spins) {
+                bool miss = false;
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    pv[r] = load_coherent(PB + r);
+                    miss = miss || is_unsolved_mark(pv[r]);
+                }
+                if (!__any(miss))
+                    break;
+                if (wait_give_up(status, spins, wlim))
+                    break;
+                __builtin_amdgcn_s_sleep(1);
+            }
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                acc[r] += pv[r];
+        }
+    }
+    /* z = D^{-1} (b - acc) through LDS, then the last two blocks, polled, into
+     * their own accumulator so that neither waits for z */
+    double *Rl = sm.t0; /* 64 x 16, pitch 17 */
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+        Rl[(16 * w + acc_row<double>(lk, r)) * 17 + lr] = rhs[r] - (acc[r] + acc2[r]);
+    __syncthreads();
+    d4 x = {0, 0, 0, 0}, xw = {0, 0, 0, 0};
+#pragma unroll
+    for (int i = 0; i < 16; ++i)
+        x = mfma16(dA[i], Rl[row_of(i) * 17 + lr], x);
+#pragma unroll
+    for (int slot = 1; slot >= 0; --slot)
+        if (nd >= slot + 1) {
+            double wa[16], y[16];
+#pragma unroll
+            for (int i = 0; i < 16; ++i)
+                wa[i] = wls[slot][i][t];
+            load_y(dep_blk(nd - 1 - slot), y);
+#pragma unroll
+            for (int i = 0; i < 16; ++i)
+                xw = mfma16(wa[i], y[i], xw);
+        }
+    /* all 64 rows and 16 columns of the exchange block are written (zeros
+     * outside the system), the solution rows also to B */
+    double *X = rows(blk);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int row = 16 * w + acc_row<double>(lk, r);
+        const bool ok = row < nr && lr < nrhs_here;
+        const double v = x[r] + xw[r];
+        store_coherent(X + row * 16 + lr, ok ? v : 0.0);
+        if (ok)
+            B[(int64_t)(r0 + row) * ldb + lr] = v;
+    }
+    __syncthreads();
+    if (t == 0)
+        __hip_atomic_fetch_max(solved, pos + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 hipError_t skyline_pack(const SkyPlan &pl, const int32_t *f, const int64_t *rp, double *AL, const int32_t *g,
@@ -3146,51 +3250,18 @@ hipError_t skyline_pack(const SkyPlan &pl, const int32_t *f, const int64_t *rp, 
     return hipGetLastError();
 }
 
-template <int NR>
-static hipError_t sky_sweeps(const SkyPlan &pl, const double *tiles, const double *P, double *B, int64_t ldb, int nh,
-                             hipStream_t st)
+hipError_t skyline_solve(const SkyPlan &pl, double *tiles, double *P, int *ctl, double *B, int64_t ldb, int nrhs,
+                         long wlim, hipStream_t st)
 {
-    const int nt = pl.nt;
-    /* forward: the launch for J = -1 solves block 0; the launch for J
-     * updates the blocks below J from Y_J and solves block J + 1 */
-    for (int J = -1; J + 1 < nt; ++J) {
-        int cnt = 0;
-        bool has_next = false;
-        for (int R = J + 1; J >= 0 && R < nt; ++R)
-            if (pl.F[R] <= J) {
-                ++cnt;
-                has_next |= R == J + 1;
-            }
-        hipLaunchKernelGGL((k_sky_sweep<NR, true>), dim3(cnt + (has_next ? 0 : 1)), dim3(NT), 0, st, pl, tiles, P,
-                           B, ldb, nh, J, cnt);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess)
-            return e;
-    }
-    /* backward: the launch for J = nt solves block nt - 1; the launch for J
-     * updates the blocks above J from X_J and solves block J - 1 */
-    for (int J = nt; J > 0; --J) {
-        const int cnt = J < nt ? J - pl.G[J] : 0;
-        const bool has_next = J < nt && pl.G[J] <= J - 1;
-        hipLaunchKernelGGL((k_sky_sweep<NR, false>), dim3(cnt + (has_next ? 0 : 1)), dim3(NT), 0, st, pl, tiles, P,
-                           B, ldb, nh, J, cnt);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess)
-            return e;
-    }
-    return hipSuccess;
-}
-
-hipError_t skyline_solve(const SkyPlan &pl, const double *tiles, double *P, double *B, int64_t ldb, int nrhs,
-                         hipStream_t st)
-{
-    hipLaunchKernelGGL(k_sky_packs, dim3(pl.nt), dim3(NT), 0, st, pl, tiles, P);
+    hipLaunchKernelGGL(k_sky_packs, dim3(pl.nt), dim3(NT), 0, st, pl, tiles, P, ctl);
     hipError_t e = hipGetLastError();
-    for (int c0 = 0; c0 < nrhs && e == hipSuccess; c0 += 8) {
-        const int nh = min(8, nrhs - c0);
-        e = nh == 1 ? sky_sweeps<1>(pl, tiles, P, B + c0, ldb, nh, st)
-            : nh <= 4 ? sky_sweeps<4>(pl, tiles, P, B + c0, ldb, nh, st)
-                      : sky_sweeps<8>(pl, tiles, P, B + c0, ldb, nh, st);
+    for (int c0 = 0; c0 < nrhs && e == hipSuccess; c0 += 16) {
+        const int nh = min(16, nrhs - c0);
+        if (c0 > 0)
+            hipLaunchKernelGGL(k_sky_marks, dim3(pl.nt), dim3(NT), 0, st, pl, tiles, ctl);
+        hipLaunchKernelGGL(k_sky_trsv<true>, dim3(2 * pl.nt), dim3(NT), 0, st, pl, tiles, P, B + c0, ldb, nh, ctl, wlim);
+        hipLaunchKernelGGL(k_sky_trsv<false>, dim3(2 * pl.nt), dim3(NT), 0, st, pl, tiles, P, B + c0, ldb, nh, ctl, wlim);
+        e = hipGetLastError();
     }
     return e;
 }
