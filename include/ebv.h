@@ -311,13 +311,11 @@ int ebv_pipeline_factor_solve(ebv_handle h, ebv_dtype dtype, int64_t count, int6
  *          tiles (64 * 64 doubles each), one more per 64-row block for the
  *          inverses of the diagonal tiles' factors (the solve forms them all
  *          in parallel and applies each as one matrix-core product), then
- *          the control words (rounded to 256 bytes).  The factor is
- *          right-looking, one launch per 64-wide block step: the diagonal tile (published 16 columns at a time
- *          while it is factored), the envelope tiles of its block column
- *          and row (each step of their block substitution waits, bounded,
- *          for the strip it needs), and every
- *          trailing envelope tile that receives the previous step's rank-64
- *          term, one workgroup each.
+ *          the control words (rounded to 256 bytes).  The factor is one
+ *          launch, one workgroup per envelope tile, each of which receives
+ *          its products as the tiles they need are finished (bounded waits)
+ *          and is then factored (the diagonal tiles, published 16 columns at
+ *          a time) or solved against its diagonal tile.
  *   info   device int32 or NULL: zero pivot (1-based) or 0; for the factor
  *          -status when a bounded wait gave up (results then invalid).
  * ebv_lu_solve_skyline: forward then backward substitution (Eq. 1) on the

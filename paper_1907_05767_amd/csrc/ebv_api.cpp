@@ -806,24 +806,26 @@ static int skyline_plan(int64_t n, const int32_t *f, const int32_t *g, ebv::SkyP
         return -1;
     pl.n = (int)n;
     pl.nt = (int)((n + 63) / 64);
-    for (int b = 0; b < pl.nt; ++b) {
-        pl.F[b] = (int16_t)b;
-        pl.G[b] = (int16_t)b;
-    }
+    int F[ebv::kSkyMaxBlocks], G[ebv::kSkyMaxBlocks];
+    for (int b = 0; b < pl.nt; ++b)
+        F[b] = G[b] = b;
     for (int64_t i = 0; i < n; ++i) {
         if (f[i] < 0 || f[i] > i || g[i] < 0 || g[i] > i)
             return -1;
         const int b = (int)(i / 64);
-        pl.F[b] = (int16_t)std::min<int>(pl.F[b], f[i] / 64);
-        pl.G[b] = (int16_t)std::min<int>(pl.G[b], g[i] / 64);
+        F[b] = std::min<int>(F[b], f[i] / 64);
+        G[b] = std::min<int>(G[b], g[i] / 64);
     }
-    pl.LTo[0] = 0;
-    pl.UTo[0] = 0;
-    for (int b = 0; b < pl.nt; ++b) {
-        pl.LTo[b + 1] = pl.LTo[b] + (b - pl.F[b] + 1);
-        pl.UTo[b + 1] = pl.UTo[b] + (b - pl.G[b]);
+    uint32_t lto = 0, uto = 0;
+    for (int b = 0; b <= pl.nt; ++b) {
+        pl.to[b] = lto | uto << 16;
+        if (b == pl.nt)
+            break;
+        pl.fg[b] = (uint32_t)F[b] | (uint32_t)G[b] << 16;
+        lto += (uint32_t)(b - F[b] + 1);
+        uto += (uint32_t)(b - G[b]);
     }
-    ntiles = (int64_t)pl.LTo[pl.nt] + pl.UTo[pl.nt];
+    ntiles = (int64_t)lto + uto;
     return 0;
 }
 
@@ -836,9 +838,8 @@ static int64_t skyline_lower_entries(int64_t n, const int32_t *f)
     return e;
 }
 
-/* The envelope tiles, one inverse pack per diagonal tile (the factor uses
- * the first for the current step, the solve all of them), then the factor's
- * control words (status, a ticket and a flag per block step). */
+/* The envelope tiles, one inverse pack per diagonal tile (of the factor its
+ * diagonal blocks only, and the block's flags), then the control words. */
 static size_t skyline_tiles_bytes(int nb, int64_t ntiles)
 {
     return align_up((size_t)(ntiles + nb) * 64 * 64 * sizeof(double));

@@ -747,99 +747,6 @@ __device__ __forceinline__ void stage_tile_identity(T *S, const T *__restrict__ 
                  [&](int r, int c, T v) { S[r * LDT + c] = v; });
 }
 
-/* Operands of one 16-deep chunk of a streamed product, in the matrix cores'
- * operand layout. */
-template <typename T> struct StreamRegs {
-    T a[2][4], b[2][4];
-};
-
-/*
- * acc -= sum_t A_t B_t over a list of npairs pairs of 64 x 64 tiles (pitch
- * 64, the inner index fully inside the matrix).  Each wave loads its operands
- * straight from memory into registers in the matrix-core operand layout, a
- * chunk of 16 inner indices at a time, and keeps two chunks in flight while it
- * multiplies the third: no LDS, no barrier.  Within a chunk lane group g =
- * lane / 16 supplies inner indices 4g .. 4g+3 (one per product), so a lane's
- * four A elements are contiguous in memory.  pair(t, A, B) sets the addresses
- * of the t-th pair (uniform in the workgroup); rows of A past nr and columns
- * of B past nc read as zero.
- *
- * Every prefetch is issued, its chunk index clamped to the last chunk (the
- * last two re-read it from cache): with a prefetch behind a branch the
- * compiler's wait counts at the merge must cover the path that skipped it,
- * so the product before it waited for the chunk just requested as well.
- */
-template <typename T, typename PairFn>
-__device__ __forceinline__ void acc64_stream_pairs(Acc64<T> &acc, int npairs, PairFn &&pair, int nr, int nc)
-{
-    const int nch = 4 * npairs;
-    if (nch == 0)
-        return;
-    const int w = wave_id(), l = threadIdx.x & 63, lr = l & 15, g = l >> 4;
-    const int wm = (w >> 1) * 32, wn = (w & 1) * 32;
-    int aoff[2], boff[2];
-    bool aok[2], bok[2];
-#pragma unroll
-    for (int bi = 0; bi < 2; ++bi) {
-        const int r = wm + 16 * bi + lr;
-        aok[bi] = r < nr;
-        aoff[bi] = min(r, nr - 1) * TB + 4 * g;
-    }
-#pragma unroll
-    for (int bj = 0; bj < 2; ++bj) {
-        const int c = wn + 16 * bj + lr;
-        bok[bj] = c < nc;
-        boff[bj] = 4 * g * TB + min(c, nc - 1);
-    }
-    auto load = [&](StreamRegs<T> &R, int ci) {
-        ci = min(ci, nch - 1); 
-        const T *A;
-        const T *B;
-        pair(ci >> 2, A, B);
-        const int k0 = 16 * (ci & 3);
-#pragma unroll
-        for (int bi = 0; bi < 2; ++bi)
-#pragma unroll
-            for (int s = 0; s < 4; ++s)
-                R.a[bi][s] = A[aoff[bi] + k0 + s];
-#pragma unroll
-        for (int bj = 0; bj < 2; ++bj)
-#pragma unroll
-            for (int s = 0; s < 4; ++s)
-                R.b[bj][s] = B[boff[bj] + (k0 + s) * TB];
-        asm volatile("" ::: "memory");
-        __builtin_amdgcn_sched_barrier(0);
-    };
-    auto mul = [&](const StreamRegs<T> &R) {
-#pragma unroll
-        for (int s = 0; s < 4; ++s)
-#pragma unroll
-            for (int bi = 0; bi < 2; ++bi)
-#pragma unroll
-                for (int bj = 0; bj < 2; ++bj)
-                    acc.v[bi][bj] = mfma16(aok[bi] ? -R.a[bi][s] : T(0), bok[bj] ? R.b[bj][s] : T(0),
-                                           acc.v[bi][bj]);
-    };
-    StreamRegs<T> r0, r1, r2;
-    load(r0, 0);
-    load(r1, 1); /* nch >= 4 */
-    /* whole triples in a straight-line body (an exit between its products
-     * would merge load states again), the last one or two chunks after */
-    int c = 0;
-    for (; c + 3 <= nch; c += 3) {
-        load(r2, c + 2);
-        mul(r0);
-        load(r0, c + 3);
-        mul(r1);
-        load(r1, c + 4);
-        mul(r2);
-    }
-    if (c < nch)
-        mul(r0);
-    if (c + 1 < nch)
-        mul(r1);
-}
-
 /*
  * Product of a BM x K and a K x BN block of a matrix in memory (K a multiple
  * of 16) into the accumulators of four waves, each a 16 MB x 16 NB part of the

@@ -78,23 +78,29 @@ template <typename T>
 hipError_t lu_inverse(const T *LU, int64_t lda, int n, T *X, int64_t ldx, T *P, hipStream_t st);
 
 /* Block envelope of a skyline (profile) system, at 64 x 64 tile granularity:
- * block row I holds its lower tiles J = F[I] .. I (the diagonal tile last),
- * block column J its upper tiles I = G[J] .. J-1, packed 64 x 64 (pitch 64)
- * at tile indices LTo[I] + (J - F[I]) and LTo[nt] + UTo[J] + (I - G[J]) of
- * the tile array.  Passed to the kernels by value. */
-constexpr int kSkyMaxBlocks = 256; /* n <= 16384 */
+ * block row I holds its lower tiles J = F(I) .. I (the diagonal tile last),
+ * block column J its upper tiles I = G(J) .. J-1, packed 64 x 64 (pitch 64)
+ * at tile indices LTo(I) + (J - F(I)) and LTo(nt) + UTo(J) + (I - G(J)) of
+ * the tile array.  Passed to the kernels by value, two values to a word: byte
+ * and half-word arrays are read through vector memory, and the compiler has
+ * split the address of a word beside them into a base and an offset that are
+ * not multiples of four, which scalar loads round down one by one. */
+constexpr int kSkyMaxBlocks = 256; /* n <= 16384; tile indices fit 16 bits */
 struct SkyPlan {
     int n, nt;
-    int16_t F[kSkyMaxBlocks], G[kSkyMaxBlocks];
-    int32_t LTo[kSkyMaxBlocks + 1], UTo[kSkyMaxBlocks + 1];
+    uint32_t fg[kSkyMaxBlocks], to[kSkyMaxBlocks + 1];
+    __host__ __device__ int F(int b) const { return (int)(fg[b] & 0xFFFF); }
+    __host__ __device__ int G(int b) const { return (int)(fg[b] >> 16); }
+    __host__ __device__ int LTo(int b) const { return (int)(to[b] & 0xFFFF); }
+    __host__ __device__ int UTo(int b) const { return (int)(to[b] >> 16); }
 };
 /* Pack the skyline arrays into the tiles (unpack = false) or the tiles back
  * into them (only entries inside the envelope are written). */
 hipError_t skyline_pack(const SkyPlan &pl, const int32_t *f, const int64_t *rp, double *AL, const int32_t *g,
                         const int64_t *cp, double *AU, double *tiles, bool unpack, hipStream_t st);
-/* P: 64 x 64 doubles of workspace for the diagonal tile's inverse pack; ctl:
- * kCtlHead + 2 nt ints of control words (cleared here); wlim: spins before a
- * bounded wait gives up (its status then lands in info as -status). */
+/* P: 64 x 64 doubles per block (inverses of the diagonal blocks, flags); ctl:
+ * kCtlHead ints (all cleared here); wlim: spins before a bounded wait gives up
+ * (its status then lands in info as -status). */
 hipError_t skyline_factor(const SkyPlan &pl, double *tiles, double *P, int *ctl, int32_t *info, long wlim,
                           hipStream_t st);
 /* tiles: the packed factors, their diagonal tiles overwritten; P: an inverse

@@ -293,6 +293,44 @@ __device__ __forceinline__ void publish_strip(const T *S, const T *P, int q, T *
     }
 }
 
+/* The publishing waves of a diagonal tile's workgroup: two more than the four
+ * that factor the tile, so that neither the stores nor the wait for them lie
+ * on the chain of its strips (they took 3 of the 11 us of a tile).  Called by
+ * those waves while the others are in tile_lu64, whose barriers they share,
+ * three a strip: strip read, strip final, rest updated.  D's 64 x 64 tile and
+ * the pack Pg as publish_strip leaves them; flag counts 4 per strip. */
+constexpr int kPubWaves = 2, NTP = NT + 64 * kPubWaves;
+template <int PP, typename T>
+__device__ __forceinline__ void publish_strips(const T *S, const T *P, T *Pg, T *D, int64_t ldd, int n, int *flag)
+{
+    constexpr int R = 4 * kPubWaves; /* rows of 16 lanes */
+    const int t = (int)threadIdx.x - NT, r0 = t >> 4, c = t & 15;
+#pragma unroll 1
+    for (int q = 0; q < 4; ++q) {
+        const int b0 = 16 * q;
+        __syncthreads();
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < 16 / R; ++i) {
+            const int r = r0 + R * i;
+            store_coherent(Pg + (b0 + r) * TB + b0 + c, P[(b0 + r) * PP + (PP == LDT ? b0 : 0) + c]);
+            if (b0 + r < n && b0 + c < n)
+                D[(int64_t)(b0 + r) * ldd + b0 + c] = S[(b0 + r) * LDT + b0 + c];
+#pragma unroll 3
+            for (int a = b0 + 16; a < TB; a += 16) {
+                if (a + r < n && b0 + c < n)
+                    store_coherent(D + (int64_t)(a + r) * ldd + b0 + c, S[(a + r) * LDT + b0 + c]);
+                if (b0 + r < n && a + c < n)
+                    store_coherent(D + (int64_t)(b0 + r) * ldd + a + c, S[(b0 + r) * LDT + a + c]);
+            }
+        }
+        __syncthreads();
+        __builtin_amdgcn_s_waitcnt(0);
+        if ((t & 63) == 0)
+            __hip_atomic_fetch_add(flag, 4 / kPubWaves, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+}
+
 /* Counts a published strip, one per wave, once the wave's stores have landed. */
 __device__ __forceinline__ void count_strip(int *flag)
 {
@@ -2665,8 +2703,8 @@ hipError_t lu_inverse(const T *LU, int64_t lda, int n, T *X, int64_t ldx, T *P, 
 __device__ __forceinline__ double *sky_tile(const SkyPlan &pl, double *tiles, int I, int J)
 {
     if (J <= I)
-        return J >= pl.F[I] ? tiles + (int64_t)(pl.LTo[I] + J - pl.F[I]) * TB * TB : nullptr;
-    return I >= pl.G[J] ? tiles + (int64_t)(pl.LTo[pl.nt] + pl.UTo[J] + I - pl.G[J]) * TB * TB : nullptr;
+        return J >= pl.F(I) ? tiles + (int64_t)(pl.LTo(I) + J - pl.F(I)) * TB * TB : nullptr;
+    return I >= pl.G(J) ? tiles + (int64_t)(pl.LTo(pl.nt) + pl.UTo(J) + I - pl.G(J)) * TB * TB : nullptr;
 }
 
 /* Pack (or unpack) the skyline arrays and the envelope tiles: workgroup b < nt
@@ -2681,8 +2719,8 @@ __global__ __launch_bounds__(NT) void k_sky_pack(SkyPlan pl, const int32_t *__re
 {
     const int b = blockIdx.x, n = pl.n, lane = threadIdx.x & 63, r4 = threadIdx.x >> 6;
     const bool lower = b < pl.nt;
-    const int I0 = lower ? b : pl.G[b - pl.nt], I1 = lower ? b : b - pl.nt - 1;
-    const int J0 = lower ? pl.F[b] : b - pl.nt, J1 = lower ? b : b - pl.nt;
+    const int I0 = lower ? b : pl.G(b - pl.nt), I1 = lower ? b : b - pl.nt - 1;
+    const int J0 = lower ? pl.F(b) : b - pl.nt, J1 = lower ? b : b - pl.nt;
     for (int I = I0; I <= I1; ++I)
         for (int J = J0; J <= J1; ++J) {
             double *T = sky_tile(pl, tiles, I, J);
@@ -2707,35 +2745,306 @@ __global__ __launch_bounds__(NT) void k_sky_pack(SkyPlan pl, const int32_t *__re
         }
 }
 
+/* ------------------------------------------------- factor as a dataflow --- */
+
 /*
- * Skyline LU on the envelope tiles, right-looking (Eq. 6-a/6-c restricted to
- * the envelope, which the elimination keeps: if L_IJ and U_JK exist, so does
- * tile (I, K)), one launch per block step J whose workgroups take their roles
- * from a ticket (the first to arrive is the diagonal one, so the waits below
- * always end):
- *   role 0, the diagonal tile: receives step J-1's rank-64 term, is factored
- *     (tile_lu64), and published for the panel tiles strip by strip (the
- *     inverses of its diagonal blocks in P, then a flag);
- *   the panel tiles (I, J) below and (J, I) right of it in the envelope:
- *     each receives step J-1's term, waits for the flag, and is multiplied by
- *     the diagonal tile's inverses;
- *   the other tiles (I, K), I, K > J, for which L_{I,J-1} and U_{J-1,K}
- *     exist: each receives step J-1's term, all in parallel.
- * A tile has thereby received the terms of all the steps before its own when
- * it is factored or solved, and the long inner products of the block Crout
- * order are spread over the launches as rank-64 terms off the chain.  Tiles
- * outside the envelope stay zero and are never touched.  ctl: the status word
- * (bounded waits), then per step a ticket counter and the flag.
+ * Blocked LU with the tiles as the units, one workgroup each, that wait for
+ * the tiles they need instead of for a launch: tile (I, K) keeps its elements
+ * in accumulators while it receives the products L_Ik U_kK (Eq. 6-c), k
+ * ascending, as their operands appear, and then
+ *   - K = I: is factored (tile_lu64, Eq. 6-a) and published a strip at a time;
+ *   - K < I (I < K): is solved against the diagonal tile of block K (I), step p
+ *     as soon as strip p is out.
+ * The chain of the elimination is diagonal tile -> the two tiles below and
+ * right of it -> next diagonal tile.  Those two are published 16 columns (rows)
+ * at a time, as they are solved, and the next diagonal tile subtracts each
+ * rank-16 product when it appears, its operands read straight to registers:
+ * after the last strip one such product is left.
+ *
+ * Workgroups take their tiles from a ticket in the order of steps J: the
+ * diagonal tile, then the tiles (I, J) below, then (J, K) right of it.  A tile
+ * needs only tiles with smaller tickets, which run or have run, so that every
+ * wait ends (they are bounded all the same, into the status word).
+ *
+ * What bounds it is the chain: per block 9 us for the diagonal tile, 1 us each
+ * for a flag to be seen and for a strip to be loaded, on both hops, and the
+ * last products.  Skyline systems, FP64, one launch per block step (the
+ * trailing tiles updated by one product a launch) against this: n = 16384 with
+ * half-widths up to 1024, 5.6 -> 4.07 ms (15.9 us a block); full profile of n =
+ * 4096, 5.0 -> 2.7 ms, of n = 16384, 161 -> 68 ms.
+ *
+ * F describes the matrix: tile(I, J), pitch ld(), rows(I) of block I that
+ * exist, first(I, K) the first k with a product; the flags lflag(I), uflag(K)
+ * count 16 per finished tile of block row I's L part (block column K's U part),
+ * 4 per strip, which finish in order, lcount(I, J), ucount(K, J) being the
+ * tiles before (I, J), (J, K).  dflag(J) counts 4 per published strip of the
+ * diagonal tile, and pack(J) holds the inverses of its diagonal blocks (64 x
+ * 64, pitch 64).  Finished tiles are written through (store_coherent) and read
+ * coherently or after an acquire; a waiting workgroup polls with one thread.
  */
-__device__ __forceinline__ int sky_nth(const int16_t *X, int from, int nt, int lim, int cnt)
+template <typename T> struct FlowSmem {
+    union alignas(16) {
+        StepSmem<T> tile;
+        char gemm[TileGemm<T, 2, 2>::LDS];
+    };
+    int seen[3]; /* flag values seen: L, U, strips */
+    int ticket, zero;
+};
+
+/* Returns (all threads) once *pa >= na and *pb >= nb (pb may be null); off the
+ * chain a workgroup polls less often. */
+__device__ __forceinline__ void flow_wait(const int *pa, int na, int *sa, const int *pb, int nb, int *sb, int *status,
+                                          long limit, bool chain)
 {
-    /* the cnt-th block index x >= from with X[x] <= lim, or -1: 64 entries
-     * per round, one per lane (a scan entry by entry waits for each load),
-     * the hit picked from the wave's ballot; every wave gets the same */
+    if (threadIdx.x == 0 && (*sa < na || (pb && *sb < nb))) {
+        long spins = 0;
+        int va = *sa, vb = pb ? *sb : nb;
+        for (;;) {
+            if (va < na)
+                va = load_coherent(pa);
+            if (vb < nb)
+                vb = load_coherent(pb);
+            if (va >= na && vb >= nb)
+                break;
+            if (chain)
+                __builtin_amdgcn_s_sleep(1);
+            else
+                __builtin_amdgcn_s_sleep(16);
+            if (wait_give_up(status, ++spins, limit)) {
+                va = max(va, na);
+                vb = max(vb, nb);
+                break;
+            }
+        }
+        *sa = va;
+        if (pb)
+            *sb = vb;
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    }
+    __syncthreads();
+}
+
+/* Adds c per wave to a flag, once the wave's stores have landed. */
+__device__ __forceinline__ void flow_count(int *flag, int c)
+{
+    __builtin_amdgcn_s_waitcnt(0);
+    if ((threadIdx.x & 63) == 0)
+        __hip_atomic_fetch_add(flag, c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+/* acc = C - sum of the products of tile (I, K), k < k1. */
+template <typename T, typename F>
+__device__ __forceinline__ void flow_products(typename vec4<T>::type (&acc)[2][2], const F &f, int I, int K, int k1,
+                                              bool chain, FlowSmem<T> &sm)
+{
+    const int nr = f.rows(I), nc = f.rows(K);
+    const T *C = f.tile(I, K);
+    for_tile<T, 2>([&](int bi, int bj, int r, int i, int j) {
+        acc[bi][bj][r] = C[(int64_t)min(i, nr - 1) * f.ld() + min(j, nc - 1)];
+    });
+    for (int k = f.first(I, K); k < k1; ++k) {
+        flow_wait(f.lflag(I), 16 * (f.lcount(I, k) + 1), sm.seen, f.uflag(K), 16 * (f.ucount(K, k) + 1), sm.seen + 1,
+                  f.status(), f.limit, chain);
+        tile_minus<T, 2>(acc, f.tile(I, k), f.ld(), nr, f.tile(k, K), f.ld(), nc, TB, sm.gemm);
+    }
+    __syncthreads(); /* the products' last operand reads */
+}
+
+/* Strip p of the factored diagonal tile D to LDS, by rows of the lower
+ * operator, pitch DBP: rows 16p.. of columns 16p..16p+15 (L), or RIGHT the
+ * columns 16p.. of rows 16p..16p+15 (U^T); its diagonal block from the pack. */
+template <typename T, bool RIGHT>
+__device__ __forceinline__ void flow_strip(T *dst, int p, const T *Pg, const T *D, int64_t ld)
+{
+    const int len = TB - 16 * p;
+    T v[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int idx = threadIdx.x + NT * i;
+        const int r = RIGHT ? 16 * p + idx / len : 16 * p + (idx >> 4);
+        const int c = RIGHT ? 16 * p + idx % len : 16 * p + (idx & 15);
+        v[i] = idx >= len * 16          ? T(0)
+               : (r >> 4) == (c >> 4)   ? load_coherent(Pg + r * TB + c)
+                                        : load_coherent(D + (int64_t)r * ld + c);
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int idx = threadIdx.x + NT * i;
+        if (idx < len * 16)
+            dst[RIGHT ? (16 * p + idx % len) * DBP + idx / len : (16 * p + (idx >> 4)) * DBP + (idx & 15)] = v[i];
+    }
+}
+
+/* Block step p of a wave's 16-wide slab (transposed for an L tile, X = A
+ * U^{-1} solved as U^T X^T = A^T) against a staged strip. */
+template <typename T, bool RIGHT>
+__device__ __forceinline__ void flow_solve(typename vec4<T>::type (&a)[4], const T *strip, int p)
+{
+    typename vec4<T>::type x = {0, 0, 0, 0};
+    wave_mma16_acc<T>(
+        x,
+        [&](int r, int k) {
+            const T u = strip[(16 * p + r) * DBP + k];
+            return r > k ? u : (r == k ? (RIGHT ? u : T(1)) : T(0));
+        },
+        a[p]);
+    a[p] = x;
+#pragma unroll
+    for (int q = p + 1; q < 4; ++q)
+        wave_mma16_acc<T>(a[q], [&](int r, int k) { return -strip[(16 * q + r) * DBP + k]; }, a[p]);
+}
+
+/* Tile (I, J) below (RIGHT) or (J, I) right of the diagonal tile J. */
+template <typename T, bool RIGHT, typename F>
+__device__ __forceinline__ void flow_panel(const F &f, int J, int I, FlowSmem<T> &sm)
+{
+    typedef typename vec4<T>::type V;
+    const int r0 = RIGHT ? I : J, c0 = RIGHT ? J : I, nr = f.rows(r0), nc = f.rows(c0);
+    T *S = sm.tile.S, *G = f.tile(r0, c0);
+    const bool next = I == J + 1;  /* the next diagonal tile waits for it */
+    const bool chain = I <= J + 2; /* or the next but one */
+    V acc[2][2];
+    flow_products<T>(acc, f, r0, c0, J, chain, sm);
+    tile_to_lds<T, 2>(acc, S, nr, nc, false);
+    __syncthreads();
+    int *flag = RIGHT ? f.lflag(I) : f.uflag(I), *seen = sm.seen + (RIGHT ? 0 : 1);
+    const int before = 16 * (RIGHT ? f.lcount(I, J) : f.ucount(I, J)); /* a row's (column's) tiles count in order */
+    const int w = wave_id(), l = threadIdx.x & 63, lr = l & 15, lk = l >> 4;
+    const bool ok = 16 * w + lr < (RIGHT ? nr : nc);
+    V a[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+            a[q][r] = RIGHT ? S[(16 * w + lr) * LDT + 16 * q + acc_row<T>(lk, r)]
+                            : S[(16 * q + acc_row<T>(lk, r)) * LDT + 16 * w + lr];
+    if (next)
+        flow_wait(flag, before, seen, nullptr, 0, nullptr, f.status(), f.limit, chain);
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+        flow_wait(f.dflag(J), 4 * p + 4, sm.seen + 2, nullptr, 0, nullptr, f.status(), f.limit, chain);
+        flow_strip<T, RIGHT>(sm.tile.P, p, f.pack(J), f.tile(J, J), f.ld());
+        if (next && p > 0) /* the strip before; its stores landed with this one's loads */
+            flow_count(flag, 1);
+        __syncthreads();
+        flow_solve<T, RIGHT>(a, sm.tile.P, p);
+        if (next) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int k = 16 * p + acc_row<T>(lk, r), o = 16 * w + lr;
+                if (ok)
+                    store_coherent(G + (RIGHT ? (int64_t)o * f.ld() + k : (int64_t)k * f.ld() + o), a[p][r]);
+            }
+        }
+    }
+    if (next) {
+        flow_count(flag, 1);
+        return;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+            S[RIGHT ? (16 * w + lr) * LDT + 16 * q + acc_row<T>(lk, r)
+                    : (16 * q + acc_row<T>(lk, r)) * LDT + 16 * w + lr] = a[q][r];
+    __syncthreads();
+    tile_xfer<T>([&](int r, int c) { return S[r * LDT + c]; },
+                 [&](int r, int c, T v) {
+                     if (r < nr && c < nc)
+                         store_coherent(G + (int64_t)r * f.ld() + c, v);
+                 });
+    flow_wait(flag, before, seen, nullptr, 0, nullptr, f.status(), f.limit, chain);
+    flow_count(flag, 4);
+}
+
+/* Diagonal tile J. */
+template <typename T, typename F>
+__device__ __forceinline__ void flow_diagonal(const F &f, int J, int32_t *info, FlowSmem<T> &sm)
+{
+    typedef typename vec4<T>::type V;
+    const int nr = f.rows(J), valid = f.valid(J), w = wave_id(), l = threadIdx.x & 63, lr = l & 15, lk = l >> 4;
+    const bool last = J > 0 && f.has_l(J, J - 1) && f.has_u(J - 1, J); /* a product with block J - 1 */
+    T *S = sm.tile.S, *D = f.tile(J, J);
+    constexpr bool chain = true;
+    const bool pub = f.publish(J);
+    if (w >= NT / 64) { /* the publishing waves: past the barriers of the others up to tile_lu64 */
+        if (!pub)
+            return;
+        const int products = max(0, J - 1 - f.first(J, J));
+        for (int b = products * (1 + TB / 16) + 2 + (last ? 3 : 0); b > 0; --b)
+            __syncthreads();
+        publish_strips<DBP>(S, sm.tile.P, f.pack(J), D, f.ld(), valid, f.dflag(J));
+        return;
+    }
+    V acc[2][2];
+    flow_products<T>(acc, f, J, J, J - 1, chain, sm);
+    tile_to_lds<T, 2>(acc, S, valid, valid, true);
+    __syncthreads();
+    if (last) {
+        const T *TL = f.tile(J, J - 1), *TU = f.tile(J - 1, J);
+        const int fl = 16 * f.lcount(J, J - 1), fu = 16 * f.ucount(J, J - 1);
+        V d[4];
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                d[c][r] = S[(16 * w + acc_row<T>(lk, r)) * LDT + 16 * c + lr];
+        /* rows and columns past the matrix end: the last one again, dropped below */
+        const int64_t row = (int64_t)min(16 * w + lr, nr - 1) * f.ld();
+        /* two strips at a time: a wait and the loads cost more than a strip's
+         * products */
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            flow_wait(f.lflag(J), fl + 8 * h + 8, sm.seen, f.uflag(J), fu + 8 * h + 8, sm.seen + 1, f.status(), f.limit,
+                      chain);
+            T a[8], b[4][8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const int k = 32 * h + 16 * (e >> 2) + acc_row<T>(lk, e & 3);
+                a[e] = load_coherent(TL + row + k);
+#pragma unroll
+                for (int c = 0; c < 4; ++c)
+                    b[c][e] = load_coherent(TU + (int64_t)k * f.ld() + min(16 * c + lr, nr - 1));
+            }
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+#pragma unroll
+                for (int c = 0; c < 4; ++c)
+                    d[c] = mfma16(-a[e], b[c][e], d[c]);
+        }
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int i = 16 * w + acc_row<T>(lk, r), j = 16 * c + lr;
+                if (i < valid && j < valid)
+                    S[i * LDT + j] = d[c][r];
+            }
+        __syncthreads();
+    }
+    const int z = tile_lu64<T, true>(S, sm.tile.P, (T *)nullptr, valid, &sm.zero);
+    if (!pub)
+        lds_store_tile(S, D, f.ld(), valid, valid);
+    if (threadIdx.x == 0 && info && z) { /* the smallest over the diagonal tiles */
+        const int at = J * TB + z;
+        int was = 0;
+        while (!__hip_atomic_compare_exchange_strong(info, &was, at, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                     __HIP_MEMORY_SCOPE_AGENT) &&
+               (was == 0 || was > at))
+            ;
+    }
+}
+
+/* The cnt-th of the indices x >= from, x < nt, with X(x) <= lim, or -1. */
+template <typename X> __device__ __forceinline__ int sky_nth(X &&first, int from, int nt, int lim, int cnt)
+{
+    /* 64 entries per round, one per lane (a scan entry by entry waits for each
+     * load), the hit picked from the wave's ballot; every wave gets the same */
     const int lane = threadIdx.x & 63;
     for (int base = from; base < nt; base += 64) {
         const int x = base + lane;
-        const int16_t v = X[min(x, nt - 1)];
+        const int v = first(min(x, nt - 1));
         const unsigned long long m = __ballot(x < nt && v <= lim);
         const int c = __popcll(m);
         if (cnt < c) {
@@ -2749,196 +3058,111 @@ __device__ __forceinline__ int sky_nth(const int16_t *X, int from, int nt, int l
     return -1;
 }
 
-__global__ __launch_bounds__(NT) void k_sky_step(SkyPlan pl, double *__restrict__ tiles, double *__restrict__ P,
-                                                 int J, int nl, int nu, int nlp, int nup, int *ctl, int32_t *info,
-                                                 long wlim)
+/* Skyline LU on the envelope tiles as a dataflow (above), restricted to the
+ * envelope, which the elimination keeps: if L_Ik and U_kK exist, so does tile
+ * (I, K).  Tiles outside stay zero and are never touched.  ctl: the status word
+ * and the ticket.  A block's flags lie in its pack, in parts that the diagonal
+ * blocks leave free, each in a cache line of its own: side by side in the
+ * control words the polls for all of them met in a few lines (18.2 -> 21.7 us a
+ * block). */
+struct SkyOrder {
+    int32_t first[kSkyMaxBlocks + 1]; /* first ticket of each step */
+};
+struct SkyFlow {
+    const SkyPlan &pl;
+    double *tiles, *P;
+    int *ctl;
+    long limit;
+    __device__ __forceinline__ double *tile(int I, int J) const { return sky_tile(pl, tiles, I, J); }
+    __device__ __forceinline__ static constexpr int ld() { return TB; }
+    __device__ __forceinline__ int rows(int) const { return TB; } /* zero-padded */
+    __device__ __forceinline__ int valid(int I) const { return min(TB, pl.n - I * TB); }
+    __device__ __forceinline__ int first(int I, int K) const { return max(pl.F(I), pl.G(K)); }
+    __device__ __forceinline__ bool has_l(int I, int J) const { return pl.F(I) <= J; }
+    __device__ __forceinline__ bool has_u(int J, int K) const { return pl.G(K) <= J; }
+    __device__ __forceinline__ int lcount(int I, int J) const { return J - pl.F(I); }
+    __device__ __forceinline__ int ucount(int K, int J) const { return J - pl.G(K); }
+    __device__ __forceinline__ bool publish(int J) const { return order_n > 1; }
+    __device__ __forceinline__ int *status() const { return ctl; }
+    __device__ __forceinline__ int *lflag(int I) const { return reinterpret_cast<int *>(pack(I) + 48); }
+    __device__ __forceinline__ int *uflag(int K) const { return reinterpret_cast<int *>(pack(K) + TB + 48); }
+    __device__ __forceinline__ double *pack(int J) const { return P + (int64_t)J * TB * TB; }
+    __device__ __forceinline__ int *dflag(int J) const { return reinterpret_cast<int *>(pack(J) + 32); }
+    int order_n; /* tiles of this workgroup's step */
+};
+__global__ __launch_bounds__(NT) void k_sky_clear(SkyPlan pl, double *P, int *ctl, int32_t *info)
 {
-    __shared__ TileSmem<double> sm;
-    __shared__ int s_ticket;
-    const int n = pl.n, nt = pl.nt;
-    int *status = ctl, *ticket = ctl + kCtlHead + 2 * J, *flag = ticket + 1;
+    for (int i = threadIdx.x; i < kCtlHead + 2 * pl.nt; i += NT)
+        ctl[i] = 0;
+    for (int b = threadIdx.x; b < pl.nt; b += NT) {
+        double *pb = P + (int64_t)b * TB * TB;
+        pb[32] = pb[48] = pb[TB + 48] = 0.0;
+    }
+    if (threadIdx.x == 0 && info)
+        *info = 0;
+}
+__global__ __launch_bounds__(NTP, 2) void k_sky_factor(SkyPlan pl, SkyOrder ord, double *tiles, double *P,
+                                                               int *ctl, int32_t *info, long wlim)
+{
+    __shared__ FlowSmem<double> sm;
     if (threadIdx.x == 0) {
-        s_ticket = atomicAdd(ticket, 1);
-        sm.avail = 0;
+        sm.ticket = atomicAdd(ctl + 1, 1);
+        sm.seen[0] = sm.seen[1] = sm.seen[2] = 0;
     }
     __syncthreads();
-    int q = s_ticket;
-    const int kJ = min(TB, n - J * TB);
-    /* step J-1's rank-64 term for tile (I, K): L_{I,J-1} U_{J-1,K}, when both exist */
-    auto pending = [&](Acc64<double> &acc, int I, int K, int nr, int nc) {
-        if (J == 0 || pl.F[I] > J - 1 || pl.G[K] > J - 1)
-            return;
-        acc64_stream_pairs(
-            acc, 1,
-            [&](int, const double *&a, const double *&b) {
-                a = sky_tile(pl, tiles, I, J - 1);
-                b = sky_tile(pl, tiles, J - 1, K);
-            },
-            nr, nc);
-    };
-    double *D = sky_tile(pl, tiles, J, J);
-    if (q == 0) { /* the diagonal tile */
-        Acc64<double> acc;
-        acc64_load(acc, DenseC<double>{D, TB, kJ, kJ});
-        pending(acc, J, J, kJ, kJ);
-        acc64_store(acc, LdsTile<double>{sm.t0});
-        __syncthreads();
-        if (threadIdx.x >= kJ && threadIdx.x < TB)
-            sm.t0[threadIdx.x * LDT + threadIdx.x] = 1.0;
-        __syncthreads();
-        const bool pub = nl + nu > 0;
-        /* what the panel tiles read, published a strip at a time as in the
-         * dense block step */
-        const int z = tile_lu64(sm.t0, sm.t1, sm.rinv, kJ, &sm.zflag, [&](int p, int stage) __attribute__((always_inline)) {
-            if (!pub)
-                return;
-            if (stage == 0)
-                publish_strip<LDT>(sm.t0, sm.t1, p, P, D, TB, kJ);
-            else
-                count_strip(flag);
-        });
-        if (threadIdx.x == 0 && info && (J == 0 || (z && *info == 0)))
-            *info = z ? J * TB + z : 0;
-        if (pub)
-            count_strip(flag);
-        else
-            lds_store_tile(sm.t0, D, TB, kJ, kJ);
+    const int nt = pl.nt, q0 = __builtin_amdgcn_readfirstlane(sm.ticket);
+    if (q0 >= ord.first[nt]) { /* counter not reset: refuse */
+        if (threadIdx.x == 0)
+            atomicOr(ctl, 2);
         return;
     }
-    q -= 1;
-    if (q < nl + nu) { /* a panel tile */
-        const bool lower = q < nl;
-        const int I = lower ? sky_nth(pl.F, J + 1, nt, J, q) : sky_nth(pl.G, J + 1, nt, J, q - nl);
-        if (I < 0)
-            return;
-        const int kI = min(TB, n - I * TB);
-        const int r0 = lower ? I : J, c0 = lower ? J : I, nr = lower ? kI : kJ, nc = lower ? kJ : kI;
-        double *G = sky_tile(pl, tiles, r0, c0);
-        Acc64<double> acc;
-        acc64_load(acc, DenseC<double>{G, TB, nr, nc});
-        pending(acc, r0, c0, nr, nc);
-        acc64_store(acc, LdsTile<double>{sm.t0});
-        __syncthreads();
-        /* the solve against the factored diagonal tile, block step p as soon
-         * as strip p is published (the flag counts 4 per strip): each wave
-         * keeps its 16-wide slab of the tile in accumulators (transposed for
-         * the L tiles, L_IJ = A_IJ U_JJ^{-1} solved as U^T X^T = A^T) and runs
-         * step p with the strip staged in t1: the diagonal block times the
-         * inverse of the strip's diagonal block, then its contribution
-         * removed from the blocks after it, each product taking the finished
-         * block as its B operand */
-        const bool from_right = lower; /* L_IJ = A_IJ U_JJ^{-1}: U^{-1} applied from the right */
-        const int w = wave_id(), l = threadIdx.x & 63, lr = l & 15, lk = l >> 4;
-        d4 a[4];
-#pragma unroll
-        for (int q2 = 0; q2 < 4; ++q2)
-#pragma unroll
-            for (int r = 0; r < 4; ++r)
-                a[q2][r] = from_right ? sm.t0[(16 * w + lr) * LDT + 16 * q2 + acc_row<double>(lk, r)]
-                                 : sm.t0[(16 * q2 + acc_row<double>(lk, r)) * LDT + 16 * w + lr];
-#pragma unroll
-        for (int p = 0; p < 4; ++p) {
-            wait_solved(flag, 4 * p + 3, &sm.avail, status, wlim);
-            /* strip p: for a U tile rows 16p.. of columns 16p..16p+15 (L),
-             * for an L tile columns 16p.. of rows 16p..16p+15 (U); diagonal
-             * block from P, identity past the matrix end */
-            const int len = 64 - 16 * p;
-            double v[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int idx = threadIdx.x + NT * i;
-                const int r = from_right ? 16 * p + idx / len : 16 * p + (idx >> 4);
-                const int c = from_right ? 16 * p + idx % len : 16 * p + (idx & 15);
-                v[i] = idx >= len * 16           ? 0.0
-                       : (r >> 4) == (c >> 4)    ? load_coherent(P + r * TB + c)
-                       : (r < kJ && c < kJ)      ? load_coherent(D + r * TB + c)
-                                                 : 0.0;
-            }
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int idx = threadIdx.x + NT * i;
-                const int r = from_right ? 16 * p + idx / len : 16 * p + (idx >> 4);
-                const int c = from_right ? 16 * p + idx % len : 16 * p + (idx & 15);
-                if (idx < len * 16)
-                    sm.t1[r * LDT + c] = v[i];
-            }
-            __syncthreads();
-            d4 x = {0.0, 0.0, 0.0, 0.0};
-            if (from_right) {
-                wave_mma16_acc<double>(
-                    x,
-                    [&](int r, int k) {
-                        const double u = sm.t1[(16 * p + k) * LDT + 16 * p + r];
-                        return k <= r ? u : 0.0;
-                    },
-                    a[p]);
-                a[p] = x;
-#pragma unroll
-                for (int q2 = p + 1; q2 < 4; ++q2)
-                    wave_mma16_acc<double>(a[q2], [&](int r, int k) { return -sm.t1[(16 * p + k) * LDT + 16 * q2 + r]; },
-                                           a[p]);
-            } else {
-                wave_mma16_acc<double>(
-                    x,
-                    [&](int r, int k) {
-                        const double u = sm.t1[(16 * p + r) * LDT + 16 * p + k];
-                        return r > k ? u : (r == k ? 1.0 : 0.0);
-                    },
-                    a[p]);
-                a[p] = x;
-#pragma unroll
-                for (int q2 = p + 1; q2 < 4; ++q2)
-                    wave_mma16_acc<double>(a[q2], [&](int r, int k) { return -sm.t1[(16 * q2 + r) * LDT + 16 * p + k]; },
-                                           a[p]);
-            }
-        }
-        __syncthreads();
-#pragma unroll
-        for (int q2 = 0; q2 < 4; ++q2)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                if (from_right)
-                    sm.t0[(16 * w + lr) * LDT + 16 * q2 + acc_row<double>(lk, r)] = a[q2][r];
-                else
-                    sm.t0[(16 * q2 + acc_row<double>(lk, r)) * LDT + 16 * w + lr] = a[q2][r];
-            }
-        __syncthreads();
-        lds_store_tile(sm.t0, G, TB, nr, nc);
+    int J = 0; /* the step: the last with first[J] <= q0 */
+    for (int step = kSkyMaxBlocks / 2; step; step >>= 1)
+        if (J + step < nt && ord.first[J + step] <= q0)
+            J += step;
+    const int q = q0 - ord.first[J];
+    const SkyFlow f{pl, tiles, P, ctl, wlim, ord.first[J + 1] - ord.first[J]};
+    if (q == 0) {
+        __builtin_amdgcn_s_setprio(3); /* the chain, ahead of its compute unit's other waves */
+        flow_diagonal<double>(f, J, info, sm);
         return;
     }
-    q -= nl + nu;
-    if (q >= nlp * nup)
+    if (threadIdx.x >= NT)
         return;
-    { /* a trailing tile (I, K), I, K > J: step J-1's term only */
-        const int I = sky_nth(pl.F, J + 1, nt, J - 1, q / nup), K = sky_nth(pl.G, J + 1, nt, J - 1, q % nup);
-        if (I < 0 || K < 0)
-            return;
-        const int nr = min(TB, n - I * TB), nc = min(TB, n - K * TB);
-        double *C = sky_tile(pl, tiles, I, K);
-        Acc64<double> acc;
-        acc64_load(acc, DenseC<double>{C, TB, nr, nc});
-        pending(acc, I, K, nr, nc);
-        acc64_store(acc, DenseC<double>{C, TB, nr, nc});
+    int I = sky_nth([&](int x) { return pl.F(x); }, J + 1, nt, J, q - 1);
+    if (I >= 0) {
+        if (I == J + 1)
+            __builtin_amdgcn_s_setprio(2);
+        flow_panel<double, true>(f, J, I, sm);
+        return;
     }
+    int nl = 0;
+    for (int base = J + 1; base < nt; base += 64) {
+        const int x = base + (threadIdx.x & 63);
+        nl += __popcll(__ballot(x < nt && pl.F(min(x, nt - 1)) <= J));
+    }
+    I = sky_nth([&](int x) { return pl.G(x); }, J + 1, nt, J, q - 1 - nl);
+    if (I < 0)
+        return;
+    if (I == J + 1)
+        __builtin_amdgcn_s_setprio(2);
+    flow_panel<double, false>(f, J, I, sm);
 }
 
 hipError_t skyline_factor(const SkyPlan &pl, double *tiles, double *P, int *ctl, int32_t *info, long wlim,
                           hipStream_t st)
 {
-    hipError_t e = fill_i32(ctl, kCtlHead + 2 * pl.nt, 0, st);
-    for (int J = 0; J < pl.nt && e == hipSuccess; ++J) {
-        int nl = 0, nu = 0, nlp = 0, nup = 0;
-        for (int I = J + 1; I < pl.nt; ++I) {
-            nl += pl.F[I] <= J;
-            nu += pl.G[I] <= J;
-            nlp += pl.F[I] <= J - 1;
-            nup += pl.G[I] <= J - 1;
-        }
-        const int grid = 1 + nl + nu + nlp * nup;
-        hipLaunchKernelGGL(k_sky_step, dim3(grid), dim3(NT), 0, st, pl, tiles, P, J, nl, nu, nlp, nup, ctl, info,
-                           wlim);
-        e = hipGetLastError();
+    SkyOrder ord;
+    ord.first[0] = 0;
+    for (int J = 0; J < pl.nt; ++J) {
+        int c = 1;
+        for (int I = J + 1; I < pl.nt; ++I)
+            c += (pl.F(I) <= J) + (pl.G(I) <= J);
+        ord.first[J + 1] = ord.first[J] + c;
     }
+    hipLaunchKernelGGL(k_sky_clear, dim3(1), dim3(NT), 0, st, pl, P, ctl, info);
+    hipLaunchKernelGGL(k_sky_factor, dim3(ord.first[pl.nt]), dim3(NTP), 0, st, pl, ord, tiles, P, ctl, info, wlim);
+    hipError_t e = hipGetLastError();
     if (e == hipSuccess && info)
         e = fold_status(ctl, info, st);
     return e;
@@ -2958,7 +3182,7 @@ __device__ __forceinline__ void sky_mark(double *T)
     for (int i = threadIdx.x; i < TB * TB; i += NT)
         x[i] = kUnsolvedMark64;
 }
-__device__ __forceinline__ void sky_clear(int *ctl, bool all)
+__device__ __forceinline__ void sky_ctl_clear(int *ctl, bool all)
 {
     if (blockIdx.x == 0 && threadIdx.x < kSkyCtl && (all || threadIdx.x > 0))
         ctl[threadIdx.x] = 0;
@@ -2972,7 +3196,7 @@ __global__ __launch_bounds__(NT) void k_sky_packs(SkyPlan pl, double *__restrict
     stage_tile_identity(sm.t0, D, TB, kb, kb);
     __syncthreads();
     sky_mark(D);
-    sky_clear(ctl, true);
+    sky_ctl_clear(ctl, true);
     if (threadIdx.x < TB)
         sm.rinv[threadIdx.x] = recip(sm.t0[threadIdx.x * LDT + threadIdx.x]);
     __syncthreads();
@@ -2985,7 +3209,7 @@ __global__ __launch_bounds__(NT) void k_sky_packs(SkyPlan pl, double *__restrict
 __global__ __launch_bounds__(NT) void k_sky_marks(SkyPlan pl, double *__restrict__ tiles, int *ctl)
 {
     sky_mark(sky_tile(pl, tiles, blockIdx.x, blockIdx.x));
-    sky_clear(ctl, false);
+    sky_ctl_clear(ctl, false);
 }
 
 /*
@@ -3033,13 +3257,13 @@ __global__ __launch_bounds__(NT) void k_sky_trsv(SkyPlan pl, double *__restrict_
     /* dependencies, oldest first */
     int nd = 0;
     if (FWD) {
-        nd = blk - pl.F[blk];
+        nd = blk - pl.F(blk);
         for (int d = t; d < nd; d += NT)
-            dl[d] = (int16_t)(pl.F[blk] + d);
+            dl[d] = (int16_t)(pl.F(blk) + d);
     } else {
         for (int base = blk + 1 + (nt - blk - 2) / 64 * 64; base > blk; base -= 64) {
             const int J = base + l;
-            const bool dep = J < nt && pl.G[min(J, nt - 1)] <= blk;
+            const bool dep = J < nt && pl.G(min(J, nt - 1)) <= blk;
             const unsigned long long m = __ballot(dep);
             if (w == 0 && dep)
                 dl[nd + __popcll(m & ~((2ull << l) - 1))] = (int16_t)J;

@@ -1,4 +1,4 @@
-"""GPU parity of the chained skyline substitutions at their edges: block counts
+"""GPU parity of the skyline factor and its chained substitutions at their edges: block counts
 around the number of dependencies a block treats apart (the last two in
 registers, the third polled, older ones shared with the helper), empty and
 far-apart dependencies, one to several chunks of 16 right-hand sides, and
@@ -68,3 +68,14 @@ def test_skyline_chain(kind, n, nrhs):
         torch.cuda.synchronize()
         assert fwd_err(host(buf[1:n + 1]), oracle.lu_solve_skyline(f, rp, LL, g, cp, UU, B)) <= 1e-12
         assert bool((buf[0] == 7.25).all()) and bool((buf[n + 1] == 7.25).all())
+
+
+def test_skyline_first_zero_pivot():
+    """Independent diagonal tiles finish in any order: the smallest zero pivot is reported."""
+    case("skyline first zero pivot")
+    f, rp, AL, g, cp, AU = _system("diagonal", 1000, 5)
+    for i in (900, 333, 70):
+        AU[i] = 0.0
+    sk = ebv.Skyline(f, rp, AL, g, cp, AU)
+    assert int(sk.factor_().item()) == 71
+    assert oracle.lu_factor_skyline(f, rp, AL, g, cp, AU)[2] == 71
