@@ -381,8 +381,8 @@ template <typename T> struct StepSmem {
 };
 constexpr int kStepPerCu = 3; /* workgroups per compute unit that k_step's LDS and registers admit */
 
-template <typename T, int MB>
-__global__ __launch_bounds__(NT, kStepPerCu) void k_step(T *__restrict__ A, int64_t lda, int n, int s, int G, int upd,
+template <typename T, int MB, bool PUB>
+__global__ __launch_bounds__(PUB ? NTP : NT, PUB ? 2 : kStepPerCu) void k_step(T *__restrict__ A, int64_t lda, int n, int s, int G, int upd,
                                                          int pendp, int first_wave, int32_t *info, T *__restrict__ Pg,
                                                          T *__restrict__ B, int64_t ldb, int nrhs, int *ctl, long wlim)
 {
@@ -420,6 +420,14 @@ __global__ __launch_bounds__(NT, kStepPerCu) void k_step(T *__restrict__ A, int6
     if (q >= 1 + nt2 + nb2 + npan) { /* counter not reset: refuse */
         if (threadIdx.x == 0)
             atomicOr(status, 2);
+        return;
+    }
+    if (PUB && wave_id() >= NT / 64) { /* the publishing waves: only the diagonal tile's workgroup has work for them */
+        if (q > 0 || npan == 0)
+            return;
+        for (int b = kw_of(s) / 16 + 2; b > 0; --b) /* the others' barriers up to tile_lu64 */
+            __syncthreads();
+        publish_strips<DBP>(sm.S, sm.P, Pg, A + (int64_t)d0 * lda + d0, lda, dw, flag);
         return;
     }
 
@@ -499,7 +507,7 @@ __global__ __launch_bounds__(NT, kStepPerCu) void k_step(T *__restrict__ A, int6
          * in the flag a little later, the last strip's at the end */
         const int z = tile_lu64<T, true>(sm.S, sm.P, (T *)nullptr, dw, &s_zero,
                                          [&](int p, int stage) __attribute__((always_inline)) {
-                                             if (!pub)
+                                             if (PUB || !pub)
                                                  return;
                                              if (stage == 0)
                                                  publish_strip<DBP>(sm.S, sm.P, p, Pg, C, lda, dw);
@@ -508,10 +516,10 @@ __global__ __launch_bounds__(NT, kStepPerCu) void k_step(T *__restrict__ A, int6
                                          });
         if (threadIdx.x == 0 && info && z && *info == 0)
             *info = d0 + z;
-        if (pub)
-            count_strip(flag);
-        else
+        if (!pub)
             lds_store_tile(sm.S, C, lda, dw, dw);
+        else if (!PUB)
+            count_strip(flag);
         return;
     }
     /* the solve against the factored diagonal tile, block step p as soon as
@@ -747,12 +755,18 @@ static hipError_t factor_lookahead(T *A, int64_t lda, int n, int32_t *info, T *P
         }
         int pslot = -1;
         const bool prof = s > 0 && profile_slot(pr, st, fl, pslot);
+        const auto launch = [&](auto kernel, int nt) {
+            hipLaunchKernelGGL(kernel, dim3(grid), dim3(nt), 0, st, A, lda, n, s, G, upd, pendp, first_wave, info, Pg, B,
+                               ldb, nrhs, ctl, wlim);
+        };
+        /* publishing waves where two workgroups per compute unit take the
+         * whole launch: it is as long as its chain then; they would displace
+         * the third of a larger launch */
+        const bool pub = grid <= 2 * cus;
         if (bm == 128)
-            hipLaunchKernelGGL((k_step<T, kTallBlocks<T>>), dim3(grid), dim3(NT), 0, st, A, lda, n, s, G, upd, pendp,
-                               first_wave, info, Pg, B, ldb, nrhs, ctl, wlim);
+            pub ? launch(k_step<T, kTallBlocks<T>, true>, NTP) : launch(k_step<T, kTallBlocks<T>, false>, NT);
         else
-            hipLaunchKernelGGL((k_step<T, 2>), dim3(grid), dim3(NT), 0, st, A, lda, n, s, G, upd, pendp, first_wave,
-                               info, Pg, B, ldb, nrhs, ctl, wlim);
+            pub ? launch(k_step<T, 2, true>, NTP) : launch(k_step<T, 2, false>, NT);
         if ((e = hipGetLastError()) != hipSuccess)
             return e;
         if (prof)
