@@ -44,7 +44,8 @@ constexpr int64_t kWgMaxSystemBytes = int64_t(1) << 31;
  * kCtlHead words above, then per block step s the words kCtlHead + 2s
  * (ticket counter) and kCtlHead + 1 + 2s (the diagonal tile's ready flag)
  * -- then the factored diagonal tile's pack for the panel solves (64 x 64
- * elements). */
+ * elements).  The one-launch factor uses the same bytes for its own words,
+ * flags and packs (DenseFlow). */
 constexpr size_t factor_ctl_bytes(int64_t n)
 {
     const int64_t nb = (n + 63) / 64;
@@ -115,8 +116,8 @@ hipError_t fill_i32(int *p, int64_t count, int value, hipStream_t st);
 /* info = -status when the workspace's status word is nonzero (one thread). */
 hipError_t fold_status(const int *status, int32_t *info, hipStream_t st);
 
-/* Single-system factor; prefilled: info and the control words were cleared
- * by the caller on the same stream. */
+/* Single-system factor; prefilled: info, the control words and the flags
+ * behind them were cleared by the caller on the same stream. */
 template <typename T>
 hipError_t dense_factor(T *A, int64_t lda, int n, int32_t *info, void *ws, const DenseTuning &tun, UpdateProfile *prof,
                         hipStream_t st, T *B = nullptr, int64_t ldb = 0, int nrhs = 0, bool prefilled = false);

@@ -293,44 +293,6 @@ __device__ __forceinline__ void publish_strip(const T *S, const T *P, int q, T *
     }
 }
 
-/* The publishing waves of a diagonal tile's workgroup: two more than the four
- * that factor the tile, so that neither the stores nor the wait for them lie
- * on the chain of its strips (they took 3 of the 11 us of a tile).  Called by
- * those waves while the others are in tile_lu64, whose barriers they share,
- * three a strip: strip read, strip final, rest updated.  D's 64 x 64 tile and
- * the pack Pg as publish_strip leaves them; flag counts 4 per strip. */
-constexpr int kPubWaves = 2, NTP = NT + 64 * kPubWaves;
-template <int PP, typename T>
-__device__ __forceinline__ void publish_strips(const T *S, const T *P, T *Pg, T *D, int64_t ldd, int n, int *flag)
-{
-    constexpr int R = 4 * kPubWaves; /* rows of 16 lanes */
-    const int t = (int)threadIdx.x - NT, r0 = t >> 4, c = t & 15;
-#pragma unroll 1
-    for (int q = 0; q < 4; ++q) {
-        const int b0 = 16 * q;
-        __syncthreads();
-        __syncthreads();
-#pragma unroll
-        for (int i = 0; i < 16 / R; ++i) {
-            const int r = r0 + R * i;
-            store_coherent(Pg + (b0 + r) * TB + b0 + c, P[(b0 + r) * PP + (PP == LDT ? b0 : 0) + c]);
-            if (b0 + r < n && b0 + c < n)
-                D[(int64_t)(b0 + r) * ldd + b0 + c] = S[(b0 + r) * LDT + b0 + c];
-#pragma unroll 3
-            for (int a = b0 + 16; a < TB; a += 16) {
-                if (a + r < n && b0 + c < n)
-                    store_coherent(D + (int64_t)(a + r) * ldd + b0 + c, S[(a + r) * LDT + b0 + c]);
-                if (b0 + r < n && a + c < n)
-                    store_coherent(D + (int64_t)(b0 + r) * ldd + a + c, S[(b0 + r) * LDT + a + c]);
-            }
-        }
-        __syncthreads();
-        __builtin_amdgcn_s_waitcnt(0);
-        if ((t & 63) == 0)
-            __hip_atomic_fetch_add(flag, 4 / kPubWaves, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-}
-
 /* Counts a published strip, one per wave, once the wave's stores have landed. */
 __device__ __forceinline__ void count_strip(int *flag)
 {
@@ -381,8 +343,8 @@ template <typename T> struct StepSmem {
 };
 constexpr int kStepPerCu = 3; /* workgroups per compute unit that k_step's LDS and registers admit */
 
-template <typename T, int MB, bool PUB>
-__global__ __launch_bounds__(PUB ? NTP : NT, PUB ? 2 : kStepPerCu) void k_step(T *__restrict__ A, int64_t lda, int n, int s, int G, int upd,
+template <typename T, int MB>
+__global__ __launch_bounds__(NT, kStepPerCu) void k_step(T *__restrict__ A, int64_t lda, int n, int s, int G, int upd,
                                                          int pendp, int first_wave, int32_t *info, T *__restrict__ Pg,
                                                          T *__restrict__ B, int64_t ldb, int nrhs, int *ctl, long wlim)
 {
@@ -420,14 +382,6 @@ __global__ __launch_bounds__(PUB ? NTP : NT, PUB ? 2 : kStepPerCu) void k_step(T
     if (q >= 1 + nt2 + nb2 + npan) { /* counter not reset: refuse */
         if (threadIdx.x == 0)
             atomicOr(status, 2);
-        return;
-    }
-    if (PUB && wave_id() >= NT / 64) { /* the publishing waves: only the diagonal tile's workgroup has work for them */
-        if (q > 0 || npan == 0)
-            return;
-        for (int b = kw_of(s) / 16 + 2; b > 0; --b) /* the others' barriers up to tile_lu64 */
-            __syncthreads();
-        publish_strips<DBP>(sm.S, sm.P, Pg, A + (int64_t)d0 * lda + d0, lda, dw, flag);
         return;
     }
 
@@ -507,7 +461,7 @@ __global__ __launch_bounds__(PUB ? NTP : NT, PUB ? 2 : kStepPerCu) void k_step(T
          * in the flag a little later, the last strip's at the end */
         const int z = tile_lu64<T, true>(sm.S, sm.P, (T *)nullptr, dw, &s_zero,
                                          [&](int p, int stage) __attribute__((always_inline)) {
-                                             if (PUB || !pub)
+                                             if (!pub)
                                                  return;
                                              if (stage == 0)
                                                  publish_strip<DBP>(sm.S, sm.P, p, Pg, C, lda, dw);
@@ -516,10 +470,10 @@ __global__ __launch_bounds__(PUB ? NTP : NT, PUB ? 2 : kStepPerCu) void k_step(T
                                          });
         if (threadIdx.x == 0 && info && z && *info == 0)
             *info = d0 + z;
-        if (!pub)
-            lds_store_tile(sm.S, C, lda, dw, dw);
-        else if (!PUB)
+        if (pub)
             count_strip(flag);
+        else
+            lds_store_tile(sm.S, C, lda, dw, dw);
         return;
     }
     /* the solve against the factored diagonal tile, block step p as soon as
@@ -755,18 +709,12 @@ static hipError_t factor_lookahead(T *A, int64_t lda, int n, int32_t *info, T *P
         }
         int pslot = -1;
         const bool prof = s > 0 && profile_slot(pr, st, fl, pslot);
-        const auto launch = [&](auto kernel, int nt) {
-            hipLaunchKernelGGL(kernel, dim3(grid), dim3(nt), 0, st, A, lda, n, s, G, upd, pendp, first_wave, info, Pg, B,
-                               ldb, nrhs, ctl, wlim);
-        };
-        /* publishing waves where two workgroups per compute unit take the
-         * whole launch: it is as long as its chain then; they would displace
-         * the third of a larger launch */
-        const bool pub = grid <= 2 * cus;
         if (bm == 128)
-            pub ? launch(k_step<T, kTallBlocks<T>, true>, NTP) : launch(k_step<T, kTallBlocks<T>, false>, NT);
+            hipLaunchKernelGGL((k_step<T, kTallBlocks<T>>), dim3(grid), dim3(NT), 0, st, A, lda, n, s, G, upd, pendp,
+                               first_wave, info, Pg, B, ldb, nrhs, ctl, wlim);
         else
-            pub ? launch(k_step<T, 2, true>, NTP) : launch(k_step<T, 2, false>, NT);
+            hipLaunchKernelGGL((k_step<T, 2>), dim3(grid), dim3(NT), 0, st, A, lda, n, s, G, upd, pendp, first_wave,
+                               info, Pg, B, ldb, nrhs, ctl, wlim);
         if ((e = hipGetLastError()) != hipSuccess)
             return e;
         if (prof)
@@ -778,6 +726,495 @@ static hipError_t factor_lookahead(T *A, int64_t lda, int n, int32_t *info, T *P
             applied[upd] = s;
     }
     return e;
+}
+
+/* ------------------------------------------------- factor as a dataflow --- */
+
+/*
+ * Blocked LU with the tiles as the units, one workgroup each, that wait for
+ * the tiles they need instead of for a launch: tile (I, K) keeps its elements
+ * in accumulators while it receives the products L_Ik U_kK (Eq. 6-c), k
+ * ascending, as their operands appear, and then
+ *   - K = I: is factored (tile_lu64, Eq. 6-a) and published a strip at a time;
+ *   - K < I (I < K): is solved against the diagonal tile of block K (I), step p
+ *     as soon as strip p is out.
+ * The chain of the elimination is diagonal tile -> the two tiles below and
+ * right of it -> next diagonal tile.  Those two are published 16 columns (rows)
+ * at a time, as they are solved, and the next diagonal tile subtracts each
+ * rank-16 product when it appears, its operands read straight to registers:
+ * after the last strip one such product is left.
+ *
+ * Workgroups take their tiles from a ticket in the order of steps J: the
+ * diagonal tile, then the tiles (I, J) below, then (J, K) right of it.  A tile
+ * needs only tiles with smaller tickets, which run or have run, so that every
+ * wait ends (they are bounded all the same, into the status word).
+ *
+ * What bounds it is the chain, 16 us a block: 9 us for the diagonal tile (FP32
+ * 8), 2 us on each of the two hops until a flag is seen, 1 us until what it
+ * announces is loaded, and the last products; from n = 8192 (dense) the update
+ * work, 50 TFLOP/s of the 72 that a large FP64 product reaches.  Against one
+ * launch per block step: dense FP64 n = 4096 2031 -> 1207 us (use_flow has
+ * more); skyline, n = 16384 with half-widths up to 1024, 5.6 -> 4.07 ms; full
+ * profile of n = 16384, 161 -> 68 ms.  Tried and slower: the diagonal's
+ * workgroup solving both neighbours itself (25.6 us a block, its coherent stores
+ * hold up every later wait), strips handed over one at a time.
+ *
+ * F describes the matrix: tile(I, K), pitch ld(K), rows(I) of block I that
+ * exist, first(I, K) the first k with a product; the flags lflag(I), uflag(K)
+ * count 16 per finished tile of block row I's L part (block column K's U part),
+ * 4 per strip, which finish in order, lcount(I, J), ucount(K, J) being the
+ * tiles before (I, J), (J, K).  dflag(J) counts 4 per published strip of the
+ * diagonal tile, pack(J) holds the inverses of its diagonal blocks (64 x 16),
+ * and guard(J), called by the publishing waves, returns when pack(J) is free.
+ * Finished tiles are written through (store_coherent) and read coherently or
+ * after an acquire; a waiting workgroup polls with one thread.
+ */
+template <typename T> struct FlowSmem {
+    union alignas(16) {
+        StepSmem<T> tile;
+        char gemm[TileGemm<T, 2, 2>::LDS];
+    };
+    int seen[3]; /* flag values seen: L, U, strips */
+    int ticket, zero;
+};
+
+/* The publishing waves of a diagonal tile's workgroup: two more than the four
+ * that factor the tile, so that neither the stores nor the wait for them lie
+ * on the chain of its strips (they took 2 of the 11 us of a tile).  Called by
+ * those waves while the others are in tile_lu64, whose barriers they share,
+ * three a strip: strip read, strip final, rest updated.  S, P: the tile and its
+ * diagonal blocks' inverses (pitch DBP); they go to D (n x n of it exist) and to
+ * the pack Pg; flag counts 4 per strip. */
+constexpr int kPubWaves = 2, NTP = NT + 64 * kPubWaves;
+template <typename T>
+__device__ __forceinline__ void publish_strips(const T *S, const T *P, T *Pg, T *D, int64_t ldd, int n, int *flag)
+{
+    constexpr int R = 4 * kPubWaves; /* rows of 16 lanes */
+    const int t = (int)threadIdx.x - NT, r0 = t >> 4, c = t & 15;
+#pragma unroll 1
+    for (int q = 0; q < 4; ++q) {
+        const int b0 = 16 * q;
+        __syncthreads();
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < 16 / R; ++i) {
+            const int r = r0 + R * i;
+            store_coherent(Pg + (b0 + r) * 16 + c, P[(b0 + r) * DBP + c]);
+            if (b0 + r < n && b0 + c < n)
+                store_coherent(D + (int64_t)(b0 + r) * ldd + b0 + c, S[(b0 + r) * LDT + b0 + c]);
+#pragma unroll 3
+            for (int a = b0 + 16; a < TB; a += 16) {
+                if (a + r < n && b0 + c < n)
+                    store_coherent(D + (int64_t)(a + r) * ldd + b0 + c, S[(a + r) * LDT + b0 + c]);
+                if (b0 + r < n && a + c < n)
+                    store_coherent(D + (int64_t)(b0 + r) * ldd + a + c, S[(b0 + r) * LDT + a + c]);
+            }
+        }
+        __syncthreads();
+        __builtin_amdgcn_s_waitcnt(0);
+        if ((t & 63) == 0)
+            __hip_atomic_fetch_add(flag, 4 / kPubWaves, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+}
+
+/* Returns (all threads) once *pa >= na and *pb >= nb (pb may be null); off the
+ * chain a workgroup polls less often. */
+__device__ __forceinline__ void flow_wait(const int *pa, int na, int *sa, const int *pb, int nb, int *sb, int *status,
+                                          long limit, bool chain)
+{
+    if (threadIdx.x == 0 && (*sa < na || (pb && *sb < nb))) {
+        long spins = 0;
+        int va = *sa, vb = pb ? *sb : nb;
+        for (;;) {
+            if (va < na)
+                va = load_coherent(pa);
+            if (vb < nb)
+                vb = load_coherent(pb);
+            if (va >= na && vb >= nb)
+                break;
+            if (chain)
+                __builtin_amdgcn_s_sleep(1);
+            else
+                __builtin_amdgcn_s_sleep(16);
+            if (wait_give_up(status, ++spins, limit)) {
+                va = max(va, na);
+                vb = max(vb, nb);
+                break;
+            }
+        }
+        *sa = va;
+        if (pb)
+            *sb = vb;
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    }
+    __syncthreads();
+}
+
+/* Adds c per wave to a flag, once the wave's stores have landed. */
+__device__ __forceinline__ void flow_count(int *flag, int c)
+{
+    __builtin_amdgcn_s_waitcnt(0);
+    if ((threadIdx.x & 63) == 0)
+        __hip_atomic_fetch_add(flag, c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+/* End of the run of products from k on whose operands have been seen: more
+ * than one where the tiles of a row lie side by side (F::joined; no flag counts
+ * less than 16 per tile then). */
+template <typename T, typename F> __device__ __forceinline__ int flow_run(int k, int k1, const FlowSmem<T> &sm)
+{
+    return F::joined ? min(k1, __builtin_amdgcn_readfirstlane(min(sm.seen[0], sm.seen[1])) / 16) : k + 1;
+}
+
+/* acc = C - sum of the products of tile (I, K), k < k1. */
+template <typename T, typename F>
+__device__ __forceinline__ void flow_products(typename vec4<T>::type (&acc)[2][2], const F &f, int I, int K, int k1,
+                                              bool chain, FlowSmem<T> &sm)
+{
+    const int nr = f.rows(I), nc = f.rows(K);
+    const T *C = f.tile(I, K);
+    for_tile<T, 2>([&](int bi, int bj, int r, int i, int j) {
+        acc[bi][bj][r] = C[(int64_t)min(i, nr - 1) * f.ld(K) + min(j, nc - 1)];
+    });
+    for (int k = f.first(I, K); k < k1;) {
+        flow_wait(f.lflag(I), 16 * (f.lcount(I, k) + 1), sm.seen, f.uflag(K), 16 * (f.ucount(K, k) + 1), sm.seen + 1,
+                  f.status(), f.limit, chain);
+        const int kn = flow_run<T, F>(k, k1, sm);
+        tile_minus<T, 2>(acc, f.tile(I, k), f.ld(k), nr, f.tile(k, K), f.ld(K), nc, TB * (kn - k), sm.gemm);
+        k = kn;
+    }
+    __syncthreads(); /* the products' last operand reads */
+}
+
+/* Strip p of the factored diagonal tile D to LDS, by rows of the lower
+ * operator, pitch DBP: rows 16p.. of columns 16p..16p+15 (L), or RIGHT the
+ * columns 16p.. of rows 16p..16p+15 (U^T); its diagonal block from the pack,
+ * zero past its n rows and columns. */
+template <typename T, bool RIGHT>
+__device__ __forceinline__ void flow_strip(T *dst, int p, const T *Pg, const T *D, int64_t ld, int n)
+{
+    const int len = TB - 16 * p;
+    T v[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int idx = threadIdx.x + NT * i;
+        const int r = RIGHT ? 16 * p + idx / len : 16 * p + (idx >> 4);
+        const int c = RIGHT ? 16 * p + idx % len : 16 * p + (idx & 15);
+        v[i] = idx >= len * 16          ? T(0)
+               : (r >> 4) == (c >> 4)   ? load_coherent(Pg + r * 16 + (c & 15))
+               : (r < n && c < n)       ? load_coherent(D + (int64_t)r * ld + c)
+                                        : T(0);
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int idx = threadIdx.x + NT * i;
+        if (idx < len * 16)
+            dst[RIGHT ? (16 * p + idx % len) * DBP + idx / len : (16 * p + (idx >> 4)) * DBP + (idx & 15)] = v[i];
+    }
+}
+
+/* Block step p of a wave's 16-wide slab (transposed for an L tile, X = A
+ * U^{-1} solved as U^T X^T = A^T) against a staged strip. */
+template <typename T, bool RIGHT>
+__device__ __forceinline__ void flow_solve(typename vec4<T>::type (&a)[4], const T *strip, int p)
+{
+    typename vec4<T>::type x = {0, 0, 0, 0};
+    wave_mma16_acc<T>(
+        x,
+        [&](int r, int k) {
+            const T u = strip[(16 * p + r) * DBP + k];
+            return r > k ? u : (r == k ? (RIGHT ? u : T(1)) : T(0));
+        },
+        a[p]);
+    a[p] = x;
+#pragma unroll
+    for (int q = p + 1; q < 4; ++q)
+        wave_mma16_acc<T>(a[q], [&](int r, int k) { return -strip[(16 * q + r) * DBP + k]; }, a[p]);
+}
+
+/* Tile (I, J) below (RIGHT) or (J, I) right of the diagonal tile J. */
+template <typename T, bool RIGHT, typename F>
+__device__ __forceinline__ void flow_panel(const F &f, int J, int I, FlowSmem<T> &sm)
+{
+    typedef typename vec4<T>::type V;
+    const int r0 = RIGHT ? I : J, c0 = RIGHT ? J : I, nr = f.rows(r0), nc = f.rows(c0);
+    T *S = sm.tile.S, *G = f.tile(r0, c0);
+    const bool next = f.next(J, I); /* the next diagonal tile waits for it */
+    const bool chain = I <= J + 2;  /* or the next but one */
+    V acc[2][2];
+    flow_products<T>(acc, f, r0, c0, J, chain, sm);
+    tile_to_lds<T, 2>(acc, S, nr, nc, false);
+    __syncthreads();
+    int *flag = RIGHT ? f.lflag(I) : f.uflag(I), *seen = sm.seen + (RIGHT ? 0 : 1);
+    const int before = 16 * (RIGHT ? f.lcount(I, J) : f.ucount(I, J)); /* a row's (column's) tiles count in order */
+    const int w = wave_id(), l = threadIdx.x & 63, lr = l & 15, lk = l >> 4;
+    const bool ok = 16 * w + lr < (RIGHT ? nr : nc);
+    V a[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+            a[q][r] = RIGHT ? S[(16 * w + lr) * LDT + 16 * q + acc_row<T>(lk, r)]
+                            : S[(16 * q + acc_row<T>(lk, r)) * LDT + 16 * w + lr];
+    if (next)
+        flow_wait(flag, before, seen, nullptr, 0, nullptr, f.status(), f.limit, chain);
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+        flow_wait(f.dflag(J), 4 * p + 4, sm.seen + 2, nullptr, 0, nullptr, f.status(), f.limit, chain);
+        flow_strip<T, RIGHT>(sm.tile.P, p, f.pack(J), f.tile(J, J), f.ld(J), f.valid(J));
+        if (next && p > 0) /* the strip before; its stores landed with this one's loads */
+            flow_count(flag, 1);
+        __syncthreads();
+        flow_solve<T, RIGHT>(a, sm.tile.P, p);
+        if (next) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int k = 16 * p + acc_row<T>(lk, r), o = 16 * w + lr;
+                if (ok)
+                    store_coherent(G + (RIGHT ? (int64_t)o * f.ld(J) + k : (int64_t)k * f.ld(I) + o), a[p][r]);
+            }
+        }
+    }
+    if (next) {
+        flow_count(flag, 1);
+        return;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+            S[RIGHT ? (16 * w + lr) * LDT + 16 * q + acc_row<T>(lk, r)
+                    : (16 * q + acc_row<T>(lk, r)) * LDT + 16 * w + lr] = a[q][r];
+    __syncthreads();
+    tile_xfer<T>([&](int r, int c) { return S[r * LDT + c]; },
+                 [&](int r, int c, T v) {
+                     if (r < nr && c < nc)
+                         store_coherent(G + (int64_t)r * f.ld(c0) + c, v);
+                 });
+    flow_wait(flag, before, seen, nullptr, 0, nullptr, f.status(), f.limit, chain);
+    flow_count(flag, 4);
+}
+
+/* Diagonal tile J. */
+template <typename T, typename F>
+__device__ __forceinline__ void flow_diagonal(const F &f, int J, int32_t *info, FlowSmem<T> &sm)
+{
+    typedef typename vec4<T>::type V;
+    const int nr = f.rows(J), valid = f.valid(J), w = wave_id(), l = threadIdx.x & 63, lr = l & 15, lk = l >> 4;
+    const bool last = J > 0 && f.has_l(J, J - 1) && f.has_u(J - 1, J); /* a product with block J - 1 */
+    T *S = sm.tile.S, *D = f.tile(J, J);
+    constexpr bool chain = true;
+    const bool pub = f.publish(J);
+    if (w >= NT / 64) { /* the publishing waves: past the barriers of the others up to tile_lu64 */
+        if (!pub)
+            return;
+        for (int k = f.first(J, J); k < J - 1;) { /* flow_products */
+            __syncthreads();
+            const int kn = flow_run<T, F>(k, J - 1, sm);
+            for (int b = TB / 16 * (kn - k); b > 0; --b)
+                __syncthreads();
+            k = kn;
+        }
+        for (int b = last ? 5 : 2; b > 0; --b)
+            __syncthreads();
+        f.guard(J);
+        publish_strips(S, sm.tile.P, f.pack(J), D, f.ld(J), valid, f.dflag(J));
+        return;
+    }
+    V acc[2][2];
+    flow_products<T>(acc, f, J, J, J - 1, chain, sm);
+    tile_to_lds<T, 2>(acc, S, valid, valid, true);
+    __syncthreads();
+    if (last) {
+        const T *TL = f.tile(J, J - 1), *TU = f.tile(J - 1, J);
+        const int fl = 16 * f.lcount(J, J - 1), fu = 16 * f.ucount(J, J - 1);
+        V d[4];
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                d[c][r] = S[(16 * w + acc_row<T>(lk, r)) * LDT + 16 * c + lr];
+        /* rows and columns past the matrix end: the last one again, dropped below */
+        const int64_t row = (int64_t)min(16 * w + lr, nr - 1) * f.ld(J - 1);
+        /* two strips at a time: a wait and the loads cost more than a strip's
+         * products */
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            flow_wait(f.lflag(J), fl + 8 * h + 8, sm.seen, f.uflag(J), fu + 8 * h + 8, sm.seen + 1, f.status(), f.limit,
+                      chain);
+            T a[8], b[4][8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const int k = 32 * h + 16 * (e >> 2) + acc_row<T>(lk, e & 3);
+                a[e] = load_coherent(TL + row + k);
+#pragma unroll
+                for (int c = 0; c < 4; ++c)
+                    b[c][e] = load_coherent(TU + (int64_t)k * f.ld(J) + min(16 * c + lr, nr - 1));
+            }
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+#pragma unroll
+                for (int c = 0; c < 4; ++c)
+                    d[c] = mfma16(-a[e], b[c][e], d[c]);
+        }
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int i = 16 * w + acc_row<T>(lk, r), j = 16 * c + lr;
+                if (i < valid && j < valid)
+                    S[i * LDT + j] = d[c][r];
+            }
+        __syncthreads();
+    }
+    const int z = tile_lu64<T, true>(S, sm.tile.P, (T *)nullptr, valid, &sm.zero);
+    if (!pub)
+        lds_store_tile(S, D, f.ld(J), valid, valid);
+    if (threadIdx.x == 0 && info && z) { /* the smallest over the diagonal tiles */
+        const int at = J * TB + z;
+        int was = 0;
+        while (!__hip_atomic_compare_exchange_strong(info, &was, at, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                     __HIP_MEMORY_SCOPE_AGENT) &&
+               (was == 0 || was > at))
+            ;
+    }
+}
+
+/* The dense matrix as a dataflow, right-hand sides (if any) as block columns
+ * nb .. of U: Y_J = L_JJ^{-1} (B_J - sum L_Jk Y_k).  ctl: the status word, then
+ * from word 3 the ticket, the strip flags, the flags of the right-hand sides'
+ * columns; behind the control words the flags of the block rows and columns, a
+ * cache line each, then the packs of the last two diagonal tiles.  A pack is
+ * free again when every tile of its step is finished. */
+constexpr int kFlowLine = 32; /* ints of a cache line */
+template <typename T> struct DenseFlow {
+    T *A, *B;
+    int64_t lda, ldb;
+    int n, nb, nrhs, nbc, line; /* line: ints from one flag to the next */
+    int *ctl, *flags;
+    T *packs;
+    long limit;
+    static constexpr bool joined = true;
+    __device__ __forceinline__ T *tile(int I, int K) const
+    {
+        return K < nb ? A + (int64_t)I * TB * lda + K * TB : B + (int64_t)I * TB * ldb + (K - nb) * TB;
+    }
+    __device__ __forceinline__ int64_t ld(int K) const { return K < nb ? lda : ldb; }
+    __device__ __forceinline__ int rows(int I) const { return min(TB, I < nb ? n - I * TB : nrhs - (I - nb) * TB); }
+    __device__ __forceinline__ int valid(int I) const { return rows(I); }
+    __device__ __forceinline__ int first(int, int) const { return 0; }
+    __device__ __forceinline__ bool has_l(int, int) const { return true; }
+    __device__ __forceinline__ bool has_u(int, int) const { return true; }
+    __device__ __forceinline__ int lcount(int, int J) const { return J; }
+    __device__ __forceinline__ int ucount(int, int J) const { return J; }
+    __device__ __forceinline__ bool next(int J, int I) const { return I == J + 1 && I < nb; }
+    __device__ __forceinline__ bool publish(int J) const { return J + 1 < nb || nbc > 0; }
+    __device__ __forceinline__ int *status() const { return ctl; }
+    __device__ __forceinline__ int *ticket() const { return ctl + 3; }
+    __device__ __forceinline__ int *dflag(int J) const { return ctl + 4 + J; }
+    __device__ __forceinline__ int *lflag(int I) const { return flags + line * I; }
+    __device__ __forceinline__ int *uflag(int K) const
+    {
+        return K < nb ? flags + line * (nb + K) : ctl + 4 + K;
+    }
+    __device__ __forceinline__ T *pack(int J) const { return packs + (J & 1) * TB * 16; }
+    __device__ __forceinline__ int tiles(int J) const { return 1 + 2 * (nb - 1 - J) + nbc; } /* of step J */
+    __device__ __forceinline__ void guard(int J) const
+    {
+        const int rows = nb - (J - 1); /* block rows below and columns right of tile J - 2 */
+        for (int e = (int)threadIdx.x - NT; J >= 2 && e < 2 * rows + nbc; e += NTP - NT) {
+            const int *flag = e < rows ? lflag(J - 1 + e) : uflag(J - 1 + e - rows);
+            long spins = 0;
+            while (load_coherent(flag) < 16 * (J - 1)) {
+                __builtin_amdgcn_s_sleep(1);
+                if (wait_give_up(status(), ++spins, limit))
+                    break;
+            }
+        }
+    }
+};
+template <typename T> __global__ __launch_bounds__(NTP, 2) void k_flow(DenseFlow<T> f, int32_t *info)
+{
+    __shared__ FlowSmem<T> sm;
+    if (threadIdx.x == 0) {
+        sm.ticket = atomicAdd(f.ticket(), 1);
+        sm.seen[0] = sm.seen[1] = sm.seen[2] = 0;
+    }
+    __syncthreads();
+    int q = __builtin_amdgcn_readfirstlane(sm.ticket), J = 0;
+    while (J < f.nb && q >= f.tiles(J))
+        q -= f.tiles(J++);
+    if (J == f.nb) { /* counter not reset: refuse */
+        if (threadIdx.x == 0)
+            atomicOr(f.status(), 2);
+        return;
+    }
+    if (q == 0) {
+        __builtin_amdgcn_s_setprio(3); /* the chain, ahead of its compute unit's other waves */
+        flow_diagonal<T>(f, J, info, sm);
+        return;
+    }
+    if (threadIdx.x >= NT)
+        return;
+    q -= 1;
+    const int m = f.nb - 1 - J;
+    if (q < 2)
+        __builtin_amdgcn_s_setprio(2);
+    if (q < 2 * m && (q & 1) == 0)
+        flow_panel<T, true>(f, J, J + 1 + (q >> 1), sm);
+    else
+        flow_panel<T, false>(f, J, q < 2 * m ? J + 1 + (q >> 1) : f.nb + q - 2 * m, sm);
+}
+
+/* Ints from one flag of a block row or column to the next: a cache line, or
+ * less where there are more than the room in front of the two packs (of the
+ * 64 x 64 elements that a block step's pack takes) holds. */
+template <typename T> static int flow_line(int nb)
+{
+    const size_t room = (factor_pg_bytes(sizeof(T)) - 2 * TB * 16 * sizeof(T)) / sizeof(int);
+    int line = kFlowLine;
+    while (line > 1 && (size_t)2 * nb * line > room)
+        line /= 2;
+    return (size_t)2 * nb * line <= room ? line : 0;
+}
+
+/* Whether the factor runs as one dataflow launch.  FP64 | FP32, us, dataflow
+ * against block steps: n = 256 69 against 75 | 66, 66; 1024 270, 298 | 247, 261;
+ * 4096 1207, 2031 | 1253, 1483; 8192 7328, 9625 | 4470, 6662; 16384 58.2, 61.8
+ * ms | 32.4, 36.2; 24576 193, 201 | 107, 108; 32768 449, 469 | 251, 236: the
+ * block steps' taller FP32 tiles win once there is nothing but update work.
+ * Block-step launches that are to be measured, deferral that is asked for at
+ * every size (defer_above 0) and the other factor variants stay launches. */
+constexpr int kFlowF32 = 28672;
+template <typename T>
+static bool use_flow(int n, int nrhs, const DenseTuning &tun, const UpdateProfile *pr)
+{
+    const int nb = (n + TB - 1) / TB, nbc = (nrhs + TB - 1) / TB;
+    return (sizeof(T) == 8 || n <= kFlowF32) && tun.lookahead && tun.defer_above > 0 && flow_line<T>(nb) > 0 && !(pr && !pr->flops.empty()) &&
+           (size_t)(4 + nb + nbc) * sizeof(int) <= factor_ctl_bytes(n);
+}
+/* Words of the workspace to clear before a factor: the control words and, right
+ * behind them, the dataflow's flags. */
+template <typename T> static int factor_words(int n)
+{
+    const int nb = (n + TB - 1) / TB;
+    return (int)(factor_ctl_bytes(n) / sizeof(int)) + 2 * nb * flow_line<T>(nb);
+}
+template <typename T>
+static hipError_t factor_flow(T *A, int64_t lda, int n, int32_t *info, void *ws, const DenseTuning &tun, hipStream_t st,
+                              T *B, int64_t ldb, int nrhs)
+{
+    char *p = static_cast<char *>(ws) + factor_ctl_bytes(n);
+    DenseFlow<T> f;
+    f.A = A, f.B = B, f.lda = lda, f.ldb = ldb, f.n = n, f.nb = (n + TB - 1) / TB;
+    f.nrhs = B ? nrhs : 0, f.nbc = (f.nrhs + TB - 1) / TB;
+    f.ctl = static_cast<int *>(ws), f.flags = reinterpret_cast<int *>(p);
+    f.line = flow_line<T>(f.nb);
+    f.packs = reinterpret_cast<T *>(p + factor_pg_bytes(sizeof(T))) - 2 * TB * 16;
+    f.limit = tun.wait_limit > 0 ? (long)tun.wait_limit : 1L << 24;
+    hipLaunchKernelGGL(k_flow<T>, dim3(f.nb * (f.nb + f.nbc)), dim3(NTP), 0, st, f, info);
+    return hipGetLastError();
 }
 
 template <typename T>
@@ -794,10 +1231,12 @@ hipError_t dense_factor(T *A, int64_t lda, int n, int32_t *info, void *ws, const
     int *ctl = static_cast<int *>(ws);
     T *Pg = reinterpret_cast<T *>(static_cast<char *>(ws) + factor_ctl_bytes(n));
     if (!prefilled) { /* status word and the block steps' counters */
-        hipError_t e = fill_i32(ctl, kCtlHead + 2 * (int64_t)((n + TB - 1) / TB), 0, st);
+        hipError_t e = fill_i32(ctl, factor_words<T>(n), 0, st);
         if (e != hipSuccess)
             return e;
     }
+    if (use_flow<T>(n, B ? nrhs : 0, tun, pr))
+        return factor_flow(A, lda, n, info, ws, tun, st, B, ldb, nrhs);
     if (tun.lookahead)
         return factor_lookahead(A, lda, n, info, Pg, ctl, tun, pr, st, B, ldb, nrhs, prefilled);
     return factor_phases(A, lda, n, info, Pg, tun, pr, st, B, ldb, nrhs);
@@ -842,7 +1281,7 @@ hipError_t factor_solve(T *A, int64_t lda, int n, int32_t *info, void *ws, int c
     /* the exchange rows are marked here when one chunk at a time uses them */
     const bool mark = nrhs > 0 && (chunks == 1 || nrhs <= 16);
     const int64_t nxb = mark ? (int64_t)(kTrsvHelpers + 1) * nb * TB * 16 : 0;
-    hipError_t e = solve_init<T>(ctl, kCtlHead + 2 * nb, info, xb, nxb, st);
+    hipError_t e = solve_init<T>(ctl, factor_words<T>(n), info, xb, nxb, st);
     if (e == hipSuccess)
         e = dense_factor<T>(A, lda, n, info, ws, tun, pr, st, B, ldb, nrhs, true);
     if (e != hipSuccess)
@@ -2759,297 +3198,6 @@ __global__ __launch_bounds__(NT) void k_sky_pack(SkyPlan pl, const int32_t *__re
         }
 }
 
-/* ------------------------------------------------- factor as a dataflow --- */
-
-/*
- * Blocked LU with the tiles as the units, one workgroup each, that wait for
- * the tiles they need instead of for a launch: tile (I, K) keeps its elements
- * in accumulators while it receives the products L_Ik U_kK (Eq. 6-c), k
- * ascending, as their operands appear, and then
- *   - K = I: is factored (tile_lu64, Eq. 6-a) and published a strip at a time;
- *   - K < I (I < K): is solved against the diagonal tile of block K (I), step p
- *     as soon as strip p is out.
- * The chain of the elimination is diagonal tile -> the two tiles below and
- * right of it -> next diagonal tile.  Those two are published 16 columns (rows)
- * at a time, as they are solved, and the next diagonal tile subtracts each
- * rank-16 product when it appears, its operands read straight to registers:
- * after the last strip one such product is left.
- *
- * Workgroups take their tiles from a ticket in the order of steps J: the
- * diagonal tile, then the tiles (I, J) below, then (J, K) right of it.  A tile
- * needs only tiles with smaller tickets, which run or have run, so that every
- * wait ends (they are bounded all the same, into the status word).
- *
- * What bounds it is the chain: per block 9 us for the diagonal tile, 1 us each
- * for a flag to be seen and for a strip to be loaded, on both hops, and the
- * last products.  Skyline systems, FP64, one launch per block step (the
- * trailing tiles updated by one product a launch) against this: n = 16384 with
- * half-widths up to 1024, 5.6 -> 4.07 ms (15.9 us a block); full profile of n =
- * 4096, 5.0 -> 2.7 ms, of n = 16384, 161 -> 68 ms.
- *
- * F describes the matrix: tile(I, J), pitch ld(), rows(I) of block I that
- * exist, first(I, K) the first k with a product; the flags lflag(I), uflag(K)
- * count 16 per finished tile of block row I's L part (block column K's U part),
- * 4 per strip, which finish in order, lcount(I, J), ucount(K, J) being the
- * tiles before (I, J), (J, K).  dflag(J) counts 4 per published strip of the
- * diagonal tile, and pack(J) holds the inverses of its diagonal blocks (64 x
- * 64, pitch 64).  Finished tiles are written through (store_coherent) and read
- * coherently or after an acquire; a waiting workgroup polls with one thread.
- */
-template <typename T> struct FlowSmem {
-    union alignas(16) {
-        StepSmem<T> tile;
-        char gemm[TileGemm<T, 2, 2>::LDS];
-    };
-    int seen[3]; /* flag values seen: L, U, strips */
-    int ticket, zero;
-};
-
-/* Returns (all threads) once *pa >= na and *pb >= nb (pb may be null); off the
- * chain a workgroup polls less often. */
-__device__ __forceinline__ void flow_wait(const int *pa, int na, int *sa, const int *pb, int nb, int *sb, int *status,
-                                          long limit, bool chain)
-{
-    if (threadIdx.x == 0 && (*sa < na || (pb && *sb < nb))) {
-        long spins = 0;
-        int va = *sa, vb = pb ? *sb : nb;
-        for (;;) {
-            if (va < na)
-                va = load_coherent(pa);
-            if (vb < nb)
-                vb = load_coherent(pb);
-            if (va >= na && vb >= nb)
-                break;
-            if (chain)
-                __builtin_amdgcn_s_sleep(1);
-            else
-                __builtin_amdgcn_s_sleep(16);
-            if (wait_give_up(status, ++spins, limit)) {
-                va = max(va, na);
-                vb = max(vb, nb);
-                break;
-            }
-        }
-        *sa = va;
-        if (pb)
-            *sb = vb;
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-    }
-    __syncthreads();
-}
-
-/* Adds c per wave to a flag, once the wave's stores have landed. */
-__device__ __forceinline__ void flow_count(int *flag, int c)
-{
-    __builtin_amdgcn_s_waitcnt(0);
-    if ((threadIdx.x & 63) == 0)
-        __hip_atomic_fetch_add(flag, c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-/* acc = C - sum of the products of tile (I, K), k < k1. */
-template <typename T, typename F>
-__device__ __forceinline__ void flow_products(typename vec4<T>::type (&acc)[2][2], const F &f, int I, int K, int k1,
-                                              bool chain, FlowSmem<T> &sm)
-{
-    const int nr = f.rows(I), nc = f.rows(K);
-    const T *C = f.tile(I, K);
-    for_tile<T, 2>([&](int bi, int bj, int r, int i, int j) {
-        acc[bi][bj][r] = C[(int64_t)min(i, nr - 1) * f.ld() + min(j, nc - 1)];
-    });
-    for (int k = f.first(I, K); k < k1; ++k) {
-        flow_wait(f.lflag(I), 16 * (f.lcount(I, k) + 1), sm.seen, f.uflag(K), 16 * (f.ucount(K, k) + 1), sm.seen + 1,
-                  f.status(), f.limit, chain);
-        tile_minus<T, 2>(acc, f.tile(I, k), f.ld(), nr, f.tile(k, K), f.ld(), nc, TB, sm.gemm);
-    }
-    __syncthreads(); /* the products' last operand reads */
-}
-
-/* Strip p of the factored diagonal tile D to LDS, by rows of the lower
- * operator, pitch DBP: rows 16p.. of columns 16p..16p+15 (L), or RIGHT the
- * columns 16p.. of rows 16p..16p+15 (U^T); its diagonal block from the pack. */
-template <typename T, bool RIGHT>
-__device__ __forceinline__ void flow_strip(T *dst, int p, const T *Pg, const T *D, int64_t ld)
-{
-    const int len = TB - 16 * p;
-    T v[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int idx = threadIdx.x + NT * i;
-        const int r = RIGHT ? 16 * p + idx / len : 16 * p + (idx >> 4);
-        const int c = RIGHT ? 16 * p + idx % len : 16 * p + (idx & 15);
-        v[i] = idx >= len * 16          ? T(0)
-               : (r >> 4) == (c >> 4)   ? load_coherent(Pg + r * TB + c)
-                                        : load_coherent(D + (int64_t)r * ld + c);
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int idx = threadIdx.x + NT * i;
-        if (idx < len * 16)
-            dst[RIGHT ? (16 * p + idx % len) * DBP + idx / len : (16 * p + (idx >> 4)) * DBP + (idx & 15)] = v[i];
-    }
-}
-
-/* Block step p of a wave's 16-wide slab (transposed for an L tile, X = A
- * U^{-1} solved as U^T X^T = A^T) against a staged strip. */
-template <typename T, bool RIGHT>
-__device__ __forceinline__ void flow_solve(typename vec4<T>::type (&a)[4], const T *strip, int p)
-{
-    typename vec4<T>::type x = {0, 0, 0, 0};
-    wave_mma16_acc<T>(
-        x,
-        [&](int r, int k) {
-            const T u = strip[(16 * p + r) * DBP + k];
-            return r > k ? u : (r == k ? (RIGHT ? u : T(1)) : T(0));
-        },
-        a[p]);
-    a[p] = x;
-#pragma unroll
-    for (int q = p + 1; q < 4; ++q)
-        wave_mma16_acc<T>(a[q], [&](int r, int k) { return -strip[(16 * q + r) * DBP + k]; }, a[p]);
-}
-
-/* Tile (I, J) below (RIGHT) or (J, I) right of the diagonal tile J. */
-template <typename T, bool RIGHT, typename F>
-__device__ __forceinline__ void flow_panel(const F &f, int J, int I, FlowSmem<T> &sm)
-{
-    typedef typename vec4<T>::type V;
-    const int r0 = RIGHT ? I : J, c0 = RIGHT ? J : I, nr = f.rows(r0), nc = f.rows(c0);
-    T *S = sm.tile.S, *G = f.tile(r0, c0);
-    const bool next = I == J + 1;  /* the next diagonal tile waits for it */
-    const bool chain = I <= J + 2; /* or the next but one */
-    V acc[2][2];
-    flow_products<T>(acc, f, r0, c0, J, chain, sm);
-    tile_to_lds<T, 2>(acc, S, nr, nc, false);
-    __syncthreads();
-    int *flag = RIGHT ? f.lflag(I) : f.uflag(I), *seen = sm.seen + (RIGHT ? 0 : 1);
-    const int before = 16 * (RIGHT ? f.lcount(I, J) : f.ucount(I, J)); /* a row's (column's) tiles count in order */
-    const int w = wave_id(), l = threadIdx.x & 63, lr = l & 15, lk = l >> 4;
-    const bool ok = 16 * w + lr < (RIGHT ? nr : nc);
-    V a[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-            a[q][r] = RIGHT ? S[(16 * w + lr) * LDT + 16 * q + acc_row<T>(lk, r)]
-                            : S[(16 * q + acc_row<T>(lk, r)) * LDT + 16 * w + lr];
-    if (next)
-        flow_wait(flag, before, seen, nullptr, 0, nullptr, f.status(), f.limit, chain);
-#pragma unroll
-    for (int p = 0; p < 4; ++p) {
-        flow_wait(f.dflag(J), 4 * p + 4, sm.seen + 2, nullptr, 0, nullptr, f.status(), f.limit, chain);
-        flow_strip<T, RIGHT>(sm.tile.P, p, f.pack(J), f.tile(J, J), f.ld());
-        if (next && p > 0) /* the strip before; its stores landed with this one's loads */
-            flow_count(flag, 1);
-        __syncthreads();
-        flow_solve<T, RIGHT>(a, sm.tile.P, p);
-        if (next) {
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int k = 16 * p + acc_row<T>(lk, r), o = 16 * w + lr;
-                if (ok)
-                    store_coherent(G + (RIGHT ? (int64_t)o * f.ld() + k : (int64_t)k * f.ld() + o), a[p][r]);
-            }
-        }
-    }
-    if (next) {
-        flow_count(flag, 1);
-        return;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-            S[RIGHT ? (16 * w + lr) * LDT + 16 * q + acc_row<T>(lk, r)
-                    : (16 * q + acc_row<T>(lk, r)) * LDT + 16 * w + lr] = a[q][r];
-    __syncthreads();
-    tile_xfer<T>([&](int r, int c) { return S[r * LDT + c]; },
-                 [&](int r, int c, T v) {
-                     if (r < nr && c < nc)
-                         store_coherent(G + (int64_t)r * f.ld() + c, v);
-                 });
-    flow_wait(flag, before, seen, nullptr, 0, nullptr, f.status(), f.limit, chain);
-    flow_count(flag, 4);
-}
-
-/* Diagonal tile J. */
-template <typename T, typename F>
-__device__ __forceinline__ void flow_diagonal(const F &f, int J, int32_t *info, FlowSmem<T> &sm)
-{
-    typedef typename vec4<T>::type V;
-    const int nr = f.rows(J), valid = f.valid(J), w = wave_id(), l = threadIdx.x & 63, lr = l & 15, lk = l >> 4;
-    const bool last = J > 0 && f.has_l(J, J - 1) && f.has_u(J - 1, J); /* a product with block J - 1 */
-    T *S = sm.tile.S, *D = f.tile(J, J);
-    constexpr bool chain = true;
-    const bool pub = f.publish(J);
-    if (w >= NT / 64) { /* the publishing waves: past the barriers of the others up to tile_lu64 */
-        if (!pub)
-            return;
-        const int products = max(0, J - 1 - f.first(J, J));
-        for (int b = products * (1 + TB / 16) + 2 + (last ? 3 : 0); b > 0; --b)
-            __syncthreads();
-        publish_strips<DBP>(S, sm.tile.P, f.pack(J), D, f.ld(), valid, f.dflag(J));
-        return;
-    }
-    V acc[2][2];
-    flow_products<T>(acc, f, J, J, J - 1, chain, sm);
-    tile_to_lds<T, 2>(acc, S, valid, valid, true);
-    __syncthreads();
-    if (last) {
-        const T *TL = f.tile(J, J - 1), *TU = f.tile(J - 1, J);
-        const int fl = 16 * f.lcount(J, J - 1), fu = 16 * f.ucount(J, J - 1);
-        V d[4];
-#pragma unroll
-        for (int c = 0; c < 4; ++c)
-#pragma unroll
-            for (int r = 0; r < 4; ++r)
-                d[c][r] = S[(16 * w + acc_row<T>(lk, r)) * LDT + 16 * c + lr];
-        /* rows and columns past the matrix end: the last one again, dropped below */
-        const int64_t row = (int64_t)min(16 * w + lr, nr - 1) * f.ld();
-        /* two strips at a time: a wait and the loads cost more than a strip's
-         * products */
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            flow_wait(f.lflag(J), fl + 8 * h + 8, sm.seen, f.uflag(J), fu + 8 * h + 8, sm.seen + 1, f.status(), f.limit,
-                      chain);
-            T a[8], b[4][8];
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const int k = 32 * h + 16 * (e >> 2) + acc_row<T>(lk, e & 3);
-                a[e] = load_coherent(TL + row + k);
-#pragma unroll
-                for (int c = 0; c < 4; ++c)
-                    b[c][e] = load_coherent(TU + (int64_t)k * f.ld() + min(16 * c + lr, nr - 1));
-            }
-#pragma unroll
-            for (int e = 0; e < 8; ++e)
-#pragma unroll
-                for (int c = 0; c < 4; ++c)
-                    d[c] = mfma16(-a[e], b[c][e], d[c]);
-        }
-#pragma unroll
-        for (int c = 0; c < 4; ++c)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int i = 16 * w + acc_row<T>(lk, r), j = 16 * c + lr;
-                if (i < valid && j < valid)
-                    S[i * LDT + j] = d[c][r];
-            }
-        __syncthreads();
-    }
-    const int z = tile_lu64<T, true>(S, sm.tile.P, (T *)nullptr, valid, &sm.zero);
-    if (!pub)
-        lds_store_tile(S, D, f.ld(), valid, valid);
-    if (threadIdx.x == 0 && info && z) { /* the smallest over the diagonal tiles */
-        const int at = J * TB + z;
-        int was = 0;
-        while (!__hip_atomic_compare_exchange_strong(info, &was, at, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
-                                                     __HIP_MEMORY_SCOPE_AGENT) &&
-               (was == 0 || was > at))
-            ;
-    }
-}
-
 /* The cnt-th of the indices x >= from, x < nt, with X(x) <= lim, or -1. */
 template <typename X> __device__ __forceinline__ int sky_nth(X &&first, int from, int nt, int lim, int cnt)
 {
@@ -3075,8 +3223,8 @@ template <typename X> __device__ __forceinline__ int sky_nth(X &&first, int from
 /* Skyline LU on the envelope tiles as a dataflow (above), restricted to the
  * envelope, which the elimination keeps: if L_Ik and U_kK exist, so does tile
  * (I, K).  Tiles outside stay zero and are never touched.  ctl: the status word
- * and the ticket.  A block's flags lie in its pack, in parts that the diagonal
- * blocks leave free, each in a cache line of its own: side by side in the
+ * and the ticket.  A block's flags lie behind its diagonal blocks' inverses,
+ * each in a cache line of its own: side by side in the
  * control words the polls for all of them met in a few lines (18.2 -> 21.7 us a
  * block). */
 struct SkyOrder {
@@ -3088,7 +3236,10 @@ struct SkyFlow {
     int *ctl;
     long limit;
     __device__ __forceinline__ double *tile(int I, int J) const { return sky_tile(pl, tiles, I, J); }
-    __device__ __forceinline__ static constexpr int ld() { return TB; }
+    static constexpr bool joined = false;
+    __device__ __forceinline__ static constexpr int ld(int) { return TB; }
+    __device__ __forceinline__ static bool next(int J, int I) { return I == J + 1; }
+    __device__ __forceinline__ static void guard(int) {}
     __device__ __forceinline__ int rows(int) const { return TB; } /* zero-padded */
     __device__ __forceinline__ int valid(int I) const { return min(TB, pl.n - I * TB); }
     __device__ __forceinline__ int first(int I, int K) const { return max(pl.F(I), pl.G(K)); }
@@ -3098,10 +3249,10 @@ struct SkyFlow {
     __device__ __forceinline__ int ucount(int K, int J) const { return J - pl.G(K); }
     __device__ __forceinline__ bool publish(int J) const { return order_n > 1; }
     __device__ __forceinline__ int *status() const { return ctl; }
-    __device__ __forceinline__ int *lflag(int I) const { return reinterpret_cast<int *>(pack(I) + 48); }
-    __device__ __forceinline__ int *uflag(int K) const { return reinterpret_cast<int *>(pack(K) + TB + 48); }
+    __device__ __forceinline__ int *lflag(int I) const { return reinterpret_cast<int *>(pack(I) + TB * 16 + 16); }
+    __device__ __forceinline__ int *uflag(int K) const { return reinterpret_cast<int *>(pack(K) + TB * 16 + 32); }
     __device__ __forceinline__ double *pack(int J) const { return P + (int64_t)J * TB * TB; }
-    __device__ __forceinline__ int *dflag(int J) const { return reinterpret_cast<int *>(pack(J) + 32); }
+    __device__ __forceinline__ int *dflag(int J) const { return reinterpret_cast<int *>(pack(J) + TB * 16); }
     int order_n; /* tiles of this workgroup's step */
 };
 __global__ __launch_bounds__(NT) void k_sky_clear(SkyPlan pl, double *P, int *ctl, int32_t *info)
@@ -3109,8 +3260,8 @@ __global__ __launch_bounds__(NT) void k_sky_clear(SkyPlan pl, double *P, int *ct
     for (int i = threadIdx.x; i < kCtlHead + 2 * pl.nt; i += NT)
         ctl[i] = 0;
     for (int b = threadIdx.x; b < pl.nt; b += NT) {
-        double *pb = P + (int64_t)b * TB * TB;
-        pb[32] = pb[48] = pb[TB + 48] = 0.0;
+        double *flags = P + (int64_t)b * TB * TB + TB * 16;
+        flags[0] = flags[16] = flags[32] = 0.0;
     }
     if (threadIdx.x == 0 && info)
         *info = 0;
@@ -3837,8 +3988,8 @@ hipError_t mixed_init(int n, int nrhs, int *ctl, int32_t *info, int *conv, unsig
                       unsigned long long *rbits, unsigned long long *xbits, int32_t *iters, float *xb, hipStream_t st)
 {
     const int64_t nxb = mixed_marks(n, 1);
-    hipLaunchKernelGGL(k_mixed_init, dim3(mark_grid(nxb)), dim3(256), 0, st, ctl, kCtlHead + 2 * ((n + TB - 1) / TB), info,
-                       conv, mbits, rbits, xbits, iters, nrhs, reinterpret_cast<unsigned int *>(xb), nxb);
+    hipLaunchKernelGGL(k_mixed_init, dim3(mark_grid(nxb)), dim3(256), 0, st, ctl, factor_words<float>(n), info, conv,
+                       mbits, rbits, xbits, iters, nrhs, reinterpret_cast<unsigned int *>(xb), nxb);
     return hipGetLastError();
 }
 
