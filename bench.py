@@ -33,7 +33,7 @@ PEAK_FP64_TFLOPS = 78.6
 PEAK_FP32_TFLOPS = 157.3
 PEAK_HBM_GBS = 8000.0
 COPY_CAL_BYTES = 256 << 20  # plain device copy used to calibrate the HBM byte counters
-TRAFFIC_FILE = os.path.join(ROOT, "profiles", "k_step_dense_n4096_hbm_traffic.json")
+TRAFFIC_FILE = os.path.join(ROOT, "profiles", "k_flow_dense_n4096_hbm_traffic.json")
 KERNEL_SOURCES = ["paper_1907_05767_amd/csrc/ebv_kernels.hip", "paper_1907_05767_amd/csrc/ebv_device.hpp"]
 
 
@@ -49,7 +49,7 @@ def kernel_source_hash() -> str:
 
 
 def stored_traffic():
-    """HBM bytes per k_step launch from the committed counter summary, or
+    """HBM bytes per k_flow launch from the committed counter summary, or
     None when it is missing or was taken on different kernel sources."""
     try:
         with open(TRAFFIC_FILE) as fh:
@@ -65,7 +65,7 @@ def summarize_counters(fetch_dir: str, write_dir: str):
     """Build the traffic summary from two rocprofv3 --pmc runs of
     `bench.py --steps 1 --warmup 0 --no-secondary --no-cpu-baseline
     --copy-calibration` (FETCH_SIZE, then WRITE_SIZE): per-dispatch KiB of the
-    k_step launches, scaled by what the same counter reads for the plain
+    k_flow launches, scaled by what the same counter reads for the plain
     copy of COPY_CAL_BYTES."""
     import csv
     import glob
@@ -75,18 +75,18 @@ def summarize_counters(fetch_dir: str, write_dir: str):
         if not f:
             raise SystemExit(f"no counter_collection.csv under {d}")
         rows = [r for r in csv.DictReader(open(f[0])) if r.get("Counter_Name") == counter]
-        step = [float(r["Counter_Value"]) for r in rows if "k_step<double" in r["Kernel_Name"]]
+        step = [float(r["Counter_Value"]) for r in rows if "k_flow<double" in r["Kernel_Name"]]
         copy = [float(r["Counter_Value"]) for r in rows
                 if "copyBuffer" in r["Kernel_Name"] or "copy" in r["Kernel_Name"].lower()]
         if not step or not copy:
-            raise SystemExit(f"{counter}: no k_step or copy dispatches in {f[0]}")
+            raise SystemExit(f"{counter}: no k_flow or copy dispatches in {f[0]}")
         cal = max(copy) * 1024.0 / COPY_CAL_BYTES  # counter bytes per true byte
         return sum(step) * 1024.0 / cal, len(step), cal
 
     rd, nl, cal_r = read(fetch_dir, "FETCH_SIZE")
     wr, nl2, cal_w = read(write_dir, "WRITE_SIZE")
     rec = {
-        "kernel": "k_step (dense factor block step, FP64)", "workload": "dense FP64 n=4096, 8 RHS",
+        "kernel": "k_flow (dense factor, FP64)", "workload": "dense FP64 n=4096, 8 RHS",
         "launches": nl, "read_bytes_per_launch": rd / nl, "write_bytes_per_launch": wr / nl2,
         "bytes_per_launch": rd / nl + wr / nl2,
         "copy_calibration": {"bytes": COPY_CAL_BYTES, "fetch_counter_bytes_per_byte": cal_r,
@@ -752,7 +752,7 @@ def main():
     ap.add_argument("--copy-calibration", action="store_true",
                     help="after the timed steps, run a plain device copy of 256 MiB (HBM counter calibration)")
     ap.add_argument("--summarize-counters", nargs=2, metavar=("FETCH_DIR", "WRITE_DIR"),
-                    help="write the k_step HBM traffic summary from two rocprofv3 --pmc runs and exit")
+                    help="write the k_flow HBM traffic summary from two rocprofv3 --pmc runs and exit")
     ap.add_argument("--summarize-trace", nargs=4, metavar=("TRACE_DIR", "WORKLOAD", "COMMAND", "OUT"),
                     help="write a kernel-trace summary (markdown) from a rocprofv3 --stats csv run and exit")
     ap.add_argument("--line", default=None,
@@ -813,7 +813,7 @@ def main():
         step(i)
     torch.cuda.synchronize()
     wall = time.perf_counter() - t0
-    # instrumented pass over K more pristine copies: every block-step launch
+    # instrumented pass over K more pristine copies: every factor launch
     # bracketed by HIP events on its stream (the events add a few microseconds
     # per launch, so they stay out of the timed pass)
     nupd = (n + 63) // 64
@@ -839,7 +839,7 @@ def main():
         torch.cuda.synchronize()
         del src, dst
     achieved = upd_flops / (upd_ms / 1e3) / 1e12 if upd_ms > 0 else None
-    roof = {"kernel": "k_step (block step: rank-64 trailing update on FP64 MFMA 16x16x4 + diagonal tile + panel)",
+    roof = {"kernel": "k_flow (the factor: rank-64 updates on FP64 MFMA 16x16x4 + diagonal tiles + panels, one launch)",
             "bound": "mfma",
             "achieved": achieved, "peak": PEAK_FP64_TFLOPS, "unit": "TFLOP/s",
             "frac": (achieved / PEAK_FP64_TFLOPS) if achieved else None, "traffic": stored_traffic(),

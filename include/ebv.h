@@ -139,11 +139,13 @@ size_t ebv_workspace_size(int op, ebv_dtype dtype, int64_t n, int64_t nrhs, int6
 /* Tuning of the single-system factor (ebv_lu_factor with batch = 1 and
  * ebv_lu_factor_solve) held by handle h.  small_update_below: the FP32
  * factor's update tiles are 128 x 64 while the trailing block is larger than
- * this, else 64 x 64 (default 0; FP64 update tiles are 64 x 64).  lookahead: 1 (default) runs one launch per 64-wide block step,
+ * this, else 64 x 64 (default 0; FP64 update tiles are 64 x 64).  lookahead: 1 (default) runs the whole
+ * elimination in one launch, its tiles waiting for each other (FP32 up to n =
+ * 28672), and beyond that, or with defer_above 0, one launch per 64-wide block step,
  * in which the next diagonal tile and panel are formed while the trailing
  * update of the current step runs; 0 runs the panel and the update as
  * separate launches.  defer_group G (1..4, default 3) and defer_above
- * (default 1024), look-ahead only: while the trailing block is larger than
+ * (default 1024), block steps with look-ahead only: while the trailing block is larger than
  * defer_above, block column J is brought up to date only in every G-th
  * launch (those with (s + 1) mod G = J mod G) with K = 64 G, so the trailing
  * block is read and written once per G steps and each launch updates about
@@ -169,10 +171,11 @@ int ebv_get_batched_tuning(ebv_handle h, ebv_dtype dtype, int mixed, int *wg_per
  * that call are invalid.  Small values exist to exercise that path. */
 int ebv_set_wait_limit(ebv_handle h, int64_t spins);
 
-/* Measurement of the block-step kernel of the single-system factor.
+/* Measurement of the elimination kernel of the single-system factor.
  * ebv_profile_update_enable(h, m): create 2*m events up front (on the current
- * device); each later block-step launch of a factor made with h (batch = 1)
- * is then bracketed by an event pair on its stream, up to m launches; m = 0
+ * device); each later launch of it in a factor made with h (batch = 1; one per
+ * factor, or one per block step where the factor runs in steps) is then
+ * bracketed by an event pair on its stream, up to m launches; m = 0
  * turns this off and destroys the events.  ebv_profile_update_read
  * synchronizes on the recorded events and returns (and resets) the summed
  * elapsed milliseconds, the number of launches and their summed algorithmic
@@ -196,7 +199,8 @@ int ebv_profile_update_read(ebv_handle h, double *ms_total, int64_t *launches, d
  *          control words first (the status word at offset 0, two words of a
  *          solve that may follow, then two per 64-wide block step, the whole
  *          rounded up to 256 bytes), then the current diagonal tile's pack
- *          for the panel solves (64*64 elements); none when batch > 1 (ws may
+ *          for the panel solves (64*64 elements), or the flags and packs of
+ *          the one-launch factor in the same bytes; none when batch > 1 (ws may
  *          then be NULL).
  * Single systems (batch = 1) use a multi-workgroup blocked factorization;
  * batch > 1 factors one system per workgroup and needs

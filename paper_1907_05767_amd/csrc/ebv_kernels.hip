@@ -2,11 +2,15 @@
  * HIP kernels and their launchers for libebv (gfx950).
  *
  * Dense single system (Eq. 6-a/6-c applied 64 steps at a time):
- *   k_step    one launch per 64-wide block step (the default schedule): the
- *             diagonal tile's update and factor, the panel tiles solved
- *             against it strip by strip, and the update of the trailing
- *             region's column classes that are due, as ticket-ordered work
- *             items;
+ *   k_flow    the whole factor in one launch (the default schedule): a
+ *             workgroup per 64 x 64 tile, which receives its products as
+ *             their operands are finished and is factored or solved at the
+ *             end; k_sky_factor is the same on a skyline's tiles;
+ *   k_step    one launch per 64-wide block step (very large FP32 systems, or
+ *             by tuning): the diagonal tile's update and factor, the panel
+ *             tiles solved against it strip by strip, and the update of the
+ *             trailing region's column classes that are due, as
+ *             ticket-ordered work items;
  *   k_diag, k_panel, k_update: the schedule without look-ahead (one launch
  *             per phase), kept as a tuning choice.
  * Triangular solves (Eq. 1): k_trsv, three workgroups per 64-row block (two
@@ -1184,14 +1188,13 @@ template <typename T> static int flow_line(int nb)
  * 4096 1207, 2031 | 1253, 1483; 8192 7328, 9625 | 4470, 6662; 16384 58.2, 61.8
  * ms | 32.4, 36.2; 24576 193, 201 | 107, 108; 32768 449, 469 | 251, 236: the
  * block steps' taller FP32 tiles win once there is nothing but update work.
- * Block-step launches that are to be measured, deferral that is asked for at
- * every size (defer_above 0) and the other factor variants stay launches. */
+ * Deferral that is asked for at every size (defer_above 0) and the other factor
+ * variants stay launches. */
 constexpr int kFlowF32 = 28672;
-template <typename T>
-static bool use_flow(int n, int nrhs, const DenseTuning &tun, const UpdateProfile *pr)
+template <typename T> static bool use_flow(int n, int nrhs, const DenseTuning &tun)
 {
     const int nb = (n + TB - 1) / TB, nbc = (nrhs + TB - 1) / TB;
-    return (sizeof(T) == 8 || n <= kFlowF32) && tun.lookahead && tun.defer_above > 0 && flow_line<T>(nb) > 0 && !(pr && !pr->flops.empty()) &&
+    return (sizeof(T) == 8 || n <= kFlowF32) && tun.lookahead && tun.defer_above > 0 && flow_line<T>(nb) > 0 &&
            (size_t)(4 + nb + nbc) * sizeof(int) <= factor_ctl_bytes(n);
 }
 /* Words of the workspace to clear before a factor: the control words and, right
@@ -1202,8 +1205,8 @@ template <typename T> static int factor_words(int n)
     return (int)(factor_ctl_bytes(n) / sizeof(int)) + 2 * nb * flow_line<T>(nb);
 }
 template <typename T>
-static hipError_t factor_flow(T *A, int64_t lda, int n, int32_t *info, void *ws, const DenseTuning &tun, hipStream_t st,
-                              T *B, int64_t ldb, int nrhs)
+static hipError_t factor_flow(T *A, int64_t lda, int n, int32_t *info, void *ws, const DenseTuning &tun,
+                              UpdateProfile *pr, hipStream_t st, T *B, int64_t ldb, int nrhs)
 {
     char *p = static_cast<char *>(ws) + factor_ctl_bytes(n);
     DenseFlow<T> f;
@@ -1213,8 +1216,16 @@ static hipError_t factor_flow(T *A, int64_t lda, int n, int32_t *info, void *ws,
     f.line = flow_line<T>(f.nb);
     f.packs = reinterpret_cast<T *>(p + factor_pg_bytes(sizeof(T))) - 2 * TB * 16;
     f.limit = tun.wait_limit > 0 ? (long)tun.wait_limit : 1L << 24;
+    double fl = 0.0; /* update flops: step k takes 2 * 64 for each element of the region past its panel */
+    for (int e0 = TB; e0 < n; e0 += TB)
+        fl += 2.0 * TB * (double)(n - e0) * (double)(n - e0);
+    int pslot = -1;
+    const bool prof = profile_slot(pr, st, fl, pslot);
     hipLaunchKernelGGL(k_flow<T>, dim3(f.nb * (f.nb + f.nbc)), dim3(NTP), 0, st, f, info);
-    return hipGetLastError();
+    const hipError_t e = hipGetLastError();
+    if (prof)
+        (void)hipEventRecord(pr->ev[2 * pslot + 1], st);
+    return e;
 }
 
 template <typename T>
@@ -1235,8 +1246,8 @@ hipError_t dense_factor(T *A, int64_t lda, int n, int32_t *info, void *ws, const
         if (e != hipSuccess)
             return e;
     }
-    if (use_flow<T>(n, B ? nrhs : 0, tun, pr))
-        return factor_flow(A, lda, n, info, ws, tun, st, B, ldb, nrhs);
+    if (use_flow<T>(n, B ? nrhs : 0, tun))
+        return factor_flow(A, lda, n, info, ws, tun, pr, st, B, ldb, nrhs);
     if (tun.lookahead)
         return factor_lookahead(A, lda, n, info, Pg, ctl, tun, pr, st, B, ldb, nrhs, prefilled);
     return factor_phases(A, lda, n, info, Pg, tun, pr, st, B, ldb, nrhs);
