@@ -790,6 +790,7 @@ template <typename T> struct FlowSmem {
  * diagonal blocks' inverses (pitch DBP); they go to D (n x n of it exist) and to
  * the pack Pg; flag counts 4 per strip. */
 constexpr int kPubWaves = 2, NTP = NT + 64 * kPubWaves;
+constexpr int kFlowWaves = 3; /* waves per SIMD: two workgroups per compute unit */
 template <typename T>
 __device__ __forceinline__ void publish_strips(const T *S, const T *P, T *Pg, T *D, int64_t ldd, int n, int *flag)
 {
@@ -1089,13 +1090,14 @@ __device__ __forceinline__ void flow_diagonal(const F &f, int J, int32_t *info, 
  * nb .. of U: Y_J = L_JJ^{-1} (B_J - sum L_Jk Y_k).  ctl: the status word, then
  * from word 3 the ticket, the strip flags, the flags of the right-hand sides'
  * columns; behind the control words the flags of the block rows and columns, a
- * cache line each, then the packs of the last two diagonal tiles.  A pack is
+ * cache line each, then the packs of the last two (three) diagonal tiles.  A pack is
  * free again when every tile of its step is finished. */
 constexpr int kFlowLine = 32; /* ints of a cache line */
-template <typename T> struct DenseFlow {
+template <typename T, bool WIDE> struct DenseFlow { /* WIDE: tickets in the order of pairs of steps */
     T *A, *B;
     int64_t lda, ldb;
     int n, nb, nrhs, nbc, line; /* line: ints from one flag to the next */
+    static constexpr int npacks = WIDE ? 3 : 2;
     int *ctl, *flags;
     T *packs;
     long limit;
@@ -1122,15 +1124,20 @@ template <typename T> struct DenseFlow {
     {
         return K < nb ? flags + line * (nb + K) : ctl + 4 + K;
     }
-    __device__ __forceinline__ T *pack(int J) const { return packs + (J & 1) * TB * 16; }
-    __device__ __forceinline__ int tiles(int J) const { return 1 + 2 * (nb - 1 - J) + nbc; } /* of step J */
+    __device__ __forceinline__ T *pack(int J) const { return packs + (J % npacks) * TB * 16; }
+    /* tiles of step J, or WIDE of the steps J, J + 1 */
+    __device__ __forceinline__ int tiles(int J) const
+    {
+        const bool pair = WIDE && J + 1 < nb;
+        return (pair ? 2 : 1) * (2 * (nb - 1 - J) + nbc) + (pair ? 0 : 1);
+    }
     __device__ __forceinline__ void guard(int J) const
     {
-        const int rows = nb - (J - 1); /* block rows below and columns right of tile J - 2 */
-        for (int e = (int)threadIdx.x - NT; J >= 2 && e < 2 * rows + nbc; e += NTP - NT) {
-            const int *flag = e < rows ? lflag(J - 1 + e) : uflag(J - 1 + e - rows);
+        const int done = J - npacks, rows = nb - 1 - done; /* block rows below and columns right of that tile */
+        for (int e = (int)threadIdx.x - NT; done >= 0 && e < 2 * rows + nbc; e += NTP - NT) {
+            const int *flag = e < rows ? lflag(done + 1 + e) : uflag(done + 1 + e - rows);
             long spins = 0;
-            while (load_coherent(flag) < 16 * (J - 1)) {
+            while (load_coherent(flag) < 16 * (done + 1)) {
                 __builtin_amdgcn_s_sleep(1);
                 if (wait_give_up(status(), ++spins, limit))
                     break;
@@ -1138,7 +1145,8 @@ template <typename T> struct DenseFlow {
         }
     }
 };
-template <typename T> __global__ __launch_bounds__(NTP, 2) void k_flow(DenseFlow<T> f, int32_t *info)
+template <typename T, bool WIDE>
+__global__ __launch_bounds__(NTP, kFlowWaves) void k_flow(DenseFlow<T, WIDE> f, int32_t *info)
 {
     __shared__ FlowSmem<T> sm;
     if (threadIdx.x == 0) {
@@ -1147,36 +1155,70 @@ template <typename T> __global__ __launch_bounds__(NTP, 2) void k_flow(DenseFlow
     }
     __syncthreads();
     int q = __builtin_amdgcn_readfirstlane(sm.ticket), J = 0;
-    while (J < f.nb && q >= f.tiles(J))
-        q -= f.tiles(J++);
-    if (J == f.nb) { /* counter not reset: refuse */
+    for (; J < f.nb && q >= f.tiles(J); J += WIDE ? 2 : 1)
+        q -= f.tiles(J);
+    if (J >= f.nb) { /* counter not reset: refuse */
         if (threadIdx.x == 0)
             atomicOr(f.status(), 2);
         return;
     }
-    if (q == 0) {
+    /* I: the tile's other block row or column.  One step: the diagonal tile,
+     * the tiles below and right of it in turn, the right-hand sides.  Two: their
+     * corner in the order of the chain, then the rows below and the columns
+     * right of it eight at a time, so that the two tiles of a row (column) are
+     * eight tickets apart, which puts them on one XCD as workgroups are dealt
+     * out, where they read the same operand from one L2; then the right-hand
+     * sides. */
+    int I = J;
+    bool lower = false;
+    const bool pair = WIDE && J + 1 < f.nb;
+    const int R = pair ? f.nb - 2 - J : f.nb - 1 - J;
+    if (!pair) {
+        lower = q > 0 && q <= 2 * R && (q & 1);
+        I = q == 0 ? J : (q <= 2 * R ? J + 1 + (q - 1) / 2 : f.nb + q - 1 - 2 * R);
+    } else if (q < 4) {
+        I = q == 0 ? J : J + 1;
+        lower = q == 1;
+        J += q == 3;
+    } else if (q < 4 + 4 * R) {
+        const int g = (q - 4) / 32, p = (q - 4) % 32, c8 = min(8, R - 8 * g), h = p / c8;
+        I = J + 2 + 8 * g + p % c8;
+        lower = (h & 1) == 0;
+        J += h >> 1;
+    } else {
+        q -= 4 + 4 * R;
+        I = f.nb + q % f.nbc;
+        J += q / f.nbc;
+    }
+    if (I == J) {
         __builtin_amdgcn_s_setprio(3); /* the chain, ahead of its compute unit's other waves */
         flow_diagonal<T>(f, J, info, sm);
         return;
     }
     if (threadIdx.x >= NT)
         return;
-    q -= 1;
-    const int m = f.nb - 1 - J;
-    if (q < 2)
+    if (I == J + 1)
         __builtin_amdgcn_s_setprio(2);
-    if (q < 2 * m && (q & 1) == 0)
-        flow_panel<T, true>(f, J, J + 1 + (q >> 1), sm);
+    if (lower)
+        flow_panel<T, true>(f, J, I, sm);
     else
-        flow_panel<T, false>(f, J, q < 2 * m ? J + 1 + (q >> 1) : f.nb + q - 2 * m, sm);
+        flow_panel<T, false>(f, J, I, sm);
 }
 
+/* Beyond this the tickets go by pairs of steps: what bounds the factor then is
+ * the operands' way past L2 (6 TB/s).  One step | two, ms: FP64 n = 4096 1.20 |
+ * 1.21, 6000 2.95 | 3.06, 8192 7.26 | 7.20, 16384 57.3 | 54.9; FP32 4096 1.26 |
+ * 1.28, 6000 2.24 | 2.23, 8192 4.54 | 4.28, 16384 32.3 | 30.0 (the mixed-
+ * precision solve of that size 38.9 | 36.6). */
+constexpr int kFlowWide = 7168;
+
 /* Ints from one flag of a block row or column to the next: a cache line, or
- * less where there are more than the room in front of the two packs (of the
+ * less where there are more than the room in front of the packs (of the
  * 64 x 64 elements that a block step's pack takes) holds. */
-template <typename T> static int flow_line(int nb)
+template <typename T> static int flow_line(int n)
 {
-    const size_t room = (factor_pg_bytes(sizeof(T)) - 2 * TB * 16 * sizeof(T)) / sizeof(int);
+    const int nb = (n + TB - 1) / TB, npacks = n > kFlowWide ? 3 : 2;
+    const size_t room = (factor_pg_bytes(sizeof(T)) - npacks * TB * 16 * sizeof(T)) / sizeof(int);
     int line = kFlowLine;
     while (line > 1 && (size_t)2 * nb * line > room)
         line /= 2;
@@ -1185,8 +1227,8 @@ template <typename T> static int flow_line(int nb)
 
 /* Whether the factor runs as one dataflow launch.  FP64 | FP32, us, dataflow
  * against block steps: n = 256 69 against 75 | 66, 66; 1024 270, 298 | 247, 261;
- * 4096 1207, 2031 | 1253, 1483; 8192 7328, 9625 | 4470, 6662; 16384 58.2, 61.8
- * ms | 32.4, 36.2; 24576 193, 201 | 107, 108; 32768 449, 469 | 251, 236: the
+ * 4096 1207, 2031 | 1253, 1483; 8192 7328, 9625 | 4470, 6662; 16384 54.9, 61.8
+ * ms | 30.0, 36.2; 24576 193, 201 | 107, 108; 32768 449, 469 | 251, 236: the
  * block steps' taller FP32 tiles win once there is nothing but update work.
  * Deferral that is asked for at every size (defer_above 0) and the other factor
  * variants stay launches. */
@@ -1194,7 +1236,7 @@ constexpr int kFlowF32 = 28672;
 template <typename T> static bool use_flow(int n, int nrhs, const DenseTuning &tun)
 {
     const int nb = (n + TB - 1) / TB, nbc = (nrhs + TB - 1) / TB;
-    return (sizeof(T) == 8 || n <= kFlowF32) && tun.lookahead && tun.defer_above > 0 && flow_line<T>(nb) > 0 &&
+    return (sizeof(T) == 8 || n <= kFlowF32) && tun.lookahead && tun.defer_above > 0 && flow_line<T>(n) > 0 &&
            (size_t)(4 + nb + nbc) * sizeof(int) <= factor_ctl_bytes(n);
 }
 /* Words of the workspace to clear before a factor: the control words and, right
@@ -1202,26 +1244,26 @@ template <typename T> static bool use_flow(int n, int nrhs, const DenseTuning &t
 template <typename T> static int factor_words(int n)
 {
     const int nb = (n + TB - 1) / TB;
-    return (int)(factor_ctl_bytes(n) / sizeof(int)) + 2 * nb * flow_line<T>(nb);
+    return (int)(factor_ctl_bytes(n) / sizeof(int)) + 2 * nb * flow_line<T>(n);
 }
-template <typename T>
+template <bool WIDE, typename T>
 static hipError_t factor_flow(T *A, int64_t lda, int n, int32_t *info, void *ws, const DenseTuning &tun,
                               UpdateProfile *pr, hipStream_t st, T *B, int64_t ldb, int nrhs)
 {
     char *p = static_cast<char *>(ws) + factor_ctl_bytes(n);
-    DenseFlow<T> f;
+    DenseFlow<T, WIDE> f;
     f.A = A, f.B = B, f.lda = lda, f.ldb = ldb, f.n = n, f.nb = (n + TB - 1) / TB;
     f.nrhs = B ? nrhs : 0, f.nbc = (f.nrhs + TB - 1) / TB;
     f.ctl = static_cast<int *>(ws), f.flags = reinterpret_cast<int *>(p);
-    f.line = flow_line<T>(f.nb);
-    f.packs = reinterpret_cast<T *>(p + factor_pg_bytes(sizeof(T))) - 2 * TB * 16;
+    f.line = flow_line<T>(n);
+    f.packs = reinterpret_cast<T *>(p + factor_pg_bytes(sizeof(T))) - f.npacks * TB * 16;
     f.limit = tun.wait_limit > 0 ? (long)tun.wait_limit : 1L << 24;
     double fl = 0.0; /* update flops: step k takes 2 * 64 for each element of the region past its panel */
     for (int e0 = TB; e0 < n; e0 += TB)
         fl += 2.0 * TB * (double)(n - e0) * (double)(n - e0);
     int pslot = -1;
     const bool prof = profile_slot(pr, st, fl, pslot);
-    hipLaunchKernelGGL(k_flow<T>, dim3(f.nb * (f.nb + f.nbc)), dim3(NTP), 0, st, f, info);
+    hipLaunchKernelGGL((k_flow<T, WIDE>), dim3(f.nb * (f.nb + f.nbc)), dim3(NTP), 0, st, f, info);
     const hipError_t e = hipGetLastError();
     if (prof)
         (void)hipEventRecord(pr->ev[2 * pslot + 1], st);
@@ -1247,7 +1289,8 @@ hipError_t dense_factor(T *A, int64_t lda, int n, int32_t *info, void *ws, const
             return e;
     }
     if (use_flow<T>(n, B ? nrhs : 0, tun))
-        return factor_flow(A, lda, n, info, ws, tun, pr, st, B, ldb, nrhs);
+        return n > kFlowWide ? factor_flow<true>(A, lda, n, info, ws, tun, pr, st, B, ldb, nrhs)
+                             : factor_flow<false>(A, lda, n, info, ws, tun, pr, st, B, ldb, nrhs);
     if (tun.lookahead)
         return factor_lookahead(A, lda, n, info, Pg, ctl, tun, pr, st, B, ldb, nrhs, prefilled);
     return factor_phases(A, lda, n, info, Pg, tun, pr, st, B, ldb, nrhs);
