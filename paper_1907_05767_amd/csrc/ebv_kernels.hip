@@ -2858,40 +2858,54 @@ template <bool FWD> __global__ __launch_bounds__(NT) void k_band_sweep_segments(
                             ybuf);
 }
 
-/* Whether the state T a segment started from is its predecessor's end S to
- * 2^-51 of the block's largest value in each right-hand side; the same in
- * every thread. */
-__device__ __forceinline__ bool band_same_state(const double *S, const double *T, double (*cmax)[16])
+/* Whether the state t that segment j + 1 started from is its predecessor's end
+ * s: each component to 2^-51 of the terms it was formed from, |z| + |M| |y_prev|
+ * at the predecessor's last position (y_prev stands in B), which is what that
+ * product's own rounding is measured by.  The largest value of the block is no
+ * measure: y scales with the rows of L (the columns of U), and in a block of two
+ * scales a small component's error would pass and reach the next block whole.
+ * The same in every thread; not a number, and a sum that overflows, never agree. */
+template <bool FWD> __device__ __forceinline__ bool band_same_state(const BandSweep &a, int j, int ch)
 {
-    const int w = wave_id(), l = threadIdx.x & 63;
-    const d4 s = band_y_load(S, w), t = band_y_load(T, w);
-    double m = fmax(fmax(fabs(s[0]), fabs(s[1])), fmax(fabs(s[2]), fabs(s[3])));
-    m = fmax(m, __shfl_xor(m, 16));
-    m = fmax(m, __shfl_xor(m, 32));
-    __syncthreads();
-    if (l < 16)
-        cmax[w][l] = m;
-    __syncthreads();
-    m = fmax(fmax(cmax[0][l & 15], cmax[1][l & 15]), fmax(cmax[2][l & 15], cmax[3][l & 15]));
+    typedef vec4<double>::type V;
+    const int w = wave_id(), l = threadIdx.x & 63, lr = l & 15, lk = l >> 4;
+    const int pos = (j + 1) * a.m - 1, b = band_blk<FWD>(a, pos), prev = band_blk<FWD>(a, pos - 1);
+    const d4 s = band_y_load(band_end<FWD>(a, j, ch), w), t = band_y_load(band_start<FWD>(a, j + 1, ch), w);
+    d4 bound = band_y_load(band_room(a, b) + ch * TB * 16, w);
+    V M[4];
+    band_pack_load(a.P + ((int64_t)b * kBandSolveTiles + (FWD ? 1 : 2)) * TB * TB, M);
+    const int c = 16 * ch + lr;
+    double y[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+        const int row = prev * TB + 16 * (i >> 2) + acc_row<double>(lk, i & 3);
+        const double v = a.B[(int64_t)min(row, a.n - 1) * a.ldb + min(c, a.nrhs - 1)];
+        y[i] = row < a.n && c < a.nrhs ? fabs(v) : 0.0;
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+        bound[r] = fabs(bound[r]);
+#pragma unroll
+    for (int i = 0; i < 16; ++i)
+        bound = mfma16(fabs(M[i >> 2][i & 3]), y[i], bound);
     bool same = true;
 #pragma unroll
     for (int r = 0; r < 4; ++r)
-        same = same && fabs(s[r] - t[r]) <= 0x1p-51 * m;
+        same = same && (s[r] == t[r] || (fabs(s[r] - t[r]) <= 0x1p-51 * bound[r] && bound[r] <= 0x1.fffffffffffffp1023));
     return __syncthreads_and(same);
 }
 
 template <bool FWD> __global__ __launch_bounds__(NT) void k_band_sweep_check(BandSweep a)
 {
-    __shared__ double cmax[4][16];
     const int j = blockIdx.x, ch = blockIdx.y;
-    const bool ok = band_same_state(band_end<FWD>(a, j, ch), band_start<FWD>(a, j + 1, ch), cmax);
+    const bool ok = band_same_state<FWD>(a, j, ch);
     if (threadIdx.x == 0)
         *band_ok<FWD>(a, j, ch) = ok;
 }
 
 template <bool FWD> __global__ __launch_bounds__(NT) void k_band_sweep_fix(BandSweep a, int nseg)
 {
-    __shared__ double ybuf[2][TB * 16], cmax[4][16];
+    __shared__ double ybuf[2][TB * 16];
     const int ch = blockIdx.x, nt = (a.n + TB - 1) / TB;
     bool mine = true;
     for (int j = threadIdx.x; j < nseg - 1; j += NT)
@@ -2900,8 +2914,7 @@ template <bool FWD> __global__ __launch_bounds__(NT) void k_band_sweep_fix(BandS
         return;
     bool redone = false; /* segment j was swept again */
     for (int j = 0; j < nseg - 1; ++j) {
-        const bool ok = redone ? band_same_state(band_end<FWD>(a, j, ch), band_start<FWD>(a, j + 1, ch), cmax)
-                               : *band_ok<FWD>(a, j, ch) != 0;
+        const bool ok = redone ? band_same_state<FWD>(a, j, ch) : *band_ok<FWD>(a, j, ch) != 0;
         redone = !ok;
         if (ok)
             continue;

@@ -112,3 +112,47 @@ def test_band_segments_zero_pivot(rows):
     info = ebv.lu_factor_band_(t, 64, 64)
     torch.cuda.synchronize()
     assert int(info.item()) == info_ref == min(rows) + 1
+
+
+def _two_scales(n, c, couple):
+    """Even and odd unknowns coupled to their like 64 away, the odd ones more
+    strongly (and with `couple` to the even one before them): dominant, and
+    slow enough to forget that the segments' starts differ from the chain."""
+    i = np.arange(n)
+    odd = i % 2 == 1
+    AB = np.zeros((n, 129))
+    AB[:, 64] = 1.0
+    o = np.where(odd, -c, -0.1)
+    AB[i >= 64, 0] = o[i >= 64]
+    AB[i < n - 64, 128] = o[i < n - 64]
+    AB[odd, 63] = couple
+    return AB
+
+
+def _times(AB, X):
+    n, Y = len(AB), np.zeros_like(X)
+    for d in range(129):
+        lo, hi = max(0, 64 - d), min(n, n + 64 - d)
+        Y[lo:hi] += AB[lo:hi, d:d + 1] * X[lo + d - 64:hi + d - 64]
+    return Y
+
+
+@pytest.mark.parametrize("c,scale", [(0.35, 1e-10), (0.25, 1e-8), (0.45, 1e-14), (0.25, 1e8), (0.35, 1.0)])
+@pytest.mark.parametrize("what", ["rows", "unknowns"])
+def test_band_sweep_of_two_scales(what, c, scale):
+    """Rows, or the unknowns themselves, of two scales within every block: the
+    small ones are as accurate as the large ones (kappa of either half <= 10)."""
+    n = 4096
+    case(f"band sweep two scales {what} c={c} scale={scale}")
+    AB, X0 = _two_scales(n, c, 0.05 if what == "rows" else 0.0), inputs.rhs(n, 2, 3)
+    if what == "rows":
+        AB[1::2] *= scale
+    else:
+        X0[1::2] *= scale
+    B = _times(AB, X0)
+    LU_ref, _ = oracle.lu_factor_band(AB, 64, 64)
+    X_ref = oracle.lu_solve_band(LU_ref, 64, 64, B)
+    _, X, info = _run(AB, 64, 64, B)
+    assert info == 0
+    for half in (slice(0, None, 2), slice(1, None, 2)):
+        assert fwd_err(X[half], X_ref[half]) <= 1e-12
