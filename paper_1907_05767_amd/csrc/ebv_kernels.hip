@@ -2459,10 +2459,10 @@ __global__ __launch_bounds__(NT) void k_band_factor(double *AB, int64_t ldab, in
  * starts kBandWarm block rows early from A's own tile, which leaves the
  * starting error below the last bit.  That is checked, not assumed: the tile
  * a segment started from is compared with the one its predecessor ended with
- * (k_band_check), and segments that do not agree to two units in the last
- * place of the row's largest element are factored again from the true tile,
- * in order (k_band_fix) -- for a matrix that forgets slowly all of them, which
- * costs what the serial chain costs.
+ * (k_band_check), element by element against the terms it was formed from, and
+ * segments that do not agree are factored again from the true tile, in order
+ * (k_band_fix) -- for a matrix that forgets slowly all of them, which costs what
+ * the serial chain costs.
  *
  * Segments are four block rows long (longer once that makes more than 256,
  * one per compute unit): at n = 16384 the chain is 10 steps instead of 256.
@@ -2532,34 +2532,61 @@ __global__ __launch_bounds__(NT) void k_band_segments(double *AB, int64_t ldab, 
         ws.zero[j] = z;
 }
 
-/* Whether the diagonal tile T that a segment started from is the true one S
- * (64 x 64 each) to 2^-51 of the largest element of S's row; the same in every
- * thread.  Not a number is never equal. */
-__device__ __forceinline__ bool band_same_tile(const double *S, const double *T)
+/* Whether the diagonal tile t that segment j started from is the one s that its
+ * predecessor ended with: each element to 2^-51 of the terms it was formed from,
+ * |A| + |L| |U| of the factor's tiles left of and above it, which is what the
+ * product's own rounding is measured by.  A row's largest element is no measure:
+ * where a row meets columns of two scales, an element of the small scale would
+ * pass with none of its digits right.  The same in every thread; not a number,
+ * and a sum that overflows, never agree. */
+__device__ __forceinline__ bool band_same_tile(double *AB, int64_t ldab, int n, int kl, int ku, const BandWs &ws, int m,
+                                               int j, BandSmem &sm)
 {
-    const int w = wave_id(), l = threadIdx.x & 63;
-    double s[16], t[16];
+    typedef vec4<double>::type V;
+    const int w = wave_id(), l = threadIdx.x & 63, lr = l & 15, lk = l >> 4, kb = j * m;
+    const BandTile tl(AB, ldab, n, kl, ku, kb, kb - 1), tu(AB, ldab, n, kl, ku, kb - 1, kb);
+    auto stage = [&](const BandTile &x, double *D) {
+        tile_xfer<double>(
+            [&](int r, int c) {
+                const double v = x.raw(r, c);
+                return x.in(r, c) ? fabs(v) : 0.0;
+            },
+            [&](int r, int c, double v) { D[r * LDT + c] = v; });
+    };
+    stage(tl, sm.l);
+    stage(tu, sm.s);
+    const double *S = ws.send + (int64_t)(j - 1) * TB * TB, *T = ws.sstart + (int64_t)j * TB * TB;
+    V s[4], t[4], bound[4];
+    band_pack_load(ws.pk + (int64_t)kb * kBandPackTiles * TB * TB, bound);
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-        s[i] = S[(w + 4 * i) * TB + l];
-        t[i] = T[(w + 4 * i) * TB + l];
-    }
+    for (int a = 0; a < 4; ++a)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int e = (16 * a + acc_row<double>(lk, r)) * TB + 16 * w + lr;
+            s[a][r] = S[e];
+            t[a][r] = T[e];
+            bound[a][r] = fabs(bound[a][r]);
+        }
+    __syncthreads();
     bool same = true;
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-        double m = fabs(s[i]);
+    for (int a = 0; a < 4; ++a) {
+        wave_mma16<double, TB>(
+            bound[a], [&](int r, int k) { return sm.l[(16 * a + r) * LDT + k]; },
+            [&](int k, int c) { return sm.s[k * LDT + 16 * w + c]; });
 #pragma unroll
-        for (int o = 32; o > 0; o >>= 1)
-            m = fmax(m, __shfl_xor(m, o));
-        same = same && fabs(s[i] - t[i]) <= 0x1p-51 * m;
+        for (int r = 0; r < 4; ++r)
+            same = same && (s[a][r] == t[a][r] || (fabs(s[a][r] - t[a][r]) <= 0x1p-51 * bound[a][r] &&
+                                                   bound[a][r] <= 0x1.fffffffffffffp1023));
     }
     return __syncthreads_and(same);
 }
 
-__global__ __launch_bounds__(NT) void k_band_check(BandWs ws)
+__global__ __launch_bounds__(NT) void k_band_check(double *AB, int64_t ldab, int n, int kl, int ku, BandWs ws, int m)
 {
+    __shared__ BandSmem sm;
     const int j = blockIdx.x + 1;
-    const bool ok = band_same_tile(ws.send + (int64_t)(j - 1) * TB * TB, ws.sstart + (int64_t)j * TB * TB);
+    const bool ok = band_same_tile(AB, ldab, n, kl, ku, ws, m, j, sm);
     if (threadIdx.x == 0)
         ws.ok[j] = ok;
 }
@@ -2576,8 +2603,7 @@ __global__ __launch_bounds__(NT) void k_band_fix(double *AB, int64_t ldab, int n
     if (!__syncthreads_and(mine)) {
         bool redone = false; /* segment j - 1 was factored again */
         for (int j = 1; j < nseg; ++j) {
-            const bool ok = redone ? band_same_tile(ws.send + (int64_t)(j - 1) * TB * TB, ws.sstart + (int64_t)j * TB * TB)
-                                   : ws.ok[j] != 0;
+            const bool ok = redone ? band_same_tile(AB, ldab, n, kl, ku, ws, m, j, sm) : ws.ok[j] != 0;
             redone = !ok;
             if (ok)
                 continue;
@@ -3003,7 +3029,7 @@ hipError_t band_factor(double *AB, int64_t ldab, int n, int kl, int ku, int32_t 
     const int nt = (n + TB - 1) / TB, m = band_segment_rows(nt, 4), nseg = (nt + m - 1) / m;
     hipLaunchKernelGGL(k_band_pack, dim3(nt), dim3(NT), 0, st, AB, ldab, n, kl, ku, b.pk);
     hipLaunchKernelGGL(k_band_segments, dim3(nseg), dim3(NT), 0, st, AB, ldab, n, kl, ku, b, m);
-    hipLaunchKernelGGL(k_band_check, dim3(nseg - 1), dim3(NT), 0, st, b);
+    hipLaunchKernelGGL(k_band_check, dim3(nseg - 1), dim3(NT), 0, st, AB, ldab, n, kl, ku, b, m);
     hipLaunchKernelGGL(k_band_fix, dim3(1), dim3(NT), 0, st, AB, ldab, n, kl, ku, b, m, nseg, info);
     return hipGetLastError();
 }

@@ -114,7 +114,7 @@ def test_band_segments_zero_pivot(rows):
     assert int(info.item()) == info_ref == min(rows) + 1
 
 
-def _two_scales(n, c, couple):
+def _two_scales(n, c, couple, even=0.1):
     """Even and odd unknowns coupled to their like 64 away, the odd ones more
     strongly (and with `couple` to the even one before them): dominant, and
     slow enough to forget that the segments' starts differ from the chain."""
@@ -122,7 +122,7 @@ def _two_scales(n, c, couple):
     odd = i % 2 == 1
     AB = np.zeros((n, 129))
     AB[:, 64] = 1.0
-    o = np.where(odd, -c, -0.1)
+    o = np.where(odd, -c, -even)
     AB[i >= 64, 0] = o[i >= 64]
     AB[i < n - 64, 128] = o[i < n - 64]
     AB[odd, 63] = couple
@@ -156,3 +156,26 @@ def test_band_sweep_of_two_scales(what, c, scale):
     assert info == 0
     for half in (slice(0, None, 2), slice(1, None, 2)):
         assert fwd_err(X[half], X_ref[half]) <= 1e-12
+
+
+@pytest.mark.parametrize("c,scale", [(0.25, 1e-10), (0.35, 1e-12), (0.45, 1e-15), (0.25, 1e10), (0.35, 1.0)])
+def test_band_factor_of_two_scales(c, scale):
+    """Columns of two scales: the factors, scales taken off, are O(1) and as
+    accurate in the small columns as in the large ones."""
+    n = 4096
+    case(f"band factor two scales c={c} scale={scale}")
+    col = np.where(np.arange(n) % 2 == 1, scale, 1.0)
+    j = np.clip(np.arange(n)[:, None] + np.arange(129)[None, :] - 64, 0, n - 1)
+    AB = _two_scales(n, c, 0.0, 0.0)
+    i = np.arange(n)
+    AB[(i % 2 == 1) & (i % 64 != 63), 65] = 0.05  # a large element in every odd row, which the
+    AB[i % 64 == 63, 63] = 0.05                   # elimination leaves alone
+    AB *= col[j]
+    LU_ref, _ = oracle.lu_factor_band(AB, 64, 64)
+    t = dev(AB)
+    info = ebv.lu_factor_band_(t, 64, 64)
+    torch.cuda.synchronize()
+    assert int(info.item()) == 0
+    off = np.where(np.arange(129)[None, :] >= 64, 1.0 / col[j], 1.0)  # U carries the columns' scales, L does not
+    diff = np.where(_mask(n, 64, 64), (host(t) - LU_ref) * off, 0)
+    assert np.abs(diff).max() <= 1e-12
