@@ -151,11 +151,11 @@ hipError_t batched_mixed_run(int count, const int *ns, const int64_t *offA, cons
                              double *B, const int *order, int32_t *info, int *queue, float *W, float *R32,
                              double *X, int max_iter, double tol, int32_t *iters, int grid, hipStream_t st);
 /* Workspace of the segmented band factor (ws may be null: sizes only): per
- * segment its first zero pivot, whether its start agreed with its
- * predecessor's end and both diagonal tiles; then the band as tiles.  bytes =
+ * segment its first zero pivot, what is known of its start and pivots, and the
+ * diagonal tiles that it started from and ended with; then the band as tiles.  bytes =
  * 0 where the serial chain is used. */
 struct BandWs {
-    int *zero, *ok;
+    int *zero, *flags;
     double *sstart, *send, *pk;
 };
 BandWs band_ws(void *ws, int64_t n, size_t &bytes);

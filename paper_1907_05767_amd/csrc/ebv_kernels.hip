@@ -2528,19 +2528,25 @@ __global__ __launch_bounds__(NT) void k_band_segments(double *AB, int64_t ldab, 
     __shared__ BandSmem sm;
     const int j = blockIdx.x;
     const int z = band_range<true>(AB, ldab, n, kl, ku, band_segment(ws, (n + TB - 1) / TB, m, j, false), sm);
-    if (threadIdx.x == 0)
+    if (threadIdx.x == 0) {
         ws.zero[j] = z;
+        ws.flags[j] = 0;
+    }
 }
+
+/* What is known of a segment: its start differs from its predecessor's end; by
+ * more than rounding; a pivot of it is tiny. */
+enum { kBandInexact = 1, kBandOff = 2, kBandTiny = 4 };
 
 /* Whether the diagonal tile t that segment j started from is the one s that its
  * predecessor ended with: each element to 2^-51 of the terms it was formed from,
  * |A| + |L| |U| of the factor's tiles left of and above it, which is what the
  * product's own rounding is measured by.  A row's largest element is no measure:
  * where a row meets columns of two scales, an element of the small scale would
- * pass with none of its digits right.  The same in every thread; not a number,
- * and a sum that overflows, never agree. */
-__device__ __forceinline__ bool band_same_tile(double *AB, int64_t ldab, int n, int kl, int ku, const BandWs &ws, int m,
-                                               int j, BandSmem &sm)
+ * pass with none of its digits right.  Returns kBand* flags, the same in every
+ * thread; not a number, and a sum that overflows, never agree. */
+__device__ __forceinline__ int band_seam(double *AB, int64_t ldab, int n, int kl, int ku, const BandWs &ws, int m,
+                                         int j, double *sl, double *su)
 {
     typedef vec4<double>::type V;
     const int w = wave_id(), l = threadIdx.x & 63, lr = l & 15, lk = l >> 4, kb = j * m;
@@ -2553,8 +2559,8 @@ __device__ __forceinline__ bool band_same_tile(double *AB, int64_t ldab, int n, 
             },
             [&](int r, int c, double v) { D[r * LDT + c] = v; });
     };
-    stage(tl, sm.l);
-    stage(tu, sm.s);
+    stage(tl, sl);
+    stage(tu, su);
     const double *S = ws.send + (int64_t)(j - 1) * TB * TB, *T = ws.sstart + (int64_t)j * TB * TB;
     V s[4], t[4], bound[4];
     band_pack_load(ws.pk + (int64_t)kb * kBandPackTiles * TB * TB, bound);
@@ -2568,49 +2574,101 @@ __device__ __forceinline__ bool band_same_tile(double *AB, int64_t ldab, int n, 
             bound[a][r] = fabs(bound[a][r]);
         }
     __syncthreads();
-    bool same = true;
+    bool same = true, exact = true;
 #pragma unroll
     for (int a = 0; a < 4; ++a) {
         wave_mma16<double, TB>(
-            bound[a], [&](int r, int k) { return sm.l[(16 * a + r) * LDT + k]; },
-            [&](int k, int c) { return sm.s[k * LDT + 16 * w + c]; });
+            bound[a], [&](int r, int k) { return sl[(16 * a + r) * LDT + k]; },
+            [&](int k, int c) { return su[k * LDT + 16 * w + c]; });
 #pragma unroll
-        for (int r = 0; r < 4; ++r)
-            same = same && (s[a][r] == t[a][r] || (fabs(s[a][r] - t[a][r]) <= 0x1p-51 * bound[a][r] &&
-                                                   bound[a][r] <= 0x1.fffffffffffffp1023));
+        for (int r = 0; r < 4; ++r) {
+            const bool eq = s[a][r] == t[a][r];
+            exact = exact && eq;
+            same = same && (eq || (fabs(s[a][r] - t[a][r]) <= 0x1p-51 * bound[a][r] &&
+                                   bound[a][r] <= 0x1.fffffffffffffp1023));
+        }
     }
-    return __syncthreads_and(same);
+    same = __syncthreads_and(same);
+    return __syncthreads_and(exact) ? 0 : (same ? kBandInexact : kBandInexact | kBandOff);
 }
 
-__global__ __launch_bounds__(NT) void k_band_check(double *AB, int64_t ldab, int n, int kl, int ku, BandWs ws, int m)
+/* Whether a pivot of block rows b0 .. b1 - 1 is tiny against the terms it was
+ * formed from, sum_k |l_ik u_ki| (four threads a pivot), or not a number: it, or
+ * one near it, may then be zero but for a start's last bits.  The same in every
+ * thread. */
+__device__ __forceinline__ bool band_tiny_pivot(const double *AB, int64_t ldab, int n, int kl, int ku, int b0, int b1)
 {
-    __shared__ BandSmem sm;
-    const int j = blockIdx.x + 1;
-    const bool ok = band_same_tile(AB, ldab, n, kl, ku, ws, m, j, sm);
-    if (threadIdx.x == 0)
-        ws.ok[j] = ok;
+    const int q = threadIdx.x & 3, depth = min(kl, ku);
+    bool tiny = false;
+    for (int b = b0; b < b1; ++b) {
+        const int i = b * TB + (threadIdx.x >> 2);
+        const double *row = AB + (int64_t)min(i, n - 1) * ldab + kl;
+        double sum = 0.0;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+            const int d = 1 + q + 4 * e;
+            const bool in = i < n && d <= min(depth, i);
+            const double x = *(in ? row - d : row), y = *(in ? row - d * ldab + d : row);
+            sum += in ? fabs(x * y) : 0.0;
+        }
+        sum += __shfl_xor(sum, 1);
+        sum += __shfl_xor(sum, 2);
+        tiny = tiny || (i < n && !(fabs(*row) > 0x1p-40 * sum));
+    }
+    return __syncthreads_or(tiny);
 }
 
+/* The seams, a workgroup each, and the block rows past the first segment, whose
+ * start is exact. */
+__global__ __launch_bounds__(NT) void k_band_check(double *AB, int64_t ldab, int n, int kl, int ku, BandWs ws, int m,
+                                                   int nseg)
+{
+    __shared__ double sl[TB * LDT], su[TB * LDT];
+    const bool seam = (int)blockIdx.x < nseg - 1;
+    const int j = seam ? blockIdx.x + 1 : 0, b = m + (int)blockIdx.x - (nseg - 1);
+    const int f = seam ? band_seam(AB, ldab, n, kl, ku, ws, m, j, sl, su)
+                       : (band_tiny_pivot(AB, ldab, n, kl, ku, b, b + 1) ? kBandTiny : 0);
+    if (threadIdx.x == 0 && f)
+        atomicOr(ws.flags + (seam ? j : b / m), f);
+}
+
+/* Segments that started wrong are factored again in order.  A kept segment may
+ * differ from the chain's in its last bits, which a pivot formed by cancellation
+ * shows whole: the chain's exact zero is then a rounding error there.  Where a
+ * pivot is tiny, all segments from the first inexact start on are therefore
+ * factored again, and the answer is the chain's. */
 __global__ __launch_bounds__(NT) void k_band_fix(double *AB, int64_t ldab, int n, int kl, int ku, BandWs ws, int m,
                                                  int nseg, int32_t *info)
 {
     __shared__ BandSmem sm;
     __shared__ int first_zero;
     const int nt = (n + TB - 1) / TB;
-    bool mine = true;
-    for (int j = 1 + threadIdx.x; j < nseg; j += NT)
-        mine = mine && ws.ok[j];
-    if (!__syncthreads_and(mine)) {
-        bool redone = false; /* segment j - 1 was factored again */
+    bool off = false, tiny = false;
+    for (int j = 1 + threadIdx.x; j < nseg; j += NT) {
+        off = off || (ws.flags[j] & kBandOff);
+        tiny = tiny || (ws.flags[j] & kBandTiny);
+    }
+    bool strict = __syncthreads_or(tiny);
+    for (bool more = __syncthreads_or(off) || strict; more;) {
+        bool redone = false, kept = false; /* segment j - 1 was factored again; an inexact start was kept */
+        more = false;
         for (int j = 1; j < nseg; ++j) {
-            const bool ok = redone ? band_same_tile(AB, ldab, n, kl, ku, ws, m, j, sm) : ws.ok[j] != 0;
-            redone = !ok;
-            if (ok)
+            const int f = strict   ? (redone || (ws.flags[j] & kBandInexact) ? kBandOff : 0)
+                          : redone ? band_seam(AB, ldab, n, kl, ku, ws, m, j, sm.l, sm.s)
+                                   : ws.flags[j];
+            redone = f & kBandOff;
+            if (!redone) {
+                kept = kept || (f & kBandInexact);
                 continue;
-            const int z = band_range<true>(AB, ldab, n, kl, ku, band_segment(ws, nt, m, j, true), sm);
+            }
+            const BandRange R = band_segment(ws, nt, m, j, true);
+            const int z = band_range<true>(AB, ldab, n, kl, ku, R, sm);
             if (threadIdx.x == 0)
                 ws.zero[j] = z;
+            if (kept)
+                more = band_tiny_pivot(AB, ldab, n, kl, ku, R.first, R.end) || more;
         }
+        strict = true; /* once more if a pivot of the new ones is tiny */
     }
     if (threadIdx.x == 0)
         first_zero = 0x7fffffff;
@@ -3010,7 +3068,7 @@ BandWs band_ws(void *ws, int64_t n, size_t &bytes)
     if (ws) {
         char *p = static_cast<char *>(ws);
         b.zero = reinterpret_cast<int *>(p);
-        b.ok = b.zero + nseg;
+        b.flags = b.zero + nseg;
         b.sstart = reinterpret_cast<double *>(p + tiles);
         b.send = reinterpret_cast<double *>(p + tiles + (size_t)nseg * tile);
         b.pk = reinterpret_cast<double *>(p + pk);
@@ -3029,7 +3087,7 @@ hipError_t band_factor(double *AB, int64_t ldab, int n, int kl, int ku, int32_t 
     const int nt = (n + TB - 1) / TB, m = band_segment_rows(nt, 4), nseg = (nt + m - 1) / m;
     hipLaunchKernelGGL(k_band_pack, dim3(nt), dim3(NT), 0, st, AB, ldab, n, kl, ku, b.pk);
     hipLaunchKernelGGL(k_band_segments, dim3(nseg), dim3(NT), 0, st, AB, ldab, n, kl, ku, b, m);
-    hipLaunchKernelGGL(k_band_check, dim3(nseg - 1), dim3(NT), 0, st, AB, ldab, n, kl, ku, b, m);
+    hipLaunchKernelGGL(k_band_check, dim3(nseg - 1 + nt - m), dim3(NT), 0, st, AB, ldab, n, kl, ku, b, m, nseg);
     hipLaunchKernelGGL(k_band_fix, dim3(1), dim3(NT), 0, st, AB, ldab, n, kl, ku, b, m, nseg, info);
     return hipGetLastError();
 }

@@ -179,3 +179,49 @@ def test_band_factor_of_two_scales(c, scale):
     off = np.where(np.arange(129)[None, :] >= 64, 1.0 / col[j], 1.0)  # U carries the columns' scales, L does not
     diff = np.where(_mask(n, 64, 64), (host(t) - LU_ref) * off, 0)
     assert np.abs(diff).max() <= 1e-12
+
+
+def test_band_segments_zero_pivot_by_cancellation():
+    """A pivot that the chain forms as an exact zero, in the first block row of a
+    later segment: reported with the segments too, whose starts agree with the
+    chain's tiles only to the last bits.
+
+    Row m opens the segment with nothing above its diagonal 1; row r = m + 1
+    meets only it on the left, with 1/2.  So u_rr = a_rr - u_mr / 2 exactly,
+    u_mr being an element of the segment's first tile."""
+    n = 4096
+    case("band segments, zero pivots by cancellation")
+    for m in range(256, n, 256):
+        r = m + 1
+        AB = inputs.band(n, 64, 64, 0.9, 11)
+        for k in range(m - 64, m):
+            AB[k, 64 + m - k] = 0.0
+        AB[r, :64] = 0.0
+        AB[r, 63] = 0.5
+        t = dev(AB)
+        assert int(ebv.lu_factor_band_(t, 64, 64, ws=_serial_ws()).item()) == 0
+        AB[r, 64] = float(t[m, 65].item()) / 2
+        t1, t2 = dev(AB), dev(AB)
+        assert int(ebv.lu_factor_band_(t1, 64, 64, ws=_serial_ws()).item()) == r + 1
+        assert int(ebv.lu_factor_band_(t2, 64, 64).item()) == r + 1
+
+
+def test_band_segments_zero_pivot_in_a_repeated_segment():
+    """The same in a segment that is factored again, behind others whose starts
+    were kept although their last bits differ: all of them are taken again."""
+    n, m = 2048, 1536
+    r = m + 1
+    case("band segments, zero pivot in a repeated segment")
+    AB = inputs.band(n, 64, 64, 0.9, 11)
+    AB[1024:] = _grid(n)[1024:]
+    for k in range(m - 64, m):
+        AB[k, 64 + m - k] = 0.0
+    AB[r, :64] = 0.0
+    AB[r, 63] = AB[m, 64] / 2
+    t = dev(AB)
+    assert int(ebv.lu_factor_band_(t, 64, 64, ws=_serial_ws()).item()) == 0
+    AB[r, 64] = float(t[m, 65].item()) / 2
+    t1, t2 = dev(AB), dev(AB)
+    assert int(ebv.lu_factor_band_(t1, 64, 64, ws=_serial_ws()).item()) == r + 1
+    assert int(ebv.lu_factor_band_(t2, 64, 64).item()) == r + 1
+    assert torch.equal(t1[:m], t2[:m])  # the chain's factor, bit for bit
