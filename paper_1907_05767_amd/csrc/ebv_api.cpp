@@ -1082,7 +1082,16 @@ int ebv_lu_factor_batched(ebv_handle h, ebv_dtype dtype, int64_t count, const in
     DeviceInfo d;
     current_device_info(d);
     const int wpc = wg_per_cu ? wg_per_cu : h->batched[batched_slot(dtype, mixed)].wg_per_cu;
-    const int grid = std::max(1, d.cus * wpc);
+    /* Few systems: a workgroup each and no more, which the dispatcher spreads over
+     * the chip.  Of a full grid the workgroups that one XCD starts first take all
+     * the tickets, several to a compute unit, while others idle (full grid | this,
+     * ms: FP64 40 x n=1500 23.5 | 14.6, 256 x 700 3.18 | 2.10; FP32 200 x 1000 6.45
+     * | 3.58, 512 x 700 2.81 | 2.20; mixed 300 x 1500 30.4 | 23.5).  FP64 with more
+     * systems than units keeps it, two to a unit being all it holds (300 x 1500
+     * 25.0 | 26.8). */
+    int grid = std::max(1, d.cus * wpc);
+    if (dtype == EBV_F32 || mixed || count <= d.cus)
+        grid = (int)std::min<int64_t>(count, grid);
     char *w = (char *)ws;
     int *hdr = (int *)(w + lay.hdr);
     hipError_t e = ebv::fill_i32(hdr, 2, 0, stream);
