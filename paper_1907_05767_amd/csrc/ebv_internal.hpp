@@ -147,9 +147,10 @@ hipError_t batch_solve(bool adjoint, const T *LU, int64_t lda, int n, int64_t st
 template <typename T>
 hipError_t batched_run(int count, const int *ns, const int64_t *offA, T *A, const int64_t *offB, T *B,
                        const int *order, int32_t *info, int *queue, int grid, hipStream_t st);
+/* two: two workgroups to a compute unit instead of three. */
 hipError_t batched_mixed_run(int count, const int *ns, const int64_t *offA, const double *A, const int64_t *offB,
                              double *B, const int *order, int32_t *info, int *queue, float *W, float *R32,
-                             double *X, int max_iter, double tol, int32_t *iters, int grid, hipStream_t st);
+                             double *X, int max_iter, double tol, int32_t *iters, int grid, bool two, hipStream_t st);
 /* Workspace of the segmented band factor (ws may be null: sizes only): per
  * segment its first zero pivot, what is known of its start and pivots, and the
  * diagonal tiles that it started from and ended with; then the band as tiles.  bytes =

@@ -1886,10 +1886,10 @@ __global__ __launch_bounds__(NT, kCroutPerCu<T>) void k_batched(int count, const
 
 /* Largest system whose refinement keeps its float vector in LDS (t1). */
 constexpr int kMixLdsN = TB * LDT;
-/* ... and x in double beside it, in what the products' buffers leave of LDS
- * past the diagonal blocks' place (a third workgroup per compute unit against
- * reading x through L2 for larger systems). */
-constexpr int kMixXdN = (CroutSmem<float>::GEMM - sizeof(float) * TB * LDT) / sizeof(double); /* 1312 */
+/* ... and, three workgroups to a compute unit, x in double beside it, in what the
+ * products' buffers leave of LDS past the diagonal blocks' place. */
+constexpr int kMixXdN = (CroutSmem<float>::GEMM - sizeof(float) * TB * LDT) / sizeof(double);
+static_assert(kMixXdN == 1568, "both sides of it are tested");
 
 /* Workgroup-wide maximum (result valid in every thread). */
 __device__ double wg_max(double v, double *red)
@@ -1911,8 +1911,12 @@ __device__ double wg_max(double v, double *red)
  * update x += solve_float(r)).  The stop test bounds the forward error: with
  * the system's dominance margin m = min_i (|a_ii| - sum_{j != i} |a_ij|) > 0,
  * ||x - x*||_inf <= ||r||_inf / m, and the loop ends once
- * ||r||_inf <= tol m ||x||_inf (never for m = 0: iters reports -1). */
-__global__ __launch_bounds__(NT, kCroutPerCu<float>) void k_batched_mixed(int count, const int *__restrict__ ns, const int64_t *__restrict__ offA,
+ * ||r||_inf <= tol m ||x||_inf (never for m = 0: iters reports -1).
+ *
+ * TWO workgroups to a compute unit have LDS for x and the registers the
+ * refinement wants; three spill 53 of them. */
+template <bool TWO>
+__global__ __launch_bounds__(NT, TWO ? 2 : kCroutPerCu<float>) void k_batched_mixed(int count, const int *__restrict__ ns, const int64_t *__restrict__ offA,
                                                          const double *__restrict__ A, const int64_t *__restrict__ offB,
                                                          double *__restrict__ B, const int *__restrict__ order,
                                                          int32_t *info, int *queue, float *__restrict__ W,
@@ -1921,7 +1925,7 @@ __global__ __launch_bounds__(NT, kCroutPerCu<float>) void k_batched_mixed(int co
 {
     __shared__ union { CroutSmem<float> c; TileSmem<float> s; } smu;
     CroutSmem<float> &sm = smu.c;
-    __shared__ double red[4];
+    __shared__ double red[4], xlds[TWO ? kMixLdsN : 1];
     const int t = threadIdx.x, w = wave_id(), l = t & 63;
     for (;;) {
         if (t == 0)
@@ -1948,9 +1952,9 @@ __global__ __launch_bounds__(NT, kCroutPerCu<float>) void k_batched_mixed(int co
         float *Ws = W + offA[s];
         float *rs = R32 + offB[s];
         double *xs = X + offB[s];
-        /* x in double: in LDS, past the diagonal blocks' place in t0, while it
-         * fits there, else in memory */
-        double *xd = n <= kMixXdN ? reinterpret_cast<double *>(sm.gemm + sizeof(sm.t0)) : xs;
+        /* x in double: in LDS of its own, or past the diagonal blocks' place in t0
+         * while it fits there, else in memory */
+        double *xd = TWO ? xlds : n <= kMixXdN ? reinterpret_cast<double *>(sm.gemm + sizeof(sm.t0)) : xs;
         /* float copy and dominance margin: wave w takes rows 4w .. 4w+3,
          * 4w+16 .., four rows at a time, its lanes the columns (all of a
          * group's loads issued before its sums) */
@@ -2128,13 +2132,14 @@ hipError_t batched_run(int count, const int *ns, const int64_t *offA, T *A, cons
 
 hipError_t batched_mixed_run(int count, const int *ns, const int64_t *offA, const double *A, const int64_t *offB,
                              double *B, const int *order, int32_t *info, int *queue, float *W, float *R32,
-                             double *X, int max_iter, double tol, int32_t *iters, int grid, hipStream_t st)
+                             double *X, int max_iter, double tol, int32_t *iters, int grid, bool two, hipStream_t st)
 {
     hipError_t e = fill_i32(queue, 1, 0, st);
     if (e != hipSuccess)
         return e;
-    hipLaunchKernelGGL(k_batched_mixed, dim3(grid), dim3(NT), 0, st, count, ns, offA, A, offB, B, order, info, queue,
-                       W, R32, X, max_iter, tol, iters);
+    auto run = two ? k_batched_mixed<true> : k_batched_mixed<false>;
+    hipLaunchKernelGGL(run, dim3(grid), dim3(NT), 0, st, count, ns, offA, A, offB, B, order, info, queue, W, R32, X,
+                       max_iter, tol, iters);
     return hipGetLastError();
 }
 
