@@ -1092,6 +1092,19 @@ int ebv_lu_factor_batched(ebv_handle h, ebv_dtype dtype, int64_t count, const in
     int grid = std::max(1, d.cus * wpc);
     if (dtype == EBV_F32 || mixed || count <= d.cus)
         grid = (int)std::min<int64_t>(count, grid);
+    /* Two workgroups to a unit, with more registers (mixed: and LDS) each, or three
+     * (FP64: always two).  Two while a unit has no more than two systems, in mixed
+     * precision also where three save no round, and for up to six uneven systems a
+     * unit, whose largest are the end of the launch (squares' sum against the
+     * sum's square: gaps between the systems at most mislead it).  Three | two, ms,
+     * mixed: 16..512 in 300 systems 2.04 | 1.75, 700 2.45 | 1.89, 1300 2.77 | 2.26,
+     * 1600 2.74 | 2.72, 2000 3.29 | 3.37; n = 400 in 600 systems 2.07 | 2.45, 1000
+     * 3.52 | 2.97, 1536 4.27 | 4.45; FP32: 16..512 in 1000 systems 1.24 | 0.98, 1500
+     * 1.31 | 1.17; n = 400 in 1000 1.32 | 1.38. */
+    auto rounds = [&](int64_t per_cu) { return (count - 1) / (per_cu * d.cus); };
+    const bool uneven = totB > 0 && (double)count * (double)totA > 1.1 * (double)totB * (double)totB;
+    const bool two = wpc <= 2 || (mixed ? rounds(2) == rounds(3) : count <= 2 * d.cus) ||
+                     (uneven && count <= 6 * d.cus);
     char *w = (char *)ws;
     int *hdr = (int *)(w + lay.hdr);
     hipError_t e = ebv::fill_i32(hdr, 2, 0, stream);
@@ -1099,19 +1112,11 @@ int ebv_lu_factor_batched(ebv_handle h, ebv_dtype dtype, int64_t count, const in
         return EBV_ERR_HIP;
     if (!mixed) {
         e = dtype == EBV_F64
-                ? ebv::batched_run<double>((int)count, n, offA, (double *)A, offB, (double *)B, order, info, hdr + 1, grid, stream)
-                : ebv::batched_run<float>((int)count, n, offA, (float *)A, offB, (float *)B, order, info, hdr + 1, grid, stream);
+                ? ebv::batched_run<double>((int)count, n, offA, (double *)A, offB, (double *)B, order, info, hdr + 1, grid,
+                                           two, stream)
+                : ebv::batched_run<float>((int)count, n, offA, (float *)A, offB, (float *)B, order, info, hdr + 1, grid, two,
+                                          stream);
     } else {
-        /* Two workgroups to a unit, with more registers and LDS each, or three: two
-         * where they take no more rounds, and for up to six uneven systems a unit,
-         * whose largest are the end of the launch (sum of squares against square of
-         * the sum: gaps between systems at most mislead it).  Three | two, ms: 16..512
-         * in 300 systems 2.04 | 1.75, 700 2.45 | 1.89, 1300 2.77 | 2.26, 1600 2.74 |
-         * 2.72, 2000 3.29 | 3.37; n = 400 in 512 systems 2.3 | 1.9, 600 2.07 | 2.45,
-         * 1000 3.52 | 2.97, 1536 4.27 | 4.45. */
-        auto rounds = [&](int64_t per_cu) { return (count - 1) / (per_cu * d.cus); };
-        const bool uneven = (double)count * (double)totA > 1.1 * (double)totB * (double)totB;
-        const bool two = rounds(2) == rounds(3) || (uneven && count <= 6 * d.cus);
         e = ebv::batched_mixed_run((int)count, n, offA, (const double *)A, offB, (double *)B, order, info, hdr + 1,
                                    (float *)(w + lay.w), (float *)(w + lay.r32), (double *)(w + lay.x), max_iter, tol,
                                    iters, grid, two, stream);

@@ -144,10 +144,11 @@ hipError_t batch_factor(T *A, int64_t lda, int n, int64_t batch, int64_t strideA
 template <typename T>
 hipError_t batch_solve(bool adjoint, const T *LU, int64_t lda, int n, int64_t strideLU, T *B, int64_t ldb,
                        int64_t strideB, int nrhs, int64_t batch, hipStream_t st);
+/* Ragged batches; two: two workgroups to a compute unit (FP64's always), else
+ * three. */
 template <typename T>
 hipError_t batched_run(int count, const int *ns, const int64_t *offA, T *A, const int64_t *offB, T *B,
-                       const int *order, int32_t *info, int *queue, int grid, hipStream_t st);
-/* two: two workgroups to a compute unit instead of three. */
+                       const int *order, int32_t *info, int *queue, int grid, bool two, hipStream_t st);
 hipError_t batched_mixed_run(int count, const int *ns, const int64_t *offA, const double *A, const int64_t *offB,
                              double *B, const int *order, int32_t *info, int *queue, float *W, float *R32,
                              double *X, int max_iter, double tol, int32_t *iters, int grid, bool two, hipStream_t st);

@@ -1836,9 +1836,10 @@ hipError_t batch_solve(bool adjoint, const T *LU, int64_t lda, int n, int64_t st
 /* Persistent factor + solve of a ragged batch: each workgroup repeatedly
  * takes the next system from the queue (in `order`, the EbV schedule), and
  * factors and solves it alone.  Every workgroup leaves the loop once the
- * queue is exhausted. */
-template <typename T>
-__global__ __launch_bounds__(NT, kCroutPerCu<T>) void k_batched(int count, const int *__restrict__ ns, const int64_t *__restrict__ offA,
+ * queue is exhausted.  TWO workgroups to a compute unit, or as many as
+ * kCroutPerCu. */
+template <typename T, bool TWO>
+__global__ __launch_bounds__(NT, TWO ? 2 : kCroutPerCu<T>) void k_batched(int count, const int *__restrict__ ns, const int64_t *__restrict__ offA,
                                                    T *__restrict__ A, const int64_t *__restrict__ offB, T *__restrict__ B,
                                                    const int *__restrict__ order, int32_t *info, int *queue)
 {
@@ -2121,12 +2122,13 @@ __global__ __launch_bounds__(NT, TWO ? 2 : kCroutPerCu<float>) void k_batched_mi
 
 template <typename T>
 hipError_t batched_run(int count, const int *ns, const int64_t *offA, T *A, const int64_t *offB, T *B,
-                       const int *order, int32_t *info, int *queue, int grid, hipStream_t st)
+                       const int *order, int32_t *info, int *queue, int grid, bool two, hipStream_t st)
 {
     hipError_t e = fill_i32(queue, 1, 0, st);
     if (e != hipSuccess)
         return e;
-    hipLaunchKernelGGL(k_batched<T>, dim3(grid), dim3(NT), 0, st, count, ns, offA, A, offB, B, order, info, queue);
+    auto run = two || kCroutPerCu<T> == 2 ? k_batched<T, true> : k_batched<T, kCroutPerCu<T> == 2>;
+    hipLaunchKernelGGL(run, dim3(grid), dim3(NT), 0, st, count, ns, offA, A, offB, B, order, info, queue);
     return hipGetLastError();
 }
 
@@ -4185,8 +4187,8 @@ template hipError_t batch_factor<double>(double *, int64_t, int, int64_t, int64_
 template hipError_t batch_factor<float>(float *, int64_t, int, int64_t, int64_t, int32_t *, hipStream_t);
 template hipError_t batch_solve<double>(bool, const double *, int64_t, int, int64_t, double *, int64_t, int64_t, int, int64_t, hipStream_t);
 template hipError_t batch_solve<float>(bool, const float *, int64_t, int, int64_t, float *, int64_t, int64_t, int, int64_t, hipStream_t);
-template hipError_t batched_run<double>(int, const int *, const int64_t *, double *, const int64_t *, double *, const int *, int32_t *, int *, int, hipStream_t);
-template hipError_t batched_run<float>(int, const int *, const int64_t *, float *, const int64_t *, float *, const int *, int32_t *, int *, int, hipStream_t);
+template hipError_t batched_run<double>(int, const int *, const int64_t *, double *, const int64_t *, double *, const int *, int32_t *, int *, int, bool, hipStream_t);
+template hipError_t batched_run<float>(int, const int *, const int64_t *, float *, const int64_t *, float *, const int *, int32_t *, int *, int, bool, hipStream_t);
 template hipError_t lu_inverse<double>(const double *, int64_t, int, double *, int64_t, double *, hipStream_t);
 template hipError_t lu_inverse<float>(const float *, int64_t, int, float *, int64_t, float *, hipStream_t);
 template hipError_t outer_neg<double>(int, int, const double *, int64_t, int64_t, const double *, int64_t, int64_t, double *, int64_t, int64_t, int64_t, hipStream_t);
