@@ -3159,8 +3159,8 @@ __global__ __launch_bounds__(NT) void k_diag_packs(const T *__restrict__ LU, int
  * elementary upper factors times the elementary lower factors), as two
  * right-looking blocked triangular solves on the identity, one launch per
  * 64-wide block step, one workgroup per 64 x 64 tile of the result.  A tile
- * takes the terms of G = kInvGroup steps at a time, so that it is read and
- * written once per G steps and its product is G times as deep:
+ * takes the terms of G steps at a time, so that it is read and written once per
+ * G steps and its product is G times as deep:
  *   forward, W = L^{-1} (block lower triangular): launch k takes the rows r =
  *     k+1, k+1+G, ... and subtracts L_rs W_sc of the steps s = k-G+1 .. k
  *     (those >= c: W_sc is zero before; a tile first touched here starts from
@@ -3179,15 +3179,23 @@ __global__ __launch_bounds__(NT) void k_diag_packs(const T *__restrict__ LU, int
  * than the chip holds, one tile's own length.  n = 4096, forward | backward
  * launches on average: one step a tile, operands streamed without LDS, 26 | 58
  * us, two steps backward 26 | 54, tile_gemm and four steps 17 | 29.
+ *
+ * G: a launch of a few tiles lasts as long as one tile, whose product one step
+ * keeps short; a launch that fills the chip gains by the tiles' reads and writes
+ * saved.  One | two | four steps, us, FP64 n = 1000 324 | 357 | 438, 2000 841 | 814
+ * | 934, 3000 1864 | 1669 | 1766, 4000 3331 | 2981 | 2860; FP32 1000 312 | 366 |
+ * 472, 2000 709 | 792 | 996, 4000 2281 | 2164 | 2393, 6000 5918 | 5135 | 5443, 7000
+ * (two | four) 7700 | 7650, 8000 9590 | 9140.
  */
-constexpr int kInvGroup = 4;
+constexpr int kInvOne = 2048;                                       /* largest n for one step, */
+template <typename T> constexpr int kInvTwo = sizeof(T) == 8 ? 3072 : 6144; /* for two */
 
-template <typename T, bool FWD, int NB>
+template <typename T, bool FWD, int NB, int G>
 __global__ __launch_bounds__(NT, 3) void k_inv_step(const T *__restrict__ LU, int64_t lda, int n,
                                                     const T *__restrict__ P, T *__restrict__ X, int64_t ldx, int k)
 {
     typedef typename vec4<T>::type V;
-    constexpr int G = kInvGroup, H = 2 / NB; /* H workgroups per 64 x 64 tile */
+    constexpr int H = 2 / NB; /* H workgroups per 64 x 64 tile */
     __shared__ __attribute__((aligned(16))) char lds_raw[std::max(TileGemm<T, 2, NB>::LDS, sizeof(T) * TB * LDT)];
     T *S = reinterpret_cast<T *>(lds_raw);
     const int nt = (n + TB - 1) / TB, b = blockIdx.x / H, h0 = blockIdx.x % H * 32;
@@ -3281,7 +3289,7 @@ __global__ __launch_bounds__(NT, 3) void k_inv_step(const T *__restrict__ LU, in
     tile_store<T, NB>(x, C, ldx, nr, nc);
 }
 
-template <typename T, bool FWD>
+template <typename T, bool FWD, int G>
 static hipError_t inv_step(int tiles, const T *LU, int64_t lda, int n, const T *P, T *X, int64_t ldx, int k,
                            hipStream_t st)
 {
@@ -3289,10 +3297,22 @@ static hipError_t inv_step(int tiles, const T *LU, int64_t lda, int n, const T *
      * once and finish in half the time; more: whole tiles, half the operand
      * traffic (n = 4096: 264 tiles 21 -> 18 us, 1024 tiles 43 us) */
     if (tiles <= 384)
-        hipLaunchKernelGGL((k_inv_step<T, FWD, 1>), dim3(2 * tiles), dim3(NT), 0, st, LU, lda, n, P, X, ldx, k);
+        hipLaunchKernelGGL((k_inv_step<T, FWD, 1, G>), dim3(2 * tiles), dim3(NT), 0, st, LU, lda, n, P, X, ldx, k);
     else
-        hipLaunchKernelGGL((k_inv_step<T, FWD, 2>), dim3(tiles), dim3(NT), 0, st, LU, lda, n, P, X, ldx, k);
+        hipLaunchKernelGGL((k_inv_step<T, FWD, 2, G>), dim3(tiles), dim3(NT), 0, st, LU, lda, n, P, X, ldx, k);
     return hipGetLastError();
+}
+
+template <typename T, int G>
+static hipError_t inv_steps(const T *LU, int64_t lda, int n, T *X, int64_t ldx, const T *P, hipStream_t st)
+{
+    const int nt = (n + TB - 1) / TB;
+    hipError_t e = hipSuccess;
+    for (int k = -1; k + 1 < nt && e == hipSuccess; ++k) /* rows k+1, k+1+G, ... and the diagonal tile */
+        e = inv_step<T, true, G>((nt - 1 - k + G - 1) / G * (k + 1) + 1, LU, lda, n, P, X, ldx, k, st);
+    for (int k = nt; k > 0 && e == hipSuccess; --k) /* rows k-1, k-1-G, ... */
+        e = inv_step<T, false, G>(k == nt ? nt : (k + G - 1) / G * nt, LU, lda, n, P, X, ldx, k, st);
+    return e;
 }
 
 template <typename T>
@@ -3301,10 +3321,10 @@ hipError_t lu_inverse(const T *LU, int64_t lda, int n, T *X, int64_t ldx, T *P, 
     const int nt = (n + TB - 1) / TB;
     hipLaunchKernelGGL(k_diag_packs<T>, dim3(nt), dim3(NT), 0, st, LU, lda, n, P);
     hipError_t e = hipGetLastError();
-    for (int k = -1; k + 1 < nt && e == hipSuccess; ++k) /* rows k+1, k+1+G, ... and the diagonal tile */
-        e = inv_step<T, true>((nt - 1 - k + kInvGroup - 1) / kInvGroup * (k + 1) + 1, LU, lda, n, P, X, ldx, k, st);
-    for (int k = nt; k > 0 && e == hipSuccess; --k) /* rows k-1, k-1-G, ... */
-        e = inv_step<T, false>(k == nt ? nt : (k + kInvGroup - 1) / kInvGroup * nt, LU, lda, n, P, X, ldx, k, st);
+    if (e == hipSuccess)
+        e = n <= kInvOne      ? inv_steps<T, 1>(LU, lda, n, X, ldx, P, st)
+            : n <= kInvTwo<T> ? inv_steps<T, 2>(LU, lda, n, X, ldx, P, st)
+                              : inv_steps<T, 4>(LU, lda, n, X, ldx, P, st);
     return e;
 }
 

@@ -32,3 +32,18 @@ def test_inverse_groups(n, dtype):
     # differs from I by a few n eps
     eps = 2.2e-16 if dtype == torch.float64 else 1.2e-7
     assert np.abs(A @ X - np.eye(n)).max() <= 4 * n * eps
+
+
+@pytest.mark.parametrize("n", [2047, 2048, 2049, 3072, 3073, 3137, 3201, 3265, 3330, 6144, 6145])
+def test_inverse_groups_by_size(n):
+    """The sizes at which a tile takes one, two or four block steps at a time, and
+    every remainder of the four (the residual formed on the device in FP64)."""
+    case(f"inverse group sizes n={n}")
+    A = dev(inputs.dense(n, 0.5, 40 + n))
+    for dtype, eps in ((torch.float64, 2.2e-16), (torch.float32, 1.2e-7)):
+        LU, info = ebv.lu_factor(A.to(dtype))
+        X = ebv.lu_inverse(LU).double()
+        assert int(info.item()) == 0
+        R = A @ X
+        R.diagonal().sub_(1.0)
+        assert float(R.abs().max()) <= 4 * n * eps
