@@ -1,17 +1,18 @@
 """Autotuner of the library's schedule knobs on the GPU it runs on.
 
-Sweeps, on the benchmark workloads themselves (seeded synthetic inputs):
+Sweeps, on seeded synthetic inputs:
 
 * the ragged batch (4096 systems, n ~ U{16..512}, one right-hand side), for
   each form -- FP64, FP32, FP32 factor + FP64 refinement -- over workgroups
   per compute unit of the persistent grid and the order in which workgroups
   take the systems (EbV pairing of the costliest with the cheapest remaining
   system, index order, longest first);
-* the single dense factor + solve (n = 4096, 8 right-hand sides) over the
-  column-class group size G and the trailing-block size above which column
-  classes are used;
-* the group size G of the FP32 factor, on the mixed-precision dense solve
-  (n = 16384, s = 0.9, 4 right-hand sides), set through a one-key table.
+* the single dense factor's column-class group size G and the trailing-block size
+  above which column classes are used.  They act in block steps only, so on a
+  call that takes those: more right-hand sides than the one-launch factor has
+  flags for (n = 4096 with 8000 of them, FP64);
+* the group size G of the FP32 factor, likewise where it runs in block steps
+  (n = 28736), set through a one-key table.
 
 Every point is timed with HIP events over repeated calls (inputs restored
 outside the timed region) and the fastest setting per form is written as a
@@ -100,8 +101,28 @@ def sweep_batched(torch, ebv, inputs, reps: int, wpcs, policies):
     return results, best
 
 
-def sweep_dense(torch, ebv, inputs, reps: int, groups, aboves):
-    n, nrhs = 4096, 8
+def time_steps(torch, ebv, call, restore, reps: int) -> float:
+    """Median milliseconds that the block steps of a dense factor take, the launches
+    bracketed one by one; refuses a call that runs as one launch, where the knobs
+    of the block steps do nothing."""
+    ts = []
+    ebv.profile_update_enable(4096)
+    try:
+        for r in range(reps + 1):
+            restore()
+            call()
+            torch.cuda.synchronize()
+            ms, launches, _ = ebv.profile_update_read()
+            if launches < 2:
+                raise SystemExit("dense: this call does not run in block steps")
+            if r:
+                ts.append(ms)
+    finally:
+        ebv.profile_update_enable(0)
+    return float(np.median(ts))
+
+
+def sweep_dense(torch, ebv, inputs, reps: int, groups, aboves, n: int = 4096, nrhs: int = 8000):
     log(f"dense n={n} nrhs={nrhs}: inputs")
     a0 = torch.from_numpy(inputs.dense(n, 0.5, 2)).cuda()
     b0 = torch.from_numpy(inputs.rhs(n, nrhs, 2)).cuda()
@@ -123,7 +144,7 @@ def sweep_dense(torch, ebv, inputs, reps: int, groups, aboves):
                     tA.copy_(a0)
                     tB.copy_(b0)
 
-                ms = time_calls(torch, call, restore, reps)
+                ms = time_steps(torch, ebv, call, restore, reps)
                 if int(info.item()) != 0:
                     raise SystemExit(f"dense: info {int(info.item())} at G={g} above={above}")
                 log(f"dense: defer_group={g} defer_above={above}: {ms:.3f} ms")
@@ -133,12 +154,14 @@ def sweep_dense(torch, ebv, inputs, reps: int, groups, aboves):
     return results, min(results, key=lambda r: r["ms"])
 
 
-def sweep_f32_group(torch, ebv, inputs, reps: int, groups):
-    n, nrhs = 16384, 4
-    log(f"mixed dense n={n} s=0.9 nrhs={nrhs}: inputs")
-    A = torch.from_numpy(inputs.dense(n, 0.9, 5)).cuda()
-    B = torch.from_numpy(inputs.rhs(n, nrhs, 5)).cuda()
-    ws = ebv.workspace(ebv.OP_MIXED, ebv.F64, n, nrhs, 1)
+def sweep_f32_group(torch, ebv, reps: int, groups, n: int = 28736):
+    log(f"dense FP32 n={n}: inputs")
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    a0 = torch.rand((n, n), generator=gen, device="cuda", dtype=torch.float32).sub_(0.5).mul_(2.0 / n)
+    a0.diagonal().fill_(1.0)
+    tA = a0.clone()
+    ws = ebv.workspace(ebv.OP_FACTOR, ebv.F32, n, 0, 1)
+    info = torch.zeros(1, dtype=torch.int32, device="cuda")
     tmpdir = tempfile.mkdtemp()
     path = os.path.join(tmpdir, "f32_group.txt")
 
@@ -152,15 +175,10 @@ def sweep_f32_group(torch, ebv, inputs, reps: int, groups):
     try:
         for g in groups:
             set_group(g)
-            info = []
-
-            def call():
-                info.append(ebv.solve_mixed(A, B, ws=ws)[3])
-
-            ms = time_calls(torch, call, lambda: None, reps)
-            if any(int(i.item()) != 0 for i in info):
-                raise SystemExit(f"mixed dense: nonzero info at FP32 group {g}")
-            log(f"mixed dense: f32 defer_group={g}: {ms:.3f} ms")
+            ms = time_steps(torch, ebv, lambda: ebv.lu_factor_(tA, info=info, ws=ws), lambda: tA.copy_(a0), reps)
+            if int(info.item()) != 0:
+                raise SystemExit(f"dense FP32: nonzero info at group {g}")
+            log(f"dense FP32: defer_group={g}: {ms:.3f} ms")
             results.append({"f32_defer_group": g, "ms": ms})
     finally:
         set_group(4)
@@ -207,7 +225,7 @@ def main():
     bres, bbest = sweep_batched(torch, ebv, inputs, args.reps, wpcs, policies)
     dres, dbest = sweep_dense(torch, ebv, inputs, args.reps, groups, aboves)
     os.makedirs(os.path.dirname(args.out), exist_ok=True)
-    fres, fbest = sweep_f32_group(torch, ebv, inputs, max(3, args.reps // 3), (3, 4) if args.quick else (2, 3, 4))
+    fres, fbest = sweep_f32_group(torch, ebv, max(3, args.reps // 3), (3, 4) if args.quick else (2, 3, 4))
     write_table(bbest, dbest, args.out, fbest)
     sweep_path = os.path.splitext(args.out)[0] + "_sweep.json"
     with open(sweep_path, "w") as fh:

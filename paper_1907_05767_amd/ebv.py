@@ -191,12 +191,13 @@ def set_wait_limit(spins: int = 0):
 
 
 def profile_update_enable(max_launches: int):
-    """Bracket the next single-system block-step launches with HIP events (0 = off)."""
+    """Bracket the next launches of single-system factors (one each, or one per block
+    step) with HIP events (0 = off)."""
     _check(lib().ebv_profile_update_enable(handle(), int(max_launches)), "ebv_profile_update_enable")
 
 
 def profile_update_read():
-    """(summed ms, launches, summed algorithmic flops) of the bracketed block-step launches."""
+    """(summed ms, launches, summed algorithmic flops) of the bracketed launches."""
     ms, n, fl = ctypes.c_double(), ctypes.c_int64(), ctypes.c_double()
     _check(lib().ebv_profile_update_read(handle(), ctypes.byref(ms), ctypes.byref(n), ctypes.byref(fl)),
            "ebv_profile_update_read")

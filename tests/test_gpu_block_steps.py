@@ -53,6 +53,7 @@ def test_block_steps_by_default(dtype, nrhs, steps):
     case(f"block steps by default nrhs={nrhs} {dtype}")
     A = inputs.dense(n, 0.5, 17)
     X0 = torch.rand((n, nrhs), dtype=dtype, device="cuda") - 0.5
+    ebv.set_dense_tuning()
     LU, X, info, launches = _run(A, X0, dtype)
     assert launches == (23 if steps else 1)
     _check(A, X0, dtype, LU, X, info)
