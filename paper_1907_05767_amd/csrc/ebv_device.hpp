@@ -93,30 +93,6 @@ __device__ __forceinline__ float bcast(float v, int lane)
 
 /* ---------------------------------------------- compiler controls --- */
 
-/* Keeps the compiler (IR passes and the machine scheduler) from moving
- * loads across this point, which bounds the registers a fully unrolled
- * substitution would otherwise fill with preloaded coefficients; emits no
- * instruction. */
-__device__ __forceinline__ void lds_fence_compiler()
-{
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_sched_barrier(0);
-}
-
-/* Pins the 16 values of a substitution step: every update of them issued
- * before this point is complete here, and no load is moved across it, so a
- * fully unrolled substitution keeps only one step's coefficients live. */
-template <typename T> __device__ __forceinline__ void pin16(T (&x)[16])
-{
-    asm volatile(""
-                 : "+v"(x[0]), "+v"(x[1]), "+v"(x[2]), "+v"(x[3]), "+v"(x[4]), "+v"(x[5]), "+v"(x[6]),
-                   "+v"(x[7]), "+v"(x[8]), "+v"(x[9]), "+v"(x[10]), "+v"(x[11]), "+v"(x[12]), "+v"(x[13]),
-                   "+v"(x[14]), "+v"(x[15])
-                 :
-                 : "memory");
-    __builtin_amdgcn_sched_barrier(0);
-}
-
 /* Returns p unchanged, opaquely: address arithmetic based on the result
  * cannot be hoisted above this point (out of an enclosing loop), which keeps
  * the many LDS addresses of a fully unrolled tile routine from staying live
@@ -664,33 +640,6 @@ __device__ __forceinline__ void acc64_mma(Acc64<T> &acc, FA &&fa, FB &&fb)
     }
 }
 
-/* acc64_mma restricted to the inner indices klo <= k < khi (multiples of 32,
- * uniform within the wave): the terms a triangular operand makes zero.  Each
- * 32-wide chunk is unrolled, so its operand reads are issued together. */
-template <typename T, bool NEG, typename FA, typename FB>
-__device__ __forceinline__ void acc64_mma_range(Acc64<T> &acc, FA &&fa, FB &&fb, int klo, int khi)
-{
-    const int w = wave_id(), l = threadIdx.x & 63, lr = l & 15, lk = l >> 4;
-    const int wm = (w >> 1) * 32, wn = (w & 1) * 32;
-#pragma unroll 1
-    for (int kc = klo; kc < khi; kc += 32)
-#pragma unroll
-        for (int k = kc; k < kc + 32; k += 4) {
-            T a[2], b[2];
-#pragma unroll
-            for (int bi = 0; bi < 2; ++bi)
-                a[bi] = NEG ? -fa(wm + 16 * bi + lr, k + lk) : fa(wm + 16 * bi + lr, k + lk);
-#pragma unroll
-            for (int bj = 0; bj < 2; ++bj)
-                b[bj] = fb(k + lk, wn + 16 * bj + lr);
-#pragma unroll
-            for (int bi = 0; bi < 2; ++bi)
-#pragma unroll
-                for (int bj = 0; bj < 2; ++bj)
-                    acc.v[bi][bj] = mfma16(a[bi], b[bj], acc.v[bi][bj]);
-        }
-}
-
 /* C = A * B (SET) or C -= A * B for one 64 x 64 tile (see above). */
 template <typename T, bool SET, int K = TB, typename CRef, typename FA, typename FB>
 __device__ __forceinline__ void wg_gemm64f(const CRef &cref, FA &&fa, FB &&fb)
@@ -1151,8 +1100,6 @@ __device__ __forceinline__ int wg_crout(T *__restrict__ A, int64_t lda, int n, T
     __syncthreads();
     return zero_at;
 }
-
-/* ------------------------------------------------ workgroup-level LU --- */
 
 /* ------------------------------------------------- triangular solves --- */
 

@@ -666,13 +666,12 @@ static hipError_t factor_phases(T *A, int64_t lda, int n, int32_t *info, T *Pg, 
 template <typename T>
 static hipError_t factor_lookahead(T *A, int64_t lda, int n, int32_t *info, T *Pg, int *ctl,
                                    const DenseTuning &tun, UpdateProfile *pr, hipStream_t st, T *B, int64_t ldb,
-                                   int nrhs, bool prefilled)
+                                   int nrhs)
 {
     const int nb = (n + TB - 1) / TB;
     const int nbc = B ? (nrhs + TB - 1) / TB : 0;
     const int G = max(1, min(4, sizeof(T) == 4 ? tun.defer_group_f32 : tun.defer_group));
     hipError_t e = hipSuccess;
-    (void)prefilled;
     /* workgroups resident at once, less the diagonal
      * tile's: the size of the first wave of region tiles */
     int dev = 0, cus = 0;
@@ -1292,7 +1291,7 @@ hipError_t dense_factor(T *A, int64_t lda, int n, int32_t *info, void *ws, const
         return n > kFlowWide ? factor_flow<true>(A, lda, n, info, ws, tun, pr, st, B, ldb, nrhs)
                              : factor_flow<false>(A, lda, n, info, ws, tun, pr, st, B, ldb, nrhs);
     if (tun.lookahead)
-        return factor_lookahead(A, lda, n, info, Pg, ctl, tun, pr, st, B, ldb, nrhs, prefilled);
+        return factor_lookahead(A, lda, n, info, Pg, ctl, tun, pr, st, B, ldb, nrhs);
     return factor_phases(A, lda, n, info, Pg, tun, pr, st, B, ldb, nrhs);
 }
 
