@@ -95,9 +95,9 @@ int trsv_fit(size_t bytes, size_t elem, int64_t n, int64_t nrhs)
 
 /* Mixed precision (dense): [factor workspace: control words + diagonal
  * tile][exchange rows][conv int, margin u64][rbits u64[nrhs]][xbits u64[nrhs]]
- * [A32 n*n floats][R32 n*nrhs floats][n*nrhs doubles, unused] */
+ * [A32 n*n floats][R32 n*nrhs floats] */
 struct MixedLayout {
-    size_t trsv, dtile, xb, conv, mbits, rbits, xbits, a32, r32, r64, total;
+    size_t trsv, dtile, xb, conv, mbits, rbits, xbits, a32, r32, total;
     MixedLayout(int64_t n, int64_t nrhs, int chunks)
     {
         trsv = 0; /* the factor's first control words serve the solves */
@@ -109,8 +109,7 @@ struct MixedLayout {
         xbits = rbits + align_up(8 * (size_t)nrhs);
         a32 = xbits + align_up(8 * (size_t)nrhs);
         r32 = a32 + align_up(4 * (size_t)n * (size_t)n);
-        r64 = r32 + align_up(4 * (size_t)n * (size_t)nrhs);
-        total = r64 + align_up(8 * (size_t)n * (size_t)nrhs);
+        total = r32 + align_up(4 * (size_t)n * (size_t)nrhs);
     }
 };
 

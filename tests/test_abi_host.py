@@ -288,3 +288,12 @@ def test_pairing_map_invariants(tmp_path):
                            str(src), "-o", str(exe)])
     out = subprocess.run([str(exe)], capture_output=True, text=True)
     assert out.returncode == 0, out.stdout
+
+
+def test_mixed_workspace_holds_no_double_residual(lib):
+    """The residual goes to float at once: beside the float matrix, its factor's
+    and the substitutions' rows, 4 bytes an element of the right-hand sides (and
+    16 per right-hand side)."""
+    def size(nrhs):
+        return lib.ebv_workspace_size(ebv.OP_MIXED, 0, 8192, nrhs, 1)
+    assert size(16) - size(8) == 4 * 8192 * 8
