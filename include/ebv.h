@@ -83,7 +83,7 @@ enum {
 };
 
 /* Library handle: holds the tuning of the single-system factor and of the
- * ragged batch, and the event hook of the factor's block steps.  It owns no
+ * ragged batch, and the event hook of the factor's launches.  It owns no
  * device memory and serves every device.  A handle must not be used by two
  * host threads at once; give each thread its own. */
 typedef struct ebv_ctx *ebv_handle;
@@ -371,8 +371,11 @@ int64_t ebv_noalloc_max_n(void);
  * The factor is a chain over the block-tridiagonal 64 x 64 tiles, walked by
  * one workgroup, or, given a workspace, by one workgroup per segment of block
  * rows: each starts a few block rows early, the diagonal tile it started from
- * is checked against the one its predecessor ended with, and a segment that
- * does not agree to the last bits is factored again in order.  The solve
+ * is checked against the one its predecessor ended with, each element to 2^-51
+ * of the terms it was formed from, and a segment that does not agree is factored
+ * again in order.  Bands whose off-diagonals have random signs agree at once; those
+ * that forget slowly (one sign, grids) are factored again, in about the time of
+ * the chain.  Zero pivots are reported as by the chain.  The solve
  * first forms, in parallel, the inverses of the diagonal tiles' factors and
  * their products with the off-diagonal tiles (into ws), then sweeps the
  * 64-row blocks forward and backward, one matrix-core product per block, long
@@ -423,7 +426,7 @@ int ebv_lu_solve_band(ebv_handle h, int64_t n, int64_t kl, int64_t ku, int64_t n
  *          (-EBV_ERR_UNSUPPORTED) for a system with n_s^2 * 8 >= 2^31 bytes,
  *          which one workgroup does not address (left untouched).
  *   wg_per_cu  workgroups per compute unit in the persistent grid (0 = the
- *          handle's tuned value for this form).
+ *          handle's tuned value for this form); small batches launch fewer.
  */
 int ebv_lu_factor_batched(ebv_handle h, ebv_dtype dtype, int64_t count, const int32_t *n, const int64_t *offA,
                           void *A, int64_t totA, const int64_t *offB, void *B, int64_t totB,

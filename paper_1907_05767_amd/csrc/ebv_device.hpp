@@ -924,7 +924,7 @@ __device__ __forceinline__ void tile_to_lds(const typename vec4<T>::type (&acc)[
 
 /* Workgroups per compute unit of the kernels around wg_crout: what LDS (70 KB
  * in FP64, 46 KB in FP32) admits; FP32's third one took the mixed-precision
- * batch from 6.6 to 6.4 ms. */
+ * batch of 4096 systems from 6.6 to 6.4 ms (smaller ragged batches run two). */
 template <typename T> constexpr int kCroutPerCu = sizeof(T) == 8 ? 2 : 3;
 
 template <typename T> struct CroutSmem {

@@ -22,8 +22,8 @@ int profile_update_read(UpdateProfile &p, double *ms_total, int64_t *launches, d
 
 struct DenseTuning {
     int small_update_below; /* trailing size at or below which 64-row update tiles are used */
-    int lookahead;          /* 1: one launch per block step (k_step); 0: panel + update launches */
-    int defer_group;        /* look-ahead: column classes G; a class is updated every G-th step (1..4) */
+    int lookahead;          /* 1: one launch (k_flow), or one per block step (k_step); 0: panel + update launches */
+    int defer_group;        /* block steps: column classes G; a class is updated every G-th step (1..4) */
     int defer_above;        /* ... while the region past the panel is larger than this */
     long long wait_limit;   /* spins before a bounded wait gives up (0: the defaults) */
     int defer_group_f32;    /* defer_group of the FP32 factor (1..4) */

@@ -2457,26 +2457,27 @@ __global__ __launch_bounds__(NT) void k_band_factor(double *AB, int64_t ldab, in
 
 /*
  * The band factor in segments.  The only thing block row k hands to the next
- * is the diagonal tile S_{k+1}, and for the diagonally dominant systems of
- * Eq. 2 what S_k was fades quadratically fast: a change D of S_k arrives in
- * S_{k+1} as B S^{-1} D S^{-1} C with B, C the off-diagonal tiles, a factor of
- * about 1e-3 per block row for 64 + 1 + 64 diagonals of row sum 0.5.  So the
- * block rows are split into segments, one workgroup each, and a segment
- * starts kBandWarm block rows early from A's own tile, which leaves the
- * starting error below the last bit.  That is checked, not assumed: the tile
- * a segment started from is compared with the one its predecessor ended with
+ * is the diagonal tile S_{k+1}, and what S_k was fades quadratically fast: a change
+ * D of S_k arrives in S_{k+1} as B S^{-1} D S^{-1} C with B, C the off-diagonal
+ * tiles.  So the block rows are split into segments, one workgroup each, and a
+ * segment starts kBandWarm block rows early from A's own tile.  How far that fades
+ * depends on the values: with 64 + 1 + 64 diagonals of random sign a factor of
+ * about 1e-3 (row sum 0.5) to 1e-2 (0.9) per block row, and six rows pass with at
+ * most half of what the check allows; off-diagonals of one sign need 9 (0.5) to 24
+ * (0.9), a five-point grid 25 and more.  Nothing rests on it: the tile a
+ * segment started from is compared with the one its predecessor ended with
  * (k_band_check), element by element against the terms it was formed from, and
  * segments that do not agree are factored again from the true tile, in order
- * (k_band_fix) -- for a matrix that forgets slowly all of them, which costs what
- * the serial chain costs.
+ * (k_band_fix) -- for a matrix that forgets slowly all of them.
  *
  * Segments are four block rows long (longer once that makes more than 256,
  * one per compute unit): at n = 16384 the chain is 10 steps instead of 256.
  * Below 16 block rows the serial chain is as fast (10 steps, and four more
  * launches).  Before that the band is copied as tiles (k_band_pack: the
  * segments' early rows are written by their neighbours, and the chain then
- * loads whole vectors without masks).  n = 16384, 64 + 1 + 64: 190 us (pack 8,
- * segments 168, check and fix 11) against 5.3 ms for the chain of 256.
+ * loads whole vectors without masks).  n = 16384, 64 + 1 + 64: 0.20 ms (pack 9 us,
+ * segments 171, check 11, fix 5) where the starts agree, 5.0 ms where every segment
+ * is repaired (one-signed bands, grids), 5.3 ms for the serial chain.
  */
 constexpr int kBandWarm = 6;
 
@@ -2763,13 +2764,16 @@ __global__ __launch_bounds__(NT) void k_band_packs(const double *AB, int64_t lda
  * columns).  The blocks are taken in positions, 0 the first one solved.  With
  * m < nt block rows the positions are split into segments as the factor's
  * are: a segment starts kBandSweepWarm positions early from zero, which the
- * products M_b (N_b), about 0.05 in norm at a row sum of 0.5, fade below the
- * last bit; its start is compared with its predecessor's end (k_band_sweep_check)
- * and it is swept again from there if they disagree (k_band_sweep_fix).  Its
+ * products M_b (N_b) fade below the last bit where they are small enough (0.05 in
+ * norm for random signs at row sum 0.5; one-signed bands of that sum take 18
+ * positions, a five-point grid 22); its start is compared with its predecessor's
+ * end, component by component (k_band_sweep_check), and it is swept again from
+ * there if they disagree (k_band_sweep_fix).  Its
  * own operands are then formed ahead (k_band_z): z_b = L_bb^{-1} b_b, held in
  * tile 3 of the block, whose rest holds the segment's ends and flags.
  * n = 16384, 8 right-hand sides: 40 us a direction and 22 us for the operands,
- * against 1.42 ms for two chains of 256 with two products a block.
+ * 0.79 ms in all where every segment is swept again, against 1.42 ms for two
+ * chains of 256 with two products a block.
  */
 struct BandSweep {
     int n;
