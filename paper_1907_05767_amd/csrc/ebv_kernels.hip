@@ -2462,7 +2462,7 @@ __global__ __launch_bounds__(NT) void k_band_factor(double *AB, int64_t ldab, in
  * tiles.  So the block rows are split into segments, one workgroup each, and a
  * segment starts kBandWarm block rows early from A's own tile.  How far that fades
  * depends on the values: with 64 + 1 + 64 diagonals of random sign a factor of
- * about 1e-3 (row sum 0.5) to 1e-2 (0.9) per block row, and six rows pass with at
+ * about 3e-4 (row sum 0.5) to 1e-3 (0.9) per block row, and six rows pass with at
  * most half of what the check allows; off-diagonals of one sign need 9 (0.5) to 24
  * (0.9), a five-point grid 25 and more.  Nothing rests on it: the tile a
  * segment started from is compared with the one its predecessor ended with
@@ -2477,7 +2477,7 @@ __global__ __launch_bounds__(NT) void k_band_factor(double *AB, int64_t ldab, in
  * segments' early rows are written by their neighbours, and the chain then
  * loads whole vectors without masks).  n = 16384, 64 + 1 + 64: 0.20 ms (pack 9 us,
  * segments 171, check 11, fix 5) where the starts agree, 5.0 ms where every segment
- * is repaired (one-signed bands, grids), 5.3 ms for the serial chain.
+ * is repaired (one-signed bands, grids), 5.2 ms for the serial chain.
  */
 constexpr int kBandWarm = 6;
 
