@@ -225,3 +225,20 @@ def test_band_segments_zero_pivot_in_a_repeated_segment():
     assert int(ebv.lu_factor_band_(t1, 64, 64, ws=_serial_ws()).item()) == r + 1
     assert int(ebv.lu_factor_band_(t2, 64, 64).item()) == r + 1
     assert torch.equal(t1[:m], t2[:m])  # the chain's factor, bit for bit
+
+
+@pytest.mark.parametrize("n", [65536, 65537, 140000])
+def test_band_segments_longer_than_four_rows(n):
+    """More than 1024 block rows: segments of more than four, at most 256 of them."""
+    case(f"band segments n={n}")
+    AB, B = inputs.band(n, 5, 9, 0.9, n), inputs.rhs(n, 2, n + 1)
+    LU_ref, _ = oracle.lu_factor_band(AB, 5, 9)
+    X_ref = oracle.lu_solve_band(LU_ref, 5, 9, B)
+    t, X = dev(AB), dev(B)
+    info = ebv.lu_factor_band_(t, 5, 9)
+    ebv.lu_solve_band_(t, 5, 9, X)
+    torch.cuda.synchronize()
+    assert int(info.item()) == 0
+    j = np.arange(n)[:, None] + np.arange(15)[None, :] - 5
+    assert np.abs(np.where((j >= 0) & (j < n), host(t) - LU_ref, 0)).max() <= 1e-12
+    assert fwd_err(host(X), X_ref) <= 1e-12
